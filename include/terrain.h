@@ -571,8 +571,10 @@ int mlp_adam_step(float* weights, const float* grad, float* m, float* v, float l
  * schedule gives the same impulses.  With tol > 0 the stopping test of
  * TR_PGS_GROUPED is taken per group of envs (one group per env when the scene
  * has at most 8 envs), that of TR_PGS_PER_ENV per env.
- *   TR_PGS_GROUPED: envs in 8 groups, one per XCD; each group is solved by
- *     blocks_per_xcd blocks that meet at a barrier after every colour.
+ *   TR_PGS_GROUPED: envs in 8 groups, one per XCD; each group is solved by up
+ *     to blocks_per_xcd blocks, each keeping a region of the group's spheres
+ *     in its LDS (as many blocks as the spheres are worth; a single large env
+ *     takes the blocks of all XCDs, as TR_PGS_SPREAD does).
  *   TR_PGS_PER_ENV: each env is solved by one block or by a cluster of
  *     blocks of one XCD.  A block solves a set of envs at once with their
  *     bodies in its LDS (lds_particles slots; an env that does not fit keeps
@@ -585,11 +587,11 @@ int mlp_adam_step(float* weights, const float* grad, float* m, float* v, float l
  *     particles get clusters of ceil(n / T) blocks, the others sets of at
  *     most T particles.  TR_CLUSTER_NONE: no env takes more than one block
  *     (sets of at most lds_particles particles, larger envs alone).
- *   TR_PGS_SPREAD: one env (n_envs must be 1) spread over all 8 XCDs: its
- *     sorted spheres in eighths (compact regions of the Morton order), each
- *     contact solved by the XCD group of its second sphere with
- *     blocks_per_xcd blocks, all groups meeting after every colour; every
- *     body store is written through to be seen across XCDs. */
+ *   TR_PGS_SPREAD: one env (n_envs must be 1) over the blocks of all 8 XCDs,
+ *     blocks_per_xcd each: its sorted spheres in compact regions of the Morton
+ *     order, one per block, neighbouring regions on one XCD, the states of
+ *     spheres on their surfaces written through to be seen across XCDs.  (A
+ *     small env takes the blocks of one XCD.) */
 #define TR_PGS_GROUPED 0
 #define TR_PGS_PER_ENV 1
 #define TR_PGS_SPREAD 2
@@ -599,9 +601,9 @@ typedef struct tr_solver_config {
     int32_t blocks_per_xcd;    /* grouped: >= 1, clamped to the resident limit */
     int32_t lds_particles;     /* per-env: >= 0, clamped to what LDS holds */
     int32_t cluster_particles; /* per-env: T, 0 for the automatic choice, or TR_CLUSTER_NONE */
-    int32_t dataflow;          /* 1: inside a multi-block solve the colour order of each sphere's
-                                  updates is kept by per-sphere update counters instead of a
-                                  barrier after every colour (same results); 0: barriers */
+    int32_t dataflow;          /* 1: inside a multi-block solve the colour order of every sphere's
+                                  updates is kept by update counters in memory (same results);
+                                  0: regions in LDS, hand-over records between them */
 } tr_solver_config;
 
 /* Set / read the schedule.  Takes effect at the next step; TR_E_INVAL on a bad

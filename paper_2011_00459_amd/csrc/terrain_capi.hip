@@ -21,6 +21,18 @@ using namespace trk;
 
 namespace {
 
+constexpr int kFlowMaxSweeps = 8192;  // longest counter-ordered solve
+
+// Regions of the grouped and spread solves (MI355X, beds under 100 sweeps of 9
+// or 10 colours).  One block alone up to 1,400 spheres: at 1,000 it takes 0.82
+// ms against 1.05 for a cluster, at 1,500 1.07 against 1.05, at 2,500 1.47
+// against 1.08.  Clusters in regions of 400 spheres: a phase is then bound by
+// the hand-over between blocks (6,000 spheres: 1.06 ms at 400, 1.47 at 1,000,
+// 1.66 at 1,600).  All XCDs from 27,000 spheres: across XCDs the hand-over is
+// slower, but one XCD's 32 blocks are full (20,000 spheres: 1.35 ms on one
+// XCD, 1.63 on all; 35,000: 1.93 and 1.58; 70,000: 2.63 and 1.70).
+constexpr int64_t kRegionAlone = 1400, kRegionSpheres = 400, kSpreadMin = 27000;
+
 struct EnvHost {
     int64_t n = 0;
     double rmax = 0.0;
@@ -75,6 +87,11 @@ struct tr_scene {
     bool capture = false;             // set_learn_capture: every step writes the learned-start features
     bool features_last = false;       // the last step wrote them
     tr_solver_config cfg{};           // PGS schedule
+    int64_t own_alloc = 0;            // owners allocated (starts, segment ranges)
+    int64_t seg_alloc = 0;            // owner segments allocated
+    int64_t task_alloc = 0;           // grouped / spread block tasks allocated
+    int64_t flag_alloc = 0;           // progress flags allocated
+    int64_t x_alloc = 0;              // exchange records allocated (float4)
     int64_t plan_alloc = 0;           // plan tasks allocated
     int64_t plan_idx_alloc = 0;       // plan block offsets allocated
     int64_t part_alloc = 0;           // block partials allocated (doubles)
@@ -266,6 +283,14 @@ bool plan_auto(const tr_scene* s, const std::vector<int>& order, int B, int lds_
     return best < 1e300;
 }
 
+// Blocks per XCD of a grouped or spread solve of n spheres.
+int region_blocks(int64_t n, bool wide, int bpx)
+{
+    if (!wide && n <= kRegionAlone) return 1;
+    const int64_t per = wide ? (n + kGroups - 1) / kGroups : n;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(bpx, (per + kRegionSpheres - 1) / kRegionSpheres));
+}
+
 // PGS schedule: the solve unit of every env and, in per-env mode, the plan of
 // the resident blocks.  Automatic (cluster_particles 0): plan_auto.  With a
 // given T: envs larger than T spheres per block get a cluster of ceil(n / T)
@@ -399,6 +424,131 @@ int rebuild_plan(tr_scene* s)
     } else {
         for (int e = 0; e < E; ++e) s->env_host[e].unit = s->env_host[e].group;
     }
+    // Owners: the regions that the solve's blocks take.  Per-env mode: a
+    // region per cluster share, one for an env that a block solves alone.
+    // Grouped and spread modes: a region of every env of the group per block.
+    std::vector<int> own_idx;
+    std::vector<int4> own_seg, tasks_g;
+    int grp_lds = 0;
+    std::vector<int> own_x;
+    int64_t x_next = 0;
+    int masks = 0;
+    // the counter-ordered solve keeps one slot of block partials per sweep;
+    // longer solves take the ordinary one (same results)
+    const bool flow = s->cfg.dataflow != 0 && s->desc.max_sweeps <= kFlowMaxSweeps;
+    auto set_env = [&](int e, int own_base, int K, int lds_off, int res_cap, bool coded) {
+        EnvDev& D = s->env_host[e];
+        D.own_base = own_base;
+        D.chunk = std::max(1, (D.n + K - 1) / K);
+        D.lds_off = lds_off;
+        D.res_cap = res_cap;
+        D.coded = coded && !flow ? 1 : 0;
+        D.masks = coded ? 1 : 0;
+        masks |= D.masks;
+    };
+    // exchange records of env e: K regions of stride LDS indices from x_next on
+    auto set_exchange = [&](int e, int stride) {
+        s->env_host[e].x0 = (int)x_next;
+        s->env_host[e].xstride = stride;
+    };
+    auto add_seg = [&](int e, int r) {
+        const EnvDev& D = s->env_host[e];
+        const int lo = std::min(D.n, r * D.chunk), hi = std::min(D.n, (r + 1) * D.chunk);
+        if (hi > lo) own_seg.push_back(make_int4(D.slot_begin + lo, hi - lo, D.lds_off, e));
+    };
+    if (s->cfg.mode == TR_PGS_PER_ENV) {
+        std::vector<int> K(E, 1);
+        for (const int4& t : plan)
+            if (t.z >= 2) K[t.x] = t.z;
+        for (int e = 0; e < E; ++e) {
+            set_env(e, (int)own_idx.size(), K[e], 0, K[e] > 1 ? lds_cap : INT32_MAX, K[e] > 1);
+            set_exchange(e, s->env_host[e].chunk);
+            for (int r = 0; r < K[e]; ++r) {
+                own_idx.push_back((int)own_seg.size());
+                own_x.push_back((int)x_next);
+                if (K[e] > 1) x_next += s->env_host[e].chunk;
+                add_seg(e, r);
+            }
+        }
+    } else {
+        const int bpx = s->z.pgs_grid / kGroups, cap = pgs_group_max_lds() / 32;
+        tasks_g.assign(s->z.pgs_grid, make_int4(-1, 0, 0, 0));
+        for (int g = 0; g < kGroups; ++g) {
+            int64_t n = 0;
+            for (int e = 0; e < E; ++e)
+                if (s->env_host[e].group == g) n += s->env_host[e].n;
+            if (n == 0) continue;
+            const bool wide = E == 1 && !flow && n > kSpreadMin;
+            const int per = region_blocks(n, wide, bpx), K = wide ? kGroups * per : per;
+            const int base = (int)own_idx.size();
+            int off = 0;
+            for (int e = 0; e < E; ++e) {
+                if (s->env_host[e].group != g) continue;
+                set_env(e, base, K, off, cap, true);
+                off += s->env_host[e].chunk;
+            }
+            grp_lds = std::max(grp_lds, std::min(off, cap));
+            for (int e = 0; e < E; ++e)
+                if (s->env_host[e].group == g) set_exchange(e, off);
+            for (int r = 0; r < K; ++r) {
+                // neighbouring regions on one XCD
+                const int blk = wide ? (r % per) * kGroups + r / per : r * kGroups + g;
+                tasks_g[blk] = make_int4(base + r, r | (K << 16), wide ? 0 : g * bpx,
+                                         g | (wide ? (int)0x80000000 : 0));
+                own_idx.push_back((int)own_seg.size());
+                own_x.push_back((int)x_next);
+                x_next += off;
+                for (int e = 0; e < E; ++e)
+                    if (s->env_host[e].group == g) add_seg(e, r);
+            }
+        }
+    }
+    const int n_own = (int)own_idx.size();
+    own_idx.push_back((int)own_seg.size());
+    const int64_t flags = std::max<int64_t>({(int64_t)s->z.pgs_grid, (int64_t)blocks, 1});
+    if (n_own + 1 > s->own_alloc) {
+        dfree(s, s->b.own_start); dfree(s, s->b.own_idx); dfree(s, s->b.own_x);
+        s->own_alloc = 0;
+        if (!alloc_n(s, s->b.own_start, (int64_t)(n_own + 1) * kOwnStride) || !alloc_n(s, s->b.own_idx, n_own + 1) ||
+            !alloc_n(s, s->b.own_x, n_own + 1))
+            return fail(s, TR_E_NOMEM, "PGS regions");
+        s->own_alloc = n_own + 1;
+    }
+    if ((int64_t)own_seg.size() > s->seg_alloc) {
+        dfree(s, s->b.own_seg);
+        s->seg_alloc = 0;
+        if (!alloc_n(s, s->b.own_seg, (int64_t)own_seg.size())) return fail(s, TR_E_NOMEM, "PGS regions");
+        s->seg_alloc = (int64_t)own_seg.size();
+    }
+    if ((int64_t)tasks_g.size() > s->task_alloc) {
+        dfree(s, s->b.grp_task);
+        s->task_alloc = 0;
+        if (!alloc_n(s, s->b.grp_task, (int64_t)tasks_g.size())) return fail(s, TR_E_NOMEM, "PGS regions");
+        s->task_alloc = (int64_t)tasks_g.size();
+    }
+    if (flags > s->flag_alloc) {
+        dfree(s, s->b.rflags);
+        s->flag_alloc = 0;
+        if (!alloc_n(s, s->b.rflags, flags)) return fail(s, TR_E_NOMEM, "PGS regions");
+        s->flag_alloc = flags;
+    }
+    if (2 * x_next > s->x_alloc) {
+        dfree(s, s->b.xw);
+        s->x_alloc = 0;
+        if (!alloc_n(s, s->b.xw, 2 * x_next)) return fail(s, TR_E_NOMEM, "PGS exchange records");
+        s->x_alloc = 2 * x_next;
+    }
+    if (n_own > 0)
+        HIP_CHECK(s, hipMemcpyAsync(s->b.own_x, own_x.data(), sizeof(int) * n_own, hipMemcpyHostToDevice, st));
+    HIP_CHECK(s, hipMemcpyAsync(s->b.own_idx, own_idx.data(), sizeof(int) * own_idx.size(), hipMemcpyHostToDevice, st));
+    if (!own_seg.empty())
+        HIP_CHECK(s, hipMemcpyAsync(s->b.own_seg, own_seg.data(), sizeof(int4) * own_seg.size(), hipMemcpyHostToDevice, st));
+    if (!tasks_g.empty())
+        HIP_CHECK(s, hipMemcpyAsync(s->b.grp_task, tasks_g.data(), sizeof(int4) * tasks_g.size(), hipMemcpyHostToDevice, st));
+    s->z.n_own = n_own;
+    s->z.grp_lds = grp_lds;
+    s->z.n_flags = (int)flags;
+    s->z.masks = masks;
     if ((int64_t)plan.size() > s->plan_alloc) {
         dfree(s, s->b.plan);
         if (!alloc_n(s, s->b.plan, (int64_t)plan.size())) return fail(s, TR_E_NOMEM, "PGS plan");
@@ -410,9 +560,8 @@ int rebuild_plan(tr_scene* s)
         s->plan_idx_alloc = (int64_t)plan_idx.size();
     }
     // block partials: two sweeps (barrier order) or one slot per sweep (counter order)
-    s->z.part_sweeps = std::min(std::max(s->desc.max_sweeps, 2), 8192);
-    s->z.flow = s->cfg.dataflow ? 1 : 0;
-    int64_t parts = 2 * std::max<int64_t>(s->z.pgs_grid, blocks) * s->z.part_sweeps;
+    s->z.flow = flow ? 1 : 0;
+    int64_t parts = 2 * std::max<int64_t>(s->z.pgs_grid, blocks) * (flow ? std::max(s->desc.max_sweeps, 2) : 2);
     if (parts > s->part_alloc) {
         dfree(s, s->b.block_part);
         if (!alloc_n(s, s->b.block_part, parts)) return fail(s, TR_E_NOMEM, "PGS partials");
@@ -422,7 +571,6 @@ int rebuild_plan(tr_scene* s)
     if (!plan_idx.empty())
         HIP_CHECK(s, hipMemcpyAsync(s->b.plan_idx, plan_idx.data(), sizeof(uint32_t) * plan_idx.size(), hipMemcpyHostToDevice, st));
     s->z.pgs_mode = s->cfg.mode;
-    s->p.spread = s->cfg.mode == TR_PGS_SPREAD ? 1 : 0;
     s->z.plan_blocks = blocks;
     s->z.lds_cap = lds_cap;
     HIP_CHECK(s, hipMemcpyAsync(s->b.envs, s->env_host.data(), sizeof(EnvDev) * E, hipMemcpyHostToDevice, st));
@@ -573,8 +721,7 @@ int rebuild_tables(tr_scene* s)
         dfree(s, s->b.scan_tmp);
         if (!alloc_n(s, s->b.cell_count, NC) || !alloc_n(s, s->b.cell_start, NC + 1) || !alloc_n(s, s->b.cell_fill, NC))
             return fail(s, TR_E_NOMEM, "cell arrays");
-        int64_t words = std::max({scan_tmp_words(NC), scan_tmp_words(s->z.NID), scan_tmp_words(s->z.P),
-                                  scan_tmp_words((int64_t)kBuckets * s->z.NB)});
+        int64_t words = std::max({scan_tmp_words(NC), scan_tmp_words(s->z.NID), scan_tmp_words(s->z.P)});
         if (!alloc_n(s, s->b.scan_tmp, words)) return fail(s, TR_E_NOMEM, "scan scratch");
         s->cells_alloc = NC + 1;
     }
@@ -721,11 +868,9 @@ int create_scene(const tr_scene_desc* d, tr_scene** out)
     z.P = (int64_t)d->n_envs * d->cap_particles;
     z.C = (int64_t)d->n_envs * d->cap_contacts;
     z.NID = z.P;
-    z.NB = (z.C + 255) / 256;
     z.roll_C = d->material.mu_r > 0.0 ? z.C : 1;  // rolling rows only when mu_r > 0
     z.imp_C = d->material.v_imp > 0.0 ? z.C : 1;  // impact-stage rows only when v_imp > 0
     z.n_envs = d->n_envs;
-    z.pgs_block = 512;
     s->p.n_units = std::max(kGroups, d->n_envs);
     // default schedule: grouped for a few envs (XCD groups of 32 blocks, one
     // per CU), per-env blocks with LDS-resident bodies for many envs
@@ -735,7 +880,7 @@ int create_scene(const tr_scene_desc* d, tr_scene** out)
     s->cfg.lds_particles = s->max_lds_particles;
     s->cfg.cluster_particles = 0;
     s->cfg.dataflow = 0;
-    z.pgs_grid = kGroups * std::max(1, std::min(s->cfg.blocks_per_xcd, pgs_resident_blocks(512) / kGroups));
+    z.pgs_grid = kGroups * std::max(1, std::min(s->cfg.blocks_per_xcd, pgs_resident_blocks() / kGroups));
     z.col_grid = std::min(colour_resident_blocks(), 2048);
     DevBuffers& b = s->b;
     bool ok = alloc_n(s, b.xr, z.P) && alloc_n(s, b.vw, 2 * z.P) && alloc_n(s, b.xr2, z.P) &&
@@ -747,8 +892,8 @@ int create_scene(const tr_scene_desc* d, tr_scene** out)
               alloc_n(s, b.id_count, z.NID) && alloc_n(s, b.id_start, z.NID + 1) && alloc_n(s, b.id_fill, z.NID) &&
               alloc_n(s, b.pid_start, z.NID + 1) && alloc_n(s, b.inc_count, z.P) &&
               alloc_n(s, b.inc_start, z.P + 1) && alloc_n(s, b.inc_fill, z.P) && alloc_n(s, b.inc, 2 * z.C) &&
-              alloc_n(s, b.colour, z.C) && alloc_n(s, b.col_wait, z.C) && alloc_n(s, b.col_hist, (int64_t)kBuckets * z.NB) &&
-              alloc_n(s, b.col_start, (int64_t)kBuckets * z.NB + 1) && alloc_n(s, b.cpos, z.C) &&
+              alloc_n(s, b.colour, z.C) && alloc_n(s, b.col_wait, z.C) && alloc_n(s, b.icode, 2 * z.C) &&
+              alloc_n(s, b.smask, z.P) && alloc_n(s, b.seq, z.C) && alloc_n(s, b.rm, z.C) && alloc_n(s, b.cpos, z.C) &&
               alloc_n(s, b.r0, z.C) && alloc_n(s, b.r1, z.C) && alloc_n(s, b.r2, z.C) && alloc_n(s, b.rk, z.C) &&
               alloc_n(s, b.r3, z.roll_C) && alloc_n(s, b.lamr, z.roll_C) && alloc_n(s, b.lamr0, z.roll_C) &&
               alloc_n(s, b.lamrc, z.roll_C) && alloc_n(s, b.plamr, z.roll_C) &&
@@ -756,7 +901,7 @@ int create_scene(const tr_scene_desc* d, tr_scene** out)
               alloc_n(s, b.lamri, std::min(z.imp_C, z.roll_C)) && alloc_n(s, b.qg, z.imp_C) &&
               alloc_n(s, b.lam, z.C) && alloc_n(s, b.lam0, z.C) && alloc_n(s, b.wrec, 3 * z.C) &&
               alloc_n(s, b.envs, d->n_envs) && alloc_n(s, b.ustats, s->p.n_units) &&
-              alloc_n(s, b.env_col, (int64_t)d->n_envs * (kMaxColours + 1)) && alloc_n(s, b.env_ncol, d->n_envs) &&
+              alloc_n(s, b.env_ncol, d->n_envs) &&
               alloc_n(s, b.env_bar, (int64_t)d->n_envs * 16) && alloc_n(s, b.ver, z.P) &&
               alloc_n(s, b.cnt, 1) && alloc_n(s, b.env_stats, d->n_envs) && alloc_n(s, b.mlp, kMlpParams) &&
               alloc_n(s, s->staging, 12 * z.P) && alloc_n(s, b.feat, 12 * z.C) && alloc_n(s, b.frm1, z.C) &&
@@ -1642,7 +1787,7 @@ int set_solver_config(tr_scene* s, const tr_solver_config* cfg)
     if (cfg->mode == TR_PGS_SPREAD && (s->desc.n_envs != 1 || cfg->dataflow))
         return fail(s, TR_E_INVAL, "set_solver_config: the spread schedule takes one env and barriers");
     s->cfg = *cfg;
-    s->cfg.blocks_per_xcd = std::min(cfg->blocks_per_xcd, std::max(1, pgs_resident_blocks(512) / kGroups));
+    s->cfg.blocks_per_xcd = std::min(cfg->blocks_per_xcd, std::max(1, pgs_resident_blocks() / kGroups));
     s->cfg.lds_particles = std::min(cfg->lds_particles, s->max_lds_particles);
     s->z.pgs_grid = kGroups * s->cfg.blocks_per_xcd;
     return s->tables_dirty ? TR_OK : rebuild_plan(s);

@@ -8,9 +8,14 @@
 //   contacts (capacity C):
 //     raw detection output  rkey[C] u64, rpair[C] int2
 //     canonical (key order) ckey[C] u64, cpair[C] int2, lamc[C] float4
-//     colour order rows     r0 (n, l1), r1 (l2, 1/Dn, 1/Dt, Sigma),
-//                           r2 (q, lo, body1, body2), rk (kinematic velocity, update-sequence
-//                           bits), lam (impulses)
+//     solve order rows      r0 (n, l1), r1 (l2, 1/Dn, 1/Dt, Sigma),
+//                           r2 (q, lo, body1, body2), rk (velocity of a moving boundary), lam
+//                           (impulses): by owner (the block that solves the contact),
+//                           then colour, then shared before private contacts
+//   regions: the spheres of a solve cut into contiguous ranges of its Morton-sorted
+//     slots, one per block (owner); smask[P] the colours of a sphere's contacts and of
+//     those another region's block solves, xw the records through which blocks hand
+//     such spheres to each other
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -22,7 +27,7 @@ namespace trk {
 constexpr int kSlotImpact = 3;     // PGS statistics slot of the impact stage
 constexpr int kMaxColours = 64;     // colours of the contact schedule (64-bit masks)
 constexpr int kGroups = 8;          // PGS groups: one per XCD of the MI355X (block b runs on XCD b % 8)
-constexpr int kBuckets = kMaxColours * kGroups;  // (colour, group) buckets of the PGS order
+constexpr int kOwnStride = 2 * kMaxColours + 1;  // entries of an owner's table of starts (DevBuffers::own_start)
 constexpr int kMaxHits = 32;        // contacts one particle may emit per step
 constexpr int kMaxZonesPerEnv = 4;  // bodies with an active zone per environment
 constexpr int kZoneMoments = 20;    // M, mx(3), mv(3), mxx(6), m x*v(3), sum Is(1), sum Is w(3)
@@ -34,7 +39,7 @@ constexpr int kMlpParams = 64 * 12 + 64 + 64 * 64 + 64 + 3 * 64 + 3 + 12;
 enum : int {
     kModeGrouped = 0,  // envs in kGroups XCD groups, grid-wide colour barriers per group
     kModePerEnv = 1,   // each env solved by its own block (or cluster of blocks)
-    kModeSpread = 2,   // one env spread over the kGroups XCD groups by space, all groups meeting per colour
+    kModeSpread = 2,   // one env spread over the blocks of all XCDs by space
 };
 constexpr int kEnvBlk = 1024;  // threads of a per-env PGS block
 
@@ -61,6 +66,13 @@ struct EnvDev {
     int slot_begin;               // first slot of the env in sorted order
     int col_base;                 // first depth column of the env (dims[0] x dims[1] columns)
     int group;                    // PGS group (XCD) that solves this env in grouped mode
+    int own_base;                 // owner of the env's region 0; region r is owner own_base + r
+    int chunk;                    // spheres of a region: slot s lies in region (s - slot_begin) / chunk
+    int lds_off;                  // LDS index of a region's first sphere of this env
+    int res_cap;                  // LDS indices below this can hold a sphere
+    int x0, xstride;              // exchange record of LDS index i of region r: x0 + r xstride + i
+    int coded;                    // 1: rows name bodies as a region's block finds them (LDS, exchange)
+    int masks;                    // 1: the solve needs the order of each sphere's updates (smask, seq)
     int unit;                     // solve unit: the group (grouped mode) or the env (per-env mode)
     int zone_count;
     int zone_body[kMaxZonesPerEnv];  // global body index of each zone
@@ -145,7 +157,6 @@ struct StepParams {
     int n_units;        // PGS solve units (entries of ustats)
     float restitution;  // Newton restitution of the impact stage
     int n_tools;        // zone predictor tools (all envs)
-    int spread;         // 1: spread mode (the PGS groups split the env by space)
 };
 
 // per PGS solve unit: an XCD group of envs (grouped mode) or one env
@@ -169,9 +180,9 @@ struct Counters {
     uint32_t overflow;     // kOvf* / kFail* bits, sticky within a step
     uint32_t n_colours;
     uint32_t failed;       // OR of the overflow bits of every step since the host last read it
-    uint32_t pad[11];
-    uint32_t bar[kGroups][16];  // per-group barrier counters, one cache line each
-    uint32_t gbar[16];          // spread mode: arrivals of the groups at the colour barrier
+    uint32_t n_pos;        // solve-order positions handed out to owners
+    uint32_t pad[10];
+    uint32_t bar[kGroups][16];  // per-group placement and barrier counters, one cache line each
 };
 
 struct EnvStats {
@@ -204,9 +215,14 @@ struct DevBuffers {
     uint32_t *inc_count, *inc_start, *inc_fill, *inc;     // [P], [P+1], [P], [2C]
     int* colour;                                    // [C]
     uint32_t* col_wait;                             // [C] colouring: the neighbour that blocked a contact
-    uint32_t *col_hist, *col_start;                 // [kBuckets*NB], [kBuckets*NB+1]
-    uint32_t* cpos;                                 // canonical -> colour position
-    float4 *r0, *r1, *r2, *rk, *lam, *lam0;         // colour order
+    uint8_t* icode;                                 // [2C] bucket of each incidence entry in its owner's order
+    ulonglong2* smask;                              // [P] colours of a sphere's contacts, of those solved away
+    uint32_t* seq;                                  // [C] solve order: places in the bodies' update sequences (8 bits each), their lengths
+    float4* rm;                                     // [C] solve order: 1/m, 1/I of body 1, of body 2
+    float4* xw;                                     // exchange records (two float4: v, omega, each with its version)
+    int* own_x;                                     // [n_own] exchange record of an owner's LDS index 0
+    uint32_t* cpos;                                 // canonical -> solve-order position
+    float4 *r0, *r1, *r2, *rk, *lam, *lam0;         // solve order
     // [3C] canonical order: each contact's start impulse as the velocity
     // changes of its spheres, (J, slot of sphere 2), (dw of sphere 2, dw.x of
     // sphere 1), (dw.yz of sphere 1, 0, 0), per unit inverse mass / inertia
@@ -238,7 +254,13 @@ struct DevBuffers {
     Counters* cnt;
     EnvStats* env_stats;
     UnitStats* ustats;    // [n_units]
-    uint32_t* env_col;    // [n_envs][kMaxColours + 1] colour starts of each env (per-env mode)
+    // owners: starts of (colour, shared | private) in solve order, entry 2 colour + class; the slot
+    // ranges of owner o are own_seg[own_idx[o] .. own_idx[o + 1]) as (first slot, count, LDS index, env)
+    uint32_t* own_start;  // [n_own][kOwnStride]
+    int* own_idx;         // [n_own + 1]
+    int4* own_seg;
+    int4* grp_task;       // [pgs_grid] grouped / spread solve: (owner or -1, rank | K << 16, first flag, unit | write-through << 31)
+    uint32_t* rflags;     // [n_flags] sweeps each block has finished
     uint32_t* env_ncol;   // [n_envs] colours used by each env
     int4* plan;           // per-env PGS tasks: (env, rank in its cluster, cluster size, first block)
     uint32_t* plan_idx;   // [blocks + 1]: tasks of block b are plan[plan_idx[b] .. plan_idx[b + 1])
@@ -261,19 +283,20 @@ struct Sizes {
     int64_t C;      // contact capacity (all envs)
     int64_t NID;    // id space = n_envs * cap_particles
     int64_t NC;     // cells (all envs)
-    int64_t NB;     // blocks of 256 over C (colour bucketing)
     int64_t roll_C; // entries of the rolling-row arrays (C when mu_r > 0, else 1)
     int64_t imp_C;  // entries of the impact-stage arrays (C when v_imp > 0, else 1)
     int n_envs;
     int n_zone_chunks;
     int pgs_grid;   // blocks of the persistent PGS kernel (kGroups x blocks per group)
-    int pgs_block;  // threads per PGS block
+    int n_own;      // owners of the solve order
+    int grp_lds;    // spheres a block of the grouped / spread solve holds in LDS
+    int n_flags;    // entries of rflags
+    int masks;      // some env's solve needs smask
     int pgs_mode;   // kModeGrouped, kModePerEnv or kModeSpread
     int plan_blocks;  // blocks of the per-env PGS kernel
     int lds_cap;    // particles whose bodies a per-env block keeps in LDS (0: none)
     int n_units;    // entries of ustats
     int flow;       // colour order kept by per-sphere update counters instead of barriers
-    int part_sweeps;  // sweeps of block partials held (flow: one slot per sweep)
     int col_grid;   // resident blocks of the colouring kernel
     int64_t NCOL;   // depth columns (all envs)
 };
@@ -388,7 +411,8 @@ void launch_gather_by_id(const DevBuffers& b, int id_base, int n, float4* xo, fl
                          hipStream_t s);
 void launch_scatter_by_id(const DevBuffers& b, int id_base, int n, const float4* xi, const float4* vi,
                           const float4* wi, int mask, hipStream_t s);
-int pgs_resident_blocks(int block);
+int pgs_resident_blocks();
+int pgs_group_max_lds();
 int pgs_env_resident_blocks(int lds_bytes);
 int pgs_env_max_lds();
 int colour_resident_blocks();

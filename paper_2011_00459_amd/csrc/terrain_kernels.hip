@@ -522,6 +522,18 @@ __global__ void k_inc_fill(DevBuffers b, int64_t cap)
     }
 }
 
+// The block (region) that solves a contact of two regions of one env: the
+// parity of the ranks decides, so that a region owns about half of the
+// contacts on its surface.
+__device__ inline int contact_rank(int ra, int rb)
+{
+    const int lo = min(ra, rb), hi = max(ra, rb);
+    return ((lo ^ hi) & 1) ? lo : hi;
+}
+
+__device__ inline int region_of(const EnvDev& E, int slot) { return (slot - E.slot_begin) / E.chunk; }
+
+// each sphere's incident contacts in canonical order
 __global__ void k_inc_sort(DevBuffers b, int n)
 {
     int s = blockIdx.x * blockDim.x + threadIdx.x;
@@ -658,178 +670,206 @@ __global__ __launch_bounds__(kBlk) void k_colour(DevBuffers b, int64_t cap, int 
     if (left) atomicOr(&b.cnt->overflow, kFailColouring);
 }
 
-// stable bucketing of the canonical list by (colour, PGS group)
-__device__ inline int contact_group(const DevBuffers& b, unsigned long long key, uint32_t id_cap)
+// LDS index of a sphere in its region's block
+__device__ inline int lds_index(const EnvDev& E, int slot)
 {
-    return b.envs[env_of((int)(key >> 32), id_cap)].group;
+    const int t = slot - E.slot_begin;
+    return E.lds_off + t % E.chunk;
 }
 
-// Spread mode: the XCD group of a sphere slot (its env's slots in eighths:
-// the sort keeps them in Morton order, so each eighth is a compact region) and
-// of a contact (that of its second sphere, a particle for every contact).
-__device__ inline int slot_part(const DevBuffers& b, int sl, uint32_t id_cap)
+// Per sphere, the colours of its contacts (all) and of those that another
+// region's block solves (away).  A sphere's contacts have distinct colours, so
+// the masks give the order of its updates; those of a sphere without an LDS
+// place all count as away.
+__global__ void k_region_masks(DevBuffers b, StepParams p)
 {
-    const EnvDev& E = b.envs[env_of(b.pid[sl], id_cap)];
-    return (int)(((int64_t)(sl - E.slot_begin) * kGroups) / max(E.n, 1));
-}
-__device__ inline int contact_group_of(const DevBuffers& b, uint32_t c, uint32_t id_cap, int spread)
-{
-    return spread ? slot_part(b, b.cpair[c].y, id_cap) : contact_group(b, b.ckey[c], id_cap);
-}
-
-__global__ void k_col_hist(DevBuffers b, int64_t cap, int64_t NB, uint32_t id_cap, int spread)
-{
-    __shared__ uint32_t h[kBuckets];
-    uint32_t nc = n_contacts(b, cap);
-    for (int k = threadIdx.x; k < kBuckets; k += blockDim.x) h[k] = 0;
-    __syncthreads();
-    uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < nc) {
-        int col = b.colour[c];
-        if (col >= 0 && col < kMaxColours) atomicAdd(&h[col * kGroups + contact_group_of(b, c, id_cap, spread)], 1u);
+    int s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (s >= p.n_particles) return;
+    const EnvDev& E = b.envs[env_of(b.pid[s], p.id_cap)];
+    if (!E.masks) return;
+    const uint32_t beg = b.inc_start[s], end = b.inc_start[s + 1];
+    const bool split = E.chunk < E.n;
+    const int r = region_of(E, s);
+    unsigned long long all = 0, away = 0;
+    for (uint32_t t0 = beg; t0 < end; t0 += kColChunk) {
+        uint32_t e[kColChunk];
+        int col[kColChunk];
+        int2 pr[kColChunk];
+#pragma unroll
+        for (int j = 0; j < kColChunk; ++j) e[j] = b.inc[min(t0 + j, end - 1)];
+#pragma unroll
+        for (int j = 0; j < kColChunk; ++j) col[j] = b.colour[e[j]];
+#pragma unroll
+        for (int j = 0; j < kColChunk; ++j) pr[j] = split ? b.cpair[e[j]] : make_int2(-1, -1);
+#pragma unroll
+        for (int j = 0; j < kColChunk; ++j) {
+            if (col[j] < 0 || col[j] >= kMaxColours) continue;  // failed colouring: the step is abandoned
+            const unsigned long long bit = 1ull << col[j];
+            all |= bit;
+            if (pr[j].x < 0) continue;
+            const int q = region_of(E, pr[j].x == s ? pr[j].y : pr[j].x);
+            if (q != r && contact_rank(r, q) != r) away |= bit;
+        }
     }
-    __syncthreads();
-    for (int k = threadIdx.x; k < kBuckets; k += blockDim.x) b.col_hist[(int64_t)k * NB + blockIdx.x] = h[k];
+    if (lds_index(E, s) >= E.res_cap) away = all;
+    b.smask[s] = make_ulonglong2(all, away);
 }
 
-__global__ void k_col_scatter(DevBuffers b, int64_t cap, int64_t NB, uint32_t id_cap, int spread)
+// of a sphere's update by its contact of colour col: its place in the
+// sphere's sequence, and whether the one before (after) it, around the sweep,
+// is solved away from the sphere's region
+__device__ inline uint32_t seq_place(ulonglong2 m, int col) { return (uint32_t)__popcll(m.x & ((1ull << col) - 1)); }
+__device__ inline bool from_away(ulonglong2 m, int col)
 {
-    __shared__ int bk[kBlk];
-    uint32_t nc = n_contacts(b, cap);
-    uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-    int my = -1;
-    if (c < nc) {
-        int col = b.colour[c];
-        if (col >= 0 && col < kMaxColours) my = col * kGroups + contact_group_of(b, c, id_cap, spread);
-    }
-    bk[threadIdx.x] = my;
-    __syncthreads();
-    if (c >= nc) return;
-    if (my < 0) {  // failed colouring: the step is abandoned
-        b.cpos[c] = c;
-        return;
-    }
-    uint32_t rank = 0;
-    for (int t = 0; t < (int)threadIdx.x; ++t) rank += bk[t] == my;
-    b.cpos[c] = b.col_start[(int64_t)my * NB + blockIdx.x] + rank;
+    const unsigned long long below = m.x & ((1ull << col) - 1);
+    return (m.y >> (63 - __builtin_clzll(below ? below : m.x))) & 1;
+}
+__device__ inline bool to_away(ulonglong2 m, int col)
+{
+    const unsigned long long above = m.x & ~((2ull << col) - 1);
+    return (m.y >> __builtin_ctzll(above ? above : m.x)) & 1;
 }
 
-// env e's contacts in canonical order: [id_start[e id_cap], id_start[(e+1) id_cap])
-__device__ inline void env_contacts(const DevBuffers& b, int e, uint32_t id_cap, uint32_t& beg, uint32_t& end)
-{
-    beg = b.id_start[(size_t)e * id_cap];
-    end = b.id_start[(size_t)(e + 1) * id_cap];
-}
+// Solve order.  One block per owner (a region of an env's spheres, see
+// EnvDev) lists the contacts it solves: those of its spheres, each once, by
+// colour and, within a colour, the shared ones (a body that another block
+// updated last, or one without an LDS place) before the private ones; equal
+// ones in the order of its spheres and their incident contacts, which is
+// fixed, so that the residual sums are reproducible.  Which contacts share a
+// bucket does not change results.  Two passes over the owner's incidence
+// lists: counts per wave and bucket, then positions; a lane's rank among the
+// lanes of its wave comes from a ballot match on the bucket's seven bits.
+constexpr int kOrdBlk = 1024;
+constexpr int kOrdWaves = kOrdBlk / 64;
+constexpr int kOrdBuckets = 2 * kMaxColours;
+constexpr uint32_t kNotMine = 255, kUncoloured = 254;  // bucket codes of entries without a position
 
-// colours used by each env (zeroed at the step's start): max colour + 1 over
-// the canonical list; a block whose contacts all belong to one env (the
-// list is in env order) reduces first and updates once
-__global__ void k_env_ncol(DevBuffers b, int64_t cap, uint32_t id_cap)
+__global__ __launch_bounds__(kOrdBlk) void k_order(DevBuffers b)
 {
-    __shared__ int sm[kBlk / 64];
-    uint32_t nc = n_contacts(b, cap);
-    uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-    uint32_t c0 = blockIdx.x * blockDim.x;
-    if (c0 >= nc) return;
-    uint32_t c1 = min(nc, c0 + blockDim.x) - 1;
-    int e0 = (int)env_of((int)(b.ckey[c0] >> 32), id_cap), e1 = (int)env_of((int)(b.ckey[c1] >> 32), id_cap);
-    int m = c < nc ? b.colour[c] + 1 : 0;
-    if (e0 != e1) {
-        if (c < nc && m > 0) atomicMax(&b.env_ncol[env_of((int)(b.ckey[c] >> 32), id_cap)], (uint32_t)min(m, kMaxColours));
-        return;
-    }
-    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_down(m, o, 64));
-    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = m;
+    __shared__ uint32_t wc[kOrdWaves][kOrdBuckets];
+    __shared__ uint32_t bst[kOrdBuckets + 1];
+    __shared__ uint32_t base;
+    const int o = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int sg0 = b.own_idx[o], sg1 = b.own_idx[o + 1];
+    for (int k = threadIdx.x; k < kOrdWaves * kOrdBuckets; k += kOrdBlk) wc[0][k] = 0;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) m = max(m, sm[w]);
-        if (m > 0) atomicMax(&b.env_ncol[e0], (uint32_t)min(m, kMaxColours));
-    }
-}
-
-// Per-env stable counting sort of the canonical list by colour (one block per
-// env): env_col[e][k] = first colour-order position of colour k in env e, and
-// cpos[c] the position of canonical contact c.  The rank among equal colours
-// keeps canonical order: inside a wave from the lanes with the same colour
-// (a 7-bit ballot match), across waves and chunks from running counts.
-// 1024 threads, so that the largest env takes few chunks.
-constexpr int kSortBlk = 1024;
-constexpr int kSortWaves = kSortBlk / 64;
-
-__global__ __launch_bounds__(kSortBlk) void k_env_colsort(DevBuffers b, uint32_t id_cap)
-{
-    __shared__ uint32_t base[kMaxColours + 1];
-    __shared__ uint32_t wcount[kSortWaves][kMaxColours + 1];
-    __shared__ int failed;
-    const int e = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t beg, end;
-    env_contacts(b, e, id_cap, beg, end);
-    for (int k = threadIdx.x; k <= kMaxColours; k += blockDim.x) base[k] = 0;
-    if (threadIdx.x == 0) failed = 0;
-    __syncthreads();
-    // the lanes of a wave holding the same colour as this lane
-    auto same_colour = [&](int col) {
+    volatile uint32_t* mine = wc[wave];
+    const unsigned long long lower = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    // the lanes of the wave with this lane's bucket
+    auto match = [&](uint32_t code) {
         unsigned long long same = ~0ull;
-        for (int bit = 0; bit < 7; ++bit) {
-            unsigned long long m = __ballot((col >> bit) & 1);
-            same &= ((col >> bit) & 1) ? m : ~m;
+        for (int bit = 0; bit < 8; ++bit) {
+            const unsigned long long m = __ballot((code >> bit) & 1);
+            same &= ((code >> bit) & 1) ? m : ~m;
         }
         return same;
     };
-    const unsigned long long lower = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    // histogram (colour kMaxColours collects failed colourings), one LDS
-    // atomic per colour and wave
-    for (uint32_t c0 = beg; c0 < end; c0 += blockDim.x) {
-        const uint32_t c = c0 + threadIdx.x;
-        int col = kMaxColours + 1;  // past the end: counted nowhere
-        if (c < end) {
-            col = b.colour[c];
-            if (col < 0 || col >= kMaxColours) { col = kMaxColours; failed = 1; }
+    for (int sg = sg0; sg < sg1; ++sg) {
+        const int4 S = b.own_seg[sg];
+        const EnvDev& E = b.envs[S.w];
+        const int rank = o - E.own_base, lo = S.x, hi = S.x + S.y;
+        const int w1 = lo + (int)((int64_t)S.y * (wave + 1) / kOrdWaves);
+        int ncol = 0;
+        for (int s0 = lo + (int)((int64_t)S.y * wave / kOrdWaves); s0 < w1; s0 += 64) {
+            const int s = s0 + lane;
+            uint32_t t = 0, end = 0;
+            ulonglong2 ms = make_ulonglong2(1, 0);
+            if (s < w1) {
+                t = b.inc_start[s];
+                end = b.inc_start[s + 1];
+                if (E.coded) ms = b.smask[s];
+            }
+            for (; __ballot(t < end); t += kColChunk) {
+                uint32_t e[kColChunk], code[kColChunk];
+                int2 pr[kColChunk];
+#pragma unroll
+                for (int j = 0; j < kColChunk; ++j) e[j] = t + j < end ? b.inc[t + j] : ~0u;
+#pragma unroll
+                for (int j = 0; j < kColChunk; ++j) pr[j] = e[j] != ~0u ? b.cpair[e[j]] : make_int2(-1, -1);
+#pragma unroll
+                for (int j = 0; j < kColChunk; ++j) {
+                    code[j] = kNotMine;
+                    if (e[j] == ~0u) continue;
+                    const int other = pr[j].x == s ? pr[j].y : pr[j].x;
+                    const bool two = pr[j].x >= 0, inside = two && other >= lo && other < hi;
+                    const bool take = inside ? pr[j].y == s
+                                             : (!two || contact_rank(rank, region_of(E, other)) == rank);
+                    if (!take) continue;
+                    const int col = b.colour[e[j]];
+                    code[j] = kUncoloured;
+                    if (col >= 0 && col < kMaxColours) {
+                        bool priv = !E.coded || ((inside || !two) && !from_away(ms, col));
+                        if (E.coded && priv && inside) priv = !from_away(b.smask[other], col);
+                        code[j] = 2 * (uint32_t)col + (priv ? 1u : 0u);
+                        ncol = max(ncol, col + 1);
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < kColChunk; ++j) {
+                    const unsigned long long same = match(code[j]);
+                    if (code[j] < kOrdBuckets && (same & lower) == 0) mine[code[j]] += (uint32_t)__popcll(same);
+                    if (e[j] != ~0u) b.icode[t + j] = (uint8_t)code[j];
+                }
+            }
         }
-        const unsigned long long same = same_colour(col);
-        if ((same & lower) == 0 && col <= kMaxColours) atomicAdd(&base[col], (uint32_t)__popcll(same));
+        for (int k = 32; k > 0; k >>= 1) ncol = max(ncol, __shfl_xor(ncol, k, 64));
+        if (lane == 0 && ncol) atomicMax(&b.env_ncol[S.w], (uint32_t)ncol);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t run = beg, ncol = 0;
-        for (int k = 0; k <= kMaxColours; ++k) {
-            uint32_t n = base[k];
-            base[k] = run;
-            if (k < kMaxColours) b.env_col[(size_t)e * (kMaxColours + 1) + k] = run;
-            if (n && k < kMaxColours) ncol = k + 1;
+    if (threadIdx.x < kOrdBuckets) {
+        uint32_t run = 0;
+        for (int w = 0; w < kOrdWaves; ++w) {
+            const uint32_t n = wc[w][threadIdx.x];
+            wc[w][threadIdx.x] = run;
             run += n;
         }
-        b.env_col[(size_t)e * (kMaxColours + 1) + kMaxColours] = base[kMaxColours];
-        b.env_ncol[e] = ncol;
+        bst[threadIdx.x] = run;
     }
     __syncthreads();
-    for (uint32_t c0 = beg; c0 < end; c0 += blockDim.x) {
-        uint32_t c = c0 + threadIdx.x;
-        int col = kMaxColours + 1;  // past the end: matches no real colour
-        if (c < end) {
-            col = b.colour[c];
-            if (col < 0 || col >= kMaxColours) col = kMaxColours;
+    if (wave == 0) {
+        const uint32_t a = bst[2 * lane], c = bst[2 * lane + 1];
+        const uint32_t inc = wave_incl_scan(a + c);
+        bst[2 * lane] = inc - a - c;
+        bst[2 * lane + 1] = inc - c;
+        if (lane == 63) {
+            bst[kOrdBuckets] = inc;
+            base = atomicAdd(&b.cnt->n_pos, inc);
         }
-        const unsigned long long same = same_colour(col);
-        uint32_t rank = (uint32_t)__popcll(same & lower);
-        bool leader = (same & lower) == 0;
-        for (int k = lane; k <= kMaxColours; k += 64) wcount[wave][k] = 0;
-        __syncthreads();
-        if (leader && col <= kMaxColours) wcount[wave][col] = (uint32_t)__popcll(same);
-        __syncthreads();
-        if (c < end) {
-            uint32_t off = base[col] + rank;
-            for (int w = 0; w < wave; ++w) off += wcount[w][col];
-            b.cpos[c] = failed ? c : off;
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k <= kOrdBuckets; k += kOrdBlk) b.own_start[(size_t)o * kOwnStride + k] = base + bst[k];
+    for (int k = threadIdx.x; k < kOrdWaves * kOrdBuckets; k += kOrdBlk) wc[0][k] += base + bst[k % kOrdBuckets];
+    __syncthreads();
+    for (int sg = sg0; sg < sg1; ++sg) {
+        const int4 S = b.own_seg[sg];
+        const int w1 = S.x + (int)((int64_t)S.y * (wave + 1) / kOrdWaves);
+        for (int s0 = S.x + (int)((int64_t)S.y * wave / kOrdWaves); s0 < w1; s0 += 64) {
+            const int s = s0 + lane;
+            uint32_t t = 0, end = 0;
+            if (s < w1) {
+                t = b.inc_start[s];
+                end = b.inc_start[s + 1];
+            }
+            for (; __ballot(t < end); t += kColChunk) {
+                uint32_t e[kColChunk], code[kColChunk];
+#pragma unroll
+                for (int j = 0; j < kColChunk; ++j) {
+                    e[j] = t + j < end ? b.inc[t + j] : ~0u;
+                    code[j] = t + j < end ? b.icode[t + j] : kNotMine;
+                }
+#pragma unroll
+                for (int j = 0; j < kColChunk; ++j) {
+                    const unsigned long long same = match(code[j]);
+                    if (code[j] < kOrdBuckets) {
+                        const uint32_t at = mine[code[j]];
+                        b.cpos[e[j]] = at + (uint32_t)__popcll(same & lower);
+                        if ((same & lower) == 0) mine[code[j]] = at + (uint32_t)__popcll(same);
+                    } else if (code[j] == kUncoloured) {
+                        b.cpos[e[j]] = e[j];  // failed colouring: the step is abandoned
+                    }
+                }
+            }
         }
-        __syncthreads();
-        for (int k = threadIdx.x; k <= kMaxColours; k += blockDim.x) {
-            uint32_t t = 0;
-            for (int w = 0; w < kSortWaves; ++w) t += wcount[w][k];
-            base[k] += t;
-        }
-        __syncthreads();
     }
 }
 
@@ -837,16 +877,9 @@ void launch_colour(const DevBuffers& b, const StepParams& p, const Sizes& z, hip
 {
     launch_fill_u32((uint32_t*)b.colour, 0xFFFFFFFFu, z.C, s);
     hipLaunchKernelGGL(k_colour, dim3(z.col_grid), dim3(kBlk), 0, s, b, z.C, 100000);
-    if (z.pgs_mode == kModePerEnv) {
-        hipLaunchKernelGGL(k_env_colsort, dim3((unsigned)z.n_envs), dim3(kSortBlk), 0, s, b, p.id_cap);
-        return;
-    }
-    const int spread = z.pgs_mode == kModeSpread ? 1 : 0;
-    hipLaunchKernelGGL(k_col_hist, dim3((unsigned)z.NB), dim3(kBlk), 0, s, b, z.C, z.NB, p.id_cap, spread);
-    launch_scan_u32(b.col_hist, b.col_start, (int64_t)kBuckets * z.NB, b.scan_tmp, s);
-    hipLaunchKernelGGL(k_col_scatter, dim3((unsigned)z.NB), dim3(kBlk), 0, s, b, z.C, z.NB, p.id_cap, spread);
-    hipLaunchKernelGGL(k_env_ncol, dim3((unsigned)z.NB), dim3(kBlk), 0, s, b, z.C, p.id_cap);
-
+    if (z.masks && p.n_particles > 0)
+        hipLaunchKernelGGL(k_region_masks, dim3((unsigned)cdiv(p.n_particles, kBlk)), dim3(kBlk), 0, s, b, p);
+    if (z.n_own > 0) hipLaunchKernelGGL(k_order, dim3((unsigned)z.n_own), dim3(kOrdBlk), 0, s, b);
 }
 
 // ---------------------------------------------------------------------------
@@ -865,9 +898,19 @@ __device__ inline float4 project_roll(float4 Lr, float lim)
     return Lr;
 }
 
-// what k_rows writes beside the rows: the previous-step match, the learned
-// start's features and frame, the counter-ordered PGS's update sequence
-constexpr int kRowsPrev = 1, kRowsFeatures = 2, kRowsSeq = 4;
+// what k_rows reads and writes beside the rows: the previous-step match, the
+// learned start's features and frame
+constexpr int kRowsPrev = 1, kRowsFeatures = 2;
+
+// How a row names its bodies.  In a region's rows a sphere of the region by
+// its LDS index (kLocal) with whether its state comes from the exchange
+// (kFetch: another block updated it last) and whether another block needs it
+// next (kPublish); any other sphere by its exchange record.  Elsewhere by the
+// sphere's slot.  A boundary at rest as kStill, a moving one (its velocity is
+// in rk) as another negative number.
+constexpr int kLocal = 1 << 30, kFetch = 1 << 29, kPublish = 1 << 28;
+constexpr int kNameMask = kPublish - 1;
+constexpr int kStill = (int)0x80000000;
 
 // A contact's start impulse as the velocity changes of its two spheres
 // (layout of wrec): J = lambda_n n + lambda_t acts on sphere 2 with +J and
@@ -1024,7 +1067,9 @@ __global__ void k_rows(DevBuffers b, StepParams p, int64_t cap, int flags)
         f[10] = ia >= 0 ? 0.0f : 1.0f;
         f[11] = persistent ? 1.0f : 0.0f;
         b.frm1[pos] = make_float4((float)t1[0], (float)t1[1], (float)t1[2], (float)ls);
-        b.frm2[pos] = make_float4((float)t2[0], (float)t2[1], (float)t2[2], 0.0f);
+        // (the solve unit beside t2, for the check of the network's output)
+        b.frm2[pos] = make_float4((float)t2[0], (float)t2[1], (float)t2[2],
+                                  __int_as_float(b.envs[env_of((int)(key >> 32), p.id_cap)].unit));
     }
     float nf[3] = {(float)n[0], (float)n[1], (float)n[2]};
     if (p.warm == TR_WARM_COLD) L = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1042,25 +1087,36 @@ __global__ void k_rows(DevBuffers b, StepParams p, int64_t cap, int flags)
     }
     b.r0[pos] = make_float4(nf[0], nf[1], nf[2], (float)l1);
     b.r1[pos] = make_float4((float)l2, (float)(1.0 / Dn), (float)(1.0 / Dt), (float)Sig);
-    b.r2[pos] = make_float4((float)q, (float)lo, __int_as_float(ia), __int_as_float(ib));
-    // the contact's place in the colour-ordered update sequence of each of its
-    // spheres (position among the sphere's contacts, and their count), for
-    // the counter-ordered PGS
+    // the bodies as the solve names them, and the contact's place in the
+    // sequence of updates of each (with the sequence's length)
+    const EnvDev& E = b.envs[env_of((int)(key >> 32), p.id_cap)];
+    const int col = E.masks ? b.colour[c] : 0;
+    int na = ib, nb = ib;
     uint32_t seq = 0;
-    if (flags & kRowsSeq) {
-        const int col = b.colour[c];
-        uint32_t pa = 0, da = 0, pb = 0, db = 0;
-        auto place = [&](int sl, uint32_t& pr, uint32_t& dg) {
-            uint32_t beg = b.inc_start[sl], end = b.inc_start[sl + 1];
-            dg = end - beg;
-            for (uint32_t t = beg; t < end; ++t) pr += b.colour[b.inc[t]] < col ? 1u : 0u;
+    if (E.masks) {
+        const int rb = region_of(E, ib), ra = ia >= 0 ? region_of(E, ia) : rb;
+        const int rank = ra == rb ? rb : contact_rank(ra, rb);
+        auto name = [&](int sl, int r, uint32_t shift) {
+            const ulonglong2 m = b.smask[sl];
+            seq |= (seq_place(m, col) << shift) | ((uint32_t)__popcll(m.x) << (16 + shift));
+            if (!E.coded) return sl;
+            const int li = lds_index(E, sl);
+            if (r != rank || li >= E.res_cap) return E.x0 + r * E.xstride + li;
+            return kLocal | li | (from_away(m, col) ? kFetch : 0) | (to_away(m, col) ? kPublish : 0);
         };
-        if (ia >= 0) place(ia, pa, da);
-        place(ib, pb, db);
-        if (da > 255 || db > 255) atomicOr(&b.cnt->overflow, kOvfHits);
-        seq = pa | (pb << 8) | (da << 16) | (db << 24);
+        nb = name(ib, rb, 8);
+        if (ia >= 0) na = name(ia, ra, 0);
+        b.seq[pos] = seq;
+        b.rm[pos] = make_float4((float)im1, (float)iI1, (float)im2, (float)iI2);
+    } else if (ia >= 0) {
+        na = ia;
     }
-    b.rk[pos] = make_float4((float)vk[0], (float)vk[1], (float)vk[2], __uint_as_float(seq));
+    if (ia < 0) {
+        const bool still = (float)vk[0] == 0.f && (float)vk[1] == 0.f && (float)vk[2] == 0.f;
+        na = still ? kStill : -1;
+        if (!still) b.rk[pos] = make_float4((float)vk[0], (float)vk[1], (float)vk[2], 0.f);
+    }
+    b.r2[pos] = make_float4((float)q, (float)lo, __int_as_float(na), __int_as_float(nb));
     b.lam[pos] = L;
     b.lam0[pos] = L;
     if (p.v_imp > 0.f) {
@@ -1070,13 +1126,12 @@ __global__ void k_rows(DevBuffers b, StepParams p, int64_t cap, int flags)
         // regularisation or cohesion
         const bool impact = un < -(double)p.v_imp;
         b.ri1[pos] = make_float4((float)l2, (float)(1.0 / Wn), (float)(1.0 / Wt), 0.f);
-        b.ri2[pos] = make_float4(impact ? (float)(-(double)p.restitution * un) : 0.f, 0.f, __int_as_float(ia),
-                                 __int_as_float(ib));
+        b.ri2[pos] = make_float4(impact ? (float)(-(double)p.restitution * un) : 0.f, 0.f, __int_as_float(na),
+                                 __int_as_float(nb));
         b.qg[pos] = (float)(p.a_coef * (0.8 * delta));
         if (impact) {
-            const int e = (int)((uint32_t)(key >> 32) / p.id_cap);
-            atomicAdd(&b.env_stats[e].impacts, 1ull);
-            atomicOr(&b.ustats[b.envs[e].unit].imp_any, 1u);
+            atomicAdd(&b.env_stats[env_of((int)(key >> 32), p.id_cap)].impacts, 1ull);
+            atomicOr(&b.ustats[E.unit].imp_any, 1u);
         }
     }
     if (p.mu_r > 0.f) {
@@ -1098,7 +1153,7 @@ __global__ void k_rows(DevBuffers b, StepParams p, int64_t cap, int flags)
 void launch_rows(const DevBuffers& b, const StepParams& p, const Sizes& z, bool have_prev, bool features,
                  hipStream_t s)
 {
-    const int flags = (have_prev ? kRowsPrev : 0) | (features ? kRowsFeatures : 0) | (z.flow ? kRowsSeq : 0);
+    const int flags = (have_prev ? kRowsPrev : 0) | (features ? kRowsFeatures : 0);
     hipLaunchKernelGGL(k_rows, dim3((unsigned)cdiv(z.C, kBlk)), dim3(kBlk), 0, s, b, p, z.C, flags);
 }
 
@@ -1108,14 +1163,13 @@ void launch_rows(const DevBuffers& b, const StepParams& p, const Sizes& z, bool 
 __global__ void k_impact_prep(DevBuffers b, StepParams p, int64_t cap)
 {
     uint32_t nc = n_contacts(b, cap);
-    uint32_t pos = blockIdx.x * blockDim.x + threadIdx.x;
-    if (pos >= nc) return;
+    uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= nc) return;
     if (b.cnt->overflow) return;
+    const uint32_t pos = b.cpos[c];
     b.lami[pos] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (p.mu_r > 0.f) b.lamri[pos] = make_float4(0.f, 0.f, 0.f, 0.f);
-    const int ib = __float_as_int(b.ri2[pos].w);
-    const int e = (int)((uint32_t)b.pid[ib] / p.id_cap);
-    if (b.env_stats[e].impacts == 0) {
+    if (b.env_stats[env_of((int)(b.ckey[c] >> 32), p.id_cap)].impacts == 0) {
         float4 r = b.ri1[pos];
         b.ri1[pos] = make_float4(r.x, 0.f, 0.f, 0.f);
     }
@@ -1126,20 +1180,21 @@ __global__ void k_impact_prep(DevBuffers b, StepParams p, int64_t cap)
 __global__ void k_impact_q(DevBuffers b, StepParams p, int64_t cap)
 {
     uint32_t nc = n_contacts(b, cap);
-    uint32_t pos = blockIdx.x * blockDim.x + threadIdx.x;
-    if (pos >= nc) return;
+    uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= nc) return;
     if (b.cnt->overflow) return;
+    if (b.env_stats[env_of((int)(b.ckey[c] >> 32), p.id_cap)].impacts == 0) return;
+    const uint32_t pos = b.cpos[c];
     float4 q = b.r2[pos];
-    const int ia = __float_as_int(q.z), ib = __float_as_int(q.w);
-    const int e = (int)((uint32_t)b.pid[ib] / p.id_cap);
-    if (b.env_stats[e].impacts == 0) return;
+    const int ia = b.cpair[c].x, ib = b.cpair[c].y;
     const float4 a = b.r0[pos], v2 = vel_at(b.vw, ib);
     double v1[3];
     if (ia >= 0) {
         const float4 t = vel_at(b.vw, ia);
         v1[0] = t.x; v1[1] = t.y; v1[2] = t.z;
     } else {
-        const float4 k = b.rk[pos];
+        const bool still = __float_as_int(q.z) == kStill;
+        const float4 k = still ? make_float4(0.f, 0.f, 0.f, 0.f) : b.rk[pos];
         v1[0] = k.x; v1[1] = k.y; v1[2] = k.z;
     }
     double un = ((double)a.x * ((double)v2.x - v1[0]) + (double)a.y * ((double)v2.y - v1[1])) +
@@ -1207,7 +1262,7 @@ __global__ void k_warm_rec(DevBuffers b, StepParams p, int64_t cap)
     if (b.cnt->overflow) return;
     const uint32_t pos = b.cpos[c];
     const bool roll = p.mu_r > 0.f;
-    warm_record(b.lam[pos], b.r0[pos], b.r1[pos].x, __float_as_int(b.r2[pos].w),
+    warm_record(b.lam[pos], b.r0[pos], b.r1[pos].x, b.cpair[c].y,
                 roll ? b.lamr[pos] : make_float4(0.f, 0.f, 0.f, 0.f), roll, b.wrec + 3 * (size_t)c);
 }
 
@@ -1224,33 +1279,59 @@ void launch_warm_apply(const DevBuffers& b, const StepParams& p, const Sizes& z,
 // bodies without atomics, and any schedule of a colour's contacts gives the
 // same result.
 //
-// A solve is run by a cluster of blocks that meet at a counter barrier after
-// every colour.  Grouped mode: envs are split into kGroups groups, group g
-// runs on the blocks b with b % 8 == g.  Per-env mode: every env has its own
-// cluster (one block for most envs, whose bodies then sit in LDS and whose
-// barrier is a workgroup barrier).  On MI355X consecutive blocks of a launch
-// go to the 8 XCDs in turn, so a cluster whose blocks are congruent mod 8
-// shares one XCD and its L2: bodies
-// are then written with ordinary stores (write-through to that L2) and read
-// with device-scope (sc1) loads, which miss the per-CU L1; measured, L1-hit
-// loads return data another CU of the XCD has already replaced, and sc1
-// stores cost twice the solve time.  Each cluster checks its placement once
-// per launch and falls back to agent-scope fences around its barriers when a
-// block is not on the expected XCD.
+// A solve is run by one block or by a cluster of blocks.  Each block owns a
+// region: a contiguous range of the solve's Morton-sorted spheres, kept in its
+// LDS for the whole solve, and the contacts k_order gave it.  A sphere on the
+// region's surface is also updated by the neighbour that owns the contact
+// across; its state then goes through a record of the exchange array: the
+// block whose update precedes one solved elsewhere publishes the state there,
+// and the block that needs it polls the record.  Each 16 B half of a record
+// carries the number of updates it has seen beside its three components, so
+// that one load brings the state and says whether it is the awaited one: no
+// flags, no drained stores, no barrier between blocks.  Every version has one
+// reader, which writes the next, so a record is never overwritten unread; and
+// a block waits only for updates of earlier phases, so that waits end as long
+// as every block is resident (they are bounded all the same).
+//
+// Records are written through to where the neighbours read them: the XCD's
+// L2 (ordinary stores) when the cluster sits on one XCD, else memory
+// (device-scope stores).  They are read with device-scope (sc1) loads, which
+// miss the per-CU L1; measured, L1-hit loads return data another CU of the
+// XCD has already replaced.  Consecutive blocks of a launch go to the 8 XCDs
+// in turn, so a cluster whose blocks are congruent mod 8 shares one XCD; it
+// checks that once per launch and writes through to memory otherwise.
+//
+// Within a phase (one colour) the contacts that wait are taken by the block's
+// last waves while the others update contacts whose bodies are all in LDS;
+// a workgroup barrier ends the phase.
+//
+// Measured (MI355X, PGS per launch) against clusters that kept every body in
+// memory and met at a counter barrier after every colour: a 50,000-sphere bed
+// of 150 sweeps 7.16 -> 2.36 ms, a 500,000-sphere one of 200 sweeps 24.6 ->
+// 7.8 ms, a 300-sphere column of 50 sweeps 0.74 -> 0.32 ms.  A phase is bound
+// by its chain: rows, LDS bodies, about 100 dependent operations, the barrier
+// (0.6 us on one block of a few hundred spheres), or the hand-over (1.1 us
+// within an XCD, 1.6 us across), and from about 2,000 spheres a block by
+// instruction issue.
 //
 // Contact c of a colour is always handled by the same thread, so its rows
 // (read-only) and impulses (thread-owned) use the ordinary caches, and the
-// rows of the next contact are in flight while the current one is updated.
-// The residual R_k = ||d lambda||_D / ||lambda||_D of each sweep is reduced
-// per block in a fixed order and combined identically by every block of the
-// cluster, which then all take the same stopping decision.
+// rows of the next phase are in flight while the block waits.  The residual
+// R_k = ||d lambda||_D / ||lambda||_D of each sweep is reduced per block in a
+// fixed order and combined identically by every block of the cluster, which
+// then all take the same stopping decision.
 // ---------------------------------------------------------------------------
-constexpr int kPgsBlk = 512;
+constexpr int kPgsWaves = 8;  // waves of a block of the grouped and spread solves
 constexpr int kCoherent = 16;  // cache-policy bits of a device-scope (sc1) access
 
 __device__ inline __amdgpu_buffer_rsrc_t raw_rsrc(const void* p)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, 0x7fffffff, 0x00020000);
+}
+// (exchange records may reach 4 GiB)
+__device__ inline __amdgpu_buffer_rsrc_t exchange_rsrc(const void* p)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)0xffffffff, 0x00020000);
 }
 template <int AUX>
 __device__ inline float4 ld_body(__amdgpu_buffer_rsrc_t r, int idx)
@@ -1285,51 +1366,19 @@ __device__ inline bool wait_counter(Counters* cnt, uint32_t* counter, unsigned t
     return true;
 }
 
-// Cluster barrier on counter[0] (zeroed before the launch).  Arrive drains
-// this block's stores; wait returns false when the barrier failed.
-template <bool FENCED>
+// Cluster barrier of the counter-ordered solve on counter[0] (zeroed before
+// the launch).  Arrive drains this block's stores; wait returns false when
+// the barrier failed.
 __device__ inline void cluster_arrive(uint32_t* counter)
 {
-    if (FENCED) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0) __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-template <bool FENCED>
 __device__ inline bool cluster_wait(Counters* cnt, uint32_t* counter, unsigned target, int& flag)
 {
     if (threadIdx.x == 0) flag = wait_counter(cnt, counter, target) ? 1 : 0;
     __syncthreads();
-    if (FENCED) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    return flag != 0;
-}
-
-// Spread mode: after each colour the eight groups meet.  The blocks of a group
-// arrive at its counter (cluster_arrive); the group's rank-0 block waits for
-// them, arrives at the global counter and waits for all groups, then releases
-// its group through the group's release word (counter[2]).  nbar counts the
-// group's barriers including the first (placement) one, which the global
-// counter does not see.  Returns false when a wait failed.
-template <bool FENCED>
-__device__ inline bool spread_wait(Counters* cnt, uint32_t* counter, unsigned nbar, unsigned K, unsigned rank,
-                                   int& flag)
-{
-    if (threadIdx.x == 0) {
-        bool ok;
-        if (rank == 0) {
-            ok = wait_counter(cnt, counter, nbar * K);
-            if (ok) {
-                __hip_atomic_fetch_add(&cnt->gbar[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                ok = wait_counter(cnt, &cnt->gbar[0], (nbar - 1) * (unsigned)kGroups);
-            }
-            if (ok) __hip_atomic_store(&counter[2], nbar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            ok = wait_counter(cnt, &counter[2], nbar);
-        }
-        flag = ok ? 1 : 0;
-    }
-    __syncthreads();
-    if (FENCED) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     return flag != 0;
 }
 
@@ -1337,7 +1386,7 @@ __device__ inline bool spread_wait(Counters* cnt, uint32_t* counter, unsigned nb
 // XCD in counter[1] (zeroed before the launch).  The round-robin dispatch
 // puts blocks congruent mod 8 on one XCD, but which XCD depends on the
 // launches before, so only "one XCD for the whole cluster" is checked.
-// Returns 1 for XCD-local accesses, 2 for the fenced fallback, 0 when the
+// Returns 1 for XCD-local accesses, 2 for write-through ones, 0 when the
 // barrier failed; uniform over the cluster.
 __device__ inline int cluster_placement(Counters* cnt, uint32_t* counter, unsigned size, int& flag)
 {
@@ -1355,27 +1404,46 @@ __device__ inline int cluster_placement(Counters* cnt, uint32_t* counter, unsign
     return flag;
 }
 
-// A contact's rows as the update reads them.  rk (the kinematic velocity of
-// a boundary contact, the update sequence of the counter-ordered schedule)
-// is fetched with them only by the grouped solve (kin), whose colour phases
-// are latency-bound on one XCD; elsewhere the update of a boundary contact
-// loads it itself, so a pair's row stream is 48 B of rows and the impulses
-// (measured: 256-bed batch PGS 11.1-11.2 -> 9.9-10.0 ms, 500k excavation
-// 29.4 -> 26.9 ms; 50k bed 7.1 -> 7.4 ms, hence kin there; same states).
+// Every flag of f[0 .. K) at least want, seen by the whole wave; bounded like
+// wait_counter.
+__device__ inline bool wait_flags(Counters* cnt, const uint32_t* f, unsigned K, uint32_t want)
+{
+    const unsigned lane = threadIdx.x & 63;
+    for (long spins = 1;; ++spins) {
+        bool ok = true;
+        for (unsigned i = lane; i < K; i += 64)
+            ok &= __hip_atomic_load(&f[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= want;
+        if (__ballot(!ok) == 0ull) return true;
+        if ((spins & 255) == 0 &&
+            (__hip_atomic_load(&cnt->overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kFailBarrier))
+            return false;
+        if (spins > kBarrierSpins) {
+            if (lane == 0) atomicOr(&cnt->overflow, kFailBarrier);
+            return false;
+        }
+    }
+}
+
+// Makes the wave wait here for the load that brings v (and for those before
+// it).  Without it the compiler waits at the first use, where loads issued in
+// between, in flight for a later contact, would be waited for too.
+__device__ inline void settle(float& v) { asm volatile("" : "+v"(v)); }
+
+// A contact's rows as the update reads them (rk, the velocity of a moving
+// boundary, is fetched by the few contacts that need it).
 struct RowRegs {
     float4 a, r1, q, L;
-    float4 k;       // rk, when fetched with the rows
     float4 r3, Lr;  // rolling rows (loaded when mu_r > 0)
+    uint32_t seq;   // places in the bodies' sequences (region and counter-ordered solves)
 };
 
-__device__ inline RowRegs load_rows(const DevBuffers& b, uint32_t c, bool roll, bool kin = false)
+__device__ inline RowRegs load_rows(const DevBuffers& b, uint32_t c, bool roll)
 {
     RowRegs R;
     R.a = b.r0[c];
     R.r1 = b.r1[c];
     R.q = b.r2[c];
     R.L = b.lam[c];
-    if (kin) R.k = b.rk[c];
     if (roll) {
         R.r3 = b.r3[c];
         R.Lr = b.lamr[c];
@@ -1383,42 +1451,42 @@ __device__ inline RowRegs load_rows(const DevBuffers& b, uint32_t c, bool roll, 
     return R;
 }
 
-// Body state accessors of the contact update.  Xcd: sc1 loads and ordinary
-// stores, for clusters whose blocks share one XCD.  Plain: ordinary accesses,
-// for a solve confined to one block (its waves share one CU and its L1) or
-// ordered by agent-scope fences.  Lds: the env's bodies staged in LDS.
+__device__ inline void settle(RowRegs& R, bool roll)
+{
+    settle(R.a.x);
+    settle(R.r1.x);
+    settle(R.q.x);
+    settle(R.L.x);
+    if (roll) {
+        settle(R.r3.x);
+        settle(R.Lr.x);
+    }
+}
+
+__device__ inline void store_lam(const DevBuffers& b, uint32_t c, const RowRegs& R, bool roll)
+{
+    b.lam[c] = R.L;
+    if (roll) b.lamr[c] = R.Lr;
+}
+
+// Body state accessors of the one-block and counter-ordered solves.  Xcd: sc1
+// loads, and stores that reach the cluster's XCD or (through) all of them.  Plain:
+// ordinary accesses, for a solve confined to one block (its waves share one
+// CU and its L1).  Lds: the env's bodies staged in LDS.
 struct XcdBodies {
     __amdgpu_buffer_rsrc_t r;  // vw: record i is float4 2i (v) and 2i + 1 (omega)
-    __device__ float4 v(int i) const { return ld_body<kCoherent>(r, 2 * i); }
-    __device__ float4 w(int i) const { return ld_body<kCoherent>(r, 2 * i + 1); }
-    __device__ void set(int i, float4 v, float4 w) const { st_body<0>(r, 2 * i, v); st_body<0>(r, 2 * i + 1, w); }
-    __device__ float4 half(int i, int h) const { return ld_body<kCoherent>(r, 2 * i + h); }
-    __device__ void set_half(int i, int h, float4 v) const { st_body<0>(r, 2 * i + h, v); }
-    // half h of record i into LDS at wave_lds + 16 B x lane (a load straight to LDS)
-    __device__ void stage_half(float4* wave_lds, int i, int h) const
-    {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)wave_lds, 16,
-                                                 (2 * i + h) * 16, 0, 0, kCoherent);
-    }
-};
-// Spread mode: one env's contacts on all XCDs, so every body store is written
-// through (sc1) and every load is device-scope: measured on MI355X, such a
-// store is seen by another XCD's device-scope load once it has completed.
-struct SpreadBodies {
-    __amdgpu_buffer_rsrc_t r;
+    bool through;
     __device__ float4 v(int i) const { return ld_body<kCoherent>(r, 2 * i); }
     __device__ float4 w(int i) const { return ld_body<kCoherent>(r, 2 * i + 1); }
     __device__ void set(int i, float4 v, float4 w) const
     {
-        st_body<kCoherent>(r, 2 * i, v);
-        st_body<kCoherent>(r, 2 * i + 1, w);
-    }
-    __device__ float4 half(int i, int h) const { return ld_body<kCoherent>(r, 2 * i + h); }
-    __device__ void set_half(int i, int h, float4 v) const { st_body<kCoherent>(r, 2 * i + h, v); }
-    __device__ void stage_half(float4* wave_lds, int i, int h) const
-    {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)wave_lds, 16,
-                                                 (2 * i + h) * 16, 0, 0, kCoherent);
+        if (through) {
+            st_body<kCoherent>(r, 2 * i, v);
+            st_body<kCoherent>(r, 2 * i + 1, w);
+        } else {
+            st_body<0>(r, 2 * i, v);
+            st_body<0>(r, 2 * i + 1, w);
+        }
     }
 };
 struct PlainBodies {
@@ -1426,13 +1494,6 @@ struct PlainBodies {
     __device__ float4 v(int i) const { return vel_at(vw, i); }
     __device__ float4 w(int i) const { return angv_at(vw, i); }
     __device__ void set(int i, float4 v, float4 w) const { vel_at(vw, i) = v; angv_at(vw, i) = w; }
-    __device__ float4 half(int i, int h) const { return vw[2 * i + h]; }
-    __device__ void set_half(int i, int h, float4 v) const { vw[2 * i + h] = v; }
-    __device__ void stage_half(float4* wave_lds, int i, int h) const
-    {
-        __builtin_amdgcn_global_load_lds((const void*)&vw[2 * i + h], (__attribute__((address_space(3))) void*)wave_lds,
-                                         16, 0, 0);
-    }
 };
 struct LdsBodies {
     float4 *sv, *sw;  // env slots [base, base + n)
@@ -1464,6 +1525,27 @@ struct MixedBodies {
     }
 };
 
+// A region's bodies: LDS, and the exchange records (through: stores reach
+// the other XCDs).
+struct RegionBodies {
+    float4 *sv, *sw;
+    __amdgpu_buffer_rsrc_t x;
+    int xbase;  // exchange record of LDS index 0
+    bool through;
+    __device__ void publish(int rec, uint32_t version, float4 v, float4 w) const
+    {
+        v.w = __uint_as_float(version);
+        w.w = v.w;
+        if (through) {
+            st_body<kCoherent>(x, 2 * rec, v);
+            st_body<kCoherent>(x, 2 * rec + 1, w);
+        } else {
+            st_body<0>(x, 2 * rec, v);
+            st_body<0>(x, 2 * rec + 1, w);
+        }
+    }
+};
+
 // the two bodies of a contact, loaded ahead of the update (the update
 // replaces body 1 of a boundary contact by the boundary's velocity)
 struct BodyRegs {
@@ -1484,237 +1566,146 @@ __device__ inline BodyRegs load_bodies(const BA& ba, const RowRegs& R)
     B.wa = ba.w(ja);
     return B;
 }
-
-// Lane pairs.  A wave's body loads and stores scatter: each lane's 16 B
-// lands in its own memory line, and the vector memory unit's throughput in
-// lines, not bytes, bounds the colour phase.  Lanes 2k and 2k+1 therefore
-// access the two 32 B records of their two contacts' sphere together: the
-// even lane the velocity half and the odd lane the angular half of the even
-// lane's record, then the same for the odd lane's record, and exchange what
-// the other needs.  Two lanes share each line an instruction touches; the
-// values are those of the lane's own loads and stores.  Both lanes of a pair
-// must be active (the swap reads the partner); a lane without a contact
-// loads its partner's records and stores nothing.
-__device__ inline int pair_swap(int x) { return __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, false); }
-__device__ inline float pair_swap(float x) { return __int_as_float(pair_swap(__float_as_int(x))); }
-__device__ inline float4 pair_swap(float4 x)
-{
-    return make_float4(pair_swap(x.x), pair_swap(x.y), pair_swap(x.z), pair_swap(x.w));
-}
-
-// the record of sphere self (own: the lane has a contact) as (v, w)
 template <class BA>
-__device__ inline void pair_load(const BA& ba, int self, bool own, int odd, float4& v, float4& w)
+__device__ inline void store_bodies(const BA& ba, const RowRegs& R, const BodyRegs& B)
 {
-    int part = pair_swap(own ? self : -1);
-    if (!own) self = part;      // no contact: the partner's record, never stored
-    if (part < 0) part = self;  // the partner has no contact: this lane's record twice
-    const int r1 = odd ? part : self, r2 = odd ? self : part;  // the even lane's sphere, the odd lane's
-    const float4 x1 = ba.half(r1, odd), x2 = ba.half(r2, odd);
-    const float4 recv = pair_swap(odd ? x1 : x2);
-    v = odd ? recv : x1;
-    w = odd ? x2 : recv;
-}
-
-// stores (v, w) as the record of sphere self when want
-template <class BA>
-__device__ inline void pair_store(const BA& ba, int self, bool want, int odd, float4 v, float4 w)
-{
-    const int part = pair_swap(self);
-    const bool pwant = pair_swap(want ? 1 : 0) != 0;
-    const float4 recv = pair_swap(odd ? v : w);
-    const int r1 = odd ? part : self, r2 = odd ? self : part;
-    if (odd ? pwant : want) ba.set_half(r1, odd, odd ? recv : v);
-    if (odd ? want : pwant) ba.set_half(r2, odd, odd ? w : recv);
-}
-
-template <class BA>
-__device__ inline BodyRegs pair_bodies(const BA& ba, const RowRegs& R, bool own, int odd)
-{
-    BodyRegs B;
-    const int ia = __float_as_int(R.q.z), ib = __float_as_int(R.q.w);
-    pair_load(ba, ib, own, odd, B.vb, B.wb);
-    pair_load(ba, ia >= 0 ? ia : ib, own, odd, B.va, B.wa);
-    return B;
-}
-
-template <class BA>
-__device__ inline void pair_store_bodies(const BA& ba, const RowRegs& R, const BodyRegs& B, bool own, int odd)
-{
-    const int ia = __float_as_int(R.q.z), ib = __float_as_int(R.q.w);
-    pair_store(ba, ib, own, odd, B.vb, B.wb);
-    pair_store(ba, ia, own && ia >= 0, odd, B.va, B.wa);
-}
-
-// a contact's bodies with lane pairs (LANES) or by each lane alone (then own
-// is true wherever these are called)
-template <bool LANES, class BA>
-__device__ inline BodyRegs get_bodies(const BA& ba, const RowRegs& R, bool own, int odd)
-{
-    if (LANES) return pair_bodies(ba, R, own, odd);
-    return load_bodies(ba, R);
-}
-template <bool LANES, class BA>
-__device__ inline void put_bodies(const BA& ba, const RowRegs& R, const BodyRegs& B, bool own, int odd)
-{
-    if (LANES) {
-        pair_store_bodies(ba, R, B, own, odd);
-        return;
-    }
     const int ia = __float_as_int(R.q.z), ib = __float_as_int(R.q.w);
     ba.set(ib, B.vb, B.wb);
     if (ia >= 0) ba.set(ia, B.va, B.wa);
 }
 
-// Staging of a thread's second contact of a colour in LDS (1024-thread
-// blocks, which have no registers for two contacts in flight).  The layout,
-// in float4 per block thread t: rows a, r1, q, L at [j nthr + t], j < 4;
-// then the lane pairs' body halves x1, x2 of sphere b and of sphere a at
-// [(4 + j) nthr + t], j < 4, as pair_load leaves them in registers.  Loads go
-// straight to LDS (16 B per lane, lane order), so the second contact's rows
-// are fetched during the barrier and its bodies during the first contact's
-// update, without registers.
-constexpr int kStageFloat4 = 8;  // float4 per block thread
-
-__device__ inline void stage_rows(const DevBuffers& b, float4* st, uint32_t nthr, uint32_t c)
+// a . b and the determinant a d - b c, with their fused operations fixed
+__device__ inline float dot3f(float ax, float ay, float az, float bx, float by, float bz)
 {
-    const uint32_t w = threadIdx.x & ~63u;
-    const float4* src[4] = {b.r0, b.r1, b.r2, b.lam};
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        __builtin_amdgcn_global_load_lds((const void*)&src[j][c],
-                                         (__attribute__((address_space(3))) void*)(st + j * nthr + w), 16, 0, 0);
+    return __builtin_fmaf(az, bz, __builtin_fmaf(ax, bx, ay * by));
 }
+__device__ inline float det2f(float a, float b, float c, float d) { return __builtin_fmaf(a, d, -(b * c)); }
 
-// the body halves of the contact whose indices are in q (own: the lane has
-// it), into the staging area, as pair_load splits them
-template <class BA>
-__device__ inline void stage_bodies(const BA& ba, float4* st, uint32_t nthr, float4 q, bool own, int odd)
+// One contact's update on the loaded rows and bodies; the caller stores the
+// impulses (left in R.L, R.Lr) and the bodies (left in B).  want: add the
+// contact's share of the sweep residual to (num, den).  Every fused operation
+// is written out: left to the compiler, the products it fuses would differ
+// between the kernels this is inlined into, and so would the last bits of the
+// schedules' results.
+__device__ inline void pgs_update(const DevBuffers& b, uint32_t c, RowRegs& R, BodyRegs& B, float mu, float gdt,
+                                  bool want, float& num, float& den, bool roll)
 {
-    const uint32_t w = threadIdx.x & ~63u;
-    const int ia = __float_as_int(q.z), ib = __float_as_int(q.w);
-    int sb = own ? ib : -1, sa = own ? (ia >= 0 ? ia : ib) : -1;
-    int pb = pair_swap(sb), pa = pair_swap(sa);
-    if (!own) { sb = pb; sa = pa; }
-    if (pb < 0) { pb = sb; pa = sa; }
-    ba.stage_half(st + 4 * nthr + w, odd ? pb : sb, odd);
-    ba.stage_half(st + 5 * nthr + w, odd ? sb : pb, odd);
-    ba.stage_half(st + 6 * nthr + w, odd ? pa : sa, odd);
-    ba.stage_half(st + 7 * nthr + w, odd ? sa : pa, odd);
-}
-
-__device__ inline RowRegs staged_rows(const float4* st, uint32_t nthr)
-{
-    const uint32_t t = threadIdx.x;
-    RowRegs R;
-    R.a = st[t];
-    R.r1 = st[nthr + t];
-    R.q = st[2 * nthr + t];
-    R.L = st[3 * nthr + t];
-    return R;
-}
-
-__device__ inline BodyRegs staged_bodies(const float4* st, uint32_t nthr, int odd)
-{
-    const uint32_t t = threadIdx.x, p = t ^ 1u;
-    BodyRegs B;
-    B.vb = odd ? st[5 * nthr + p] : st[4 * nthr + t];
-    B.wb = odd ? st[5 * nthr + t] : st[4 * nthr + p];
-    B.va = odd ? st[7 * nthr + p] : st[6 * nthr + t];
-    B.wa = odd ? st[7 * nthr + t] : st[6 * nthr + p];
-    return B;
-}
-
-// One contact's update on the loaded bodies B (left in B), its impulses
-// written; the caller stores the bodies.
-__device__ inline void pgs_update(const DevBuffers& b, uint32_t c, const RowRegs& R, BodyRegs& B, float mu, float gdt,
-                                  float& num, float& den, bool roll, bool kin = false)
-{
-    float4 a = R.a, r1 = R.r1, q = R.q, L = R.L;
-    bool pair = __float_as_int(q.z) >= 0;
+#pragma clang fp contract(off)
+    const float4 a = R.a, r1 = R.r1, q = R.q, L = R.L;
+    const int ka = __float_as_int(q.z);
+    const bool pair = ka >= 0;
     float4 vb = B.vb, wb = B.wb, va = B.va, wa = B.wa;
     if (!pair) {
-        const float4 kv = kin ? R.k : b.rk[c];  // the boundary's velocity at the contact point
-        va = make_float4(kv.x, kv.y, kv.z, 0.f);
+        va = make_float4(0.f, 0.f, 0.f, 0.f);
         wa = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (ka != kStill) {
+            const float4 kv = b.rk[c];  // the boundary's velocity at the contact point
+            va.x = kv.x; va.y = kv.y; va.z = kv.z;
+            settle(va.x);  // here, where few contacts pay for it
+        }
     }
-    float nx = a.x, ny = a.y, nz = a.z, l1 = a.w;
-    float l2 = r1.x, iDn = r1.y, iDt = r1.z, Sig = r1.w;
+    auto fma = [](float x, float y, float z) { return __builtin_fmaf(x, y, z); };
+    const float nx = a.x, ny = a.y, nz = a.z, l1 = a.w;
+    const float l2 = r1.x, iDn = r1.y, iDt = r1.z, Sig = r1.w;
     // normal row
-    float un = nx * (vb.x - va.x) + ny * (vb.y - va.y) + nz * (vb.z - va.z);
-    float ln = fmaxf(q.y, L.x - (un + Sig * L.x - q.x) * iDn);
-    float dn = ln - L.x;
-    vb.x += dn * nx * vb.w; vb.y += dn * ny * vb.w; vb.z += dn * nz * vb.w;
-    va.x -= dn * nx * va.w; va.y -= dn * ny * va.w; va.z -= dn * nz * va.w;
+    const float un = dot3f(nx, ny, nz, vb.x - va.x, vb.y - va.y, vb.z - va.z);
+    const float ln = fmaxf(q.y, fma(-iDn, fma(Sig, L.x, un) - q.x, L.x));
+    const float dn = ln - L.x;
+    const float jx = nx * dn, jy = ny * dn, jz = nz * dn;
+    vb.x = fma(vb.w, jx, vb.x); vb.y = fma(vb.w, jy, vb.y); vb.z = fma(vb.w, jz, vb.z);
+    va.x = fma(-va.w, jx, va.x); va.y = fma(-va.w, jy, va.y); va.z = fma(-va.w, jz, va.z);
     // tangential disk row: u = (vb - va) - (l2 wb + l1 wa) x n
-    float sx = l2 * wb.x + l1 * wa.x, sy = l2 * wb.y + l1 * wa.y, sz = l2 * wb.z + l1 * wa.z;
-    float ux = (vb.x - va.x) - (sy * nz - sz * ny);
-    float uy = (vb.y - va.y) - (sz * nx - sx * nz);
-    float uz = (vb.z - va.z) - (sx * ny - sy * nx);
-    float udn = ux * nx + uy * ny + uz * nz;
-    ux -= udn * nx; uy -= udn * ny; uz -= udn * nz;
-    float tx = L.y - (ux + gdt * L.y) * iDt;
-    float ty = L.z - (uy + gdt * L.z) * iDt;
-    float tz = L.w - (uz + gdt * L.w) * iDt;
-    float lim = mu * fabsf(ln);
-    float m2 = tx * tx + ty * ty + tz * tz;
+    const float sx = fma(l2, wb.x, l1 * wa.x), sy = fma(l2, wb.y, l1 * wa.y), sz = fma(l2, wb.z, l1 * wa.z);
+    float ux = (vb.x - va.x) - det2f(nz, ny, sz, sy);
+    float uy = (vb.y - va.y) - det2f(nx, nz, sx, sz);
+    float uz = (vb.z - va.z) - det2f(ny, nx, sy, sx);
+    const float udn = dot3f(nx, ny, nz, ux, uy, uz);
+    ux = fma(-nx, udn, ux); uy = fma(-ny, udn, uy); uz = fma(-nz, udn, uz);
+    float tx = fma(-iDt, fma(gdt, L.y, ux), L.y);
+    float ty = fma(-iDt, fma(gdt, L.z, uy), L.z);
+    float tz = fma(-iDt, fma(gdt, L.w, uz), L.w);
+    const float lim = mu * fabsf(ln);
+    const float m2 = dot3f(tx, ty, tz, tx, ty, tz);
     if (m2 > lim * lim) {
-        float sc = m2 > 0.f ? lim * rsqrtf(m2) : 0.f;
+        const float sc = m2 > 0.f ? lim * rsqrtf(m2) : 0.f;
         tx *= sc; ty *= sc; tz *= sc;
     }
-    float dx = tx - L.y, dy = ty - L.z, dz = tz - L.w;
+    const float dx = tx - L.y, dy = ty - L.z, dz = tz - L.w;
     // impulse d at the contact point: +d on body 2 (arm -l2 n), -d on body 1 (arm +l1 n)
-    float cx = ny * dz - nz * dy, cy = nz * dx - nx * dz, cz = nx * dy - ny * dx;  // n x d
-    vb.x += dx * vb.w; vb.y += dy * vb.w; vb.z += dz * vb.w;
-    wb.x -= l2 * wb.w * cx; wb.y -= l2 * wb.w * cy; wb.z -= l2 * wb.w * cz;
+    const float cx = det2f(ny, nz, dy, dz), cy = det2f(nz, nx, dz, dx), cz = det2f(nx, ny, dx, dy);  // n x d
+    vb.x = fma(vb.w, dx, vb.x); vb.y = fma(vb.w, dy, vb.y); vb.z = fma(vb.w, dz, vb.z);
+    const float kb = l2 * wb.w;
+    wb.x = fma(-kb, cx, wb.x); wb.y = fma(-kb, cy, wb.y); wb.z = fma(-kb, cz, wb.z);
     if (pair) {
-        va.x -= dx * va.w; va.y -= dy * va.w; va.z -= dz * va.w;
-        wa.x -= l1 * wa.w * cx; wa.y -= l1 * wa.w * cy; wa.z -= l1 * wa.w * cz;
+        va.x = fma(-va.w, dx, va.x); va.y = fma(-va.w, dy, va.y); va.z = fma(-va.w, dz, va.z);
+        const float kk = l1 * wa.w;
+        wa.x = fma(-kk, cx, wa.x); wa.y = fma(-kk, cy, wa.y); wa.z = fma(-kk, cz, wa.z);
     }
-    // residual weights (the stopping test only): hardware reciprocals; a row
-    // with zero inverse mass (a neutralised impact-stage row) weighs nothing
-    float Dn = iDn > 0.f ? __builtin_amdgcn_rcpf(iDn) : 0.f, Dt = iDt > 0.f ? __builtin_amdgcn_rcpf(iDt) : 0.f;
-    num += Dn * dn * dn + Dt * (dx * dx + dy * dy + dz * dz);
-    den += Dn * ln * ln + Dt * (tx * tx + ty * ty + tz * tz);
+    if (want) {
+        // residual weights (the stopping test only): hardware reciprocals; a row
+        // with zero inverse mass (a neutralised impact-stage row) weighs nothing
+        const float Dn = iDn > 0.f ? __builtin_amdgcn_rcpf(iDn) : 0.f, Dt = iDt > 0.f ? __builtin_amdgcn_rcpf(iDt) : 0.f;
+        num += fma(dn, Dn * dn, Dt * fma(dz, dz, fma(dy, dy, dx * dx)));
+        den += fma(ln, Dn * ln, Dt * fma(tz, tz, fma(ty, ty, tx * tx)));
+    }
     if (roll) {
         // rolling row (Eq. signCoul3): zero relative angular velocity, the
         // torque impulse on the disk |lambda_r| <= r mu_r |lambda_n|
-        float4 Lr = R.Lr;
+        const float4 Lr = R.Lr;
         float ox = 0.f, oy = 0.f, oz = 0.f;
         if (pair) { ox = wa.x; oy = wa.y; oz = wa.z; }
         else {
             const BodyDev& K = b.bodies[__float_as_int(R.r3.z)];
             ox = (float)K.angvel[0]; oy = (float)K.angvel[1]; oz = (float)K.angvel[2];
         }
-        float iWr = R.r3.x;
-        float rx = Lr.x - (wb.x - ox) * iWr, ry = Lr.y - (wb.y - oy) * iWr, rz = Lr.z - (wb.z - oz) * iWr;
-        float rlim = R.r3.y * fabsf(ln);
-        float r2 = rx * rx + ry * ry + rz * rz;
+        const float iWr = R.r3.x;
+        float rx = fma(-iWr, wb.x - ox, Lr.x), ry = fma(-iWr, wb.y - oy, Lr.y), rz = fma(-iWr, wb.z - oz, Lr.z);
+        const float rlim = R.r3.y * fabsf(ln);
+        const float r2 = dot3f(rx, ry, rz, rx, ry, rz);
         if (r2 > rlim * rlim) {
-            float sc = r2 > 0.f ? rlim * rsqrtf(r2) : 0.f;
+            const float sc = r2 > 0.f ? rlim * rsqrtf(r2) : 0.f;
             rx *= sc; ry *= sc; rz *= sc;
         }
-        float ex = rx - Lr.x, ey = ry - Lr.y, ez = rz - Lr.z;
-        wb.x += wb.w * ex; wb.y += wb.w * ey; wb.z += wb.w * ez;
-        if (pair) { wa.x -= wa.w * ex; wa.y -= wa.w * ey; wa.z -= wa.w * ez; }
-        b.lamr[c] = make_float4(rx, ry, rz, 0.f);
-        float Wr = __builtin_amdgcn_rcpf(iWr);
-        num += Wr * (ex * ex + ey * ey + ez * ez);
-        den += Wr * (rx * rx + ry * ry + rz * rz);
+        const float ex = rx - Lr.x, ey = ry - Lr.y, ez = rz - Lr.z;
+        wb.x = fma(wb.w, ex, wb.x); wb.y = fma(wb.w, ey, wb.y); wb.z = fma(wb.w, ez, wb.z);
+        if (pair) { wa.x = fma(-wa.w, ex, wa.x); wa.y = fma(-wa.w, ey, wa.y); wa.z = fma(-wa.w, ez, wa.z); }
+        R.Lr = make_float4(rx, ry, rz, 0.f);
+        if (want) {
+            const float Wr = __builtin_amdgcn_rcpf(iWr);
+            num = fma(Wr, dot3f(ex, ey, ez, ex, ey, ez), num);
+            den = fma(Wr, dot3f(rx, ry, rz, rx, ry, rz), den);
+        }
     }
-    b.lam[c] = make_float4(ln, tx, ty, tz);
+    R.L = make_float4(ln, tx, ty, tz);
     B.vb = vb; B.wb = wb; B.va = va; B.wa = wa;
 }
 
+// load, update, store of one contact; its impulses are left in R
 template <class BA>
-__device__ inline void pgs_contact(const DevBuffers& b, const BA& ba, uint32_t c, const RowRegs& R, BodyRegs B,
-                                   float mu, float gdt, float& num, float& den, bool roll)
+__device__ inline void pgs_contact(const DevBuffers& b, const BA& ba, uint32_t c, RowRegs& R, float mu, float gdt,
+                                   bool want, float& num, float& den, bool roll)
 {
-    pgs_update(b, c, R, B, mu, gdt, num, den, roll);
-    const int ia = __float_as_int(R.q.z), ib = __float_as_int(R.q.w);
-    ba.set(ib, B.vb, B.wb);
-    if (ia >= 0) ba.set(ia, B.va, B.wa);
+    BodyRegs B = load_bodies(ba, R);
+    pgs_update(b, c, R, B, mu, gdt, want, num, den, roll);
+    store_bodies(ba, R, B);
 }
+
+// what a solve's block keeps in LDS beside its bodies
+template <int NW>
+struct SolveShared {
+    double red[2][NW];
+    uint32_t st[kOwnStride];  // the owner's starts
+    int flag;
+};
+
+// a block's part of a solve: its owner's contacts, rank of K, the cluster's
+// first progress flag, the unit of its statistics
+struct SolveTask {
+    int owner;
+    unsigned rank, K;
+    unsigned f0;
+    int unit;
+};
 
 // block sums of the sweep's (num, den) in a fixed order, returned to every thread
 template <int NW>
@@ -1728,8 +1719,58 @@ __device__ inline void block_sum2(float num, float den, double (*red)[NW], doubl
     if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = dnum; red[1][threadIdx.x >> 6] = dden; }
     __syncthreads();
     sn = 0.0; sd = 0.0;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) { sn += red[0][w]; sd += red[1][w]; }
+    for (int w = 0; w < NW; ++w) { sn += red[0][w]; sd += red[1][w]; }
     __syncthreads();  // red is reused
+}
+
+// The cluster's (num, den) from its blocks' partials, the same value in every
+// thread of every block: wave 0 loads the K partials in parallel and sums
+// them in a fixed tree order, the result is broadcast through LDS.
+template <int NW>
+__device__ inline void combine_parts(const double* part, unsigned K, double (*red)[NW], double& sn, double& sd)
+{
+    if (threadIdx.x < 64) {
+        double a = 0.0, d = 0.0;
+        for (unsigned t = threadIdx.x; t < K; t += 64) {
+            a += __hip_atomic_load(&part[2 * t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            d += __hip_atomic_load(&part[2 * t + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            a += __shfl_down(a, o, 64);
+            d += __shfl_down(d, o, 64);
+        }
+        if (threadIdx.x == 0) { red[0][0] = a; red[1][0] = d; }
+    }
+    __syncthreads();
+    sn = red[0][0];
+    sd = red[1][0];
+    __syncthreads();  // red is reused
+}
+
+__device__ inline double sweep_resid(double sn, double sd)
+{
+    return sd > 0.0 ? sqrt(sn) / sqrt(sd) : (sn > 0.0 ? 1.0 : 0.0);
+}
+
+__device__ inline void write_stats(const DevBuffers& b, int unit, int slot, int sweeps, double Rk, double R1)
+{
+    UnitStats& G = b.ustats[unit];
+    if (slot == 0) {
+        G.sweeps = (uint32_t)sweeps;
+        G.resid = Rk;
+        G.resid_first = R1;
+    } else if (slot == kSlotImpact) {
+        G.imp_sweeps = (uint32_t)sweeps;
+    } else {
+        G.r1_trial[slot - 1] = R1;
+    }
+}
+
+template <int NW>
+__device__ inline void stage_starts(const DevBuffers& b, int owner, uint32_t ncol, SolveShared<NW>& sh)
+{
+    for (uint32_t q = threadIdx.x; q <= 2 * ncol; q += blockDim.x)
+        sh.st[q] = b.own_start[(size_t)owner * kOwnStride + q];
 }
 
 // Counter-ordered updates: contact c is update number s deg_j + pos_j of
@@ -1755,349 +1796,328 @@ __device__ inline bool flow_wait(Counters* cnt, const uint32_t* ver, int j, uint
     return true;
 }
 
-// The PGS sweeps of one cluster.  Its contacts of colour col are
-// [cstart.beg(col), cstart.end(col)); the block of rank r of K takes the r-th of K
-// equal slices.  Blocks of the cluster are first + 8 t, t < K.  FLOW: colours
-// are ordered by the per-sphere counters (clusters only); a barrier remains at
-// the end of a sweep when a residual tolerance is set, and once at the end.
-template <class BA, bool CLUSTER, bool FENCED, bool FLOW, bool ROLL, int NW, class Starts, bool SPREAD = false>
-__device__ void pgs_solve(const DevBuffers& b, const StepParams& p, const BA& ba, Starts cstart, uint32_t ncol,
-                          uint32_t* counter, unsigned nbar, unsigned rank, unsigned K, unsigned first, int sweeps_cap,
-                          int slot, int unit, double (*red)[NW], uint32_t (*cb)[kMaxColours], int& flag,
-                          float4* stage = nullptr)
+// The counter-ordered solve of a cluster (every body in memory): a barrier remains at the end of a sweep when a residual tolerance is set,
+// and once at the end.
+template <bool ROLL, int NW>
+__device__ void pgs_flow(const DevBuffers& b, const StepParams& p, const SolveTask& T, uint32_t ncol,
+                         uint32_t* counter, bool through, int sweeps_cap, int slot, SolveShared<NW>& sh)
 {
+    constexpr uint32_t kThreads = NW * 64;
+    const XcdBodies ba{raw_rsrc(b.vw), through};
+    const size_t nblk = gridDim.x;
+    unsigned nbar = 1;
     int sweeps = 0;
-    double Rk = 0.0, R1 = 0.0;
-    const unsigned nblk = gridDim.x;
-    constexpr uint32_t kThreads = NW * 64;  // the launch's block size (a constant stride)
+    double Rk = 0.0, R1 = 0.0, sn = 0.0, sd = 0.0;
     bool alive = true;
-    // Trailing colours of at most one block's threads each are solved by the
-    // rank-0 block alone, with workgroup barriers between them and a single
-    // cluster barrier after the last (same colour order, same results).
-    // colour bounds staged in LDS (cb: the kernel's) once: no global load
-    // between a barrier and the next colour's row prefetch
-    uint32_t* cbeg = cb[0];
-    uint32_t* clen = cb[1];
-    for (uint32_t q = threadIdx.x; q < ncol; q += blockDim.x) {
-        cbeg[q] = cstart.beg(q);
-        clen[q] = cstart.end(q) - cbeg[q];
-    }
+    stage_starts(b, T.owner, ncol, sh);
     __syncthreads();
-    uint32_t tail = ncol;
-    if (CLUSTER && !FLOW && !SPREAD)
-        while (tail > 0 && clen[tail - 1] <= kThreads) --tail;
-    auto range = [&](uint32_t col, uint32_t& lo, uint32_t& hi) {
-        uint32_t beg = cbeg[col], len = clen[col];
-        if (col >= tail) {
-            lo = beg;
-            hi = rank == 0 ? beg + len : beg;
-            return;
-        }
-        lo = beg + (uint32_t)(((uint64_t)len * rank) / K);
-        hi = beg + (uint32_t)(((uint64_t)len * (rank + 1)) / K);
-    };
-    // The cluster's (num, den) of sweep sw, the same value in every thread of
-    // every block: wave 0 loads the K block partials in parallel and sums them
-    // in a fixed tree order, the result is broadcast through LDS.
-    auto combine = [&](int sw, double& sn, double& sd) {
-        const double* part = b.block_part + (size_t)(FLOW ? sw : (sw & 1)) * nblk * 2;
-        if (threadIdx.x < 64) {
-            double a = 0.0, d = 0.0;
-            // spread mode: the partials of every block of every group
-            const unsigned nb = SPREAD ? nblk : K;
-            for (unsigned t = threadIdx.x; t < nb; t += 64) {
-                const unsigned blk = SPREAD ? t : first + 8 * t;
-                a += __hip_atomic_load(&part[2 * blk], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                d += __hip_atomic_load(&part[2 * blk + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            for (int o = 32; o > 0; o >>= 1) {
-                a += __shfl_down(a, o, 64);
-                d += __shfl_down(d, o, 64);
-            }
-            if (threadIdx.x == 0) { red[0][0] = a; red[1][0] = d; }
-        }
-        __syncthreads();
-        sn = red[0][0];
-        sd = red[1][0];
-        __syncthreads();  // red is reused
-    };
-    auto resid = [](double sn, double sd) { return sd > 0.0 ? sqrt(sn) / sqrt(sd) : (sn > 0.0 ? 1.0 : 0.0); };
-    uint32_t lo = 0, hi = 0, c = 0;
-    // 512-thread instances: a thread's first contact of a colour and, when the
-    // colour needs a second pass, its second, both fetched ahead (while the
-    // block waits at a barrier), and the following two fetched during their
-    // updates.  The 1024-thread instances take one contact at a time (two
-    // would spill registers: measured slower).  Lane pairs (pair_load) in
-    // every instance but the rolling 1024-thread one, which has no registers
-    // for them.
-    constexpr bool kPair = !FLOW && NW <= 8;
-    constexpr bool kLanes = !FLOW && (NW <= 8 || !ROLL);
-    // the 1024-thread plain instance: a thread's second contact of a colour
-    // staged in LDS (stage_rows) when the block has the room
-    constexpr bool kStage = kLanes && !kPair && !ROLL;
-    constexpr bool kKin = NW <= 8 && !SPREAD && !FLOW;  // the grouped solve fetches rk with the rows
-    const bool staged = kStage && stage != nullptr;
-    RowRegs cur, cur2;
-    auto fetch = [&]() {
-        if (c < hi) cur = load_rows(b, c, ROLL, kKin);
-        if (kPair && c + kThreads < hi) cur2 = load_rows(b, c + kThreads, ROLL, kKin);
-        if (staged && c + kThreads < hi) stage_rows(b, stage, kThreads, c + kThreads);
-    };
-    if (ncol > 0) {
-        range(0, lo, hi);
-        c = lo + threadIdx.x;
-        fetch();
-    }
+    auto part_of = [&](int sw) { return b.block_part + 2 * ((size_t)sw * nblk + T.f0); };
     for (int sw = 0; sw < sweeps_cap && ncol > 0; ++sw) {
         float num = 0.f, den = 0.f;
-        double* part = b.block_part + (size_t)(FLOW ? sw : (sw & 1)) * nblk * 2;
         for (uint32_t col = 0; col < ncol; ++col) {
-            // the rows prefetched for this colour: settled here, outside the
-            // loop, so that the loop waits only for its own loads
-            if (!FLOW) __builtin_amdgcn_s_waitcnt(0);
-            if (FLOW) {
-                while (c < hi) {
-                    const uint32_t cn = c + kThreads;
-                    RowRegs nxt;
-                    if (cn < hi) nxt = load_rows(b, cn, ROLL, kKin);
-                    const uint32_t seq = __float_as_uint(b.rk[c].w);
-                    const int ia = __float_as_int(cur.q.z), ib = __float_as_int(cur.q.w);
-                    const uint32_t wa = (uint32_t)sw * ((seq >> 16) & 255u) + (seq & 255u);
-                    const uint32_t wb = (uint32_t)sw * (seq >> 24) + ((seq >> 8) & 255u);
-                    if (alive) alive = flow_wait(b.cnt, b.ver, ib, wb) && (ia < 0 || flow_wait(b.cnt, b.ver, ia, wa));
-                    if (alive) {
-                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");  // body loads after the counters
-                        pgs_contact(b, ba, c, cur, load_bodies(ba, cur), p.mu, p.gamma_dt, num, den, ROLL);
-                        __builtin_amdgcn_s_waitcnt(0);  // the sphere state has reached the XCD's L2
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                        __hip_atomic_store(&b.ver[ib], wb + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        if (ia >= 0) __hip_atomic_store(&b.ver[ia], wa + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                    cur = nxt;
-                    c = cn;
+            const uint32_t hi = sh.st[2 * col + 2];
+            for (uint32_t c = sh.st[2 * col] + threadIdx.x; c < hi; c += kThreads) {
+                RowRegs R = load_rows(b, c, ROLL);
+                const uint32_t seq = b.seq[c];
+                const int ia = __float_as_int(R.q.z), ib = __float_as_int(R.q.w);
+                const uint32_t wa = (uint32_t)sw * ((seq >> 16) & 255u) + (seq & 255u);
+                const uint32_t wb = (uint32_t)sw * (seq >> 24) + ((seq >> 8) & 255u);
+                if (alive) alive = flow_wait(b.cnt, b.ver, ib, wb) && (ia < 0 || flow_wait(b.cnt, b.ver, ia, wa));
+                if (alive) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");  // body loads after the counters
+                    pgs_contact(b, ba, c, R, p.mu, p.gamma_dt, true, num, den, ROLL);
+                    store_lam(b, c, R, ROLL);
+                    __builtin_amdgcn_s_waitcnt(0);  // the sphere state has reached the XCD's L2
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                    __hip_atomic_store(&b.ver[ib], wb + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (ia >= 0) __hip_atomic_store(&b.ver[ia], wa + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
-            } else {
-                // lane pairs (pair_load): a pair runs while its even lane has a
-                // contact (kThreads is even, so the even lane's contacts are
-                // c - odd + k kThreads); the odd lane may have one fewer
-                const int odd = kLanes ? (int)(threadIdx.x & 1u) : 0;
-                bool first = true;  // the second contact of the colour is the staged one
-                while (c - odd < hi) {
-                    const uint32_t cn = c + kThreads;
-                    const bool own = c < hi;
-                    if (staged && first && cn - odd < hi) {
-                        // the second contact's rows arrived in LDS with the first's
-                        // registers; its bodies go there while the first updates
-                        const bool own2 = cn < hi;
-                        BodyRegs B = get_bodies<kLanes>(ba, cur, own, odd);
-                        stage_bodies(ba, stage, kThreads, stage[2 * kThreads + threadIdx.x], own2, odd);
-                        pgs_update(b, c, cur, B, p.mu, p.gamma_dt, num, den, ROLL, kKin);
-                        put_bodies<kLanes>(ba, cur, B, own, odd);
-                        __builtin_amdgcn_s_waitcnt(0);
-                        const RowRegs R2 = staged_rows(stage, kThreads);
-                        BodyRegs B2 = staged_bodies(stage, kThreads, odd);
-                        if (own2) pgs_update(b, cn, R2, B2, p.mu, p.gamma_dt, num, den, ROLL, kKin);
-                        put_bodies<kLanes>(ba, R2, B2, own2, odd);
-                        first = false;
-                        c = cn + kThreads;
-                        if (c < hi) cur = load_rows(b, c, ROLL, kKin);  // a third (rare): one chain
-                        continue;
-                    }
-                    first = false;
-                    if (kPair && cn - odd < hi) {
-                        // two contacts of one colour share no sphere: both gathers
-                        // in flight before either update (same order of updates
-                        // and of the residual sums as one contact at a time)
-                        const bool own2 = cn < hi;
-                        BodyRegs B1 = get_bodies<kLanes>(ba, cur, true, odd);
-                        BodyRegs B2 = get_bodies<kLanes>(ba, cur2, own2, odd);
-                        const uint32_t c3 = cn + kThreads;
-                        RowRegs n1, n2;
-                        if (c3 < hi) n1 = load_rows(b, c3, ROLL, kKin);
-                        if (c3 + kThreads < hi) n2 = load_rows(b, c3 + kThreads, ROLL, kKin);
-                        pgs_update(b, c, cur, B1, p.mu, p.gamma_dt, num, den, ROLL, kKin);
-                        if (own2) pgs_update(b, cn, cur2, B2, p.mu, p.gamma_dt, num, den, ROLL, kKin);
-                        put_bodies<kLanes>(ba, cur, B1, true, odd);
-                        put_bodies<kLanes>(ba, cur2, B2, own2, odd);
-                        cur = n1;
-                        cur2 = n2;
-                        c = c3;
-                        continue;
-                    }
-                    BodyRegs B = get_bodies<kLanes>(ba, cur, own, odd);
-                    RowRegs nxt;
-                    if (cn < hi) nxt = load_rows(b, cn, ROLL, kKin);
-                    if (own) pgs_update(b, c, cur, B, p.mu, p.gamma_dt, num, den, ROLL, kKin);
-                    put_bodies<kLanes>(ba, cur, B, own, odd);
-                    cur = nxt;
-                    c = cn;
-                }
-            }
-            if (CLUSTER && !FLOW && col >= tail && col + 1 < ncol) {
-                // inside the tail: the block's stores drained, then a workgroup
-                // barrier orders the rank-0 block's colours
-                __builtin_amdgcn_s_waitcnt(0);
-                range(col + 1, lo, hi);
-                c = lo + threadIdx.x;
-                fetch();
-                __syncthreads();
-            } else if (CLUSTER && !FLOW) {
-                if (col + 1 == ncol && (p.tol > 0.f || sw == 0 || sw + 1 == sweeps_cap)) {
-                    // block partials of this sweep, published before the last barrier
-                    double sn, sd;
-                    block_sum2<NW>(num, den, red, sn, sd);
-                    if (threadIdx.x == 0) {
-                        __hip_atomic_store(&part[2 * blockIdx.x], sn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        __hip_atomic_store(&part[2 * blockIdx.x + 1], sd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                }
-                cluster_arrive<FENCED>(counter);
-                ++nbar;
-                // the next phase's first rows are fetched while the block waits
-                range(col + 1 < ncol ? col + 1 : 0, lo, hi);
-                c = lo + threadIdx.x;
-                fetch();
-                if (SPREAD) {
-                    if (!spread_wait<FENCED>(b.cnt, counter, nbar, K, rank, flag)) return;  // every block leaves
-                } else if (!cluster_wait<FENCED>(b.cnt, counter, nbar * K, flag)) {
-                    __builtin_amdgcn_s_waitcnt(0);  // no load into LDS outlives the solve
-                    return;                         // every block leaves
-                }
-            } else {
-                range(col + 1 < ncol ? col + 1 : 0, lo, hi);
-                c = lo + threadIdx.x;
-                fetch();
-                if (!CLUSTER) __syncthreads();
             }
         }
-        double sn = 0.0, sd = 0.0;
-        if (FLOW) {
-            block_sum2<NW>(num, den, red, sn, sd);
-            if (threadIdx.x == 0) {
-                __hip_atomic_store(&part[2 * blockIdx.x], sn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&part[2 * blockIdx.x + 1], sd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            sweeps = sw + 1;
-            if (p.tol > 0.f) {
-                // the stopping test needs every block's partial of this sweep
-                cluster_arrive<false>(counter);
-                ++nbar;
-                if (!cluster_wait<false>(b.cnt, counter, nbar * K, flag)) return;
-                combine(sw, sn, sd);
-                Rk = resid(sn, sd);
-                if (sw == 0) R1 = Rk;
-                if (Rk <= (double)p.tol) break;  // uniform: every block holds the same Rk
-            }
-            continue;
+        block_sum2<NW>(num, den, sh.red, sn, sd);
+        if (threadIdx.x == 0) {
+            double* part = part_of(sw) + 2 * T.rank;
+            __hip_atomic_store(&part[0], sn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&part[1], sd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        if (CLUSTER) {
-            // without a tolerance only the first and last residuals are reported
-            sweeps = sw + 1;
-            if (!(p.tol > 0.f) && sw != 0 && sw + 1 != sweeps_cap) continue;
-            combine(sw, sn, sd);
-        } else {
-            block_sum2<NW>(num, den, red, sn, sd);
-        }
-        Rk = resid(sn, sd);
-        if (sw == 0) R1 = Rk;
         sweeps = sw + 1;
+        if (p.tol > 0.f) {
+            // the stopping test needs every block's partial of this sweep
+            cluster_arrive(counter);
+            ++nbar;
+            if (!cluster_wait(b.cnt, counter, nbar * T.K, sh.flag)) return;
+            combine_parts<NW>(part_of(sw), T.K, sh.red, sn, sd);
+            Rk = sweep_resid(sn, sd);
+            if (sw == 0) R1 = Rk;
+            if (Rk <= (double)p.tol) break;  // uniform: every block holds the same Rk
+        }
+    }
+    if (sweeps > 0 && !(p.tol > 0.f)) {
+        // fixed sweep count: the first and last residuals once every block is done
+        cluster_arrive(counter);
+        ++nbar;
+        if (!cluster_wait(b.cnt, counter, nbar * T.K, sh.flag)) return;
+        combine_parts<NW>(part_of(0), T.K, sh.red, sn, sd);
+        R1 = sweep_resid(sn, sd);
+        combine_parts<NW>(part_of(sweeps - 1), T.K, sh.red, sn, sd);
+        Rk = sweep_resid(sn, sd);
+    }
+    if (T.rank == 0 && threadIdx.x == 0) write_stats(b, T.unit, slot, sweeps, Rk, R1);
+}
+
+// The bodies of a contact that waits: LDS, or the exchange record once it
+// shows the awaited version (with the masses from rm).  Called by whole
+// waves; on: the lane has a contact.  alive turns false when a wait gives up.
+__device__ inline BodyRegs await_bodies(const DevBuffers& b, const RegionBodies& rb, const RowRegs& R, float4 m,
+                                        uint32_t it, bool on, bool& alive)
+{
+    BodyRegs B;
+    const int ia = __float_as_int(R.q.z), ib = __float_as_int(R.q.w);
+    const bool la = (ia & kLocal) != 0, lb = (ib & kLocal) != 0;
+    const int xa = la ? rb.xbase + (ia & kNameMask) : ia, xb = lb ? rb.xbase + (ib & kNameMask) : ib;
+    const uint32_t va = it * ((R.seq >> 16) & 255u) + (R.seq & 255u), vb = it * (R.seq >> 24) + ((R.seq >> 8) & 255u);
+    bool need_a = on && ia >= 0 && (!la || (ia & kFetch)), need_b = on && (!lb || (ib & kFetch));
+    if (on && !need_b) { B.vb = rb.sv[ib & kNameMask]; B.wb = rb.sw[ib & kNameMask]; }
+    if (on && ia >= 0 && !need_a) { B.va = rb.sv[ia & kNameMask]; B.wa = rb.sw[ia & kNameMask]; }
+    const bool far_a = need_a, far_b = need_b;
+    for (long spins = 1;; ++spins) {
+        if (need_b) { B.vb = ld_body<kCoherent>(rb.x, 2 * xb); B.wb = ld_body<kCoherent>(rb.x, 2 * xb + 1); }
+        if (need_a) { B.va = ld_body<kCoherent>(rb.x, 2 * xa); B.wa = ld_body<kCoherent>(rb.x, 2 * xa + 1); }
+        if (need_b) need_b = __float_as_uint(B.vb.w) != vb || __float_as_uint(B.wb.w) != vb;
+        if (need_a) need_a = __float_as_uint(B.va.w) != va || __float_as_uint(B.wa.w) != va;
+        if (__ballot(need_a || need_b) == 0ull || !alive) break;
+        if ((spins & 255) == 0 &&
+            (__hip_atomic_load(&b.cnt->overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kFailBarrier))
+            alive = false;
+        if (spins > kBarrierSpins) {
+            if ((threadIdx.x & 63) == 0) atomicOr(&b.cnt->overflow, kFailBarrier);
+            alive = false;
+        }
+    }
+    if (far_a) { B.va.w = m.x; B.wa.w = m.y; }
+    if (far_b) { B.vb.w = m.z; B.wb.w = m.w; }
+    return B;
+}
+
+// The solve of one region (file comment above).  lds holds the bodies of the
+// region's first lds_cap spheres (v, then omega).
+template <bool ROLL, int NW>
+__device__ void pgs_region(const DevBuffers& b, const StepParams& p, const SolveTask& T, uint32_t ncol, bool through,
+                           int sweeps_cap, int slot, float4* lds, int lds_cap, SolveShared<NW>& sh)
+{
+    constexpr uint32_t kThreads = NW * 64;
+    const uint32_t tid = threadIdx.x;
+    const bool cluster = T.K > 1;
+    uint32_t* sweep_flag = b.rflags + T.f0;
+    const RegionBodies rb{lds, lds + lds_cap, exchange_rsrc(b.xw), b.own_x[T.owner], through};
+    const int sg0 = b.own_idx[T.owner], sg1 = b.own_idx[T.owner + 1];
+    stage_starts(b, T.owner, ncol, sh);
+    if (ncol > 0)
+        for (int sg = sg0; sg < sg1; ++sg) {
+            const int4 S = b.own_seg[sg];
+            for (int i = (int)tid; i < S.y && S.z + i < lds_cap; i += (int)kThreads) {
+                rb.sv[S.z + i] = vel_at(b.vw, S.x + i);
+                rb.sw[S.z + i] = angv_at(b.vw, S.x + i);
+            }
+        }
+    __syncthreads();
+    // Shared contacts go to the threads from the last one down, private ones
+    // from the first one up: the waves that wait for the neighbours are the
+    // last to get a second private contact.  A thread's first shared and
+    // first private contact of a phase are both fetched ahead by 512-thread
+    // blocks; 1024-thread ones have registers for one, and take the private
+    // contact of a thread with both as it comes.
+    constexpr bool kBoth = NW <= 8;
+    const uint32_t ts = kThreads - 1 - tid, wave_ts = ts & ~63u;  // this wave's first shared contact
+    RowRegs cs, cp;
+    float4 ms;  // masses of the shared contact's bodies
+    auto rows = [&](uint32_t c) {
+        RowRegs R = load_rows(b, c, ROLL);
+        R.seq = b.seq[c];
+        return R;
+    };
+    uint32_t s_next = 0, p_next = 0, e_next = 0;  // the phase's shared and private contacts, their end
+    auto fetch = [&](uint32_t col) {
+        s_next = sh.st[2 * col];
+        p_next = sh.st[2 * col + 1];
+        e_next = sh.st[2 * col + 2];
+        const bool has_s = ts < p_next - s_next, has_p = tid < e_next - p_next;
+        if (has_s) ms = b.rm[s_next + ts];
+        if (kBoth) {
+            if (has_s) cs = rows(s_next + ts);
+            if (has_p) cp = rows(p_next + tid);
+        } else if (has_s || has_p) {
+            cp = rows(has_s ? s_next + ts : p_next + tid);
+        }
+    };
+    if (ncol > 0) fetch(0);
+    bool alive = true;
+    int sweeps = 0;
+    double Rk = 0.0, R1 = 0.0;
+    // the updated bodies to LDS and, with the number of updates they have
+    // seen, to the exchange (a sphere without an LDS index, or needed next by
+    // another block); priv: both bodies have an LDS index
+    auto put = [&](const RowRegs& R, const BodyRegs& B, uint32_t it, bool priv) {
+        const int ia = __float_as_int(R.q.z), ib = __float_as_int(R.q.w);
+        if (priv || (ib & kLocal)) { rb.sv[ib & kNameMask] = B.vb; rb.sw[ib & kNameMask] = B.wb; }
+        if (ia >= 0 && (priv || (ia & kLocal))) { rb.sv[ia & kNameMask] = B.va; rb.sw[ia & kNameMask] = B.wa; }
+        const bool out_a = ia >= 0 && ((ia & kPublish) || !(priv || (ia & kLocal)));
+        const bool out_b = (ib & kPublish) || !(priv || (ib & kLocal));
+        if (out_a || out_b) {
+            const int rec_a = (ia & kNameMask) + ((ia & kLocal) ? rb.xbase : 0);
+            const int rec_b = (ib & kNameMask) + ((ib & kLocal) ? rb.xbase : 0);
+            if (out_b) rb.publish(rec_b, it * (R.seq >> 24) + ((R.seq >> 8) & 255u) + 1, B.vb, B.wb);
+            if (out_a) rb.publish(rec_a, it * ((R.seq >> 16) & 255u) + (R.seq & 255u) + 1, B.va, B.wa);
+        }
+    };
+    auto update_private = [&](uint32_t c, RowRegs& R, uint32_t it, bool want, float& num, float& den) {
+        const int ia = __float_as_int(R.q.z), ib = __float_as_int(R.q.w) & kNameMask;
+        const int ja = ia >= 0 ? ia & kNameMask : ib;
+        BodyRegs B{rb.sv[ja], rb.sw[ja], rb.sv[ib], rb.sw[ib]};
+        pgs_update(b, c, R, B, p.mu, p.gamma_dt, want, num, den, ROLL);
+        put(R, B, it, true);
+        store_lam(b, c, R, ROLL);
+    };
+    for (int it = 0; it < sweeps_cap && ncol > 0; ++it) {
+        // without a tolerance only the first and last residuals are reported
+        const bool want = p.tol > 0.f || it == 0 || it + 1 == sweeps_cap;
+        float num = 0.f, den = 0.f;
+        for (uint32_t col = 0; col < ncol; ++col) {
+            const uint32_t s0 = s_next, p0 = p_next, ns = p0 - s0, np = e_next - p0;
+            RowRegs& C = kBoth ? cs : cp;
+            for (uint32_t k0 = wave_ts; k0 < ns; k0 += kThreads) {
+                const uint32_t k = k0 + (ts & 63u);
+                const bool on = k < ns;
+                if (k0 != wave_ts && on) {
+                    C = rows(s0 + k);
+                    ms = b.rm[s0 + k];
+                }
+                settle(C, ROLL);
+                settle(ms.x);
+                BodyRegs B = await_bodies(b, rb, C, ms, (uint32_t)it, on, alive);
+                if (on) {
+                    pgs_update(b, s0 + k, C, B, p.mu, p.gamma_dt, want, num, den, ROLL);
+                    put(C, B, (uint32_t)it, false);
+                    store_lam(b, s0 + k, C, ROLL);
+                }
+            }
+            if (tid < np) {
+                if (!kBoth && ts < ns) cp = rows(p0 + tid);
+                settle(cp, ROLL);
+                // a second private contact is in flight during the first's update
+                RowRegs nxt;
+                if (tid + kThreads < np) nxt = rows(p0 + tid + kThreads);
+                update_private(p0 + tid, cp, (uint32_t)it, want, num, den);
+                for (uint32_t k = tid + kThreads; k < np; k += kThreads) {
+                    settle(nxt, ROLL);
+                    cp = nxt;
+                    if (k + kThreads < np) nxt = rows(p0 + k + kThreads);
+                    update_private(p0 + k, cp, (uint32_t)it, want, num, den);
+                }
+            }
+            fetch(col + 1 < ncol ? col + 1 : 0);  // in flight across the barrier
+            __syncthreads();
+        }
+        sweeps = it + 1;
+        if (!want) continue;
+        double sn, sd;
+        block_sum2<NW>(num, den, sh.red, sn, sd);
+        if (cluster) {
+            // two slots: the first and the last sweep, or with a tolerance
+            // alternating sweeps (no block is more than one sweep ahead)
+            const int q = p.tol > 0.f ? it & 1 : (it == 0 ? 0 : 1);
+            double* part = b.block_part + 2 * ((size_t)q * gridDim.x + T.f0);
+            if (tid == 0) {
+                __hip_atomic_store(&part[2 * T.rank], sn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&part[2 * T.rank + 1], sd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __builtin_amdgcn_s_waitcnt(0);
+                __hip_atomic_store(&sweep_flag[T.rank], (uint32_t)it + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (tid < 64 && alive) {
+                alive = wait_flags(b.cnt, sweep_flag, T.K, (uint32_t)it + 1);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            }
+            combine_parts<NW>(part, T.K, sh.red, sn, sd);
+        }
+        Rk = sweep_resid(sn, sd);
+        if (it == 0) R1 = Rk;
         if (p.tol > 0.f && Rk <= (double)p.tol) break;  // uniform: every thread holds the same Rk
     }
-    if (FLOW && ncol > 0 && !(p.tol > 0.f)) {
-        // fixed sweep count: the first and last residuals once every block is done
-        cluster_arrive<false>(counter);
-        ++nbar;
-        if (!cluster_wait<false>(b.cnt, counter, nbar * K, flag)) return;
-        double sn, sd;
-        combine(0, sn, sd);
-        R1 = resid(sn, sd);
-        combine(sweeps - 1, sn, sd);
-        Rk = resid(sn, sd);
-    }
-    if (staged) __builtin_amdgcn_s_waitcnt(0);  // the last prefetch into LDS has landed
-    if (rank == 0 && threadIdx.x == 0 && (!SPREAD || first == 0)) {
-        UnitStats& G = b.ustats[unit];
-        if (slot == 0) {
-            G.sweeps = (uint32_t)sweeps;
-            G.resid = Rk;
-            G.resid_first = R1;
-        } else if (slot == kSlotImpact) {
-            G.imp_sweeps = (uint32_t)sweeps;
-        } else {
-            G.r1_trial[slot - 1] = R1;
+    // the region's final states: from LDS, or from the exchange where the
+    // sphere's last update was solved away
+    if (ncol > 0 && sweeps > 0)
+        for (int sg = sg0; sg < sg1; ++sg) {
+            const int4 S = b.own_seg[sg];
+            for (int i = (int)tid; i < S.y; i += (int)kThreads) {
+                const int li = S.z + i, sl = S.x + i;
+                const ulonglong2 m = b.smask[sl];
+                if (m.y && ((m.y >> (63 - __builtin_clzll(m.x))) & 1)) {
+                    const uint32_t last = (uint32_t)sweeps * (uint32_t)__popcll(m.x);
+                    float4 v, w;
+                    long spins = 0;
+                    do {
+                        v = ld_body<kCoherent>(rb.x, 2 * (rb.xbase + li));
+                        w = ld_body<kCoherent>(rb.x, 2 * (rb.xbase + li) + 1);
+                        if (++spins > kBarrierSpins) atomicOr(&b.cnt->overflow, kFailBarrier);
+                        if ((spins & 255) == 0 && (__hip_atomic_load(&b.cnt->overflow, __ATOMIC_RELAXED,
+                                                                     __HIP_MEMORY_SCOPE_AGENT) & kFailBarrier))
+                            break;
+                    } while (alive && (__float_as_uint(v.w) != last || __float_as_uint(w.w) != last));
+                    v.w = vel_at(b.vw, sl).w;
+                    w.w = angv_at(b.vw, sl).w;
+                    vel_at(b.vw, sl) = v;
+                    angv_at(b.vw, sl) = w;
+                } else if (li < lds_cap) {
+                    vel_at(b.vw, sl) = rb.sv[li];
+                    angv_at(b.vw, sl) = rb.sw[li];
+                }
+            }
         }
-    }
+    if (T.rank == 0 && tid == 0) write_stats(b, T.unit, slot, sweeps, Rk, R1);
 }
 
-__global__ void k_pgs_reset(DevBuffers b, int n_envs)
+// Before a PGS launch: its counters and flags cleared, and the exchange
+// records of the spheres that use one at version 0.
+__global__ void k_pgs_reset(DevBuffers b, StepParams p, int n_envs, int n_flags)
 {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < kGroups) { b.cnt->bar[t][0] = 0; b.cnt->bar[t][1] = 0; b.cnt->bar[t][2] = 0; }
-    if (t == 0) b.cnt->gbar[0] = 0;
+    if (t < kGroups) { b.cnt->bar[t][0] = 0; b.cnt->bar[t][1] = 0; }
     if (t < n_envs) { b.env_bar[(size_t)t * 16] = 0; b.env_bar[(size_t)t * 16 + 1] = 0; }
+    if (t < n_flags) b.rflags[t] = 0;
+    if (t >= p.n_particles) return;
+    const EnvDev& E = b.envs[env_of(b.pid[t], p.id_cap)];
+    if (!E.coded || b.smask[t].y == 0) return;
+    const int64_t x = E.x0 + (int64_t)region_of(E, t) * E.xstride + lds_index(E, t);
+    float4 v = vel_at(b.vw, t), w = angv_at(b.vw, t);
+    v.w = w.w = 0.f;  // version 0
+    b.xw[2 * x] = v;
+    b.xw[2 * x + 1] = w;
 }
 
-// grouped mode: colour col of group g is bucket (col, g) of the bucketing
-struct GroupStarts {
-    const uint32_t* col_start;
-    int64_t NB;
-    int g;
-    __device__ uint32_t beg(uint32_t col) const { return col_start[((int64_t)col * kGroups + g) * NB]; }
-    __device__ uint32_t end(uint32_t col) const { return col_start[((int64_t)col * kGroups + g + 1) * NB]; }
-};
-// per-env mode: colours of one env are consecutive
-struct EnvStarts {
-    const uint32_t* ec;
-    __device__ uint32_t beg(uint32_t col) const { return ec[col]; }
-    __device__ uint32_t end(uint32_t col) const { return ec[col + 1]; }
-};
-
-template <bool ROLL>
-__global__ __launch_bounds__(kPgsBlk) void k_pgs(DevBuffers b, StepParams p, int64_t NB, int sweeps_cap, int slot,
-                                                   int flow)
+// Grouped and spread modes: block blockIdx takes the region of its task.
+template <bool ROLL, int NW>
+__global__ __launch_bounds__(64 * NW) void k_pgs(DevBuffers b, StepParams p, int sweeps_cap, int slot, int lds_cap,
+                                                 int flow)
 {
-    __shared__ double red[2][kPgsBlk / 64];
-    __shared__ uint32_t cb[2][kMaxColours];
-    __shared__ int flag;
+    HIP_DYNAMIC_SHARED(float4, dyn_bodies)
+    __shared__ SolveShared<NW> sh;
     if (b.cnt->overflow) return;  // uniform: written by earlier kernels only
-    const int g = blockIdx.x % kGroups;
-    const unsigned rank = blockIdx.x / kGroups, gx = gridDim.x / kGroups;
-    GroupStarts cs{b.col_start, NB, g};
+    const int4 q = b.grp_task[blockIdx.x];
+    if (q.x < 0) return;
+    const SolveTask T{q.x, (unsigned)q.y & 0xffffu, (unsigned)q.y >> 16, (unsigned)q.z, q.w & 0x7fffffff};
+    bool through = q.w < 0;
     uint32_t ncol = b.cnt->n_colours;
-    uint32_t* counter = &b.cnt->bar[g][0];
-    if (p.spread) {
-        // spread mode: the groups share one env (unit 0) and meet after every
-        // colour, so all of them run every colour, with or without contacts
-        if (slot == kSlotImpact && !b.ustats[0].imp_any) ncol = 0;  // no impact in the env
-        int mode = cluster_placement(b.cnt, counter, gx, flag);
-        if (mode == 1)
-            pgs_solve<SpreadBodies, true, false, false, ROLL, kPgsBlk / 64, GroupStarts, true>(
-                b, p, SpreadBodies{raw_rsrc(b.vw)}, cs, ncol, counter, 1, rank, gx, (unsigned)g,
-                sweeps_cap, slot, 0, red, cb, flag);
-        else if (mode == 2)
-            pgs_solve<PlainBodies, true, true, false, ROLL, kPgsBlk / 64, GroupStarts, true>(
-                b, p, PlainBodies{b.vw}, cs, ncol, counter, 1, rank, gx, (unsigned)g, sweeps_cap, slot, 0, red,
-                cb, flag);
-        return;
+    if (slot == kSlotImpact && !b.ustats[T.unit].imp_any) ncol = 0;  // no impact in the unit
+    uint32_t* counter = &b.cnt->bar[blockIdx.x % kGroups][0];
+    if ((T.K > 1 || flow) && !through) {
+        const int mode = cluster_placement(b.cnt, counter, T.K, sh.flag);
+        if (mode == 0) return;
+        through = mode == 2;
     }
-    // a group without contacts only records its (trivial) statistics
-    uint32_t total = 0;
-    for (uint32_t col = 0; col < ncol; ++col) total += cs.end(col) - cs.beg(col);
-    if (total == 0) ncol = 0;
-    if (slot == kSlotImpact && !b.ustats[g].imp_any) ncol = 0;  // no impact in the group
-    int mode = cluster_placement(b.cnt, counter, gx, flag);
-    if (mode == 1) {
-        XcdBodies ba{raw_rsrc(b.vw)};
-        if (flow)
-            pgs_solve<XcdBodies, true, false, true, ROLL>(b, p, ba, cs, ncol, counter, 1, rank, gx, (unsigned)g, sweeps_cap,
-                                                    slot, g, red, cb, flag);
-        else
-            pgs_solve<XcdBodies, true, false, false, ROLL>(b, p, ba, cs, ncol, counter, 1, rank, gx, (unsigned)g,
-                                                     sweeps_cap, slot, g, red, cb, flag);
-    }
-    else if (mode == 2)
-        pgs_solve<PlainBodies, true, true, false, ROLL>(b, p, PlainBodies{b.vw}, cs, ncol, counter, 1, rank, gx,
-                                                  (unsigned)g, sweeps_cap, slot, g, red, cb, flag);
+    if (flow)
+        pgs_flow<ROLL, NW>(b, p, T, ncol, counter, through, sweeps_cap, slot, sh);
+    else
+        pgs_region<ROLL, NW>(b, p, T, ncol, through, sweeps_cap, slot, dyn_bodies, lds_cap, sh);
 }
 
 // Per-env mode, a set of small envs solved at once by one block: env j of the
@@ -2137,7 +2157,8 @@ __device__ void pgs_local_set(const DevBuffers& b, const StepParams& p, const in
         lb.sw[i] = angv_at(b.vw, sb + i);
     }
     __syncthreads();
-    const uint32_t* ec = b.env_col + (size_t)(e >= 0 ? e : 0) * (kMaxColours + 1);
+    // one owner per env here: colour col is [ec[2 col], ec[2 col + 2])
+    const uint32_t* ec = b.own_start + (size_t)(e >= 0 ? b.envs[e].own_base : 0) * kOwnStride;
     const uint32_t ncol = e >= 0 && !(slot == kSlotImpact && !b.ustats[e].imp_any) ? b.env_ncol[e] : 0;
     bool active = ncol > 0;  // uniform over the env's waves
     int sweeps = 0;
@@ -2145,13 +2166,15 @@ __device__ void pgs_local_set(const DevBuffers& b, const StepParams& p, const in
     uint32_t c = 1, hi = 0;
     RowRegs cur;
     auto start_col = [&](uint32_t col) {
-        c = ec[col] + lt;
-        hi = ec[col + 1];
+        c = ec[2 * col] + lt;
+        hi = ec[2 * col + 2];
         if (c < hi) cur = load_rows(b, c, ROLL);
     };
     if (active) start_col(0);
     for (int sw = 0; sw < sweeps_cap; ++sw) {
         if (!__syncthreads_or(active)) break;
+        // without a tolerance only the first and last residuals are reported
+        const bool want = p.tol > 0.f || sw == 0 || sw + 1 == sweeps_cap;
         float num = 0.f, den = 0.f;
         for (uint32_t col = 0; col < maxcol; ++col) {
             if (active && col < ncol) {
@@ -2160,9 +2183,11 @@ __device__ void pgs_local_set(const DevBuffers& b, const StepParams& p, const in
                     BodyRegs B = how == 0 ? load_bodies(lb, cur) : how == 1 ? load_bodies(gb, cur) : load_bodies(mb, cur);
                     RowRegs nxt;
                     if (cn < hi) nxt = load_rows(b, cn, ROLL);
-                    if (how == 0) pgs_contact(b, lb, c, cur, B, p.mu, p.gamma_dt, num, den, ROLL);
-                    else if (how == 1) pgs_contact(b, gb, c, cur, B, p.mu, p.gamma_dt, num, den, ROLL);
-                    else pgs_contact(b, mb, c, cur, B, p.mu, p.gamma_dt, num, den, ROLL);
+                    pgs_update(b, c, cur, B, p.mu, p.gamma_dt, want, num, den, ROLL);
+                    if (how == 0) store_bodies(lb, cur, B);
+                    else if (how == 1) store_bodies(gb, cur, B);
+                    else store_bodies(mb, cur, B);
+                    store_lam(b, c, cur, ROLL);
                     cur = nxt;
                     c = cn;
                 }
@@ -2170,6 +2195,8 @@ __device__ void pgs_local_set(const DevBuffers& b, const StepParams& p, const in
             }
             __syncthreads();
         }
+        if (active) sweeps = sw + 1;
+        if (!want) continue;
         // the env's residual from its waves' partials, in wave order
         double dnum = num, dden = den;
         for (int o = 32; o > 0; o >>= 1) {
@@ -2181,9 +2208,8 @@ __device__ void pgs_local_set(const DevBuffers& b, const StepParams& p, const in
         if (active) {
             double sn = 0.0, sd = 0.0;
             for (int w = wb; w < we; ++w) { sn += red[0][w]; sd += red[1][w]; }
-            Rk = sd > 0.0 ? sqrt(sn) / sqrt(sd) : (sn > 0.0 ? 1.0 : 0.0);
+            Rk = sweep_resid(sn, sd);
             if (sw == 0) R1 = Rk;
-            sweeps = sw + 1;
             if (p.tol > 0.f && Rk <= (double)p.tol) active = false;
         }
         __syncthreads();  // red is reused
@@ -2192,18 +2218,7 @@ __device__ void pgs_local_set(const DevBuffers& b, const StepParams& p, const in
         vel_at(b.vw, sb + i) = lb.sv[i];
         angv_at(b.vw, sb + i) = lb.sw[i];
     }
-    if (e >= 0 && lt == 0) {
-        UnitStats& G = b.ustats[e];
-        if (slot == 0) {
-            G.sweeps = (uint32_t)sweeps;
-            G.resid = Rk;
-            G.resid_first = R1;
-        } else if (slot == kSlotImpact) {
-            G.imp_sweeps = (uint32_t)sweeps;
-        } else {
-            G.r1_trial[slot - 1] = R1;
-        }
-    }
+    if (e >= 0 && lt == 0) write_stats(b, e, slot, sweeps, Rk, R1);
 }
 
 // Per-env mode: block b runs plan[plan_idx[b] .. plan_idx[b + 1]) in order: at
@@ -2215,9 +2230,7 @@ __global__ __launch_bounds__(kEnvBlk) void k_pgs_env(DevBuffers b, StepParams p,
                                                       int flow)
 {
     HIP_DYNAMIC_SHARED(float4, dyn_bodies)
-    __shared__ double red[2][kEnvBlk / 64];
-    __shared__ uint32_t cb[2][kMaxColours];
-    __shared__ int flag;
+    __shared__ SolveShared<kEnvBlk / 64> sh;
     if (b.cnt->overflow) return;  // uniform: written by earlier kernels only
     const uint32_t t0 = b.plan_idx[blockIdx.x], t1 = b.plan_idx[blockIdx.x + 1];
     uint32_t t = t0;
@@ -2226,76 +2239,73 @@ __global__ __launch_bounds__(kEnvBlk) void k_pgs_env(DevBuffers b, StepParams p,
         if (pl.z < 2) {
             uint32_t u = t + 1;
             while (u < t1 && b.plan[u].z < 2 && (b.plan[u].y & 255) != 0) ++u;
-            pgs_local_set<ROLL>(b, p, b.plan + t, (int)(u - t), sweeps_cap, slot, dyn_bodies, lds_cap, red);
+            pgs_local_set<ROLL>(b, p, b.plan + t, (int)(u - t), sweeps_cap, slot, dyn_bodies, lds_cap, sh.red);
             __syncthreads();  // LDS and the reduction scratch are reused
             t = u;
             continue;
         }
         const int e = pl.x;
-        const unsigned rank = pl.y, K = pl.z, first = pl.w;
-        EnvStarts cs{b.env_col + (size_t)e * (kMaxColours + 1)};
+        // a cluster's flags are consecutive: block lane + 8 i has flag lane * (blocks / 8) + i
+        const unsigned first = (unsigned)pl.w;
+        const SolveTask T{b.envs[e].own_base + pl.y, (unsigned)pl.y, (unsigned)pl.z,
+                          (first % kGroups) * (gridDim.x / kGroups) + first / kGroups, e};
         const uint32_t ncol = slot == kSlotImpact && !b.ustats[e].imp_any ? 0u : b.env_ncol[e];
         uint32_t* counter = b.env_bar + (size_t)e * 16;
-        int mode = cluster_placement(b.cnt, counter, K, flag);
-        XcdBodies xb{raw_rsrc(b.vw)};
-        // the dynamic LDS (idle during a cluster share) stages second contacts
-        float4* stage = 2 * lds_cap >= kStageFloat4 * kEnvBlk ? dyn_bodies : nullptr;
-        if (mode == 1 && flow)
-            pgs_solve<XcdBodies, true, false, true, ROLL>(b, p, xb, cs, ncol, counter, 1, rank, K, first, sweeps_cap, slot,
-                                                    e, red, cb, flag);
-        else if (mode == 1)
-            pgs_solve<XcdBodies, true, false, false, ROLL>(b, p, xb, cs, ncol, counter, 1, rank, K, first, sweeps_cap, slot,
-                                                     e, red, cb, flag, stage);
-        else if (mode == 2)
-            pgs_solve<PlainBodies, true, true, false, ROLL>(b, p, PlainBodies{b.vw}, cs, ncol, counter, 1, rank, K,
-                                                      first, sweeps_cap, slot, e, red, cb, flag, stage);
-        if (!flag) return;  // failed barrier: the step is abandoned
+        const int mode = cluster_placement(b.cnt, counter, T.K, sh.flag);
+        if (mode == 0) return;  // failed barrier: the step is abandoned
+        if (flow)
+            pgs_flow<ROLL, kEnvBlk / 64>(b, p, T, ncol, counter, mode == 2, sweeps_cap, slot, sh);
+        else
+            pgs_region<ROLL, kEnvBlk / 64>(b, p, T, ncol, mode == 2, sweeps_cap, slot, dyn_bodies, lds_cap, sh);
         __syncthreads();
         ++t;
     }
 }
 
-// dynamic LDS one per-env block may take: the device's limit per block less
-// the larger static footprint of the two kernel instances
-int pgs_env_max_lds()
+// dynamic LDS one block of a kernel may take: the device's limit per block
+// less the larger static footprint of its two instances
+static int max_dynamic_lds(const void* k0, const void* k1)
 {
     int dev = 0, lds = 0;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
     hipFuncAttributes a0{}, a1{};
     size_t st = 2048;  // if the attributes cannot be read
-    if (hipFuncGetAttributes(&a0, (const void*)k_pgs_env<false>) == hipSuccess &&
-        hipFuncGetAttributes(&a1, (const void*)k_pgs_env<true>) == hipSuccess)
+    if (hipFuncGetAttributes(&a0, k0) == hipSuccess && hipFuncGetAttributes(&a1, k1) == hipSuccess)
         st = std::max(a0.sharedSizeBytes, a1.sharedSizeBytes);
     return std::max(0, lds - (int)((st + 255) / 256 * 256));
 }
 
-// blocks of either PGS instance (plain or with rolling rows) resident at once:
-// the persistent solves rely on every block of a cluster being resident
-int pgs_env_resident_blocks(int lds_bytes)
+int pgs_env_max_lds() { return max_dynamic_lds((const void*)k_pgs_env<false>, (const void*)k_pgs_env<true>); }
+
+int pgs_group_max_lds() { return max_dynamic_lds((const void*)k_pgs<false, kPgsWaves>, (const void*)k_pgs<true, kPgsWaves>); }
+
+// blocks of either instance (plain or with rolling rows) of a persistent
+// solve resident at once: its blocks wait for each other
+static int resident_blocks(const void* k0, const void* k1, int block, int lds_bytes)
 {
     int dev = 0, c0 = 0, c1 = 0;
     (void)hipGetDevice(&dev);
     hipDeviceProp_t pr;
     (void)hipGetDeviceProperties(&pr, dev);
     if (lds_bytes > 0) {
-        (void)hipFuncSetAttribute((const void*)k_pgs_env<false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-        (void)hipFuncSetAttribute((const void*)k_pgs_env<true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        (void)hipFuncSetAttribute(k0, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        (void)hipFuncSetAttribute(k1, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
     }
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&c0, k_pgs_env<false>, kEnvBlk, lds_bytes);
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&c1, k_pgs_env<true>, kEnvBlk, lds_bytes);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&c0, k0, block, lds_bytes);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&c1, k1, block, lds_bytes);
     return std::max(1, std::min(c0, c1)) * pr.multiProcessorCount;
 }
 
-int pgs_resident_blocks(int block)
+int pgs_env_resident_blocks(int lds_bytes)
 {
-    int dev = 0, c0 = 0, c1 = 0;
-    (void)hipGetDevice(&dev);
-    hipDeviceProp_t pr;
-    (void)hipGetDeviceProperties(&pr, dev);
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&c0, k_pgs<false>, block, 0);
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&c1, k_pgs<true>, block, 0);
-    return std::max(1, std::min(c0, c1)) * pr.multiProcessorCount;
+    return resident_blocks((const void*)k_pgs_env<false>, (const void*)k_pgs_env<true>, kEnvBlk, lds_bytes);
+}
+
+int pgs_resident_blocks()
+{
+    return resident_blocks((const void*)k_pgs<false, kPgsWaves>, (const void*)k_pgs<true, kPgsWaves>, 64 * kPgsWaves,
+                           pgs_group_max_lds());
 }
 
 // The colouring's blocks wait for each other's contacts, so all of them must
@@ -2317,24 +2327,25 @@ int colour_resident_blocks()
 void launch_pgs(const DevBuffers& b, const StepParams& p, const Sizes& z, hipStream_t s, int sweeps_cap, int slot)
 {
     int sw = sweeps_cap < 0 ? p.max_sweeps : sweeps_cap;
-    int nr = std::max(kGroups, z.pgs_mode == kModePerEnv ? z.n_envs : 0);
-    hipLaunchKernelGGL(k_pgs_reset, dim3((unsigned)cdiv(nr, 64)), dim3(64), 0, s, b, z.pgs_mode == kModePerEnv ? z.n_envs : 0);
-    // counter-ordered solves keep one partial slot per sweep
-    int flow = z.flow && sw <= z.part_sweeps ? 1 : 0;
+    const int ne = z.pgs_mode == kModePerEnv ? z.n_envs : 0;
+    StepParams pr = p;
+    if (!z.masks) pr.n_particles = 0;
+    const int nr = std::max({kGroups, ne, z.n_flags, pr.n_particles});
+    hipLaunchKernelGGL(k_pgs_reset, dim3((unsigned)cdiv(nr, kBlk)), dim3(kBlk), 0, s, b, pr, ne, z.n_flags);
+    const int flow = z.flow;
     if (flow && p.n_particles > 0) launch_fill_u32(b.ver, 0u, p.n_particles, s);
-    if (z.pgs_mode == kModePerEnv) {
-        const dim3 grid((unsigned)z.plan_blocks), blk(kEnvBlk);
-        const size_t lds = (size_t)z.lds_cap * 32;
-        if (z.plan_blocks > 0 && p.mu_r > 0.f)
-            hipLaunchKernelGGL(k_pgs_env<true>, grid, blk, lds, s, b, p, sw, slot, z.lds_cap, flow);
-        else if (z.plan_blocks > 0)
-            hipLaunchKernelGGL(k_pgs_env<false>, grid, blk, lds, s, b, p, sw, slot, z.lds_cap, flow);
-        return;
-    }
-    if (p.mu_r > 0.f)
-        hipLaunchKernelGGL(k_pgs<true>, dim3(z.pgs_grid), dim3(kPgsBlk), 0, s, b, p, z.NB, sw, slot, flow);
+    const bool env = z.pgs_mode == kModePerEnv;
+    const dim3 grid((unsigned)(env ? z.plan_blocks : z.pgs_grid)), blk(env ? kEnvBlk : 64 * kPgsWaves);
+    const size_t lds = (size_t)(env ? z.lds_cap : z.grp_lds) * 32;
+    if (grid.x == 0) return;
+    if (env && p.mu_r > 0.f)
+        hipLaunchKernelGGL(k_pgs_env<true>, grid, blk, lds, s, b, p, sw, slot, z.lds_cap, flow);
+    else if (env)
+        hipLaunchKernelGGL(k_pgs_env<false>, grid, blk, lds, s, b, p, sw, slot, z.lds_cap, flow);
+    else if (p.mu_r > 0.f)
+        hipLaunchKernelGGL((k_pgs<true, kPgsWaves>), grid, blk, lds, s, b, p, sw, slot, z.grp_lds, flow);
     else
-        hipLaunchKernelGGL(k_pgs<false>, dim3(z.pgs_grid), dim3(kPgsBlk), 0, s, b, p, z.NB, sw, slot, flow);
+        hipLaunchKernelGGL((k_pgs<false, kPgsWaves>), grid, blk, lds, s, b, p, sw, slot, z.grp_lds, flow);
 }
 
 // ---------------------------------------------------------------------------
@@ -2405,15 +2416,13 @@ __global__ void k_select_start(DevBuffers b, int64_t cap, int mode, uint32_t id_
 {
     uint32_t nc = n_contacts(b, cap);
     uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= nc) return;
+    if (c >= nc || b.cnt->overflow) return;
+    const uint32_t pos = b.cpos[c];
     bool learned = mode == 1;
-    if (mode == 2) {
-        int u = b.envs[env_of(b.pid[__float_as_int(b.r2[c].w)], id_cap)].unit;
-        learned = b.ustats[u].use_learned != 0;
-    }
-    float4 L = learned ? b.lamL[c] : b.lam0[c];
-    b.lam[c] = L;
-    if (mu_r > 0.f) b.lamr[c] = project_roll(b.lamr0[c], b.r3[c].y * fabsf(L.x));
+    if (mode == 2) learned = b.ustats[b.envs[env_of((int)(b.ckey[c] >> 32), id_cap)].unit].use_learned != 0;
+    float4 L = learned ? b.lamL[pos] : b.lam0[pos];
+    b.lam[pos] = L;
+    if (mu_r > 0.f) b.lamr[pos] = project_roll(b.lamr0[pos], b.r3[pos].y * fabsf(L.x));
 }
 
 void launch_select_start(const DevBuffers& b, const StepParams& p, const Sizes& z, int mode, hipStream_t s)
