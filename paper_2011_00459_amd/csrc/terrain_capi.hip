@@ -11,6 +11,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <limits>
+#include <queue>
 #include <string>
 #include <vector>
 
@@ -182,101 +183,87 @@ void invalidate_graphs(tr_scene* s)
     s->graphs = false;
 }
 
-// The automatic per-env plan, from a cost model measured on MI355X (the
-// 256-bed batch, 100 sweeps, with a timing build that clocks every block's
-// tasks; units of microseconds): a block's share of a multi-block cluster
-// costs about 1800 (the colour phases' barriers) plus 1.77 per sphere of the
-// share, a set of envs solved from LDS by one block 1300 plus 0.6 per sphere,
-// and a sphere that a single block keeps in global memory about 2.0 (2.5
-// here: those solves vary most).  Envs that fit LDS are packed into sets
-// (first fit, largest first); envs up to Ns spheres are solved alone by one
-// block with their first slots in LDS; larger ones by clusters of
-// ceil(1.77 n / (M - 1800)) blocks of one XCD lane.  Ns and the target M are
-// searched for the smallest predicted makespan (jobs placed largest first on
-// the least loaded block).  tasks gets each block's cluster share
-// (env, rank, K, first block) and then its sets as (env, set number, 1, 0);
-// false when no candidate fits the blocks.
+// The automatic per-env plan, from a cost model measured on MI355X (256 busy
+// blocks, 100 sweeps of 9 or 10 colours; units of microseconds): a block's
+// region of a multi-block cluster costs 900 plus 0.82 per sphere (1,000
+// spheres 1.6 ms, 4,000 spheres 4.1 ms, the same for clusters of 2 to 32
+// blocks), a set of envs solved from LDS by one block 650 plus 0.72 per
+// sphere (2,000 spheres 2.0 ms, 5,000 spheres 4.4 ms), and each sphere that a
+// single block keeps in global memory 4 more.  An env of more than Ns spheres
+// takes a cluster of blocks of one XCD lane, as many as finish in M; the
+// others are packed (first fit, largest first) into sets that finish in M.
+// Ns and M are searched for the smallest predicted makespan (sets placed
+// largest first on the least loaded block).  tasks gets each block's cluster
+// share (env, rank, K, first block) and then its sets as (env, set number, 1,
+// 0); false when no candidate fits the blocks.
 bool plan_auto(const tr_scene* s, const std::vector<int>& order, int B, int lds_cap,
                std::vector<std::vector<int4>>& best_tasks)
 {
-    constexpr double kAc = 1800.0, kWc = 1.77, kWs = 0.6, kWset = 1300.0, kWg = 2.5;
+    constexpr double kAc = 900.0, kWc = 0.82, kWs = 0.72, kWset = 650.0, kWg = 4.0;
     const int G = kGroups, PL = B / G, waves = kEnvBlk / 64;
-    std::vector<std::vector<int>> sets;
-    std::vector<double> fill;
     double work0 = 0.0;
-    for (int e : order) {
-        const double n = (double)s->envs[e].n;
-        if (n > lds_cap) {
-            work0 += kWc * n;
-            continue;
-        }
-        work0 += kWs * n;
-        size_t k = 0;
-        while (k < sets.size() && (fill[k] + n > lds_cap || (int)sets[k].size() >= waves)) ++k;
-        if (k == sets.size()) {
-            sets.emplace_back();
-            fill.push_back(0.0);
-        }
-        sets[k].push_back(e);
-        fill[k] += n;
-    }
-    work0 += kWset * (double)sets.size();
+    for (int e : order) work0 += kWc * (double)s->envs[e].n;
+    const double lo = std::max(0.8 * work0 / B, kAc + 50.0);
+    auto alone = [&](double n) { return kWset + kWs * std::min(n, (double)lds_cap) + kWg * std::max(0.0, n - lds_cap); };
     double best = 1e300;
-    for (double fs : {1.0, 1.1, 1.2, 1.3, 1.4, 1.5, 1.6}) {
+    for (double fs : {0.1, 0.15, 0.22, 0.32, 0.45, 0.6, 0.8, 1.0, 1.1, 1.25}) {
         const double Ns = fs * lds_cap;
-        for (int m = 0; m <= 36; ++m) {
-            const double M = work0 / B * (0.7 + 0.025 * m);
-            std::vector<double> load(B, 0.0);
+        for (int m = 0; m <= 48; ++m) {
+            const double M = lo * std::pow(1.03, m);
+            if (M >= best) break;  // no block finishes its largest job before M
+            const double set_cap = std::min((double)lds_cap, std::max(Ns, (M - kWset) / kWs));
+            std::vector<double> load(B, 0.0), fill;
             std::vector<int> lane_next(G, 0);
             std::vector<std::vector<int4>> tasks(B);
-            std::vector<std::pair<double, int>> jobs;  // (cost, env) or (cost, -1 - set)
+            std::vector<std::vector<int>> sets;
             bool ok = true;
             for (int e : order) {
                 const double n = (double)s->envs[e].n;
-                if (n <= lds_cap) continue;
-                if (n <= Ns) {
-                    jobs.push_back({kWs * lds_cap + kWg * (n - lds_cap) + kWset, e});
+                if (n > Ns) {
+                    const int K = std::max({2, (int)std::ceil(kWc * n / (M - kAc)), (int)std::ceil(n / lds_cap)});
+                    int lane = 0;
+                    for (int x = 1; x < G; ++x)
+                        if (lane_next[x] < lane_next[lane]) lane = x;
+                    if (K > PL - lane_next[lane]) {
+                        ok = false;
+                        break;
+                    }
+                    const int first = lane + G * lane_next[lane];
+                    for (int r = 0; r < K; ++r) {
+                        tasks[first + G * r].push_back(make_int4(e, r, K, first));
+                        load[first + G * r] += kAc + kWc * n / K;
+                    }
+                    lane_next[lane] += K;
                     continue;
                 }
-                if (M <= kAc) {
-                    ok = false;
-                    break;
+                size_t k = 0;
+                while (k < sets.size() && (fill[k] + n > set_cap || (int)sets[k].size() >= waves)) ++k;
+                if (k == sets.size()) {
+                    sets.emplace_back();
+                    fill.push_back(0.0);
                 }
-                const int K = std::max(2, (int)std::ceil(kWc * n / (M - kAc)));
-                int lane = 0;
-                for (int x = 1; x < G; ++x)
-                    if (lane_next[x] < lane_next[lane]) lane = x;
-                if (K > PL - lane_next[lane]) {
-                    ok = false;
-                    break;
-                }
-                const int first = lane + G * lane_next[lane];
-                for (int r = 0; r < K; ++r) {
-                    tasks[first + G * r].push_back(make_int4(e, r, K, first));
-                    load[first + G * r] += kAc + kWc * n / K;
-                }
-                lane_next[lane] += K;
+                sets[k].push_back(e);
+                fill[k] += n;
             }
             if (!ok) continue;
-            for (size_t k = 0; k < sets.size(); ++k) jobs.push_back({kWs * fill[k] + kWset, -1 - (int)k});
-            std::stable_sort(jobs.begin(), jobs.end(), [](const std::pair<double, int>& a, const std::pair<double, int>& c) {
-                return a.first > c.first;
-            });
+            std::vector<size_t> by_cost(sets.size());
+            for (size_t k = 0; k < sets.size(); ++k) by_cost[k] = k;
+            std::stable_sort(by_cost.begin(), by_cost.end(), [&](size_t a, size_t c) { return fill[a] > fill[c]; });
+            std::priority_queue<std::pair<double, int>, std::vector<std::pair<double, int>>, std::greater<>> least;
+            for (int i = 0; i < B; ++i) least.push({load[i], i});
             int setno = 0;
-            for (const auto& j : jobs) {
-                int blk = 0;
-                for (int i = 1; i < B; ++i)
-                    if (load[i] < load[blk]) blk = i;
-                load[blk] += j.first;
-                if (j.second >= 0) tasks[blk].push_back(make_int4(j.second, setno, 1, 0));
-                else
-                    for (int e : sets[-1 - j.second]) tasks[blk].push_back(make_int4(e, setno, 1, 0));
+            for (size_t k : by_cost) {
+                const int blk = least.top().second;
+                least.pop();
+                load[blk] += alone(fill[k]);
+                least.push({load[blk], blk});
+                for (int e : sets[k]) tasks[blk].push_back(make_int4(e, setno, 1, 0));
                 ++setno;
             }
             const double mk = *std::max_element(load.begin(), load.end());
             if (mk < best) {
                 best = mk;
-                best_tasks = tasks;
+                best_tasks = std::move(tasks);
             }
         }
     }
