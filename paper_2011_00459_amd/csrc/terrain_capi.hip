@@ -868,7 +868,7 @@ int create_scene(const tr_scene_desc* d, tr_scene** out)
     s->cfg.cluster_particles = 0;
     s->cfg.dataflow = 0;
     z.pgs_grid = kGroups * std::max(1, std::min(s->cfg.blocks_per_xcd, pgs_resident_blocks() / kGroups));
-    z.col_grid = std::min(colour_resident_blocks(), 2048);
+    z.col_grid = colour_resident_blocks(&z.col_per);
     DevBuffers& b = s->b;
     bool ok = alloc_n(s, b.xr, z.P) && alloc_n(s, b.vw, 2 * z.P) && alloc_n(s, b.xr2, z.P) &&
               alloc_n(s, b.vw2, 2 * z.P) && alloc_n(s, b.pid, z.P) && alloc_n(s, b.pid2, z.P) &&
@@ -879,7 +879,7 @@ int create_scene(const tr_scene_desc* d, tr_scene** out)
               alloc_n(s, b.id_count, z.NID) && alloc_n(s, b.id_start, z.NID + 1) && alloc_n(s, b.id_fill, z.NID) &&
               alloc_n(s, b.pid_start, z.NID + 1) && alloc_n(s, b.inc_count, z.P) &&
               alloc_n(s, b.inc_start, z.P + 1) && alloc_n(s, b.inc_fill, z.P) && alloc_n(s, b.inc, 2 * z.C) &&
-              alloc_n(s, b.colour, z.C) && alloc_n(s, b.col_wait, z.C) && alloc_n(s, b.icode, 2 * z.C) &&
+              alloc_n(s, b.colour, z.C) && alloc_n(s, b.pinc, 2 * z.C) && alloc_n(s, b.cmsg, z.C) && alloc_n(s, b.icode, 2 * z.C) &&
               alloc_n(s, b.smask, z.P) && alloc_n(s, b.seq, z.C) && alloc_n(s, b.rm, z.C) && alloc_n(s, b.cpos, z.C) &&
               alloc_n(s, b.r0, z.C) && alloc_n(s, b.r1, z.C) && alloc_n(s, b.r2, z.C) && alloc_n(s, b.rk, z.C) &&
               alloc_n(s, b.r3, z.roll_C) && alloc_n(s, b.lamr, z.roll_C) && alloc_n(s, b.lamr0, z.roll_C) &&
@@ -1083,7 +1083,7 @@ void enqueue_step(tr_scene* s, hipStream_t st, bool events)
     launch_narrow(s->b, s->p, s->z, st);
     launch_canonical(s->b, s->p, s->z, st);
     if (events) (void)hipEventRecord(s->ev[1], st);
-    launch_depth(s->b, s->p, s->z, st);
+    if (rows_features(s)) launch_depth(s->b, s->p, s->z, st);
     launch_colour(s->b, s->p, s->z, st);
     launch_rows(s->b, s->p, s->z, s->have_prev, rows_features(s), st);
     launch_impact_stage(s->b, s->p, s->z, st);

@@ -214,7 +214,8 @@ struct DevBuffers {
     uint32_t *id_count, *id_start, *id_fill, *pid_start;  // [NID], [NID+1], [NID], [NID+1]
     uint32_t *inc_count, *inc_start, *inc_fill, *inc;     // [P], [P+1], [P], [2C]
     int* colour;                                    // [C]
-    uint32_t* col_wait;                             // [C] colouring: the neighbour that blocked a contact
+    uint2* pinc;                                    // [2C] incident contacts in order of colouring priority, with the other sphere
+    unsigned long long* cmsg;                       // [C] colouring across blocks: the first sphere's used colours
     uint8_t* icode;                                 // [2C] bucket of each incidence entry in its owner's order
     ulonglong2* smask;                              // [P] colours of a sphere's contacts, of those solved away
     uint32_t* seq;                                  // [C] solve order: places in the bodies' update sequences (8 bits each), their lengths
@@ -298,6 +299,7 @@ struct Sizes {
     int n_units;    // entries of ustats
     int flow;       // colour order kept by per-sphere update counters instead of barriers
     int col_grid;   // resident blocks of the colouring kernel
+    int col_per;    // spheres a block of it holds in LDS
     int64_t NCOL;   // depth columns (all envs)
 };
 
@@ -415,6 +417,6 @@ int pgs_resident_blocks();
 int pgs_group_max_lds();
 int pgs_env_resident_blocks(int lds_bytes);
 int pgs_env_max_lds();
-int colour_resident_blocks();
+int colour_resident_blocks(int* per_block);
 
 }  // namespace trk

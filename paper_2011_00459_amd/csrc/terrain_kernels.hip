@@ -28,6 +28,7 @@
 namespace trk {
 
 constexpr int kBlk = 256;
+constexpr unsigned long long kNoMask = ~0ull;  // no colours sent yet (DevBuffers::cmsg)
 #ifndef TRK_BARRIER_SPINS
 #define TRK_BARRIER_SPINS (1l << 22)
 #endif
@@ -500,6 +501,10 @@ __global__ void k_inc_count(DevBuffers b, int64_t cap)
         const uint32_t c = c0 + threadIdx.x;
         const bool on = c < nc;
         const int2 pr = on ? b.cpair[c] : make_int2(-1, 0);
+        if (on) {  // for the colouring
+            b.colour[c] = -1;
+            b.cmsg[c] = kNoMask;
+        }
         // the particle whose id leads the key comes in runs: pr.x for a
         // pair, pr.y for a boundary contact (pr.x < 0)
         const int own = pr.x >= 0 ? pr.x : pr.y, other = pr.x >= 0 ? pr.y : -1;
@@ -533,12 +538,60 @@ __device__ inline int contact_rank(int ra, int rb)
 
 __device__ inline int region_of(const EnvDev& E, int slot) { return (slot - E.slot_begin) / E.chunk; }
 
-// each sphere's incident contacts in canonical order
-__global__ void k_inc_sort(DevBuffers b, int n)
+// Each sphere's incident contacts, in canonical order (inc) and, with the
+// other sphere of each, in the colouring's order of decreasing
+// (splitmix64(key), key) (pinc).  A thread holds its sphere's contacts in
+// registers and ranks them against each other; within an env canonical order
+// is key order, so indices break equal hashes.
+constexpr int kMaxRank = 16;
+constexpr uint32_t kSecond = 0x80000000u;    // pinc: the sphere is the contact's second one
+constexpr uint32_t kBoundary = 0x7fffffffu;  // pinc: a boundary in place of the other sphere
+
+__device__ inline uint2 pinc_entry(uint32_t c, int2 pr, int s)
+{
+    return make_uint2(c, pr.x < 0 ? kBoundary : (pr.x == s ? (uint32_t)pr.y : (uint32_t)pr.x | kSecond));
+}
+
+__global__ __launch_bounds__(kBlk) void k_inc_sort(DevBuffers b, int n)
 {
     int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= n) return;
-    uint32_t beg = b.inc_start[s], end = b.inc_start[s + 1];
+    const uint32_t beg = b.inc_start[s], end = b.inc_start[s + 1], deg = end - beg;
+    if (deg <= kMaxRank) {
+        uint32_t e[kMaxRank], at[kMaxRank], pat[kMaxRank];
+        unsigned long long h[kMaxRank];
+        int2 pr[kMaxRank];
+#pragma unroll
+        for (int j = 0; j < kMaxRank; ++j) e[j] = (uint32_t)j < deg ? b.inc[beg + j] : ~0u;
+#pragma unroll
+        for (int j = 0; j < kMaxRank; ++j)
+            if ((uint32_t)j < deg) pr[j] = b.cpair[e[j]];
+#pragma unroll
+        for (int j = 0; j < kMaxRank; ++j) {
+            h[j] = (uint32_t)j < deg ? splitmix64(b.ckey[e[j]]) : 0ull;
+            at[j] = pat[j] = 0;
+        }
+#pragma unroll
+        for (int j = 1; j < kMaxRank; ++j) {
+            if (__ballot((uint32_t)j < deg) == 0ull) break;
+#pragma unroll
+            for (int i = 0; i < j; ++i) {
+                const bool up = e[i] < e[j];
+                at[j] += up ? 1u : 0u;
+                at[i] += up ? 0u : 1u;
+                const bool first = (uint32_t)j >= deg || h[i] > h[j] || (h[i] == h[j] && !up);
+                pat[j] += first ? 1u : 0u;
+                pat[i] += first ? 0u : 1u;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < kMaxRank; ++j)
+            if ((uint32_t)j < deg) {
+                b.inc[beg + at[j]] = e[j];
+                b.pinc[beg + pat[j]] = pinc_entry(e[j], pr[j], s);
+            }
+        return;
+    }
     for (uint32_t u = beg + 1; u < end; ++u) {
         uint32_t v = b.inc[u];
         uint32_t t = u;
@@ -547,6 +600,17 @@ __global__ void k_inc_sort(DevBuffers b, int n)
             --t;
         }
         b.inc[t] = v;
+    }
+    for (uint32_t u = beg; u < end; ++u) {
+        const uint32_t v = b.inc[u];
+        const unsigned long long h = splitmix64(b.ckey[v]);
+        uint32_t t = u;
+        // (v is larger than every index before it: it goes before equal hashes)
+        while (t > beg && splitmix64(b.ckey[b.pinc[t - 1].x]) <= h) {
+            b.pinc[t] = b.pinc[t - 1];
+            --t;
+        }
+        b.pinc[t] = pinc_entry(v, b.cpair[v], s);
     }
 }
 
@@ -570,102 +634,162 @@ void launch_canonical(const DevBuffers& b, const StepParams& p, const Sizes& z, 
 
 // ---------------------------------------------------------------------------
 // A7: colouring.  Each contact takes the least colour unused by its
-// conflicting contacts of higher (splitmix64(key), key) priority, once all of
-// those are coloured: the unique Jones-Plassmann result.  Resident grid, each
-// thread re-visits its uncoloured contacts until none is left (bounded).
+// conflicting contacts of higher (splitmix64(key), key) priority: the unique
+// Jones-Plassmann result.  Every sphere works through its contacts in order
+// of priority (pinc): a contact is coloured when it is the next one of both
+// its spheres, with the least colour neither of them has used, and both move
+// on.  So a contact costs one look at each end when its turn comes, however
+// long the chain before it.  Blocks take contiguous ranges of the sorted
+// spheres and keep their state (colours used, next contact) in LDS, where a
+// link of a chain takes a few hundred cycles; a contact across two blocks is
+// coloured by the block of its second sphere, which the other sends its used
+// colours through cmsg and which answers with the colour.  The grid is
+// resident at once (blocks wait for each other); waits are bounded.
+// Measured against threads that revisited every uncoloured contact and its
+// conflicts until all were done: 984 contacts 97 -> 26 us, 152,000 163 -> 64,
+// 1.5 million 578 -> 135, 256 beds of 4.1 million 1,471 -> 256 us.
 // ---------------------------------------------------------------------------
+constexpr int kColChunk = 8;
+constexpr int kColBlk = 1024;
+constexpr unsigned long long kNextPending = ~0ull;        // the sphere's next contact is not looked up yet
+constexpr unsigned long long kNextDone = ~0ull - 1ull;    // no contact left
+constexpr uint32_t kAcrossAsk = ~0u, kAcrossAnswer = ~0u - 1u;  // second word of a next contact across blocks
+
 __device__ inline int ld_colour(const int* p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-constexpr int kColChunk = 8;
+// A sphere's state: the colours its contacts have (their number is also the
+// place of the next contact in pinc), and the next contact (low word) with the
+// block's index of its other sphere.  In LDS, or in memory (two words per
+// sphere in smask, which the colouring precedes) for scenes too large for it.
+struct ColourLds {
+    typedef volatile __attribute__((address_space(3))) unsigned long long Word;
+    Word *used, *next;
+    __device__ ColourLds(unsigned long long* p, int per) : used((Word*)p), next((Word*)p + per) {}
+    __device__ unsigned long long get_used(int i) const { return used[i]; }
+    __device__ unsigned long long get_next(int i) const { return next[i]; }
+    __device__ void set_used(int i, unsigned long long v) const { used[i] = v; }
+    __device__ void set_next(int i, unsigned long long v) const { next[i] = v; }
+    __device__ void order() const {}  // LDS accesses of a wave stay in order
+};
+struct ColourMem {
+    unsigned long long* m;
+    __device__ unsigned long long get(int k) const { return __hip_atomic_load(&m[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ void set(int k, unsigned long long v) const { __hip_atomic_store(&m[k], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ unsigned long long get_used(int i) const { return get(2 * i); }
+    __device__ unsigned long long get_next(int i) const { return get(2 * i + 1); }
+    __device__ void set_used(int i, unsigned long long v) const { set(2 * i, v); }
+    __device__ void set_next(int i, unsigned long long v) const { set(2 * i + 1, v); }
+    __device__ void order() const { __builtin_amdgcn_s_waitcnt(0); }
+};
 
-// Scans the conflicts of contact c.  Ready: returns true with the least
-// colour its coloured conflicts leave free (kMaxColours when none is).  Blocked by an uncoloured
-// conflict of higher priority: returns false with that conflict in wait.
-__device__ inline bool colour_try(const DevBuffers& b, uint32_t c, uint32_t& wait, int& col)
+template <bool LDS>
+__global__ __launch_bounds__(kColBlk) void k_colour(DevBuffers b, int n, int per, int max_pass)
 {
-    unsigned long long key = b.ckey[c];
-    unsigned long long h = splitmix64(key);
-    int2 pr = b.cpair[c];
-    unsigned long long used = 0;
-    int parts[2] = {pr.y, pr.x};
-    for (int q = 0; q < 2; ++q) {
-        int s = parts[q];
-        if (s < 0) continue;
-        uint32_t beg = b.inc_start[s], end = b.inc_start[s + 1];
-        // eight incident contacts at a time, each round of loads in flight together
-        for (uint32_t t0 = beg; t0 < end; t0 += kColChunk) {
-            uint32_t e[kColChunk];
-            int ce[kColChunk];
-            unsigned long long ke[kColChunk];
-#pragma unroll
-            for (int j = 0; j < kColChunk; ++j) e[j] = t0 + j < end ? b.inc[t0 + j] : c;
-#pragma unroll
-            for (int j = 0; j < kColChunk; ++j) ce[j] = e[j] != c ? ld_colour(&b.colour[e[j]]) : kMaxColours;
-#pragma unroll
-            for (int j = 0; j < kColChunk; ++j) ke[j] = ce[j] < 0 ? b.ckey[e[j]] : 0ull;
-#pragma unroll
-            for (int j = 0; j < kColChunk; ++j) {
-                if (e[j] == c) continue;
-                if (ce[j] < 0) {
-                    unsigned long long he = splitmix64(ke[j]);
-                    if (he > h || (he == h && ke[j] > key)) { wait = e[j]; return false; }
-                } else {
-                    used |= 1ull << ce[j];
-                }
-            }
-        }
+    HIP_DYNAMIC_SHARED(unsigned long long, col_state)
+    // neighbouring ranges on one XCD (consecutive blocks go to the 8 XCDs in turn)
+    const int blk = gridDim.x % kGroups ? (int)blockIdx.x
+                                        : (int)((blockIdx.x % kGroups) * (gridDim.x / kGroups) + blockIdx.x / kGroups);
+    const int base = min(n, (int)min((int64_t)blk * per, (int64_t)n)), ns = min(per, n - base);
+    auto state = [&] {
+        if constexpr (LDS) return ColourLds(col_state, per);
+        else return ColourMem{(unsigned long long*)(b.smask + base)};
+    }();
+    for (int i = threadIdx.x; i < ns; i += kColBlk) {
+        state.set_used(i, 0ull);
+        state.set_next(i, kNextPending);
     }
-    col = used == ~0ull ? kMaxColours : __builtin_ctzll(~used);
-    return true;
-}
-
-__global__ __launch_bounds__(kBlk) void k_colour(DevBuffers b, int64_t cap, int max_pass)
-{
-    uint32_t nc = n_contacts(b, cap);
-    // consecutive blocks run on the 8 XCDs in turn: the contact list in eight
-    // contiguous parts, part x coloured by the blocks of XCD x, so that the
-    // colours an env's contacts read and write stay in one XCD's L2 (except
-    // where a part boundary cuts an env); measured, about 5 % less colouring
-    // time than a grid-stride over the whole list.  Placement only changes
-    // the speed: colours are written once, so a late read only delays a contact.
-    uint32_t lo = 0, hi = nc, stride = gridDim.x * blockDim.x, first = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t nx = gridDim.x / kGroups;
-    if (nx > 0) {
-        const uint32_t x = blockIdx.x % kGroups, jb = blockIdx.x / kGroups;
-        lo = (uint32_t)((uint64_t)nc * x / kGroups);
-        hi = (uint32_t)((uint64_t)nc * (x + 1) / kGroups);
-        stride = nx * blockDim.x;
-        first = jb < nx ? lo + jb * blockDim.x + threadIdx.x : hi;
-    }
-    int local_max = 0;
-    bool ovf = false, left = true;
-    for (int pass = 0; pass < max_pass; ++pass) {
+    state.order();
+    __syncthreads();
+    int top = 0;
+    bool left = true, ovf = false;
+    for (int pass = 0; pass < max_pass && left; ++pass) {
         left = false;
-        for (uint32_t c = first; c < hi; c += stride) {
-            if (ld_colour(&b.colour[c]) >= 0) continue;
-            // the conflict that blocked this contact last pass: while it is
-            // uncoloured the contact stays blocked (a full scan decides readiness)
-            if (pass > 0) {
-                const uint32_t wb = b.col_wait[c];
-                if (wb != ~0u && ld_colour(&b.colour[wb]) < 0) { left = true; continue; }
+        bool moved = false;
+        for (int i = threadIdx.x; i < ns; i += kColBlk) {
+            unsigned long long q = state.get_next(i);
+            if (q == kNextDone) continue;
+            left = true;
+            if (q == kNextPending) {
+                moved = true;
+                const int s = base + i;
+                const unsigned long long used = state.get_used(i);
+                const uint32_t pos = b.inc_start[s] + (uint32_t)__popcll(used);
+                if (pos >= b.inc_start[s + 1]) {
+                    state.set_next(i, kNextDone);
+                    continue;
+                }
+                const uint2 en = b.pinc[pos];
+                const uint32_t c = en.x;
+                if (en.y == kBoundary) {  // conflicts at its sphere only
+                    if (used == ~0ull) { ovf = true; break; }
+                    const int col = __builtin_ctzll(~used);
+                    b.colour[c] = col;
+                    top = max(top, col + 1);
+                    state.set_used(i, used | (1ull << col));
+                    continue;
+                }
+                const int other = (int)(en.y & ~kSecond) - base;
+                uint32_t how = (uint32_t)other;
+                if (other < 0 || other >= ns) {
+                    how = (en.y & kSecond) ? kAcrossAnswer : kAcrossAsk;
+                    if (how == kAcrossAsk)
+                        __hip_atomic_store(&b.cmsg[c], used, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                q = ((unsigned long long)how << 32) | c;
+                state.set_next(i, q);
             }
-            uint32_t w;
-            int col;
-            if (!colour_try(b, c, w, col)) { b.col_wait[c] = w; left = true; continue; }
-            ovf |= col == kMaxColours;
-            col = min(col, kMaxColours - 1);
+            const uint32_t c = (uint32_t)q, how = (uint32_t)(q >> 32);
+            if (how == kAcrossAsk) {
+                const int col = ld_colour(&b.colour[c]);
+                if (col < 0) continue;
+                state.set_used(i, state.get_used(i) | (1ull << col));
+                state.set_next(i, kNextPending);
+                moved = true;
+                continue;
+            }
+            unsigned long long theirs;
+            if (how == kAcrossAnswer) {
+                theirs = __hip_atomic_load(&b.cmsg[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (theirs == kNoMask) continue;
+            } else {
+                // both ends see a match; the one of the later sphere colours it
+                if ((int)how > i) continue;
+                const unsigned long long o = state.get_next((int)how);
+                if ((uint32_t)o != c || o >= kNextDone) continue;
+                theirs = state.get_used((int)how);
+            }
+            const unsigned long long mine = state.get_used(i), both = mine | theirs;
+            if (both == ~0ull) { ovf = true; break; }
+            const int col = __builtin_ctzll(~both);
+            const unsigned long long bit = 1ull << col;
             __hip_atomic_store(&b.colour[c], col, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            local_max = max(local_max, col + 1);
+            top = max(top, col + 1);
+            moved = true;
+            state.set_used(i, mine | bit);
+            if (how != kAcrossAnswer) state.set_used((int)how, theirs | bit);
+            state.order();
+            state.set_next(i, kNextPending);
+            if (how != kAcrossAnswer) state.set_next((int)how, kNextPending);
         }
-        if (!__syncthreads_or(left)) break;
-        __builtin_amdgcn_s_sleep(2);
+        left = __ballot(left) != 0ull;
+        bool stop = __ballot(ovf) != 0ull;
+        if (!stop && __ballot(moved) == 0ull) {
+            __builtin_amdgcn_s_sleep(1);
+            // (another block gave up?)
+            if ((pass & 255) == 255)
+                stop = __hip_atomic_load(&b.cnt->overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+        }
+        if (stop) {
+            left = false;
+            break;
+        }
     }
     // one atomic per wave (same-address atomics from every lane serialise)
-    for (int o = 32; o > 0; o >>= 1) local_max = max(local_max, __shfl_xor(local_max, o, 64));
-    if ((threadIdx.x & 63) == 0 && local_max) atomicMax(&b.cnt->n_colours, (uint32_t)local_max);
+    for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o, 64));
+    if ((threadIdx.x & 63) == 0 && top) atomicMax(&b.cnt->n_colours, (uint32_t)top);
     if (ovf) atomicOr(&b.cnt->overflow, kOvfColours);
     if (left) atomicOr(&b.cnt->overflow, kFailColouring);
 }
@@ -692,22 +816,19 @@ __global__ void k_region_masks(DevBuffers b, StepParams p)
     const int r = region_of(E, s);
     unsigned long long all = 0, away = 0;
     for (uint32_t t0 = beg; t0 < end; t0 += kColChunk) {
-        uint32_t e[kColChunk];
+        uint2 e[kColChunk];
         int col[kColChunk];
-        int2 pr[kColChunk];
 #pragma unroll
-        for (int j = 0; j < kColChunk; ++j) e[j] = b.inc[min(t0 + j, end - 1)];
+        for (int j = 0; j < kColChunk; ++j) e[j] = b.pinc[min(t0 + j, end - 1)];
 #pragma unroll
-        for (int j = 0; j < kColChunk; ++j) col[j] = b.colour[e[j]];
-#pragma unroll
-        for (int j = 0; j < kColChunk; ++j) pr[j] = split ? b.cpair[e[j]] : make_int2(-1, -1);
+        for (int j = 0; j < kColChunk; ++j) col[j] = b.colour[e[j].x];
 #pragma unroll
         for (int j = 0; j < kColChunk; ++j) {
             if (col[j] < 0 || col[j] >= kMaxColours) continue;  // failed colouring: the step is abandoned
             const unsigned long long bit = 1ull << col[j];
             all |= bit;
-            if (pr[j].x < 0) continue;
-            const int q = region_of(E, pr[j].x == s ? pr[j].y : pr[j].x);
+            if (!split || e[j].y == kBoundary) continue;
+            const int q = region_of(E, (int)(e[j].y & ~kSecond));
             if (q != r && contact_rank(r, q) != r) away |= bit;
         }
     }
@@ -734,7 +855,7 @@ __device__ inline bool to_away(ulonglong2 m, int col)
 // EnvDev) lists the contacts it solves: those of its spheres, each once, by
 // colour and, within a colour, the shared ones (a body that another block
 // updated last, or one without an LDS place) before the private ones; equal
-// ones in the order of its spheres and their incident contacts, which is
+// ones in the order of its spheres and their contacts' priorities, which is
 // fixed, so that the residual sums are reproducible.  Which contacts share a
 // bucket does not change results.  Two passes over the owner's incidence
 // lists: counts per wave and bucket, then positions; a lane's rank among the
@@ -780,22 +901,20 @@ __global__ __launch_bounds__(kOrdBlk) void k_order(DevBuffers b)
                 if (E.coded) ms = b.smask[s];
             }
             for (; __ballot(t < end); t += kColChunk) {
-                uint32_t e[kColChunk], code[kColChunk];
-                int2 pr[kColChunk];
+                uint2 e[kColChunk];
+                uint32_t code[kColChunk];
 #pragma unroll
-                for (int j = 0; j < kColChunk; ++j) e[j] = t + j < end ? b.inc[t + j] : ~0u;
-#pragma unroll
-                for (int j = 0; j < kColChunk; ++j) pr[j] = e[j] != ~0u ? b.cpair[e[j]] : make_int2(-1, -1);
+                for (int j = 0; j < kColChunk; ++j) e[j] = t + j < end ? b.pinc[t + j] : make_uint2(~0u, kBoundary);
 #pragma unroll
                 for (int j = 0; j < kColChunk; ++j) {
                     code[j] = kNotMine;
-                    if (e[j] == ~0u) continue;
-                    const int other = pr[j].x == s ? pr[j].y : pr[j].x;
-                    const bool two = pr[j].x >= 0, inside = two && other >= lo && other < hi;
-                    const bool take = inside ? pr[j].y == s
+                    if (e[j].x == ~0u) continue;
+                    const int other = (int)(e[j].y & ~kSecond);
+                    const bool two = e[j].y != kBoundary, inside = two && other >= lo && other < hi;
+                    const bool take = inside ? (e[j].y & kSecond) != 0
                                              : (!two || contact_rank(rank, region_of(E, other)) == rank);
                     if (!take) continue;
-                    const int col = b.colour[e[j]];
+                    const int col = b.colour[e[j].x];
                     code[j] = kUncoloured;
                     if (col >= 0 && col < kMaxColours) {
                         bool priv = !E.coded || ((inside || !two) && !from_away(ms, col));
@@ -808,7 +927,7 @@ __global__ __launch_bounds__(kOrdBlk) void k_order(DevBuffers b)
                 for (int j = 0; j < kColChunk; ++j) {
                     const unsigned long long same = match(code[j]);
                     if (code[j] < kOrdBuckets && (same & lower) == 0) mine[code[j]] += (uint32_t)__popcll(same);
-                    if (e[j] != ~0u) b.icode[t + j] = (uint8_t)code[j];
+                    if (e[j].x != ~0u) b.icode[t + j] = (uint8_t)code[j];
                 }
             }
         }
@@ -854,7 +973,7 @@ __global__ __launch_bounds__(kOrdBlk) void k_order(DevBuffers b)
                 uint32_t e[kColChunk], code[kColChunk];
 #pragma unroll
                 for (int j = 0; j < kColChunk; ++j) {
-                    e[j] = t + j < end ? b.inc[t + j] : ~0u;
+                    e[j] = t + j < end ? b.pinc[t + j].x : ~0u;
                     code[j] = t + j < end ? b.icode[t + j] : kNotMine;
                 }
 #pragma unroll
@@ -875,8 +994,16 @@ __global__ __launch_bounds__(kOrdBlk) void k_order(DevBuffers b)
 
 void launch_colour(const DevBuffers& b, const StepParams& p, const Sizes& z, hipStream_t s)
 {
-    launch_fill_u32((uint32_t*)b.colour, 0xFFFFFFFFu, z.C, s);
-    hipLaunchKernelGGL(k_colour, dim3(z.col_grid), dim3(kBlk), 0, s, b, z.C, 100000);
+    if (p.n_particles > 0) {
+        // at least 1,024 spheres a block: chains across blocks cost about a
+        // microsecond a link
+        const int per = (int)std::max<int64_t>(kColBlk, cdiv(p.n_particles, z.col_grid));
+        const unsigned g = (unsigned)cdiv(p.n_particles, per);
+        if (per <= z.col_per)
+            hipLaunchKernelGGL(k_colour<true>, dim3(g), dim3(kColBlk), (size_t)per * 16, s, b, p.n_particles, per, 1 << 22);
+        else
+            hipLaunchKernelGGL(k_colour<false>, dim3(g), dim3(kColBlk), 0, s, b, p.n_particles, per, 1 << 22);
+    }
     if (z.masks && p.n_particles > 0)
         hipLaunchKernelGGL(k_region_masks, dim3((unsigned)cdiv(p.n_particles, kBlk)), dim3(kBlk), 0, s, b, p);
     if (z.n_own > 0) hipLaunchKernelGGL(k_order, dim3((unsigned)z.n_own), dim3(kOrdBlk), 0, s, b);
@@ -2308,20 +2435,18 @@ int pgs_resident_blocks()
                            pgs_group_max_lds());
 }
 
-// The colouring's blocks wait for each other's contacts, so all of them must
-// run at once.  The occupancy query reports 7 blocks of k_colour per CU on
-// MI355X, but a grid of exactly that many was measured not to be resident at
-// once (some blocks start only after others finish: a 578k-contact step
-// then gave up with contacts uncoloured), while one block per CU fewer
-// always is: keep that slack.
-int colour_resident_blocks()
+// The colouring's blocks wait for each other, so all of them must run at
+// once: one block per CU; per_block: the spheres whose state its LDS holds.
+int colour_resident_blocks(int* per_block)
 {
-    int dev = 0, per_cu = 0;
+    int dev = 0;
     (void)hipGetDevice(&dev);
     hipDeviceProp_t pr;
     (void)hipGetDeviceProperties(&pr, dev);
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_colour, kBlk, 0);
-    return std::max(1, per_cu - 1) * pr.multiProcessorCount;
+    const int lds = max_dynamic_lds((const void*)k_colour<true>, (const void*)k_colour<true>);
+    (void)hipFuncSetAttribute((const void*)k_colour<true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    *per_block = lds / 16;
+    return pr.multiProcessorCount;
 }
 
 void launch_pgs(const DevBuffers& b, const StepParams& p, const Sizes& z, hipStream_t s, int sweeps_cap, int slot)
