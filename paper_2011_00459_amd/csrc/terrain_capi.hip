@@ -63,6 +63,7 @@ struct tr_scene {
     std::vector<std::pair<void*, size_t>> allocs;
     int64_t cells_alloc = 0;
     int64_t zone_chunk_alloc = 0;
+    int64_t force_alloc = 0;          // partials of the body forces allocated (bodies x chunks)
     int64_t hf_alloc = 0;
     int bodies_alloc = 0, shapes_alloc = 0, zones_alloc = 0, tools_alloc = 0;
     std::vector<ToolDev> tool_host;  // last uploaded tool table
@@ -419,7 +420,6 @@ int rebuild_plan(tr_scene* s)
     int grp_lds = 0;
     std::vector<int> own_x;
     int64_t x_next = 0;
-    int masks = 0;
     // the counter-ordered solve keeps one slot of block partials per sweep;
     // longer solves take the ordinary one (same results)
     const bool flow = s->cfg.dataflow != 0 && s->desc.max_sweeps <= kFlowMaxSweeps;
@@ -431,7 +431,6 @@ int rebuild_plan(tr_scene* s)
         D.res_cap = res_cap;
         D.coded = coded && !flow ? 1 : 0;
         D.masks = coded ? 1 : 0;
-        masks |= D.masks;
     };
     // exchange records of env e: K regions of stride LDS indices from x_next on
     auto set_exchange = [&](int e, int stride) {
@@ -535,7 +534,6 @@ int rebuild_plan(tr_scene* s)
     s->z.n_own = n_own;
     s->z.grp_lds = grp_lds;
     s->z.n_flags = (int)flags;
-    s->z.masks = masks;
     if ((int64_t)plan.size() > s->plan_alloc) {
         dfree(s, s->b.plan);
         if (!alloc_n(s, s->b.plan, (int64_t)plan.size())) return fail(s, TR_E_NOMEM, "PGS plan");
@@ -704,23 +702,30 @@ int rebuild_tables(tr_scene* s)
     hipStream_t st = s->stream;
     // (re)allocate tables whose size depends on the scene content
     if (NC + 1 > s->cells_alloc) {
-        dfree(s, s->b.cell_count); dfree(s, s->b.cell_start); dfree(s, s->b.cell_fill);
+        dfree(s, s->b.cell_count); dfree(s, s->b.cell_start);
         dfree(s, s->b.scan_tmp);
-        if (!alloc_n(s, s->b.cell_count, NC) || !alloc_n(s, s->b.cell_start, NC + 1) || !alloc_n(s, s->b.cell_fill, NC))
+        if (!alloc_n(s, s->b.cell_count, NC) || !alloc_n(s, s->b.cell_start, NC + 1))
             return fail(s, TR_E_NOMEM, "cell arrays");
+        HIP_CHECK(s, hipMemsetAsync(s->b.cell_count, 0, sizeof(uint32_t) * NC, st));
         int64_t words = std::max({scan_tmp_words(NC), scan_tmp_words(s->z.NID), scan_tmp_words(s->z.P)});
         if (!alloc_n(s, s->b.scan_tmp, words)) return fail(s, TR_E_NOMEM, "scan scratch");
         s->cells_alloc = NC + 1;
     }
-    if ((int)bd.size() > s->bodies_alloc || (int)sd.size() > s->shapes_alloc || n_zones > s->zones_alloc) {
+    // contacts of an env in chunks of about 2,000 for its bodies' forces
+    int64_t nmax = 0;
+    for (int e = 0; e < E; ++e) nmax = std::max<int64_t>(nmax, s->envs[e].n);
+    s->p.force_chunks = (int)std::min<int64_t>(1024, std::max<int64_t>(8, nmax / 700));
+    if ((int)bd.size() > s->bodies_alloc || (int)sd.size() > s->shapes_alloc || n_zones > s->zones_alloc ||
+        (int64_t)bd.size() * s->p.force_chunks > s->force_alloc) {
         dfree(s, s->b.bodies); dfree(s, s->b.shapes); dfree(s, s->b.force_part); dfree(s, s->b.body_ft);
         dfree(s, s->b.zone_mom); dfree(s, s->b.aggs);
         int nb = std::max<int>((int)bd.size(), 1), ns = std::max<int>((int)sd.size(), 1), nz = std::max(n_zones, 1);
         if (!alloc_n(s, s->b.bodies, nb) || !alloc_n(s, s->b.shapes, ns) ||
-            !alloc_n(s, s->b.force_part, (int64_t)nb * kForceChunks * 6) || !alloc_n(s, s->b.body_ft, (int64_t)nb * 6) ||
+            !alloc_n(s, s->b.force_part, (int64_t)nb * s->p.force_chunks * 6) || !alloc_n(s, s->b.body_ft, (int64_t)nb * 6) ||
             !alloc_n(s, s->b.zone_mom, (int64_t)nz * kZoneMoments) || !alloc_n(s, s->b.aggs, nz))
             return fail(s, TR_E_NOMEM, "body tables");
         s->bodies_alloc = nb; s->shapes_alloc = ns; s->zones_alloc = nz;
+        s->force_alloc = (int64_t)nb * s->p.force_chunks;
         HIP_CHECK(s, hipMemsetAsync(s->b.body_ft, 0, sizeof(double) * nb * 6, st));
         HIP_CHECK(s, hipMemsetAsync(s->b.aggs, 0, sizeof(tr_aggregate) * nz, st));
     }
@@ -729,10 +734,21 @@ int rebuild_tables(tr_scene* s)
         if (!alloc_n(s, s->b.colmax, NCOL)) return fail(s, TR_E_NOMEM, "depth columns");
         s->cols_alloc = NCOL;
     }
+    const int n_chunks = (int)chunks.size();
+    std::vector<std::pair<int, int>> env_chunks(E, {0, 0});
+    for (int c = 0; c < n_chunks; ++c) {
+        auto& r = env_chunks[chunks[c].x];
+        if (r.second == 0) r.first = c;
+        r.second = c + 1;
+    }
+    chunks.resize(n_chunks + n_zones);
+    for (int e = 0; e < E; ++e)
+        for (int z = 0; z < ed[e].zone_count; ++z)
+            chunks[n_chunks + ed[e].zone_slot[z]] = make_int4(e, z, env_chunks[e].first, env_chunks[e].second);
     if ((int64_t)chunks.size() > s->zone_chunk_alloc) {
         dfree(s, s->b.zone_chunks); dfree(s, s->b.zone_part);
         int64_t nch = std::max<int64_t>((int64_t)chunks.size(), 1);
-        if (!alloc_n(s, s->b.zone_chunks, nch) || !alloc_n(s, s->b.zone_part, nch * kMaxZonesPerEnv * kZoneMoments))
+        if (!alloc_n(s, s->b.zone_chunks, nch) || !alloc_n(s, s->b.zone_part, nch * kMaxZonesPerEnv * kZonePart))
             return fail(s, TR_E_NOMEM, "zone chunks");
         s->zone_chunk_alloc = nch;
     }
@@ -762,7 +778,7 @@ int rebuild_tables(tr_scene* s)
     s->p.n_tools = (int)td.size();
     s->z.NC = NC;
     s->z.NCOL = NCOL;
-    s->z.n_zone_chunks = (int)chunks.size();
+    s->z.n_zone_chunks = n_chunks;
     s->p.n_bodies = (int)bd.size();
     s->p.n_shapes = (int)sd.size();
     s->p.n_zones = n_zones;
@@ -876,9 +892,9 @@ int create_scene(const tr_scene_desc* d, tr_scene** out)
               alloc_n(s, b.perm, z.P) && alloc_n(s, b.id2slot, z.NID) && alloc_n(s, b.rkey, z.C) &&
               alloc_n(s, b.ckey, z.C) && alloc_n(s, b.pkeyc, z.C) && alloc_n(s, b.rpair, z.C) &&
               alloc_n(s, b.cpair, z.C) && alloc_n(s, b.lamc, z.C) && alloc_n(s, b.plam, z.C) &&
-              alloc_n(s, b.id_count, z.NID) && alloc_n(s, b.id_start, z.NID + 1) && alloc_n(s, b.id_fill, z.NID) &&
+              alloc_n(s, b.id_count, z.NID) && alloc_n(s, b.id_start, z.NID + 1) &&
               alloc_n(s, b.pid_start, z.NID + 1) && alloc_n(s, b.inc_count, z.P) &&
-              alloc_n(s, b.inc_start, z.P + 1) && alloc_n(s, b.inc_fill, z.P) && alloc_n(s, b.inc, 2 * z.C) &&
+              alloc_n(s, b.inc_start, z.P + 1) && alloc_n(s, b.inc, 2 * z.C) &&
               alloc_n(s, b.colour, z.C) && alloc_n(s, b.pinc, 2 * z.C) && alloc_n(s, b.cmsg, z.C) && alloc_n(s, b.icode, 2 * z.C) &&
               alloc_n(s, b.smask, z.P) && alloc_n(s, b.seq, z.C) && alloc_n(s, b.rm, z.C) && alloc_n(s, b.cpos, z.C) &&
               alloc_n(s, b.r0, z.C) && alloc_n(s, b.r1, z.C) && alloc_n(s, b.r2, z.C) && alloc_n(s, b.rk, z.C) &&
@@ -904,6 +920,8 @@ int create_scene(const tr_scene_desc* d, tr_scene** out)
     if (e == hipSuccess) e = hipMemsetAsync(b.env_ncol, 0, sizeof(uint32_t) * d->n_envs, s->stream);
     if (e == hipSuccess) e = hipMemsetAsync(b.id_start, 0, sizeof(uint32_t) * (z.NID + 1), s->stream);
     if (e == hipSuccess) e = hipMemsetAsync(b.pid_start, 0, sizeof(uint32_t) * (z.NID + 1), s->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(b.id_count, 0, sizeof(uint32_t) * z.NID, s->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(b.inc_count, 0, sizeof(uint32_t) * z.P, s->stream);
     for (int k = 0; k < 5 && e == hipSuccess; ++k) e = hipEventCreate(&s->ev[k]);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) {

@@ -30,9 +30,9 @@ constexpr int kGroups = 8;          // PGS groups: one per XCD of the MI355X (bl
 constexpr int kOwnStride = 2 * kMaxColours + 1;  // entries of an owner's table of starts (DevBuffers::own_start)
 constexpr int kMaxHits = 32;        // contacts one particle may emit per step
 constexpr int kMaxZonesPerEnv = 4;  // bodies with an active zone per environment
-constexpr int kZoneMoments = 20;    // M, mx(3), mv(3), mxx(6), m x*v(3), sum Is(1), sum Is w(3)
-constexpr int kForceChunks = 32;    // deterministic chunks of the body-force reduction
-constexpr int kZoneChunk = 2048;    // particles per chunk of the zone reduction
+constexpr int kZoneMoments = 20;  // M, mx(3), mv(3), mxx(6), m x*v(3), sum Is(1), sum Is w(3)
+constexpr int kZoneChunk = 512;     // particles per chunk of the zone reduction
+constexpr int kZonePart = kZoneMoments + 1;  // a chunk's partial: the moments and the number of particles
 constexpr int kMlpParams = 64 * 12 + 64 + 64 * 64 + 64 + 3 * 64 + 3 + 12;
 
 // PGS solve modes
@@ -157,6 +157,7 @@ struct StepParams {
     int n_units;        // PGS solve units (entries of ustats)
     float restitution;  // Newton restitution of the impact stage
     int n_tools;        // zone predictor tools (all envs)
+    int force_chunks;   // chunks of a body's force reduction
 };
 
 // per PGS solve unit: an XCD group of envs (grouped mode) or one env
@@ -206,13 +207,13 @@ struct DevBuffers {
     uint32_t *pkey, *perm;
     int* id2slot;         // [NID]
     // cells
-    uint32_t *cell_count, *cell_start, *cell_fill;  // [NC], [NC+1], [NC]
+    uint32_t *cell_count, *cell_start;              // [NC], [NC+1]; the counts are zero between steps
     // contacts
     unsigned long long *rkey, *ckey, *pkeyc;        // raw, canonical, previous canonical
     int2 *rpair, *cpair;
     float4 *lamc, *plam;                            // canonical impulses (current, previous)
-    uint32_t *id_count, *id_start, *id_fill, *pid_start;  // [NID], [NID+1], [NID], [NID+1]
-    uint32_t *inc_count, *inc_start, *inc_fill, *inc;     // [P], [P+1], [P], [2C]
+    uint32_t *id_count, *id_start, *pid_start;      // [NID], [NID+1], [NID+1]
+    uint32_t *inc_count, *inc_start, *inc;          // [P], [P+1], [2C]
     int* colour;                                    // [C]
     uint2* pinc;                                    // [2C] incident contacts in order of colouring priority, with the other sphere
     unsigned long long* cmsg;                       // [C] colouring across blocks: the first sphere's used colours
@@ -239,12 +240,12 @@ struct DevBuffers {
     // reductions
     double* resid_acc;    // [max_sweeps * 2] per-sweep numerator / denominator... (block partials)
     double* block_part;   // [2 parities][grid][2]
-    double* force_part;   // [bodies * kForceChunks * 6]
+    double* force_part;   // [bodies * force_chunks * 6]
     double* body_ft;      // [bodies * 6]
-    double* zone_part;    // [chunks * kMaxZonesPerEnv * kZoneMoments]
+    double* zone_part;    // [chunks * kMaxZonesPerEnv * kZonePart]
     double* zone_mom;     // [zones * kZoneMoments]
     tr_aggregate* aggs;   // [zones]
-    int4* zone_chunks;    // (env, begin, end, first zone) per chunk
+    int4* zone_chunks;    // (env, begin, end, first zone) per chunk, then (env, zone, its chunks) per zone
     // scene tables
     EnvDev* envs;
     BodyDev* bodies;
@@ -292,7 +293,6 @@ struct Sizes {
     int n_own;      // owners of the solve order
     int grp_lds;    // spheres a block of the grouped / spread solve holds in LDS
     int n_flags;    // entries of rflags
-    int masks;      // some env's solve needs smask
     int pgs_mode;   // kModeGrouped, kModePerEnv or kModeSpread
     int plan_blocks;  // blocks of the per-env PGS kernel
     int lds_cap;    // particles whose bodies a per-env block keeps in LDS (0: none)

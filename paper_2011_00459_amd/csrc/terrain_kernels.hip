@@ -116,9 +116,19 @@ __global__ void k_scan_top(uint32_t* tmp, int64_t nb)
     if (threadIdx.x == 0) tmp[nb] = carry;
 }
 
-__global__ void k_scan_down(const uint32_t* in, uint32_t* out, int64_t n, const uint32_t* tmp, int64_t nb)
+// sums: tmp holds the tiles' totals (each block adds those before its own),
+// else their exclusive scan
+__global__ void k_scan_down(const uint32_t* in, uint32_t* out, int64_t n, const uint32_t* tmp, int64_t nb, int sums)
 {
     int64_t base = (int64_t)blockIdx.x * kScanTile;
+    uint32_t before = 0;
+    if (sums) {
+        uint32_t s = 0;
+        for (unsigned k = threadIdx.x; k < blockIdx.x; k += kBlk) s += tmp[k];
+        block_excl_scan(s, &before);
+    } else {
+        before = tmp[blockIdx.x];
+    }
     uint32_t v[kScanItems];
     uint32_t s = 0;
     for (int k = 0; k < kScanItems; ++k) {
@@ -127,23 +137,66 @@ __global__ void k_scan_down(const uint32_t* in, uint32_t* out, int64_t n, const 
         s += v[k];
     }
     uint32_t tot;
-    uint32_t ex = block_excl_scan(s, &tot) + tmp[blockIdx.x];
+    uint32_t ex = block_excl_scan(s, &tot) + before;
     for (int k = 0; k < kScanItems; ++k) {
         int64_t i = base + (int64_t)threadIdx.x * kScanItems + k;
         if (i < n) out[i] = ex;
         ex += v[k];
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = tmp[nb];
+    if (blockIdx.x == nb - 1 && threadIdx.x == 0) out[n] = before + tot;
+}
+
+// one block scans it all
+constexpr int kSmallBlk = 1024;
+__global__ __launch_bounds__(kSmallBlk) void k_scan_small(const uint32_t* in, uint32_t* out, int n)
+{
+    __shared__ uint32_t wsum[kSmallBlk / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t carry = 0;
+    for (int base = 0; base < n; base += kSmallBlk * kScanItems) {
+        const int i = base + (int)threadIdx.x * kScanItems;
+        uint32_t v[kScanItems], s = 0;
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) {
+            v[k] = i + k < n ? in[i + k] : 0u;
+            s += v[k];
+        }
+        const uint32_t inc = wave_incl_scan(s);
+        if (lane == 63) wsum[wave] = inc;
+        __syncthreads();
+        uint32_t off = 0, all = 0;
+        for (int w = 0; w < kSmallBlk / 64; ++w) {
+            if (w < wave) off += wsum[w];
+            all += wsum[w];
+        }
+        uint32_t ex = carry + off + inc - s;
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) {
+            if (i + k < n) out[i + k] = ex;
+            ex += v[k];
+        }
+        carry += all;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[n] = carry;
 }
 
 int64_t scan_tmp_words(int64_t n) { return cdiv(std::max<int64_t>(n, 1), kScanTile) + 1; }
 
+// Up to 16,384 words by one block (one launch, 5 us against 9 for two); up to
+// 8,192 tiles with each block adding the totals before its own (cheaper than
+// a launch of one block over them, 12 us at 2,000 tiles).
 void launch_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* tmp, hipStream_t s)
 {
-    int64_t nb = cdiv(std::max<int64_t>(n, 1), kScanTile);
+    if (n <= 4 * kSmallBlk * kScanItems) {
+        hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(kSmallBlk), 0, s, in, out, (int)std::max<int64_t>(n, 0));
+        return;
+    }
+    const int64_t nb = cdiv(n, kScanTile);
+    const int sums = nb <= 8192 ? 1 : 0;
     hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kBlk), 0, s, in, n, tmp);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kBlk), 0, s, tmp, nb);
-    hipLaunchKernelGGL(k_scan_down, dim3((unsigned)nb), dim3(kBlk), 0, s, in, out, n, tmp, nb);
+    if (!sums) hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kBlk), 0, s, tmp, nb);
+    hipLaunchKernelGGL(k_scan_down, dim3((unsigned)nb), dim3(kBlk), 0, s, in, out, n, tmp, nb, sums);
 }
 
 // ---------------------------------------------------------------------------
@@ -195,11 +248,20 @@ __device__ inline bool pair_touch(double xi, double yi, double zi, double ri, do
 }
 
 // ---------------------------------------------------------------------------
-// step begin: world data of shapes, clears
+// step begin: world data of shapes, clears, the particles' cells (A1)
 // ---------------------------------------------------------------------------
 __global__ void k_step_begin(DevBuffers b, StepParams p)
 {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < p.n_particles) {
+        float4 x = b.xr[t];
+        const EnvDev& E = b.envs[env_of(b.pid[t], p.id_cap)];
+        int c[3];
+        cell_of(E, x.x, x.y, x.z, c);
+        uint32_t key = E.cell_base + morton(c[0], c[1], c[2], E.bits);
+        b.pkey[t] = key;
+        atomicAdd(&b.cell_count[key], 1u);
+    }
     {
         // every counter starts the step at zero except the failure word, into
         // which one thread folds the previous step's flags before clearing them
@@ -239,80 +301,50 @@ __global__ void k_step_begin(DevBuffers b, StepParams p)
 
 void launch_step_begin(const DevBuffers& b, const StepParams& p, hipStream_t s)
 {
-    int n = std::max((int)(sizeof(Counters) / 4), std::max(p.n_shapes, std::max(p.n_envs, p.n_units)));
+    int n = std::max({(int)(sizeof(Counters) / 4), p.n_shapes, p.n_envs, p.n_units, p.n_particles});
     hipLaunchKernelGGL(k_step_begin, dim3((unsigned)cdiv(n, kBlk)), dim3(kBlk), 0, s, b, p);
 }
 
 // ---------------------------------------------------------------------------
-// A1-A2: binning, counting sort by cell key, per-cell id order, gather
+// A1-A2: counting sort by cell key, per-cell id order, gather.  The counts
+// that the step's counting sorts fill are drained again as they hand out
+// places, so that every step finds them at zero.
 // ---------------------------------------------------------------------------
-__global__ void k_bin(DevBuffers b, StepParams p)
-{
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= p.n_particles) return;
-    float4 x = b.xr[i];
-    const EnvDev& E = b.envs[env_of(b.pid[i], p.id_cap)];
-    int c[3];
-    cell_of(E, x.x, x.y, x.z, c);
-    uint32_t key = E.cell_base + morton(c[0], c[1], c[2], E.bits);
-    b.pkey[i] = key;
-    atomicAdd(&b.cell_count[key], 1u);
-}
-
 __global__ void k_scatter_cells(DevBuffers b, StepParams p)
 {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= p.n_particles) return;
     uint32_t key = b.pkey[i];
-    uint32_t slot = b.cell_start[key] + atomicAdd(&b.cell_fill[key], 1u);
+    uint32_t slot = b.cell_start[key] + atomicSub(&b.cell_count[key], 1u) - 1u;
     b.perm[slot] = (uint32_t)i;
 }
 
-// the first slot of every cell orders the cell's particles by id
-__global__ void k_cell_order(DevBuffers b, StepParams p)
-{
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= p.n_particles) return;
-    uint32_t key = b.pkey[b.perm[s]];
-    uint32_t beg = b.cell_start[key], end = b.cell_start[key + 1];
-    if ((uint32_t)s != beg) return;
-    for (uint32_t a = beg + 1; a < end; ++a) {
-        uint32_t v = b.perm[a];
-        int idv = b.pid[v];
-        uint32_t t = a;
-        while (t > beg && b.pid[b.perm[t - 1]] > idv) {
-            b.perm[t] = b.perm[t - 1];
-            --t;
-        }
-        b.perm[t] = v;
-    }
-}
-
+// to the sorted place: the cell's range, in order of id inside it
 __global__ void k_gather(DevBuffers b, StepParams p)
 {
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= p.n_particles) return;
-    uint32_t i = b.perm[s];
+    int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= p.n_particles) return;
+    const uint32_t i = b.perm[t];
+    const uint32_t key = b.pkey[i];
+    const uint32_t beg = b.cell_start[key], end = b.cell_start[key + 1];
+    const int id = b.pid[i];
+    uint32_t s = beg;
+    for (uint32_t k = beg; k < end; ++k) s += b.pid[b.perm[k]] < id ? 1u : 0u;
     b.xr2[s] = b.xr[i];
     vel_at(b.vw2, s) = vel_at(b.vw, i);
     angv_at(b.vw2, s) = angv_at(b.vw, i);
     b.rho2[s] = b.rho[i];
-    int id = b.pid[i];
     b.pid2[s] = id;
-    b.id2slot[id] = s;
+    b.id2slot[id] = (int)s;
 }
 
 void launch_sort_particles(const DevBuffers& b, const StepParams& p, const Sizes& z, hipStream_t s)
 {
     int n = p.n_particles;
-    launch_fill_u32(b.cell_count, 0u, z.NC, s);
-    launch_fill_u32(b.cell_fill, 0u, z.NC, s);
+    launch_scan_u32(b.cell_count, b.cell_start, z.NC, b.scan_tmp, s);
     if (n <= 0) return;
     unsigned g = (unsigned)cdiv(n, kBlk);
-    hipLaunchKernelGGL(k_bin, dim3(g), dim3(kBlk), 0, s, b, p);
-    launch_scan_u32(b.cell_count, b.cell_start, z.NC, b.scan_tmp, s);
     hipLaunchKernelGGL(k_scatter_cells, dim3(g), dim3(kBlk), 0, s, b, p);
-    hipLaunchKernelGGL(k_cell_order, dim3(g), dim3(kBlk), 0, s, b, p);
     hipLaunchKernelGGL(k_gather, dim3(g), dim3(kBlk), 0, s, b, p);
 }
 
@@ -432,7 +464,8 @@ __device__ inline uint32_t n_contacts(const DevBuffers& b, int64_t cap)
 // equal a in consecutive lanes (same-address atomics from many lanes
 // serialise); returns the lane's old value, as its own atomic would have
 // (lanes of a run take consecutive values).  Every lane of the wave calls it.
-__device__ inline uint32_t wave_run_inc(uint32_t* counter, uint32_t a, bool active)
+// drain: the same places handed out from a filled counter, down to zero.
+__device__ inline uint32_t wave_run_inc(uint32_t* counter, uint32_t a, bool active, bool drain = false)
 {
     const int lane = threadIdx.x & 63;
     const uint32_t prev = __shfl_up(a, 1, 64);
@@ -442,7 +475,7 @@ __device__ inline uint32_t wave_run_inc(uint32_t* counter, uint32_t a, bool acti
     const unsigned long long later = lane == 63 ? 0ull : bound >> (lane + 1);
     const int len = later ? __builtin_ctzll(later) + 1 : 64 - lane;
     uint32_t old = 0;
-    if (head) old = atomicAdd(&counter[a], (uint32_t)len);
+    if (head) old = drain ? atomicSub(&counter[a], (uint32_t)len) - (uint32_t)len : atomicAdd(&counter[a], (uint32_t)len);
     const unsigned long long upto = bound & (~0ull >> (63 - lane));
     const int h = 63 - __builtin_clzll(upto | 1ull);
     return __shfl(old, h, 64) + (uint32_t)(lane - h);
@@ -466,7 +499,7 @@ __global__ void k_id_scatter(DevBuffers b, int64_t cap)
         const bool on = c < nc;
         const unsigned long long k = on ? b.rkey[c] : 0ull;
         const uint32_t a = (uint32_t)(k >> 32);
-        const uint32_t r = wave_run_inc(b.id_fill, a, on);
+        const uint32_t r = wave_run_inc(b.id_count, a, on, true);
         if (on) {
             const uint32_t pos = b.id_start[a] + r;
             b.ckey[pos] = k;
@@ -475,41 +508,61 @@ __global__ void k_id_scatter(DevBuffers b, int64_t cap)
     }
 }
 
-__global__ void k_id_sort(DevBuffers b, int64_t nid)
+// Each id's contacts in key order; their number at each of their spheres,
+// and the colouring's start values.  Up to kIdRank of them are ranked in
+// registers.
+constexpr int kIdRank = 8;
+
+__global__ __launch_bounds__(kBlk) void k_id_sort(DevBuffers b, int64_t nid)
 {
     int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (a >= nid) return;
-    uint32_t beg = b.id_start[a], end = b.id_start[a + 1];
-    for (uint32_t u = beg + 1; u < end; ++u) {
-        unsigned long long k = b.ckey[u];
-        int2 pr = b.cpair[u];
-        uint32_t t = u;
-        while (t > beg && b.ckey[t - 1] > k) {
-            b.ckey[t] = b.ckey[t - 1];
-            b.cpair[t] = b.cpair[t - 1];
-            --t;
+    const uint32_t beg = b.id_start[a], end = b.id_start[a + 1], len = end - beg;
+    if (len == 0) return;
+    if (len <= kIdRank) {
+        unsigned long long k[kIdRank];
+        int2 pr[kIdRank];
+        uint32_t at[kIdRank];
+#pragma unroll
+        for (int j = 0; j < kIdRank; ++j) {
+            k[j] = (uint32_t)j < len ? b.ckey[beg + j] : ~0ull;
+            if ((uint32_t)j < len) pr[j] = b.cpair[beg + j];
+            at[j] = 0;
         }
-        b.ckey[t] = k;
-        b.cpair[t] = pr;
+#pragma unroll
+        for (int j = 1; j < kIdRank; ++j)
+#pragma unroll
+            for (int i = 0; i < j; ++i) {
+                const bool up = k[i] <= k[j];
+                at[j] += up ? 1u : 0u;
+                at[i] += up ? 0u : 1u;
+            }
+#pragma unroll
+        for (int j = 0; j < kIdRank; ++j)
+            if ((uint32_t)j < len) {
+                b.ckey[beg + at[j]] = k[j];
+                b.cpair[beg + at[j]] = pr[j];
+                if (pr[j].x >= 0) atomicAdd(&b.inc_count[pr[j].y], 1u);
+            }
+    } else {
+        for (uint32_t u = beg; u < end; ++u) {
+            unsigned long long k = b.ckey[u];
+            int2 pr = b.cpair[u];
+            uint32_t t = u;
+            while (t > beg && b.ckey[t - 1] > k) {
+                b.ckey[t] = b.ckey[t - 1];
+                b.cpair[t] = b.cpair[t - 1];
+                --t;
+            }
+            b.ckey[t] = k;
+            b.cpair[t] = pr;
+            if (pr.x >= 0) atomicAdd(&b.inc_count[pr.y], 1u);
+        }
     }
-}
-
-__global__ void k_inc_count(DevBuffers b, int64_t cap)
-{
-    uint32_t nc = n_contacts(b, cap);
-    for (uint32_t c0 = blockIdx.x * blockDim.x; c0 < nc; c0 += gridDim.x * blockDim.x) {
-        const uint32_t c = c0 + threadIdx.x;
-        const bool on = c < nc;
-        const int2 pr = on ? b.cpair[c] : make_int2(-1, 0);
-        if (on) {  // for the colouring
-            b.colour[c] = -1;
-            b.cmsg[c] = kNoMask;
-        }
-        // the particle whose id leads the key comes in runs: pr.x for a
-        // pair, pr.y for a boundary contact (pr.x < 0)
-        const int own = pr.x >= 0 ? pr.x : pr.y, other = pr.x >= 0 ? pr.y : -1;
-        (void)wave_run_inc(b.inc_count, (uint32_t)own, on);
-        if (other >= 0) atomicAdd(&b.inc_count[other], 1u);
+    atomicAdd(&b.inc_count[b.id2slot[a]], len);
+    for (uint32_t c = beg; c < end; ++c) {
+        b.colour[c] = -1;
+        b.cmsg[c] = kNoMask;
     }
 }
 
@@ -521,9 +574,9 @@ __global__ void k_inc_fill(DevBuffers b, int64_t cap)
         const bool on = c < nc;
         const int2 pr = on ? b.cpair[c] : make_int2(-1, 0);
         const int own = pr.x >= 0 ? pr.x : pr.y, other = pr.x >= 0 ? pr.y : -1;
-        const uint32_t r = wave_run_inc(b.inc_fill, (uint32_t)own, on);
+        const uint32_t r = wave_run_inc(b.inc_count, (uint32_t)own, on, true);
         if (on) b.inc[b.inc_start[own] + r] = c;
-        if (other >= 0) b.inc[b.inc_start[other] + atomicAdd(&b.inc_fill[other], 1u)] = c;
+        if (other >= 0) b.inc[b.inc_start[other] + atomicSub(&b.inc_count[other], 1u) - 1u] = c;
     }
 }
 
@@ -617,16 +670,11 @@ __global__ __launch_bounds__(kBlk) void k_inc_sort(DevBuffers b, int n)
 void launch_canonical(const DevBuffers& b, const StepParams& p, const Sizes& z, hipStream_t s)
 {
     unsigned gc = (unsigned)std::min<int64_t>(cdiv(z.C, kBlk), 2048);
-    launch_fill_u32(b.id_count, 0u, z.NID, s);
-    launch_fill_u32(b.id_fill, 0u, z.NID, s);
     hipLaunchKernelGGL(k_id_count, dim3(gc), dim3(kBlk), 0, s, b, z.C);
     launch_scan_u32(b.id_count, b.id_start, z.NID, b.scan_tmp, s);
     hipLaunchKernelGGL(k_id_scatter, dim3(gc), dim3(kBlk), 0, s, b, z.C);
     hipLaunchKernelGGL(k_id_sort, dim3((unsigned)cdiv(z.NID, kBlk)), dim3(kBlk), 0, s, b, z.NID);
     int n = std::max(p.n_particles, 1);
-    launch_fill_u32(b.inc_count, 0u, n, s);
-    launch_fill_u32(b.inc_fill, 0u, n, s);
-    hipLaunchKernelGGL(k_inc_count, dim3(gc), dim3(kBlk), 0, s, b, z.C);
     launch_scan_u32(b.inc_count, b.inc_start, n, b.scan_tmp, s);
     hipLaunchKernelGGL(k_inc_fill, dim3(gc), dim3(kBlk), 0, s, b, z.C);
     hipLaunchKernelGGL(k_inc_sort, dim3((unsigned)cdiv(n, kBlk)), dim3(kBlk), 0, s, b, n);
@@ -801,16 +849,12 @@ __device__ inline int lds_index(const EnvDev& E, int slot)
     return E.lds_off + t % E.chunk;
 }
 
-// Per sphere, the colours of its contacts (all) and of those that another
-// region's block solves (away).  A sphere's contacts have distinct colours, so
-// the masks give the order of its updates; those of a sphere without an LDS
-// place all count as away.
-__global__ void k_region_masks(DevBuffers b, StepParams p)
+// The colours of a sphere's contacts (all) and of those that another region's
+// block solves (away).  A sphere's contacts have distinct colours, so the
+// masks give the order of its updates; those of a sphere without an LDS place
+// all count as away.
+__device__ inline ulonglong2 region_masks(const DevBuffers& b, const EnvDev& E, int s)
 {
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= p.n_particles) return;
-    const EnvDev& E = b.envs[env_of(b.pid[s], p.id_cap)];
-    if (!E.masks) return;
     const uint32_t beg = b.inc_start[s], end = b.inc_start[s + 1];
     const bool split = E.chunk < E.n;
     const int r = region_of(E, s);
@@ -833,7 +877,7 @@ __global__ void k_region_masks(DevBuffers b, StepParams p)
         }
     }
     if (lds_index(E, s) >= E.res_cap) away = all;
-    b.smask[s] = make_ulonglong2(all, away);
+    return make_ulonglong2(all, away);
 }
 
 // of a sphere's update by its contact of colour col: its place in the
@@ -873,6 +917,12 @@ __global__ __launch_bounds__(kOrdBlk) void k_order(DevBuffers b)
     const int o = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int sg0 = b.own_idx[o], sg1 = b.own_idx[o + 1];
     for (int k = threadIdx.x; k < kOrdWaves * kOrdBuckets; k += kOrdBlk) wc[0][k] = 0;
+    for (int sg = sg0; sg < sg1; ++sg) {
+        const int4 S = b.own_seg[sg];
+        const EnvDev& E = b.envs[S.w];
+        if (!E.masks) continue;
+        for (int i = threadIdx.x; i < S.y; i += kOrdBlk) b.smask[S.x + i] = region_masks(b, E, S.x + i);
+    }
     __syncthreads();
     volatile uint32_t* mine = wc[wave];
     const unsigned long long lower = lane == 0 ? 0ull : (~0ull >> (64 - lane));
@@ -1004,8 +1054,6 @@ void launch_colour(const DevBuffers& b, const StepParams& p, const Sizes& z, hip
         else
             hipLaunchKernelGGL(k_colour<false>, dim3(g), dim3(kColBlk), 0, s, b, p.n_particles, per, 1 << 22);
     }
-    if (z.masks && p.n_particles > 0)
-        hipLaunchKernelGGL(k_region_masks, dim3((unsigned)cdiv(p.n_particles, kBlk)), dim3(kBlk), 0, s, b, p);
     if (z.n_own > 0) hipLaunchKernelGGL(k_order, dim3((unsigned)z.n_own), dim3(kOrdBlk), 0, s, b);
 }
 
@@ -1058,12 +1106,8 @@ __device__ inline void warm_record(float4 L, float4 a, float l2, int ib, float4 
     rec[2] = make_float4(a1, a2, 0.f, 0.f);
 }
 
-__global__ void k_rows(DevBuffers b, StepParams p, int64_t cap, int flags)
+__device__ inline void contact_rows(const DevBuffers& b, const StepParams& p, uint32_t c, int flags)
 {
-    uint32_t nc = n_contacts(b, cap);
-    uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= nc) return;
-    if (b.cnt->overflow) return;
     unsigned long long key = b.ckey[c];
     int2 pr = b.cpair[c];
     int ia = pr.x, ib = pr.y;
@@ -1277,11 +1321,24 @@ __global__ void k_rows(DevBuffers b, StepParams p, int64_t cap, int flags)
     warm_record(L, make_float4(nf[0], nf[1], nf[2], (float)l1), (float)l2, ib, Lr, p.mu_r > 0.f, b.wrec + 3 * (size_t)c);
 }
 
+__global__ void k_rows(DevBuffers b, StepParams p, int64_t cap, int flags)
+{
+    if (b.cnt->overflow) return;
+    const uint32_t nc = n_contacts(b, cap);
+    for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < nc; c += gridDim.x * blockDim.x)
+        contact_rows(b, p, c, flags);
+}
+
+// Blocks of a kernel over the contacts, whose number the host does not know:
+// the capacity may be ten times it, and 150,000 blocks that find nothing take
+// 30 us to come and go.
+unsigned contact_grid(int64_t cap) { return (unsigned)std::min<int64_t>(cdiv(cap, kBlk), 16384); }
+
 void launch_rows(const DevBuffers& b, const StepParams& p, const Sizes& z, bool have_prev, bool features,
                  hipStream_t s)
 {
     const int flags = (have_prev ? kRowsPrev : 0) | (features ? kRowsFeatures : 0);
-    hipLaunchKernelGGL(k_rows, dim3((unsigned)cdiv(z.C, kBlk)), dim3(kBlk), 0, s, b, p, z.C, flags);
+    hipLaunchKernelGGL(k_rows, dim3(contact_grid(z.C)), dim3(kBlk), 0, s, b, p, z.C, flags);
 }
 
 // Impact stage set-up: the stage's impulses start at zero, and the rows of an
@@ -1351,9 +1408,28 @@ void launch_impact_stage(const DevBuffers& b, const StepParams& p, const Sizes& 
 // incidence list (fixed order) from the contacts' records in canonical order
 // (one 32 or 48 B record per incident contact)
 // ---------------------------------------------------------------------------
-__global__ void k_warm_apply(DevBuffers b, StepParams p)
+// Before a solve: its counters and flags cleared, and the exchange record of a
+// sphere that uses one at version 0.
+__device__ inline void solve_begin(const DevBuffers& b, int t, int n_envs, int n_flags)
+{
+    if (t < kGroups) { b.cnt->bar[t][0] = 0; b.cnt->bar[t][1] = 0; }
+    if (t < n_envs) { b.env_bar[(size_t)t * 16] = 0; b.env_bar[(size_t)t * 16 + 1] = 0; }
+    if (t < n_flags) b.rflags[t] = 0;
+}
+__device__ inline void exchange_begin(const DevBuffers& b, const StepParams& p, int s, float4 v, float4 w)
+{
+    const EnvDev& E = b.envs[env_of(b.pid[s], p.id_cap)];
+    if (!E.coded || b.smask[s].y == 0) return;
+    const int64_t x = E.x0 + (int64_t)region_of(E, s) * E.xstride + lds_index(E, s);
+    v.w = w.w = 0.f;  // version 0
+    b.xw[2 * x] = v;
+    b.xw[2 * x + 1] = w;
+}
+
+__global__ void k_warm_apply(DevBuffers b, StepParams p, int n_envs, int n_flags)
 {
     int s = blockIdx.x * blockDim.x + threadIdx.x;
+    solve_begin(b, s, n_envs, n_flags);
     if (s >= p.n_particles) return;
     if (b.cnt->overflow) return;
     const bool roll = p.mu_r > 0.f;
@@ -1377,6 +1453,7 @@ __global__ void k_warm_apply(DevBuffers b, StepParams p)
     }
     vel_at(b.vw, s) = v;
     angv_at(b.vw, s) = w;
+    exchange_begin(b, p, s, v, w);
 }
 
 // the records again from the colour-ordered impulses and rows, after a
@@ -1396,8 +1473,9 @@ __global__ void k_warm_rec(DevBuffers b, StepParams p, int64_t cap)
 void launch_warm_apply(const DevBuffers& b, const StepParams& p, const Sizes& z, bool rebuild, hipStream_t s)
 {
     if (rebuild) hipLaunchKernelGGL(k_warm_rec, dim3((unsigned)cdiv(z.C, kBlk)), dim3(kBlk), 0, s, b, p, z.C);
-    if (p.n_particles <= 0) return;
-    hipLaunchKernelGGL(k_warm_apply, dim3((unsigned)cdiv(p.n_particles, kBlk)), dim3(kBlk), 0, s, b, p);
+    const int ne = z.pgs_mode == kModePerEnv ? z.n_envs : 0;
+    const int n = std::max({kGroups, ne, z.n_flags, p.n_particles});
+    hipLaunchKernelGGL(k_warm_apply, dim3((unsigned)cdiv(n, kBlk)), dim3(kBlk), 0, s, b, p, ne, z.n_flags);
 }
 
 // ---------------------------------------------------------------------------
@@ -2203,22 +2281,12 @@ __device__ void pgs_region(const DevBuffers& b, const StepParams& p, const Solve
     if (T.rank == 0 && tid == 0) write_stats(b, T.unit, slot, sweeps, Rk, R1);
 }
 
-// Before a PGS launch: its counters and flags cleared, and the exchange
-// records of the spheres that use one at version 0.
+// solve_begin and exchange_begin for a solve that no warm apply precedes
 __global__ void k_pgs_reset(DevBuffers b, StepParams p, int n_envs, int n_flags)
 {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < kGroups) { b.cnt->bar[t][0] = 0; b.cnt->bar[t][1] = 0; }
-    if (t < n_envs) { b.env_bar[(size_t)t * 16] = 0; b.env_bar[(size_t)t * 16 + 1] = 0; }
-    if (t < n_flags) b.rflags[t] = 0;
-    if (t >= p.n_particles) return;
-    const EnvDev& E = b.envs[env_of(b.pid[t], p.id_cap)];
-    if (!E.coded || b.smask[t].y == 0) return;
-    const int64_t x = E.x0 + (int64_t)region_of(E, t) * E.xstride + lds_index(E, t);
-    float4 v = vel_at(b.vw, t), w = angv_at(b.vw, t);
-    v.w = w.w = 0.f;  // version 0
-    b.xw[2 * x] = v;
-    b.xw[2 * x + 1] = w;
+    solve_begin(b, t, n_envs, n_flags);
+    if (t < p.n_particles) exchange_begin(b, p, t, vel_at(b.vw, t), angv_at(b.vw, t));
 }
 
 // Grouped and spread modes: block blockIdx takes the region of its task.
@@ -2452,11 +2520,11 @@ int colour_resident_blocks(int* per_block)
 void launch_pgs(const DevBuffers& b, const StepParams& p, const Sizes& z, hipStream_t s, int sweeps_cap, int slot)
 {
     int sw = sweeps_cap < 0 ? p.max_sweeps : sweeps_cap;
-    const int ne = z.pgs_mode == kModePerEnv ? z.n_envs : 0;
-    StepParams pr = p;
-    if (!z.masks) pr.n_particles = 0;
-    const int nr = std::max({kGroups, ne, z.n_flags, pr.n_particles});
-    hipLaunchKernelGGL(k_pgs_reset, dim3((unsigned)cdiv(nr, kBlk)), dim3(kBlk), 0, s, b, pr, ne, z.n_flags);
+    if (slot == kSlotImpact) {
+        const int ne = z.pgs_mode == kModePerEnv ? z.n_envs : 0;
+        const int n = std::max({kGroups, ne, z.n_flags, p.n_particles});
+        hipLaunchKernelGGL(k_pgs_reset, dim3((unsigned)cdiv(n, kBlk)), dim3(kBlk), 0, s, b, p, ne, z.n_flags);
+    }
     const int flow = z.flow;
     if (flow && p.n_particles > 0) launch_fill_u32(b.ver, 0u, p.n_particles, s);
     const bool env = z.pgs_mode == kModePerEnv;
@@ -2596,13 +2664,28 @@ void launch_learn_samples(const DevBuffers& b, int64_t beg, int64_t n, float* fe
 // finish: canonical impulses, body forces (A11), integration (A10), poses,
 // zone aggregates (A12), env stats
 // ---------------------------------------------------------------------------
-__global__ void k_lam_back(DevBuffers b, int64_t cap, float mu_r)
+// the contacts' impulses in canonical order (the next step's warm start), and
+// x += dt v
+__global__ void k_finish(DevBuffers b, StepParams p, int64_t cap, unsigned contact_blocks)
 {
-    uint32_t nc = n_contacts(b, cap);
-    uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= nc) return;
-    b.lamc[c] = b.cnt->overflow ? make_float4(0.f, 0.f, 0.f, 0.f) : b.lam[b.cpos[c]];
-    if (mu_r > 0.f) b.lamrc[c] = b.cnt->overflow ? make_float4(0.f, 0.f, 0.f, 0.f) : b.lamr[b.cpos[c]];
+    const bool bad = b.cnt->overflow != 0;
+    if (blockIdx.x < contact_blocks) {
+        const uint32_t nc = n_contacts(b, cap);
+        for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < nc; c += contact_blocks * blockDim.x) {
+            const uint32_t pos = bad ? 0 : b.cpos[c];
+            b.lamc[c] = bad ? make_float4(0.f, 0.f, 0.f, 0.f) : b.lam[pos];
+            if (p.mu_r > 0.f) b.lamrc[c] = bad ? make_float4(0.f, 0.f, 0.f, 0.f) : b.lamr[pos];
+        }
+        return;
+    }
+    int s = (blockIdx.x - contact_blocks) * blockDim.x + threadIdx.x;
+    if (s >= p.n_particles || bad) return;
+    float4 x = b.xr[s];
+    float4 v = vel_at(b.vw, s);
+    x.x += p.dt * v.x;
+    x.y += p.dt * v.y;
+    x.z += p.dt * v.z;
+    b.xr[s] = x;
 }
 
 __device__ inline double block_sum_d(double v, double* sh)
@@ -2622,7 +2705,8 @@ constexpr int kRedBlk = 128;
 __global__ __launch_bounds__(kRedBlk) void k_force_part(DevBuffers b, StepParams p, int64_t cap)
 {
     __shared__ double sh[kRedBlk / 64];
-    int body = blockIdx.x / kForceChunks, ch = blockIdx.x % kForceChunks;
+    const int nch = p.force_chunks;
+    int body = blockIdx.x / nch, ch = blockIdx.x % nch;
     const BodyDev& B = b.bodies[body];
     const EnvDev& E = b.envs[B.env];
     uint32_t nc = n_contacts(b, cap);
@@ -2630,8 +2714,8 @@ __global__ __launch_bounds__(kRedBlk) void k_force_part(DevBuffers b, StepParams
     if (end > nc) end = nc;
     if (beg > end) beg = end;
     uint32_t len = end - beg;
-    uint32_t lo = beg + (uint32_t)(((uint64_t)len * ch) / kForceChunks);
-    uint32_t hi = beg + (uint32_t)(((uint64_t)len * (ch + 1)) / kForceChunks);
+    uint32_t lo = beg + (uint32_t)(((uint64_t)len * ch) / nch);
+    uint32_t hi = beg + (uint32_t)(((uint64_t)len * (ch + 1)) / nch);
     double acc[6] = {0, 0, 0, 0, 0, 0};
     if (b.cnt->overflow) hi = lo;
     for (uint32_t c = lo + threadIdx.x; c < hi; c += blockDim.x) {
@@ -2670,39 +2754,30 @@ __global__ __launch_bounds__(kRedBlk) void k_force_part(DevBuffers b, StepParams
     }
     for (int k = 0; k < 6; ++k) {
         double s = block_sum_d(acc[k], sh);
-        if (threadIdx.x == 0) b.force_part[((size_t)body * kForceChunks + ch) * 6 + k] = s;
+        if (threadIdx.x == 0) b.force_part[((size_t)body * nch + ch) * 6 + k] = s;
     }
 }
 
-__global__ void k_force_final(DevBuffers b, StepParams p)
+// One wave per body: its force from the chunks' partials, its pose advanced
+// with its constant velocities, the world zone planes of the new pose; the
+// blocks after them count the envs' contacts.
+__global__ __launch_bounds__(64) void k_bodies_end(DevBuffers b, StepParams p)
 {
-    int body = blockIdx.x * blockDim.x + threadIdx.x;
-    if (body >= p.n_bodies) return;
-    for (int k = 0; k < 6; ++k) {
-        double s = 0.0;
-        for (int ch = 0; ch < kForceChunks; ++ch) s += b.force_part[((size_t)body * kForceChunks + ch) * 6 + k];
-        b.body_ft[body * 6 + k] = s;
+    const int t = blockIdx.x;
+    if (t >= p.n_bodies) {
+        const int e = (t - p.n_bodies) * 64 + threadIdx.x;
+        if (e >= p.n_envs) return;
+        const int64_t base = (int64_t)e * p.id_cap;
+        b.env_stats[e].contacts = (int64_t)b.id_start[base + p.id_cap] - (int64_t)b.id_start[base];
+        return;
     }
-}
-
-__global__ void k_integrate(DevBuffers b, StepParams p)
-{
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= p.n_particles) return;
-    if (b.cnt->overflow) return;
-    float4 x = b.xr[s];
-    float4 v = vel_at(b.vw, s);
-    x.x += p.dt * v.x;
-    x.y += p.dt * v.y;
-    x.z += p.dt * v.z;
-    b.xr[s] = x;
-}
-
-// poses advance with their constant velocities; world zone planes of the new pose
-__global__ void k_bodies_end(DevBuffers b, StepParams p)
-{
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= p.n_bodies) return;
+    double f[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int ch = threadIdx.x; ch < p.force_chunks; ch += 64)
+        for (int k = 0; k < 6; ++k) f[k] += b.force_part[((size_t)t * p.force_chunks + ch) * 6 + k];
+    for (int k = 0; k < 6; ++k)
+        for (int o = 32; o > 0; o >>= 1) f[k] += __shfl_down(f[k], o, 64);
+    if (threadIdx.x != 0) return;
+    for (int k = 0; k < 6; ++k) b.body_ft[t * 6 + k] = f[k];
     if (b.cnt->overflow) return;
     BodyDev& B = b.bodies[t];
     double dt = p.dt;
@@ -2896,9 +2971,8 @@ __global__ __launch_bounds__(kRedBlk) void k_zone_part(DevBuffers b, StepParams 
     int4 ck = b.zone_chunks[blockIdx.x];   // env, begin, end, partial base
     const EnvDev& E = b.envs[ck.x];
     for (int z = 0; z < E.zone_count; ++z) {
-        const BodyDev& B = b.bodies[E.zone_body[z]];
-        double acc[kZoneMoments];
-        for (int k = 0; k < kZoneMoments; ++k) acc[k] = 0.0;
+        double acc[kZonePart];
+        for (int k = 0; k < kZonePart; ++k) acc[k] = 0.0;
         for (int s = ck.y + threadIdx.x; s < ck.z; s += blockDim.x) {
             float4 xf = b.xr[s];
             double x[3] = {xf.x, xf.y, xf.z};
@@ -2921,40 +2995,50 @@ __global__ __launch_bounds__(kRedBlk) void k_zone_part(DevBuffers b, StepParams 
             acc[15] += m * (x[0] * v[1] - x[1] * v[0]);
             acc[16] += Is;
             acc[17] += Is * wf.x; acc[18] += Is * wf.y; acc[19] += Is * wf.z;
+            acc[kZoneMoments] += 1.0;
         }
-        (void)B;
-        for (int k = 0; k < kZoneMoments; ++k) {
+        // most chunks hold no particle of the zone
+        double* part = b.zone_part + ((size_t)ck.w + z) * kZonePart;
+        if (!__syncthreads_or(acc[kZoneMoments] > 0.0)) {
+            if (threadIdx.x < kZonePart) part[threadIdx.x] = 0.0;
+            continue;
+        }
+        for (int k = 0; k < kZonePart; ++k) {
             double s = block_sum_d(acc[k], sh);
-            if (threadIdx.x == 0) b.zone_part[((size_t)ck.w + z) * kZoneMoments + k] = s;
+            if (threadIdx.x == 0) part[k] = s;
         }
     }
 }
 
-// per zone: sum the chunk partials in order, then the aggregate body
-__global__ void k_zone_final(DevBuffers b, StepParams p, int n_chunks)
+// One block per zone: kZoneGroups threads per moment sum every kZoneGroups-th
+// chunk's, their sums are added in order, then one thread forms the aggregate
+// body.
+constexpr int kZoneGroups = 32;
+__global__ __launch_bounds__(kZonePart* kZoneGroups) void k_zone_final(DevBuffers b, StepParams p, int n_chunks)
 {
-    int zs = blockIdx.x * blockDim.x + threadIdx.x;
-    if (zs >= p.n_zones) return;
-    // locate env and zone index of this global zone
-    int env = -1, zi = -1;
-    for (int e = 0; e < p.n_envs && env < 0; ++e)
-        for (int z = 0; z < b.envs[e].zone_count; ++z)
-            if (b.envs[e].zone_slot[z] == zs) { env = e; zi = z; }
-    if (env < 0) return;
-    double S[kZoneMoments];
-    for (int k = 0; k < kZoneMoments; ++k) S[k] = 0.0;
-    for (int c = 0; c < n_chunks; ++c) {
-        int4 ck = b.zone_chunks[c];
-        if (ck.x != env) continue;
-        for (int k = 0; k < kZoneMoments; ++k) S[k] += b.zone_part[((size_t)ck.w + zi) * kZoneMoments + k];
+    __shared__ double part[kZoneGroups][kZonePart], S[kZonePart];
+    const int zs = blockIdx.x, k0 = threadIdx.x % kZonePart, g = threadIdx.x / kZonePart;
+    const int4 zt = b.zone_chunks[n_chunks + zs];  // env, zone in it, its chunks
+    const int env = zt.x, zi = zt.y;
+    double sum = 0.0;
+    for (int c = zt.z + g; c < zt.w; c += kZoneGroups)
+        sum += b.zone_part[((size_t)c * kMaxZonesPerEnv + zi) * kZonePart + k0];
+    part[g][k0] = sum;
+    __syncthreads();
+    if (g == 0) {
+        sum = 0.0;
+        for (int q = 0; q < kZoneGroups; ++q) sum += part[q][k0];
+        S[k0] = sum;
     }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
     for (int k = 0; k < kZoneMoments; ++k) b.zone_mom[(size_t)zs * kZoneMoments + k] = S[k];
     tr_aggregate A;
     A.zone = b.bodies[b.envs[env].zone_body[zi]].user_id;
     A.pad = 0;
     double M = S[0];
     A.M = M;
-    A.n_particles = 0;
+    A.n_particles = (int64_t)S[kZoneMoments];
     for (int k = 0; k < 3; ++k) { A.x[k] = 0.0; A.v[k] = 0.0; A.w[k] = 0.0; }
     for (int k = 0; k < 6; ++k) A.I[k] = 0.0;
     if (M > 0.0) {
@@ -2992,50 +3076,19 @@ __global__ void k_zone_final(DevBuffers b, StepParams p, int n_chunks)
     b.aggs[zs] = A;
 }
 
-// zone particle counts (integers, order free)
-__global__ void k_zone_count(DevBuffers b, StepParams p)
-{
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= p.n_particles) return;
-    const EnvDev& E = b.envs[env_of(b.pid[s], p.id_cap)];
-    float4 xf = b.xr[s];
-    double x[3] = {xf.x, xf.y, xf.z};
-    for (int zz = 0; zz < E.zone_count; ++zz) {
-        if (in_body_zone(b, b.bodies[E.zone_body[zz]], x)) {
-            atomicAdd((unsigned long long*)&b.aggs[E.zone_slot[zz]].n_particles, 1ull);
-            break;
-        }
-    }
-}
-
-__global__ void k_env_stats(DevBuffers b, StepParams p)
-{
-    int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= p.n_envs) return;
-    int64_t base = (int64_t)e * p.id_cap;
-    b.env_stats[e].contacts = (int64_t)b.id_start[base + p.id_cap] - (int64_t)b.id_start[base];
-}
-
 void launch_finish(const DevBuffers& b, const StepParams& p, const Sizes& z, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_lam_back, dim3((unsigned)cdiv(z.C, kBlk)), dim3(kBlk), 0, s, b, z.C, p.mu_r);
-    if (p.n_bodies > 0) {
-        hipLaunchKernelGGL(k_force_part, dim3(p.n_bodies * kForceChunks), dim3(kRedBlk), 0, s, b, p, z.C);
-        hipLaunchKernelGGL(k_force_final, dim3((unsigned)cdiv(p.n_bodies, kBlk)), dim3(kBlk), 0, s, b, p);
-    }
-    if (p.n_particles > 0)
-        hipLaunchKernelGGL(k_integrate, dim3((unsigned)cdiv(p.n_particles, kBlk)), dim3(kBlk), 0, s, b, p);
-    if (p.n_bodies > 0)
-        hipLaunchKernelGGL(k_bodies_end, dim3((unsigned)cdiv(p.n_bodies, kBlk)), dim3(kBlk), 0, s, b, p);
+    const unsigned gc = contact_grid(z.C);
+    if (p.n_bodies > 0)  // (at the positions the contacts were found at)
+        hipLaunchKernelGGL(k_force_part, dim3(p.n_bodies * p.force_chunks), dim3(kRedBlk), 0, s, b, p, z.C);
+    hipLaunchKernelGGL(k_finish, dim3(gc + (unsigned)cdiv(std::max(p.n_particles, 0), kBlk)), dim3(kBlk), 0, s, b, p, z.C, gc);
+    hipLaunchKernelGGL(k_bodies_end, dim3((unsigned)(p.n_bodies + cdiv(p.n_envs, 64))), dim3(64), 0, s, b, p);
     if (p.n_tools > 0)  // the tools' zones at the end-of-step poses
         hipLaunchKernelGGL(k_predict_wedges, dim3((unsigned)cdiv(p.n_tools * TR_MAX_WEDGES, 64)), dim3(64), 0, s, b, p);
     if (p.n_zones > 0 && z.n_zone_chunks > 0) {
         hipLaunchKernelGGL(k_zone_part, dim3(z.n_zone_chunks), dim3(kRedBlk), 0, s, b, p);
-        hipLaunchKernelGGL(k_zone_final, dim3((unsigned)cdiv(p.n_zones, 64)), dim3(64), 0, s, b, p, z.n_zone_chunks);
-        hipLaunchKernelGGL(k_zone_count, dim3((unsigned)cdiv(std::max(p.n_particles, 1), kBlk)), dim3(kBlk), 0, s,
-                           b, p);
+        hipLaunchKernelGGL(k_zone_final, dim3(p.n_zones), dim3(kZonePart * kZoneGroups), 0, s, b, p, z.n_zone_chunks);
     }
-    hipLaunchKernelGGL(k_env_stats, dim3((unsigned)cdiv(std::max(p.n_envs, 1), 64)), dim3(64), 0, s, b, p);
 }
 
 // ---------------------------------------------------------------------------

@@ -36,20 +36,24 @@ def test_envs_share_a_range():
     check([with_(s, material=specs[0]["material"]) for s in specs])
 
 
-def test_more_contacts_than_a_thread_ranks():
-    # one sphere of ten radii in the middle of a bed: dozens of contacts
+@pytest.mark.parametrize("first", [False, True])
+def test_more_contacts_than_a_thread_ranks(first):
+    # one sphere three radii large in the middle of a bed, the last id (its
+    # contacts are keyed by the others) or the first (by itself)
     s = jammed_bed(seed=42, nx=20, ny=20, nz=14, r0=0.03, sweeps=1, blade=False)
     c = np.array([0.0, 0.0, 0.42])
     keep = np.linalg.norm(s["x"] - c, axis=1) > 0.1 + 0.5 * s["r"]
     x = np.concatenate([s["x"][keep], [c]])
     r = np.concatenate([s["r"][keep], [0.1]])
+    if first:
+        x, r = x[::-1], r[::-1]
     x, r = (np.asarray(a, np.float32).astype(np.float64) for a in (x, r))
     n = len(x)
     spec = with_(s, x=x, r=r, v=np.zeros((n, 3)), w=np.zeros((n, 3)), id=np.arange(n, dtype=np.int64))
     o = O.OracleScene(spec)
     keys = o.step()["keys"]
     ends = np.concatenate([keys >> np.uint64(32), keys & np.uint64(0xffffffff)])
-    assert 16 < np.sum(ends == n - 1) < 64
+    assert 16 < np.sum(ends == (0 if first else n - 1)) < 64
     check([spec], cap_contacts=16 * n)
 
 
