@@ -28,7 +28,6 @@ constexpr int oW1 = 0, ob1 = oW1 + kH * kIn, oW2 = ob1 + kH, ob2 = oW2 + kH * kH
 constexpr int kNP = oScale;  // trainable parameters (in_scale is fixed)
 static_assert(oScale + kIn == kMlpParams, "parameter layout");
 
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 __device__ inline float silu(float z) { return z / (1.0f + __expf(-z)); }
@@ -45,67 +44,65 @@ __device__ inline float silu_fast(float z) { return z * __builtin_amdgcn_rcpf(1.
 }  // namespace
 
 // ---------------------------------------------------------------------------
-// BF16 MFMA inference.  Each wave works alone on tiles of 32 contacts (no
-// block barrier after the weights are staged): the block's weights sit in LDS
-// as B operands, the input tile is read from global memory straight into the
-// A operand (the next tile's rows in flight meanwhile), and one per-wave LDS
-// tile turns each layer's D layout into the next layer's A layout.
-//   layer 1: X[32 x 16] (12 inputs padded) . W1^T[16 x 64]: 2 N-tiles x 1 K-step
-//   layer 2: H1[32 x 64] . W2^T[64 x 64]: 2 N-tiles x 4 K-steps
-//   layer 3: H2[32 x 64] . W3^T[64 x 32] (3 of 32 columns used): 4 K-steps
+// BF16 MFMA inference.  Each wave works alone on tiles of 32 contacts and
+// computes the transposed layers, units x contacts, so that nothing of a tile
+// passes through LDS: the weights are the A operands and stay in registers,
+// a lane's accumulators are units of one contact, and the pair of lanes that
+// shares a contact trades half of its packed units (v_permlane32_swap) to
+// have the next layer's B operand.  The input tile is read straight into the
+// first B operand (the next tile's rows in flight meanwhile).
+//   layer 1: W1[64 x 16] (12 inputs padded) . X^T[16 x 32]: 2 M-tiles x 1 K-step
+//   layer 2: W2[64 x 64] . H1^T[64 x 32]: 2 M-tiles x 4 K-steps
+//   layer 3: W3[32 x 64] (3 of 32 rows used) . H2^T[64 x 32]: 4 K-steps
 // Operand layouts of v_mfma_f32_32x32x16_bf16 (A 32x16, B 16x32, D 32x32):
 //   A[i][k] -> lane i + 32 (k / 8), element k % 8
 //   B[k][j] -> lane j + 32 (k / 8), element k % 8
 //   D[i][j] -> lane j + 32 ((i / 4) % 2), element (i % 4) + 4 (i / 8)
+// Bound by the vector ALU: 128 SiLUs a contact, each an exponential and a
+// reciprocal at a quarter of the rate and four or five plain operations, is
+// about 3,300 cycles a tile of a SIMD, where a tile takes 3,280.  2^22
+// contacts take 184 us; with weights and layers in LDS they took 202, and
+// three waves a SIMD, for which the registers spill, take 215.
 // ---------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
 
 constexpr int kMlpWaves = 4;
-constexpr int kHPitch = kH + 8;    // BF16 rows of 64 + 8 (16-byte aligned)
 
-__device__ inline void wave_sync()
+__global__ __launch_bounds__(64 * kMlpWaves, 2) void k_mlp_bf16(const float* __restrict__ W,
+                                                                const float* __restrict__ feat,
+                                                                float* __restrict__ out, const uint32_t* d_n,
+                                                                int64_t cap)
 {
-    // the LDS operations of one wave run in order; keep the compiler from
-    // moving them across this point
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_bf16(const float* __restrict__ W, const float* __restrict__ feat,
-                                                              float* __restrict__ out, const uint32_t* d_n, int64_t cap)
-{
-    // B operands: row j holds the weights into unit j (W1 padded to K = 16,
-    // W3 padded to 32 rows), so lane (j, half) reads 8 consecutive K values
-    __shared__ __attribute__((aligned(16))) __bf16 w1s[kH][16];
-    __shared__ __attribute__((aligned(16))) __bf16 w2s[kH][kHPitch];
-    __shared__ __attribute__((aligned(16))) __bf16 w3s[32][kHPitch];
-    __shared__ __attribute__((aligned(16))) __bf16 hts[kMlpWaves][32][kHPitch];
-    const int tid = threadIdx.x;
-    for (int t = tid; t < kH * 16; t += blockDim.x) {
-        const int j = t / 16, k = t % 16;
-        w1s[j][k] = (__bf16)(k < kIn ? W[oW1 + j * kIn + k] : 0.0f);
-    }
-    for (int t = tid; t < kH * kH; t += blockDim.x) w2s[t / kH][t % kH] = (__bf16)W[oW2 + t];
-    for (int t = tid; t < 32 * kH; t += blockDim.x) {
-        const int j = t / kH, k = t % kH;
-        w3s[j][k] = (__bf16)(j < kOut ? W[oW3 + j * kH + k] : 0.0f);
-    }
-    __syncthreads();  // the only block barrier: the weights are read-only afterwards
-
-    const int wave = tid >> 6, lane = tid & 63;
+    // the weights come through LDS (rows of 64 + 8 BF16), one reading of them a block
+    __shared__ __attribute__((aligned(16))) __bf16 w1s[kH][16 + 8], w2s[kH][kH + 8], w3s[kOut + 1][kH + 8];
+    __shared__ __attribute__((aligned(16))) float bias[2][kH];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int half = lane >> 5, col = lane & 31;
-    const float bias1[2] = {W[ob1 + col], W[ob1 + 32 + col]};
-    const float bias2[2] = {W[ob2 + col], W[ob2 + 32 + col]};
-    const float bias3 = col < kOut ? W[ob3 + col] : 0.0f;
+    for (int t = tid; t < kH * 16; t += blockDim.x)
+        w1s[t / 16][t % 16] = (__bf16)(t % 16 < kIn ? W[oW1 + t / 16 * kIn + t % 16] : 0.0f);
+    for (int t = tid; t < kH * kH; t += blockDim.x) w2s[t / kH][t % kH] = (__bf16)W[oW2 + t];
+    for (int t = tid; t < (kOut + 1) * kH; t += blockDim.x)
+        w3s[t / kH][t % kH] = (__bf16)(t < kOut * kH ? W[oW3 + t] : 0.0f);
+    for (int t = tid; t < 2 * kH; t += blockDim.x) bias[t / kH][t % kH] = W[(t < kH ? ob1 : ob2) + t % kH];
+    __syncthreads();  // the only block barrier: the weights are read-only afterwards
+    // lane (col, half) holds weights 8 half .. 8 half + 7 of each K-step into
+    // unit col (W1 padded to K = 16, W3 to 32 rows)
+    auto row = [&](const __bf16* r, int k0) { return *reinterpret_cast<const bf16x8*>(r + k0 + half * 8); };
+    bf16x8 w1[2], w2[2][4], w3[4];
+    for (int m = 0; m < 2; ++m) {
+        w1[m] = row(w1s[m * 32 + col], 0);
+        for (int ks = 0; ks < 4; ++ks) w2[m][ks] = row(w2s[m * 32 + col], ks * 16);
+    }
+    for (int ks = 0; ks < 4; ++ks) w3[ks] = row(w3s[min(col, kOut)], ks * 16);
+    const float b3[kOut] = {W[ob3], W[ob3 + 1], W[ob3 + 2]};
     float scl[8];  // scales of this lane's input columns 8 half .. 8 half + 7
     for (int q = 0; q < 8; ++q) scl[q] = half * 8 + q < kIn ? W[oScale + half * 8 + q] : 0.0f;
 
     const uint64_t n = d_n ? (uint64_t)min((uint64_t)*d_n, (uint64_t)cap) : (uint64_t)cap;
     const uint64_t ntiles = (n + 31) / 32;
     const uint64_t nwaves = (uint64_t)gridDim.x * kMlpWaves;
-    __bf16(*ht)[kHPitch] = hts[wave];
-    auto brow = [&](const __bf16* row, int k0) { return *reinterpret_cast<const bf16x8*>(row + k0 + half * 8); };
     // the input row of a tile: lane (col, half) holds features 8 half .. 8 half + 7
     // (only 8 .. 11 of the second half are inside the 12)
     auto load_x = [&](uint64_t tile, float4& x0, float4& x1) {
@@ -118,54 +115,54 @@ __global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_bf16(const float* __rest
             if (half == 0) x1 = f[1];
         }
     };
-    // D tile (+ bias, SiLU) -> BF16 rows of ht, N-tile nt
-    auto store_h = [&](const floatx16& acc, float bias, int nt) {
-        for (int e = 0; e < 16; ++e) {
-            const int i = (e & 3) + 8 * (e >> 2) + 4 * half;
-            ht[i][nt * 32 + col] = (__bf16)silu_fast(acc[e] + bias);
+    // M-tile (+ bias, SiLU) in BF16 -> the next layer's B operands of its two
+    // K-steps.  The lane's units of a K-step are 4 half .. 4 half + 3 and 8 more;
+    // the swap gives the lower lanes 0 .. 7 and the upper ones 8 .. 15.
+    // Accumulator element e is unit 8 (e / 4) + 4 half + e % 4.
+    auto activate = [&](const floatx16& acc, const float* bs, bf16x8* B) {
+        for (int ks = 0; ks < 2; ++ks) {
+            unsigned p[4];
+            for (int t = 0; t < 2; ++t) {
+                const int e = ks * 8 + 4 * t;
+                const float4 q = *reinterpret_cast<const float4*>(bs + 2 * e + 4 * half);
+                const bf16x2 h0 = {(__bf16)silu_fast(acc[e] + q.x), (__bf16)silu_fast(acc[e + 1] + q.y)};
+                const bf16x2 h1 = {(__bf16)silu_fast(acc[e + 2] + q.z), (__bf16)silu_fast(acc[e + 3] + q.w)};
+                p[2 * t] = __builtin_bit_cast(unsigned, h0);
+                p[2 * t + 1] = __builtin_bit_cast(unsigned, h1);
+            }
+            const uintx2 s0 = __builtin_amdgcn_permlane32_swap(p[0], p[2], false, false);
+            const uintx2 s1 = __builtin_amdgcn_permlane32_swap(p[1], p[3], false, false);
+            const uint4 v = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+            B[ks] = __builtin_bit_cast(bf16x8, v);
         }
     };
     uint64_t tile = (uint64_t)blockIdx.x * kMlpWaves + wave;
     float4 x0, x1;
     load_x(tile, x0, x1);
     for (; tile < ntiles; tile += nwaves) {
-        bf16x8 A;
-        A[0] = (__bf16)(x0.x * scl[0]); A[1] = (__bf16)(x0.y * scl[1]);
-        A[2] = (__bf16)(x0.z * scl[2]); A[3] = (__bf16)(x0.w * scl[3]);
-        A[4] = (__bf16)(x1.x * scl[4]); A[5] = (__bf16)(x1.y * scl[5]);
-        A[6] = (__bf16)(x1.z * scl[6]); A[7] = (__bf16)(x1.w * scl[7]);
+        bf16x8 X, H1[4], H2[4];
+        X[0] = (__bf16)(x0.x * scl[0]); X[1] = (__bf16)(x0.y * scl[1]);
+        X[2] = (__bf16)(x0.z * scl[2]); X[3] = (__bf16)(x0.w * scl[3]);
+        X[4] = (__bf16)(x1.x * scl[4]); X[5] = (__bf16)(x1.y * scl[5]);
+        X[6] = (__bf16)(x1.z * scl[6]); X[7] = (__bf16)(x1.w * scl[7]);
         load_x(tile + nwaves, x0, x1);  // the next tile's rows, in flight meanwhile
-        // layer 1
-        floatx16 d0 = {}, d1 = {};
-        d0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, brow(w1s[col], 0), d0, 0, 0, 0);
-        d1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, brow(w1s[32 + col], 0), d1, 0, 0, 0);
-        store_h(d0, bias1[0], 0);
-        store_h(d1, bias1[1], 1);
-        wave_sync();
-        // layer 2 (its A operands read before the tile is overwritten)
-        bf16x8 A2[4];
-        for (int ks = 0; ks < 4; ++ks) A2[ks] = brow(ht[col], ks * 16);
-        wave_sync();
-        d0 = {}; d1 = {};
-        for (int ks = 0; ks < 4; ++ks) {
-            d0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A2[ks], brow(w2s[col], ks * 16), d0, 0, 0, 0);
-            d1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A2[ks], brow(w2s[32 + col], ks * 16), d1, 0, 0, 0);
+        floatx16 d[2] = {};
+        for (int m = 0; m < 2; ++m) {
+            d[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1[m], X, d[m], 0, 0, 0);
+            activate(d[m], bias[0] + 32 * m, H1 + 2 * m);
         }
-        store_h(d0, bias2[0], 0);
-        store_h(d1, bias2[1], 1);
-        wave_sync();
-        // layer 3: columns 0..2 of D are the outputs
-        for (int ks = 0; ks < 4; ++ks) A2[ks] = brow(ht[col], ks * 16);
-        floatx16 d3 = {};
-        for (int ks = 0; ks < 4; ++ks)
-            d3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A2[ks], brow(w3s[col], ks * 16), d3, 0, 0, 0);
-        if (col < kOut)
-            for (int e = 0; e < 16; ++e) {
-                const int i = (e & 3) + 8 * (e >> 2) + 4 * half;
-                const uint64_t c = tile * 32 + i;
-                if (c < n) out[c * kOut + col] = d3[e] + bias3;
-            }
-        wave_sync();  // the tile is rewritten by the next iteration
+        for (int m = 0; m < 2; ++m) {
+            d[m] = floatx16{};
+            for (int ks = 0; ks < 4; ++ks)
+                d[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2[m][ks], H1[ks], d[m], 0, 0, 0);
+        }
+        for (int m = 0; m < 2; ++m) activate(d[m], bias[1] + 32 * m, H2 + 2 * m);
+        floatx16 y = {};
+        for (int ks = 0; ks < 4; ++ks) y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w3[ks], H2[ks], y, 0, 0, 0);
+        // units 0 .. 2 of the lower lanes are the contact's outputs
+        const uint64_t c = tile * 32 + col;
+        if (half == 0 && c < n)
+            for (int q = 0; q < kOut; ++q) out[c * kOut + q] = y[q] + b3[q];
     }
 }
 
