@@ -36,9 +36,15 @@ __global__ void k_fill_f64(double* a, int64_t n, double v)
     if (i < n) a[i] = v;
 }
 
-// one thread per particle of the env: its mass and momentum into the voxels
-__global__ void k_coarse_grain(DevBuffers b, EnvDev E, tr_voxel_grid g, int kernel, double R, double* rho,
-                               double* mom)
+__global__ void k_cg_clear(int64_t nv, double* rho, double* mom)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < nv) rho[i] = 0.0;
+    if (i < 3 * nv) mom[i] = 0.0;
+}
+
+// one thread per particle of the env: its mass and momentum into its voxel
+__global__ void k_coarse_grain(DevBuffers b, EnvDev E, tr_voxel_grid g, double* rho, double* mom)
 {
 #pragma clang fp contract(off)
     const int a = blockIdx.x * blockDim.x + threadIdx.x;
@@ -49,40 +55,164 @@ __global__ void k_coarse_grain(DevBuffers b, EnvDev E, tr_voxel_grid g, int kern
     const double r = xf.w;
     const double m = (double)b.rho[sl] * (4.0 / 3.0) * 3.14159265358979323846 * r * r * r;
     const int dims[3] = {g.nx, g.ny, g.nz};
-    if (kernel == TR_CG_HEAVISIDE) {
-        const double V0 = g.l0 * g.l0 * g.l0;
-        int c[3];
-        for (int k = 0; k < 3; ++k) {
-            const double f = floor((x[k] - g.origin[k]) / g.l0);
-            if (!(f >= 0.0 && f < (double)dims[k])) return;
-            c[k] = (int)f;
-        }
-        const int64_t id = ((int64_t)c[2] * g.ny + c[1]) * g.nx + c[0];
-        atomicAdd(&rho[id], m / V0);
-        for (int k = 0; k < 3; ++k) atomicAdd(&mom[3 * id + k], m * v[k] / V0);
-        return;
-    }
-    const double sq = sqrt(2.0 * 3.14159265358979323846) * R;
-    const double norm = 1.0 / (sq * sq * sq);
-    int lo[3], hi[3];
+    const double V0 = g.l0 * g.l0 * g.l0;
+    int c[3];
     for (int k = 0; k < 3; ++k) {
-        const double fl = ceil((x[k] - 3.0 * R - g.origin[k]) / g.l0 - 0.5);
-        const double fh = floor((x[k] + 3.0 * R - g.origin[k]) / g.l0 - 0.5);
-        lo[k] = fl < 0.0 ? 0 : (int)fl;
-        hi[k] = fh > (double)(dims[k] - 1) ? dims[k] - 1 : (int)fh;
+        const double f = floor((x[k] - g.origin[k]) / g.l0);
+        if (!(f >= 0.0 && f < (double)dims[k])) return;
+        c[k] = (int)f;
     }
-    for (int kz = lo[2]; kz <= hi[2]; ++kz)
-        for (int jy = lo[1]; jy <= hi[1]; ++jy)
-            for (int ix = lo[0]; ix <= hi[0]; ++ix) {
-                const double y[3] = {g.origin[0] + (ix + 0.5) * g.l0 - x[0], g.origin[1] + (jy + 0.5) * g.l0 - x[1],
-                                     g.origin[2] + (kz + 0.5) * g.l0 - x[2]};
-                const double r2 = (y[0] * y[0] + y[1] * y[1]) + y[2] * y[2];
-                if (r2 > 9.0 * R * R) continue;
-                const double z = norm * exp(-r2 / (2.0 * R * R));
-                const int64_t id = ((int64_t)kz * g.ny + jy) * g.nx + ix;
-                atomicAdd(&rho[id], m * z);
-                for (int k = 0; k < 3; ++k) atomicAdd(&mom[3 * id + k], m * v[k] * z);
+    const int64_t id = ((int64_t)c[2] * g.ny + c[1]) * g.nx + c[0];
+    atomicAdd(&rho[id], m / V0);
+    for (int k = 0; k < 3; ++k) atomicAdd(&mom[3 * id + k], m * v[k] / V0);
+}
+
+// the value of lane l, the same l in the whole wave
+__device__ inline int lane_value(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
+__device__ inline double lane_value(double v, int l)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
+    const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
+    return __builtin_bit_cast(double, (uint64_t)c << 32 | a);
+}
+
+// The smooth kernel spreads a particle over all voxels within 3 R, about 113
+// for R = l0: with an FP64 atomic to memory for each it is bound by those
+// atomics (22.6 million for 50,000 particles, 480 us).  Neighbours in slot
+// order are neighbours in space, so a block takes a run of them and adds
+// their shares up in LDS over the box of voxels that they reach together; one
+// atomic a voxel and value is left for the whole run (80 us with 8 waves a
+// block, 99 with 4: what bounds it is the chain of an exponential).  A run whose box
+// does not fit is cut where it stops fitting; a particle whose own box does
+// not fit goes to memory directly.  A wave takes a particle at a time, a lane
+// a column of its voxels.  (The exponential as the product of its three axes',
+// computed once a particle, took 6 us less and rounds twice more.)
+constexpr int kCgWaves = 8;
+constexpr int kCgVox = 2048;   // voxels of a run's box: 64 KB of LDS, two blocks a CU
+constexpr int kCgAxis = 64;    // voxels of a particle's box along the three axes together
+
+__global__ __launch_bounds__(64 * kCgWaves) void k_coarse_grain_smooth(DevBuffers b, EnvDev E, tr_voxel_grid g, double R,
+                                                              int run, double* rho, double* mom)
+{
+#pragma clang fp contract(off)
+    __shared__ double acc[4][kCgVox];
+    __shared__ double ax2[kCgWaves][kCgAxis];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int p0 = blockIdx.x * run, np = min(run, E.n - p0);
+    const int dims[3] = {g.nx, g.ny, g.nz};
+    // lane p of every wave: particle p of the run and its box (empty past the run's end)
+    double x[3] = {0.0, 0.0, 0.0}, mv[3] = {0.0, 0.0, 0.0}, m = 0.0;
+    int lo[3] = {0, 0, 0}, hi[3] = {-1, -1, -1};
+    if (lane < np) {
+        const int sl = E.slot_begin + p0 + lane;
+        const float4 xf = b.xr[sl], vf = vel_at(b.vw, sl);
+        const double r = xf.w;
+        x[0] = xf.x; x[1] = xf.y; x[2] = xf.z;
+        m = (double)b.rho[sl] * (4.0 / 3.0) * 3.14159265358979323846 * r * r * r;
+        mv[0] = m * (double)vf.x; mv[1] = m * (double)vf.y; mv[2] = m * (double)vf.z;
+        for (int k = 0; k < 3; ++k) {
+            const double fl = ceil((x[k] - 3.0 * R - g.origin[k]) / g.l0 - 0.5);
+            const double fh = floor((x[k] + 3.0 * R - g.origin[k]) / g.l0 - 0.5);
+            // (a bound beyond the grid on its far side leaves the box empty)
+            lo[k] = fl < 0.0 ? 0 : (fl > (double)dims[k] ? dims[k] : (int)fl);
+            hi[k] = fh > (double)(dims[k] - 1) ? dims[k] - 1 : (fh < -1.0 ? -1 : (int)fh);
+        }
+    }
+    const bool some = lane < np && lo[0] <= hi[0] && lo[1] <= hi[1] && lo[2] <= hi[2];
+    const double sq = sqrt(2.0 * 3.14159265358979323846) * R;
+    const double norm = 1.0 / (sq * sq * sq), inv = 2.0 * R * R;
+    const unsigned long long alone = __ballot(
+        some && (double)(hi[0] - lo[0] + 1) * (hi[1] - lo[1] + 1) * (hi[2] - lo[2] + 1) > (double)kCgVox);
+    for (int q0 = 0; q0 < np;) {
+        // the box of particles q0 .. lane, and the first lane at which it no longer fits
+        int bl[3], bh[3];
+        for (int k = 0; k < 3; ++k) {
+            bl[k] = some && lane >= q0 ? lo[k] : 0x7fffffff;
+            bh[k] = some && lane >= q0 ? hi[k] : -1;
+        }
+        for (int o = 1; o < 64; o <<= 1)
+            for (int k = 0; k < 3; ++k) {
+                const int l = __shfl_up(bl[k], o), h = __shfl_up(bh[k], o);
+                if (lane >= o) { bl[k] = min(bl[k], l); bh[k] = max(bh[k], h); }
             }
+        const bool any = bl[0] <= bh[0];
+        const double vol = any ? (double)(bh[0] - bl[0] + 1) * (bh[1] - bl[1] + 1) * (bh[2] - bl[2] + 1) : 0.0;
+        const unsigned long long over = __ballot(vol > (double)kCgVox && lane >= q0);
+        const int first = over ? __ffsll((long long)over) - 1 : np;
+        const bool local = first > q0;  // (else particle q0 does not fit, and neither may those after it)
+        const unsigned long long fits = ~alone >> q0;
+        const int q1 = __builtin_amdgcn_readfirstlane(
+            min(np, local ? first : (fits ? q0 + __ffsll((long long)fits) - 1 : 64)));
+        int base[3], side[3];
+        for (int k = 0; k < 3; ++k) {
+            base[k] = lane_value(bl[k], q1 - 1);
+            side[k] = lane_value(bh[k], q1 - 1) - base[k] + 1;
+        }
+        const int nbox = local && side[0] > 0 ? side[0] * side[1] * side[2] : 0;
+        for (int t = threadIdx.x; t < nbox; t += 64 * kCgWaves)
+            for (int k = 0; k < 4; ++k) acc[k][t] = 0.0;
+        __syncthreads();
+        for (int p = q0 + wave; p < q1; p += kCgWaves) {
+            if (!lane_value((int)some, p)) continue;
+            int plo[3], ps[3];
+            double px[3], pmv[3];
+            for (int k = 0; k < 3; ++k) {
+                plo[k] = lane_value(lo[k], p);
+                ps[k] = lane_value(hi[k], p) - plo[k] + 1;
+                px[k] = lane_value(x[k], p);
+                pmv[k] = lane_value(mv[k], p);
+            }
+            const double pm = lane_value(m, p);
+            auto offset2 = [&](int k, int i) {  // squared distance along an axis to voxel i of the box
+                const double y = g.origin[k] + (plo[k] + i + 0.5) * g.l0 - px[k];
+                return y * y;
+            };
+            const bool table = (int64_t)ps[0] + ps[1] + ps[2] <= kCgAxis;
+            if (table) {
+                const int k = lane < ps[0] ? 0 : (lane < ps[0] + ps[1] ? 1 : 2);
+                ax2[wave][lane] = offset2(k, lane - (k > 0 ? ps[0] : 0) - (k > 1 ? ps[1] : 0));
+            }
+            // (LDS operations of one wave run in order)
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const int64_t nxy = (int64_t)ps[0] * ps[1];
+            for (int64_t t = lane; t < nxy; t += 64) {
+                const int ix = (int)((uint32_t)t % (uint32_t)ps[0]), jy = (int)((uint32_t)t / (uint32_t)ps[0]);
+                const double dx2 = table ? ax2[wave][ix] : offset2(0, ix);
+                const double dy2 = table ? ax2[wave][ps[0] + jy] : offset2(1, jy);
+                for (int kz = 0; kz < ps[2]; ++kz) {
+                    const double dz2 = table ? ax2[wave][ps[0] + ps[1] + kz] : offset2(2, kz);
+                    const double r2 = (dx2 + dy2) + dz2;
+                    if (r2 > 9.0 * R * R) continue;
+                    const double z = norm * exp(-r2 / inv);
+                    const int cx = plo[0] + ix, cy = plo[1] + jy, cz = plo[2] + kz;
+                    if (local) {
+                        const int id = ((cz - base[2]) * side[1] + (cy - base[1])) * side[0] + (cx - base[0]);
+                        atomicAdd(&acc[0][id], pm * z);
+                        for (int k = 0; k < 3; ++k) atomicAdd(&acc[1 + k][id], pmv[k] * z);
+                    } else {
+                        const int64_t id = ((int64_t)cz * g.ny + cy) * g.nx + cx;
+                        atomicAdd(&rho[id], pm * z);
+                        for (int k = 0; k < 3; ++k) atomicAdd(&mom[3 * id + k], pmv[k] * z);
+                    }
+                }
+            }
+            __builtin_amdgcn_wave_barrier();  // the tables are rewritten for the next particle
+        }
+        __syncthreads();
+        for (int t = threadIdx.x; t < nbox; t += 64 * kCgWaves) {
+            const double mass = acc[0][t];
+            if (mass == 0.0) continue;  // reached by no particle (or by massless shares alone)
+            const int cx = t % side[0], cy = t / side[0] % side[1], cz = t / (side[0] * side[1]);
+            const int64_t id = ((int64_t)(base[2] + cz) * g.ny + (base[1] + cy)) * g.nx + (base[0] + cx);
+            atomicAdd(&rho[id], mass);
+            for (int k = 0; k < 3; ++k) atomicAdd(&mom[3 * id + k], acc[1 + k][t]);
+        }
+        __syncthreads();
+        q0 = q1;
+    }
 }
 
 __global__ void k_cg_velocity(int64_t nv, const double* rho, const double* mom, double* u)
@@ -96,11 +226,15 @@ void launch_coarse_grain(const DevBuffers& b, const EnvDev& E, const tr_voxel_gr
                          double* rho, double* mom, double* u, hipStream_t s)
 {
     const int64_t nv = (int64_t)g.nx * g.ny * g.nz;
-    hipLaunchKernelGGL(k_fill_f64, dim3((unsigned)cdiv(nv, kBlk)), dim3(kBlk), 0, s, rho, nv, 0.0);
-    hipLaunchKernelGGL(k_fill_f64, dim3((unsigned)cdiv(3 * nv, kBlk)), dim3(kBlk), 0, s, mom, 3 * nv, 0.0);
-    if (E.n > 0)
-        hipLaunchKernelGGL(k_coarse_grain, dim3((unsigned)cdiv(E.n, kBlk)), dim3(kBlk), 0, s, b, E, g, kernel, R, rho,
-                           mom);
+    hipLaunchKernelGGL(k_cg_clear, dim3((unsigned)cdiv(3 * nv, kBlk)), dim3(kBlk), 0, s, nv, rho, mom);
+    if (E.n > 0 && kernel == TR_CG_HEAVISIDE)
+        hipLaunchKernelGGL(k_coarse_grain, dim3((unsigned)cdiv(E.n, kBlk)), dim3(kBlk), 0, s, b, E, g, rho, mom);
+    else if (E.n > 0) {
+        // a particle a wave for few particles, 64 a block where that still gives two blocks a CU
+        const int run = (int)std::min<int64_t>(64, std::max<int64_t>(kCgWaves, E.n / 512));
+        hipLaunchKernelGGL(k_coarse_grain_smooth, dim3((unsigned)cdiv(E.n, run)), dim3(64 * kCgWaves), 0, s, b, E, g, R,
+                           run, rho, mom);
+    }
     if (u) hipLaunchKernelGGL(k_cg_velocity, dim3((unsigned)cdiv(nv, kBlk)), dim3(kBlk), 0, s, nv, rho, mom, u);
 }
 
