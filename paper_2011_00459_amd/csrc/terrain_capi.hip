@@ -22,6 +22,7 @@ using namespace trk;
 
 namespace {
 
+constexpr int64_t kReadChunk = 16384;  // particles of a read-back chunk: 1.3 MB of host memory
 constexpr int kFlowMaxSweeps = 8192;  // longest counter-ordered solve
 
 // Regions of the grouped and spread solves (MI355X, beds under 100 sweeps of 9
@@ -83,6 +84,11 @@ struct tr_scene {
     hipEvent_t ev[5] = {};
     bool events = false;
     float* staging = nullptr;         // 12 floats per particle (device), id-order exchange
+    double* read_buf[2] = {nullptr, nullptr};  // host, written by the device: kReadChunk particles each
+    hipEvent_t read_ev[2] = {nullptr, nullptr};
+    char* report = nullptr;           // host, written by the device after the steps of a call
+    size_t report_bytes = 0;
+    bool report_fresh = false;        // it holds the body forces of the last step
     int64_t cols_alloc = 0;
     bool mlp_loaded = false;
     bool mlp_bf16 = true;
@@ -277,6 +283,24 @@ int region_blocks(int64_t n, bool wide, int bpx)
     if (!wide && n <= kRegionAlone) return 1;
     const int64_t per = wide ? (n + kGroups - 1) / kGroups : n;
     return (int)std::max<int64_t>(1, std::min<int64_t>(bpx, (per + kRegionSpheres - 1) / kRegionSpheres));
+}
+
+// the tables of a step's report, laid out from base: the counters, the body
+// forces and, with stats, what step_stats is made of
+StepReport step_report(const tr_scene* s, char* base, bool stats)
+{
+    StepReport r{};
+    const void* from[StepReport::kParts] = {s->b.cnt, s->b.body_ft, s->b.env_stats, s->b.ustats, s->b.env_ncol};
+    const size_t size[StepReport::kParts] = {sizeof(Counters), sizeof(double) * 6 * s->p.n_bodies,
+                                             sizeof(EnvStats) * s->desc.n_envs, sizeof(UnitStats) * s->p.n_units,
+                                             sizeof(uint32_t) * s->desc.n_envs};
+    for (int k = 0; k < StepReport::kParts; ++k) {
+        r.from[k] = (const uint32_t*)from[k];
+        r.to[k] = (uint32_t*)base;
+        r.words[k] = k < 2 || stats ? (int64_t)(size[k] / sizeof(uint32_t)) : 0;
+        base += size[k];
+    }
+    return r;
 }
 
 // PGS schedule: the solve unit of every env and, in per-env mode, the plan of
@@ -783,6 +807,18 @@ int rebuild_tables(tr_scene* s)
     s->p.n_shapes = (int)sd.size();
     s->p.n_zones = n_zones;
     s->tables_dirty = false;
+    s->report_fresh = false;
+    const StepReport r = step_report(s, nullptr, true);
+    size_t need = 0;
+    for (int64_t w : r.words) need += sizeof(uint32_t) * w;
+    if (need > s->report_bytes) {
+        if (s->report) (void)hipHostFree(s->report);
+        s->report = nullptr;
+        s->report_bytes = 0;
+        if (hipHostMalloc((void**)&s->report, need, hipHostMallocDefault) != hipSuccess)
+            return fail(s, TR_E_NOMEM, "step report");
+        s->report_bytes = need;
+    }
     return rebuild_plan(s);
 }
 
@@ -923,12 +959,16 @@ int create_scene(const tr_scene_desc* d, tr_scene** out)
     if (e == hipSuccess) e = hipMemsetAsync(b.id_count, 0, sizeof(uint32_t) * z.NID, s->stream);
     if (e == hipSuccess) e = hipMemsetAsync(b.inc_count, 0, sizeof(uint32_t) * z.P, s->stream);
     for (int k = 0; k < 5 && e == hipSuccess; ++k) e = hipEventCreate(&s->ev[k]);
+    s->events = e == hipSuccess;
+    const int64_t chunk = 10 * std::min(d->cap_particles, kReadChunk);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&s->read_buf[0], sizeof(double) * 2 * chunk, hipHostMallocDefault);
+    s->read_buf[1] = s->read_buf[0] + chunk;
+    for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreateWithFlags(&s->read_ev[k], hipEventDisableTiming);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) {
         destroy_scene(s);
         return TR_E_DEVICE;
     }
-    s->events = true;
     *out = s;
     return TR_OK;
 }
@@ -943,6 +983,10 @@ int destroy_scene(tr_scene* s)
     while (!s->allocs.empty()) dfree(s, s->allocs.back().first);
     if (s->events)
         for (int k = 0; k < 5; ++k) (void)hipEventDestroy(s->ev[k]);
+    if (s->read_buf[0]) (void)hipHostFree(s->read_buf[0]);
+    for (int k = 0; k < 2; ++k)
+        if (s->read_ev[k]) (void)hipEventDestroy(s->read_ev[k]);
+    if (s->report) (void)hipHostFree(s->report);
     delete s;
     return TR_OK;
 }
@@ -1190,6 +1234,7 @@ static int step_scene(tr_scene* s, int32_t n_steps, tr_step_stats* stats)
         if (rc) return rc;
     }
     hipStream_t st = s->stream;
+    s->report_fresh = false;
     for (int k = 0; k < n_steps; ++k) {
         if (s->use_graphs && s->have_prev && !s->graphs) {
             int rc = capture_graphs(s);
@@ -1217,17 +1262,17 @@ static int step_scene(tr_scene* s, int32_t n_steps, tr_step_stats* stats)
     if (n_steps == 0 && !stats) return TR_OK;
     // every call waits for its steps and reads the failure flags of all of
     // them: the current step's word and the word earlier steps folded theirs into
+    const StepReport r = step_report(s, s->report, stats != nullptr);
+    launch_report(r, st);
+    HIP_CHECK(s, hipGetLastError());
     HIP_CHECK(s, hipStreamSynchronize(st));
-    Counters c;
-    HIP_CHECK(s, hipMemcpy(&c, s->b.cnt, sizeof(c), hipMemcpyDeviceToHost));
+    s->report_fresh = true;
+    const Counters& c = *(const Counters*)r.to[0];
     const uint32_t bad = c.failed | c.overflow;
     if (stats) {
-        std::vector<EnvStats> es(s->desc.n_envs);
-        HIP_CHECK(s, hipMemcpy(es.data(), s->b.env_stats, sizeof(EnvStats) * es.size(), hipMemcpyDeviceToHost));
-        std::vector<UnitStats> us(s->p.n_units);
-        std::vector<uint32_t> nc(s->desc.n_envs);
-        HIP_CHECK(s, hipMemcpy(us.data(), s->b.ustats, sizeof(UnitStats) * us.size(), hipMemcpyDeviceToHost));
-        HIP_CHECK(s, hipMemcpy(nc.data(), s->b.env_ncol, sizeof(uint32_t) * nc.size(), hipMemcpyDeviceToHost));
+        const EnvStats* es = (const EnvStats*)r.to[2];
+        const UnitStats* us = (const UnitStats*)r.to[3];
+        const uint32_t* nc = (const uint32_t*)r.to[4];
         for (int e2 = 0; e2 < s->desc.n_envs; ++e2) {
             tr_step_stats& o = stats[e2];
             o.contacts = es[e2].contacts;
@@ -1270,7 +1315,10 @@ int get_contact_forces(tr_scene* s, int32_t env, int32_t body_id, double force[3
     if (gi < 0) return fail(s, TR_E_INVAL, "get_contact_forces: unknown body");
     double ft[6];
     HIP_CHECK(s, hipStreamSynchronize(s->stream));
-    HIP_CHECK(s, hipMemcpy(ft, s->b.body_ft + 6 * gi, sizeof(ft), hipMemcpyDeviceToHost));
+    if (s->report_fresh)  // the last step brought them along
+        memcpy(ft, (const double*)step_report(s, s->report, false).to[1] + 6 * gi, sizeof(ft));
+    else
+        HIP_CHECK(s, hipMemcpy(ft, s->b.body_ft + 6 * gi, sizeof(ft), hipMemcpyDeviceToHost));
     for (int k = 0; k < 3; ++k) { force[k] = ft[k]; torque[k] = ft[3 + k]; }
     return TR_OK;
 }
@@ -1890,18 +1938,27 @@ int get_particles(tr_scene* s, int32_t env, double* pos, double* vel, double* an
     int64_t ne = s->envs[env].n;
     if (n) *n = ne;
     if (ne == 0) return TR_OK;
-    float4* st4 = (float4*)s->staging;
-    launch_gather_by_id(s->b, (int)(env * s->desc.cap_particles), (int)ne, st4, st4 + ne, st4 + 2 * ne, s->stream);
-    std::vector<float4> h(3 * ne);
-    HIP_CHECK(s, hipMemcpyAsync(h.data(), st4, sizeof(float4) * 3 * ne, hipMemcpyDeviceToHost, s->stream));
-    HIP_CHECK(s, hipStreamSynchronize(s->stream));
-    for (int64_t i = 0; i < ne; ++i) {
-        const float4 &x = h[i], &v = h[ne + i], &w = h[2 * ne + i];
-        if (pos) { pos[3 * i] = x.x; pos[3 * i + 1] = x.y; pos[3 * i + 2] = x.z; }
-        if (radius) radius[i] = x.w;
-        if (vel) { vel[3 * i] = v.x; vel[3 * i + 1] = v.y; vel[3 * i + 2] = v.z; }
-        if (angvel) { angvel[3 * i] = w.x; angvel[3 * i + 1] = w.y; angvel[3 * i + 2] = w.z; }
+    double* to[4] = {pos, vel, angvel, radius};
+    // chunk q is written by the device while the host copies chunk q - 1
+    const int64_t chunk = std::min(s->desc.cap_particles, kReadChunk), nq = (ne + chunk - 1) / chunk;
+    const bool any = pos || vel || angvel || radius;
+    for (int64_t q = 0; any && q <= nq; ++q) {
+        if (q < nq) {
+            const int m = (int)std::min(chunk, ne - q * chunk);
+            launch_read_particles(s->b, (int)(env * s->desc.cap_particles + q * chunk), m, s->read_buf[q & 1],
+                                  s->stream);
+            HIP_CHECK(s, hipGetLastError());
+            HIP_CHECK(s, hipEventRecord(s->read_ev[q & 1], s->stream));
+        }
+        if (q == 0) continue;
+        const int64_t i0 = (q - 1) * chunk, m = std::min(chunk, ne - i0);
+        HIP_CHECK(s, hipEventSynchronize(s->read_ev[(q - 1) & 1]));
+        for (int f = 0; f < 4; ++f)
+            if (to[f])
+                memcpy(to[f] + (f < 3 ? 3 : 1) * i0, s->read_buf[(q - 1) & 1] + 3 * m * f,
+                       sizeof(double) * m * (f < 3 ? 3 : 1));
     }
+    HIP_CHECK(s, hipStreamSynchronize(s->stream));
     return TR_OK;
 }
 

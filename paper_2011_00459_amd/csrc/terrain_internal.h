@@ -409,8 +409,15 @@ struct MacroArgs {
 void launch_macro(const DevBuffers& b, const StepParams& p, const MacroArgs& a, MacroZone* mz, tr_macro_result* out,
                   hipStream_t s);
 
-void launch_gather_by_id(const DevBuffers& b, int id_base, int n, float4* xo, float4* vo, float4* wo,
-                         hipStream_t s);
+void launch_read_particles(const DevBuffers& b, int id0, int m, double* out, hipStream_t s);
+// tables of a step copied to host memory (32-bit words)
+struct StepReport {
+    static constexpr int kParts = 5;
+    const uint32_t* from[kParts];
+    uint32_t* to[kParts];
+    int64_t words[kParts];
+};
+void launch_report(const StepReport& r, hipStream_t s);
 void launch_scatter_by_id(const DevBuffers& b, int id_base, int n, const float4* xi, const float4* vi,
                           const float4* wi, int mask, hipStream_t s);
 int pgs_resident_blocks();

@@ -574,7 +574,7 @@ class Scene:
         n = C.c_int64()
         self._check(lib().get_particles(self.h, env, None, None, None, None, C.byref(n)), "get_particles")
         m = n.value
-        x = np.zeros((m, 3)); v = np.zeros((m, 3)); w = np.zeros((m, 3)); r = np.zeros(m)
+        x, v, w, r = np.empty((m, 3)), np.empty((m, 3)), np.empty((m, 3)), np.empty(m)
         self._check(lib().get_particles(self.h, env, _dp(x), _dp(v), _dp(w), _dp(r), C.byref(n)), "get_particles")
         return dict(x=x, v=v, w=w, r=r)
 
