@@ -557,6 +557,7 @@ int rebuild_plan(tr_scene* s)
         HIP_CHECK(s, hipMemcpyAsync(s->b.grp_task, tasks_g.data(), sizeof(int4) * tasks_g.size(), hipMemcpyHostToDevice, st));
     s->z.n_own = n_own;
     s->z.grp_lds = grp_lds;
+    s->z.grp_f4 = pgs_group_max_lds() / 16;
     s->z.n_flags = (int)flags;
     if ((int64_t)plan.size() > s->plan_alloc) {
         dfree(s, s->b.plan);

@@ -292,6 +292,7 @@ struct Sizes {
     int pgs_grid;   // blocks of the persistent PGS kernel (kGroups x blocks per group)
     int n_own;      // owners of the solve order
     int grp_lds;    // spheres a block of the grouped / spread solve holds in LDS
+    int grp_f4;     // LDS of such a block (float4)
     int n_flags;    // entries of rflags
     int pgs_mode;   // kModeGrouped, kModePerEnv or kModeSpread
     int plan_blocks;  // blocks of the per-env PGS kernel

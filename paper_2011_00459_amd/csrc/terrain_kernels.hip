@@ -19,6 +19,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <cmath>
 #include <cstddef>
 
@@ -1510,14 +1511,20 @@ void launch_warm_apply(const DevBuffers& b, const StepParams& p, const Sizes& z,
 // last waves while the others update contacts whose bodies are all in LDS;
 // a workgroup barrier ends the phase.
 //
+// What LDS has left beside the bodies holds the block's rows and impulses, or
+// its impulses alone, when they fit whole (blocks of up to about 600 and 2,000
+// spheres); blocks of 1,024 threads have no registers for the extra code.
+//
 // Measured (MI355X, PGS per launch) against clusters that kept every body in
 // memory and met at a counter barrier after every colour: a 50,000-sphere bed
-// of 150 sweeps 7.16 -> 2.36 ms, a 500,000-sphere one of 200 sweeps 24.6 ->
-// 7.8 ms, a 300-sphere column of 50 sweeps 0.74 -> 0.32 ms.  A phase is bound
-// by its chain: rows, LDS bodies, about 100 dependent operations, the barrier
-// (0.6 us on one block of a few hundred spheres), or the hand-over (1.1 us
-// within an XCD, 1.6 us across), and from about 2,000 spheres a block by
-// instruction issue.
+// of 150 sweeps 7.16 -> 2.05 ms (2.36 with rows and impulses in memory), a
+// 500,000-sphere one of 200 sweeps 24.6 -> 7.9 ms (8.5), a 300-sphere column
+// of 50 sweeps 0.74 -> 0.29 ms (0.32), one of 1,000 spheres to 1e-3 4.9 ->
+// 3.0 ms (3.5).  A phase is bound by its chain: about 170 instructions issued
+// by one wave a SIMD, the bodies out of LDS and back, the barrier (0.65 us on
+// one block of a few hundred spheres), or the hand-over (1.1 us within an
+// XCD, 1.4 us across), and from about 2,000 spheres a block by instruction
+// issue.
 //
 // Contact c of a colour is always handled by the same thread, so its rows
 // (read-only) and impulses (thread-owned) use the ordinary caches, and the
@@ -1831,21 +1838,19 @@ __device__ inline void pgs_update(const DevBuffers& b, uint32_t c, RowRegs& R, B
     float tz = fma(-iDt, fma(gdt, L.w, uz), L.w);
     const float lim = mu * fabsf(ln);
     const float m2 = dot3f(tx, ty, tz, tx, ty, tz);
-    if (m2 > lim * lim) {
-        const float sc = m2 > 0.f ? lim * rsqrtf(m2) : 0.f;
-        tx *= sc; ty *= sc; tz *= sc;
-    }
+    // (a product with 1 changes nothing; cheaper than a branch)
+    const float sc = m2 > lim * lim ? (m2 > 0.f ? lim * rsqrtf(m2) : 0.f) : 1.f;
+    tx *= sc; ty *= sc; tz *= sc;
     const float dx = tx - L.y, dy = ty - L.z, dz = tz - L.w;
     // impulse d at the contact point: +d on body 2 (arm -l2 n), -d on body 1 (arm +l1 n)
     const float cx = det2f(ny, nz, dy, dz), cy = det2f(nz, nx, dz, dx), cz = det2f(nx, ny, dx, dy);  // n x d
     vb.x = fma(vb.w, dx, vb.x); vb.y = fma(vb.w, dy, vb.y); vb.z = fma(vb.w, dz, vb.z);
     const float kb = l2 * wb.w;
     wb.x = fma(-kb, cx, wb.x); wb.y = fma(-kb, cy, wb.y); wb.z = fma(-kb, cz, wb.z);
-    if (pair) {
-        va.x = fma(-va.w, dx, va.x); va.y = fma(-va.w, dy, va.y); va.z = fma(-va.w, dz, va.z);
-        const float kk = l1 * wa.w;
-        wa.x = fma(-kk, cx, wa.x); wa.y = fma(-kk, cy, wa.y); wa.z = fma(-kk, cz, wa.z);
-    }
+    // (a boundary's are not used any more)
+    va.x = fma(-va.w, dx, va.x); va.y = fma(-va.w, dy, va.y); va.z = fma(-va.w, dz, va.z);
+    const float kk = l1 * wa.w;
+    wa.x = fma(-kk, cx, wa.x); wa.y = fma(-kk, cy, wa.y); wa.z = fma(-kk, cz, wa.z);
     if (want) {
         // residual weights (the stopping test only): hardware reciprocals; a row
         // with zero inverse mass (a neutralised impact-stage row) weighs nothing
@@ -1894,6 +1899,99 @@ __device__ inline void pgs_contact(const DevBuffers& b, const BA& ba, uint32_t c
     pgs_update(b, c, R, B, mu, gdt, want, num, den, roll);
     store_bodies(ba, R, B);
 }
+
+// Where a block reads the rows and keeps the impulses of its contacts
+// [base, base + n): both in memory, the impulses in LDS, or all in LDS (one
+// record a contact: impulses, normal, row, bodies, masses, rolling row and
+// impulses; the places in the bodies' sequences after the records).
+enum RowHome { kRowsMemory, kRowsImpulses, kRowsLds };
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+template <bool ROLL, RowHome HOME>
+struct BlockRows {
+    static constexpr uint32_t kRec = HOME == kRowsLds ? (ROLL ? 7 : 5) : HOME == kRowsImpulses ? (ROLL ? 2 : 1) : 0;
+    static constexpr uint32_t kRollAt = HOME == kRowsLds ? 6 : 1;
+    typedef __attribute__((address_space(3))) f32x4 lds4;
+    typedef __attribute__((address_space(3))) uint32_t lds1;
+    lds4* l;
+    uint32_t base, n;
+
+    // float4s of LDS that n contacts take
+    static __device__ uint32_t size(uint32_t n) { return n * kRec + (HOME == kRowsLds ? (n + 3) / 4 : 0); }
+    __device__ BlockRows(float4* lds, uint32_t base, uint32_t n) : l((lds4*)lds), base(base), n(n) {}
+    static __device__ float4 get(const lds4* p)
+    {
+        const f32x4 v = *p;
+        return make_float4(v.x, v.y, v.z, v.w);
+    }
+    static __device__ void put(lds4* p, float4 v) { *p = f32x4{v.x, v.y, v.z, v.w}; }
+    __device__ lds1* seqs() const { return (lds1*)(l + n * kRec); }
+    __device__ void begin(const DevBuffers& b, uint32_t tid, uint32_t nthr) const
+    {
+        if (HOME == kRowsMemory) return;
+        for (uint32_t k = tid; k < n; k += nthr) {
+            const uint32_t c = base + k;
+            lds4* r = l + k * kRec;
+            put(r, b.lam[c]);
+            if (ROLL) put(r + kRollAt, b.lamr[c]);
+            if (HOME == kRowsLds) {
+                put(r + 1, b.r0[c]);
+                put(r + 2, b.r1[c]);
+                put(r + 3, b.r2[c]);
+                put(r + 4, b.rm[c]);
+                if (ROLL) put(r + 5, b.r3[c]);
+                seqs()[k] = b.seq[c];
+            }
+        }
+    }
+    __device__ void end(const DevBuffers& b, uint32_t tid, uint32_t nthr) const
+    {
+        if (HOME == kRowsMemory) return;
+        for (uint32_t k = tid; k < n; k += nthr) {
+            b.lam[base + k] = get(l + k * kRec);
+            if (ROLL) b.lamr[base + k] = get(l + k * kRec + kRollAt);
+        }
+    }
+    __device__ RowRegs load(const DevBuffers& b, uint32_t c) const
+    {
+        if (HOME == kRowsMemory) return load_rows(b, c, ROLL);
+        RowRegs R;
+        const lds4* r = l + (c - base) * kRec;
+        if (HOME == kRowsLds) {
+            R.a = get(r + 1);
+            R.r1 = get(r + 2);
+            R.q = get(r + 3);
+            if (ROLL) R.r3 = get(r + 5);
+        } else {
+            R.a = b.r0[c];
+            R.r1 = b.r1[c];
+            R.q = b.r2[c];
+            if (ROLL) R.r3 = b.r3[c];
+        }
+        R.L = get(r);
+        if (ROLL) R.Lr = get(r + kRollAt);
+        return R;
+    }
+    __device__ uint32_t seq(const DevBuffers& b, uint32_t c) const
+    {
+        if (HOME == kRowsLds) return seqs()[c - base];
+        return b.seq[c];
+    }
+    __device__ float4 masses(const DevBuffers& b, uint32_t c) const
+    {
+        if (HOME == kRowsLds) return get(l + (c - base) * kRec + 4);
+        return b.rm[c];
+    }
+    __device__ void store(const DevBuffers& b, uint32_t c, const RowRegs& R) const
+    {
+        if (HOME == kRowsMemory) {
+            store_lam(b, c, R, ROLL);
+            return;
+        }
+        lds4* r = l + (c - base) * kRec;
+        put(r, R.L);
+        if (ROLL) put(r + kRollAt, R.Lr);
+    }
+};
 
 // what a solve's block keeps in LDS beside its bodies
 template <int NW>
@@ -2105,26 +2203,28 @@ __device__ inline BodyRegs await_bodies(const DevBuffers& b, const RegionBodies&
 }
 
 // The solve of one region (file comment above).  lds holds the bodies of the
-// region's first lds_cap spheres (v, then omega).
-template <bool ROLL, int NW>
-__device__ void pgs_region(const DevBuffers& b, const StepParams& p, const SolveTask& T, uint32_t ncol, bool through,
-                           int sweeps_cap, int slot, float4* lds, int lds_cap, SolveShared<NW>& sh)
+// region's first nb spheres (v, then omega).
+template <bool ROLL, int NW, RowHome HOME>
+__device__ void solve_region(const DevBuffers& b, const StepParams& p, const SolveTask& T, uint32_t ncol, bool through,
+                             int sweeps_cap, int slot, float4* lds, int nb, const BlockRows<ROLL, HOME>& br,
+                             SolveShared<NW>& sh)
 {
     constexpr uint32_t kThreads = NW * 64;
     const uint32_t tid = threadIdx.x;
     const bool cluster = T.K > 1;
     uint32_t* sweep_flag = b.rflags + T.f0;
-    const RegionBodies rb{lds, lds + lds_cap, exchange_rsrc(b.xw), b.own_x[T.owner], through};
+    const RegionBodies rb{lds, lds + nb, exchange_rsrc(b.xw), b.own_x[T.owner], through};
     const int sg0 = b.own_idx[T.owner], sg1 = b.own_idx[T.owner + 1];
-    stage_starts(b, T.owner, ncol, sh);
-    if (ncol > 0)
+    if (ncol > 0) {
         for (int sg = sg0; sg < sg1; ++sg) {
             const int4 S = b.own_seg[sg];
-            for (int i = (int)tid; i < S.y && S.z + i < lds_cap; i += (int)kThreads) {
+            for (int i = (int)tid; i < S.y && S.z + i < nb; i += (int)kThreads) {
                 rb.sv[S.z + i] = vel_at(b.vw, S.x + i);
                 rb.sw[S.z + i] = angv_at(b.vw, S.x + i);
             }
         }
+        br.begin(b, tid, kThreads);
+    }
     __syncthreads();
     // Shared contacts go to the threads from the last one down, private ones
     // from the first one up: the waves that wait for the neighbours are the
@@ -2137,8 +2237,8 @@ __device__ void pgs_region(const DevBuffers& b, const StepParams& p, const Solve
     RowRegs cs, cp;
     float4 ms;  // masses of the shared contact's bodies
     auto rows = [&](uint32_t c) {
-        RowRegs R = load_rows(b, c, ROLL);
-        R.seq = b.seq[c];
+        RowRegs R = br.load(b, c);
+        R.seq = br.seq(b, c);
         return R;
     };
     uint32_t s_next = 0, p_next = 0, e_next = 0;  // the phase's shared and private contacts, their end
@@ -2147,7 +2247,7 @@ __device__ void pgs_region(const DevBuffers& b, const StepParams& p, const Solve
         p_next = sh.st[2 * col + 1];
         e_next = sh.st[2 * col + 2];
         const bool has_s = ts < p_next - s_next, has_p = tid < e_next - p_next;
-        if (has_s) ms = b.rm[s_next + ts];
+        if (has_s) ms = br.masses(b, s_next + ts);
         if (kBoth) {
             if (has_s) cs = rows(s_next + ts);
             if (has_p) cp = rows(p_next + tid);
@@ -2181,7 +2281,7 @@ __device__ void pgs_region(const DevBuffers& b, const StepParams& p, const Solve
         BodyRegs B{rb.sv[ja], rb.sw[ja], rb.sv[ib], rb.sw[ib]};
         pgs_update(b, c, R, B, p.mu, p.gamma_dt, want, num, den, ROLL);
         put(R, B, it, true);
-        store_lam(b, c, R, ROLL);
+        br.store(b, c, R);
     };
     for (int it = 0; it < sweeps_cap && ncol > 0; ++it) {
         // without a tolerance only the first and last residuals are reported
@@ -2195,7 +2295,7 @@ __device__ void pgs_region(const DevBuffers& b, const StepParams& p, const Solve
                 const bool on = k < ns;
                 if (k0 != wave_ts && on) {
                     C = rows(s0 + k);
-                    ms = b.rm[s0 + k];
+                    ms = br.masses(b, s0 + k);
                 }
                 settle(C, ROLL);
                 settle(ms.x);
@@ -2203,7 +2303,7 @@ __device__ void pgs_region(const DevBuffers& b, const StepParams& p, const Solve
                 if (on) {
                     pgs_update(b, s0 + k, C, B, p.mu, p.gamma_dt, want, num, den, ROLL);
                     put(C, B, (uint32_t)it, false);
-                    store_lam(b, s0 + k, C, ROLL);
+                    br.store(b, s0 + k, C);
                 }
             }
             if (tid < np) {
@@ -2272,13 +2372,146 @@ __device__ void pgs_region(const DevBuffers& b, const StepParams& p, const Solve
                     w.w = angv_at(b.vw, sl).w;
                     vel_at(b.vw, sl) = v;
                     angv_at(b.vw, sl) = w;
-                } else if (li < lds_cap) {
+                } else if (li < nb) {
                     vel_at(b.vw, sl) = rb.sv[li];
                     angv_at(b.vw, sl) = rb.sw[li];
                 }
             }
         }
+    if (ncol > 0) br.end(b, tid, kThreads);
     if (T.rank == 0 && tid == 0) write_stats(b, T.unit, slot, sweeps, Rk, R1);
+}
+
+// A solve of one region, all of whose bodies are in LDS: no contact waits and
+// nothing is published, so that a phase is its chain alone, which one wave a
+// SIMD issues: the update's hundred operations, its bodies out of LDS and
+// back, a barrier.  Everything else is kept off it: the rows of the next phase
+// are fetched before the update, into the other of two sets of registers,
+// unconditionally (a thread without a contact reads the last one's).
+template <bool ROLL, int NW, RowHome HOME>
+__device__ void solve_alone(const DevBuffers& b, const StepParams& p, const SolveTask& T, uint32_t ncol, int sweeps_cap,
+                            int slot, float4* lds, int nb, const BlockRows<ROLL, HOME>& br, SolveShared<NW>& sh)
+{
+    constexpr uint32_t kThreads = NW * 64;
+    const uint32_t tid = threadIdx.x;
+    float4 *sv = lds, *sw = lds + nb;
+    const int sg0 = b.own_idx[T.owner], sg1 = b.own_idx[T.owner + 1];
+    if (ncol == 0 || sweeps_cap <= 0) {
+        if (tid == 0) write_stats(b, T.unit, slot, 0, 0.0, 0.0);
+        return;
+    }
+    for (int sg = sg0; sg < sg1; ++sg) {
+        const int4 S = b.own_seg[sg];
+        for (int i = (int)tid; i < S.y; i += (int)kThreads) {
+            sv[S.z + i] = vel_at(b.vw, S.x + i);
+            sw[S.z + i] = angv_at(b.vw, S.x + i);
+        }
+    }
+    br.begin(b, tid, kThreads);
+    __syncthreads();
+    const uint32_t last = br.base + br.n - 1;
+    uint32_t s0 = sh.st[0], s1 = sh.st[2], s2 = sh.st[ncol > 1 ? 4 : 2];  // starts of the phase, its end, the next's end
+    uint32_t next = ncol > 1 ? 1 : 0;                                      // the next phase
+    int sweep = 0;
+    float num = 0.f, den = 0.f;
+    bool want = true;
+    double Rk = 0.0, R1 = 0.0;
+    auto update = [&](uint32_t c, RowRegs& R, BodyRegs& B) {
+        const int ia = __float_as_int(R.q.z), ib = __float_as_int(R.q.w) & kNameMask;
+        pgs_update(b, c, R, B, p.mu, p.gamma_dt, want, num, den, ROLL);
+        sv[ib] = B.vb;
+        sw[ib] = B.wb;
+        if (ia >= 0) { sv[ia & kNameMask] = B.va; sw[ia & kNameMask] = B.wa; }
+        br.store(b, c, R);
+    };
+    auto bodies = [&](const RowRegs& R) {
+        const int ia = __float_as_int(R.q.z), ib = __float_as_int(R.q.w) & kNameMask;
+        const int ja = ia >= 0 ? ia & kNameMask : ib;
+        return BodyRegs{sv[ja], sw[ja], sv[ib], sw[ib]};
+    };
+    // one phase on the rows in cur, the next one's into nxt; false at the end of the solve
+    auto phase = [&](RowRegs& cur, RowRegs& nxt) {
+        const uint32_t c = s0 + tid, hi = s1;
+        settle(cur, ROLL);
+        BodyRegs B = bodies(cur);
+        if (ncol > 1) nxt = br.load(b, min((next > 0 ? s1 : br.base) + tid, last));
+        const uint32_t after = next + 1 < ncol ? next + 1 : 0;
+        const uint32_t s3 = sh.st[2 * after + 2];
+        if (c < hi) update(c, cur, B);
+        for (uint32_t k = c + kThreads; k < hi; k += kThreads) {
+            RowRegs R = br.load(b, k);
+            BodyRegs C = bodies(R);
+            update(k, R, C);
+        }
+        if (ncol == 1) nxt = br.load(b, min(br.base + tid, last));  // (its impulses are those just stored)
+        __syncthreads();
+        s0 = next > 0 ? s1 : br.base;
+        s1 = s2;
+        s2 = s3;
+        const bool end = next == 0;
+        next = after;
+        if (!end) return true;
+        ++sweep;
+        bool more = sweep < sweeps_cap;
+        if (want) {
+            double sn, sd;
+            block_sum2<NW>(num, den, sh.red, sn, sd);
+            Rk = sweep_resid(sn, sd);
+            if (sweep == 1) R1 = Rk;
+            if (p.tol > 0.f && Rk <= (double)p.tol) more = false;  // uniform: every thread holds the same Rk
+        }
+        num = den = 0.f;
+        // without a tolerance only the first and last residuals are reported
+        want = p.tol > 0.f || sweep + 1 == sweeps_cap;
+        return more;
+    };
+    RowRegs A = br.load(b, min(br.base + tid, last)), Z;
+    while (phase(A, Z) && phase(Z, A)) {}
+    for (int sg = sg0; sg < sg1; ++sg) {
+        const int4 S = b.own_seg[sg];
+        for (int i = (int)tid; i < S.y; i += (int)kThreads) {
+            vel_at(b.vw, S.x + i) = sv[S.z + i];
+            angv_at(b.vw, S.x + i) = sw[S.z + i];
+        }
+    }
+    br.end(b, tid, kThreads);
+    if (tid == 0) write_stats(b, T.unit, slot, sweep, Rk, R1);
+}
+
+// The region's solve with its rows where they fit: the bodies (at most
+// lds_cap) come first in the lds_f4 float4s of LDS, then the rows and impulses
+// of its contacts, or the impulses alone.  Whole or not at all: impulses of
+// the first contacts in LDS and the others in memory took a branch or a flat
+// access at every use, and were slower than all of them in memory (3.6 and
+// 3.5 ms for the column of 1,000 above).
+template <bool ROLL, int NW>
+__device__ void pgs_region(const DevBuffers& b, const StepParams& p, const SolveTask& T, uint32_t ncol, bool through,
+                           int sweeps_cap, int slot, float4* lds, int lds_cap, int lds_f4, SolveShared<NW>& sh)
+{
+    int nb = 0;
+    for (int sg = b.own_idx[T.owner]; sg < b.own_idx[T.owner + 1]; ++sg) {
+        const int4 S = b.own_seg[sg];
+        nb = max(nb, S.z + S.y);
+    }
+    const bool alone = T.K == 1 && nb <= lds_cap;
+    nb = min(nb, lds_cap);
+    stage_starts(b, T.owner, ncol, sh);
+    __syncthreads();
+    const uint32_t base = ncol > 0 ? sh.st[0] : 0u, n = ncol > 0 ? sh.st[2 * ncol] - base : 0u;
+    const uint32_t room = (uint32_t)max(0, lds_f4 - 2 * nb);
+    auto solve = [&](auto home) {
+        const BlockRows<ROLL, decltype(home)::value> br(lds + 2 * nb, base, n);
+        if (NW <= 8 && alone)
+            solve_alone<ROLL, NW>(b, p, T, ncol, sweeps_cap, slot, lds, nb, br, sh);
+        else
+            solve_region<ROLL, NW>(b, p, T, ncol, through, sweeps_cap, slot, lds, nb, br, sh);
+    };
+    if (NW <= 8 && BlockRows<ROLL, kRowsLds>::size(n) <= room)
+        solve(std::integral_constant<RowHome, kRowsLds>{});
+    else if (NW <= 8 && BlockRows<ROLL, kRowsImpulses>::size(n) <= room)
+        solve(std::integral_constant<RowHome, kRowsImpulses>{});
+    else
+        solve(std::integral_constant<RowHome, kRowsMemory>{});
 }
 
 // solve_begin and exchange_begin for a solve that no warm apply precedes
@@ -2292,7 +2525,7 @@ __global__ void k_pgs_reset(DevBuffers b, StepParams p, int n_envs, int n_flags)
 // Grouped and spread modes: block blockIdx takes the region of its task.
 template <bool ROLL, int NW>
 __global__ __launch_bounds__(64 * NW) void k_pgs(DevBuffers b, StepParams p, int sweeps_cap, int slot, int lds_cap,
-                                                 int flow)
+                                                 int lds_f4, int flow)
 {
     HIP_DYNAMIC_SHARED(float4, dyn_bodies)
     __shared__ SolveShared<NW> sh;
@@ -2312,7 +2545,7 @@ __global__ __launch_bounds__(64 * NW) void k_pgs(DevBuffers b, StepParams p, int
     if (flow)
         pgs_flow<ROLL, NW>(b, p, T, ncol, counter, through, sweeps_cap, slot, sh);
     else
-        pgs_region<ROLL, NW>(b, p, T, ncol, through, sweeps_cap, slot, dyn_bodies, lds_cap, sh);
+        pgs_region<ROLL, NW>(b, p, T, ncol, through, sweeps_cap, slot, dyn_bodies, lds_cap, lds_f4, sh);
 }
 
 // Per-env mode, a set of small envs solved at once by one block: env j of the
@@ -2451,7 +2684,8 @@ __global__ __launch_bounds__(kEnvBlk) void k_pgs_env(DevBuffers b, StepParams p,
         if (flow)
             pgs_flow<ROLL, kEnvBlk / 64>(b, p, T, ncol, counter, mode == 2, sweeps_cap, slot, sh);
         else
-            pgs_region<ROLL, kEnvBlk / 64>(b, p, T, ncol, mode == 2, sweeps_cap, slot, dyn_bodies, lds_cap, sh);
+            pgs_region<ROLL, kEnvBlk / 64>(b, p, T, ncol, mode == 2, sweeps_cap, slot, dyn_bodies, lds_cap, 2 * lds_cap,
+                                           sh);
         __syncthreads();
         ++t;
     }
@@ -2529,16 +2763,16 @@ void launch_pgs(const DevBuffers& b, const StepParams& p, const Sizes& z, hipStr
     if (flow && p.n_particles > 0) launch_fill_u32(b.ver, 0u, p.n_particles, s);
     const bool env = z.pgs_mode == kModePerEnv;
     const dim3 grid((unsigned)(env ? z.plan_blocks : z.pgs_grid)), blk(env ? kEnvBlk : 64 * kPgsWaves);
-    const size_t lds = (size_t)(env ? z.lds_cap : z.grp_lds) * 32;
+    const size_t lds = env ? (size_t)z.lds_cap * 32 : (size_t)z.grp_f4 * 16;
     if (grid.x == 0) return;
     if (env && p.mu_r > 0.f)
         hipLaunchKernelGGL(k_pgs_env<true>, grid, blk, lds, s, b, p, sw, slot, z.lds_cap, flow);
     else if (env)
         hipLaunchKernelGGL(k_pgs_env<false>, grid, blk, lds, s, b, p, sw, slot, z.lds_cap, flow);
     else if (p.mu_r > 0.f)
-        hipLaunchKernelGGL((k_pgs<true, kPgsWaves>), grid, blk, lds, s, b, p, sw, slot, z.grp_lds, flow);
+        hipLaunchKernelGGL((k_pgs<true, kPgsWaves>), grid, blk, lds, s, b, p, sw, slot, z.grp_lds, z.grp_f4, flow);
     else
-        hipLaunchKernelGGL((k_pgs<false, kPgsWaves>), grid, blk, lds, s, b, p, sw, slot, z.grp_lds, flow);
+        hipLaunchKernelGGL((k_pgs<false, kPgsWaves>), grid, blk, lds, s, b, p, sw, slot, z.grp_lds, z.grp_f4, flow);
 }
 
 // ---------------------------------------------------------------------------

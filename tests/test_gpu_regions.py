@@ -47,6 +47,20 @@ CASES = {
     "grouped_three_blocks_rolling": ([(74, 23, 14, 11)], dict(roll=True), dict(mode="grouped", blocks_per_xcd=3)),
     # eleven envs in eight groups: blocks with a region of two envs
     "grouped_many": ([(75 + e, 19 + e % 3, 13, 9) for e in range(11)], {}, dict(mode="grouped", blocks_per_xcd=32)),
+    # a whole solve in one block: one colour, its rows in LDS, its impulses in
+    # LDS, everything in memory, colours of more contacts than threads, more
+    # bodies than LDS holds
+    "alone_one_sphere": ([(80, 1, 1, 1)], {}, dict(mode="grouped")),
+    "alone_two_spheres": ([(81, 1, 1, 2)], {}, dict(mode="grouped")),
+    "alone_rows": ([(82, 7, 7, 6)], {}, dict(mode="grouped")),
+    "alone_rows_rolling": ([(83, 5, 7, 6)], dict(roll=True), dict(mode="grouped")),
+    "alone_impulses": ([(84, 11, 11, 9)], {}, dict(mode="grouped")),
+    "alone_memory_rolling": ([(85, 12, 11, 10)], dict(roll=True), dict(mode="grouped")),
+    "alone_most_contacts": ([(86, 14, 10, 10)], {}, dict(mode="grouped", blocks_per_xcd=1)),
+    "one_block_small_lds": ([(87, 23, 17, 14)], {}, dict(mode="grouped", blocks_per_xcd=1)),
+    # regions with their impulses in LDS, and with nothing but bodies
+    "grouped_three_blocks": ([(88, 23, 14, 11)], {}, dict(mode="grouped", blocks_per_xcd=3)),
+    "grouped_two_blocks": ([(89, 23, 14, 14)], {}, dict(mode="grouped", blocks_per_xcd=2)),
     # all eight XCDs
     "spread": ([(90, 41, 27, 25)], {}, dict(mode="spread", blocks_per_xcd=32)),
     "spread_rolling": ([(91, 41, 27, 25)], dict(roll=True), dict(mode="spread", blocks_per_xcd=5)),
