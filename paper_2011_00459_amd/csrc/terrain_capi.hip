@@ -26,14 +26,16 @@ constexpr int64_t kReadChunk = 16384;  // particles of a read-back chunk: 1.3 MB
 constexpr int kFlowMaxSweeps = 8192;  // longest counter-ordered solve
 
 // Regions of the grouped and spread solves (MI355X, beds under 100 sweeps of 9
-// or 10 colours).  One block alone up to 1,400 spheres: at 1,000 it takes 0.82
-// ms against 1.05 for a cluster, at 1,500 1.07 against 1.05, at 2,500 1.47
-// against 1.08.  Clusters in regions of 400 spheres: a phase is then bound by
-// the hand-over between blocks (6,000 spheres: 1.06 ms at 400, 1.47 at 1,000,
-// 1.66 at 1,600).  All XCDs from 27,000 spheres: across XCDs the hand-over is
-// slower, but one XCD's 32 blocks are full (20,000 spheres: 1.35 ms on one
-// XCD, 1.63 on all; 35,000: 1.93 and 1.58; 70,000: 2.63 and 1.70).
-constexpr int64_t kRegionAlone = 1400, kRegionSpheres = 400, kSpreadMin = 27000;
+// or 10 colours).  One block alone up to 1,700 spheres: at 1,700 it takes 0.97
+// ms against 1.08 for a cluster, at 2,000 1.10 against 1.07, at 2,500 1.39
+// against 1.11; with rolling rows up to 1,400 (1.34 and 1.35 ms; at 1,700 1.43
+// and 1.30).  Clusters in regions of 400 spheres: a phase is then bound by
+// the hand-over between blocks, and their rows fit LDS (35,000 spheres on all
+// XCDs: 1.35 ms at 300, 1.38 at 400, 1.41 at 500, 1.58 at 600).  All XCDs from 27,000 spheres: across XCDs the hand-over is
+// slower, but one XCD's 32 blocks are full (20,000 spheres: 1.27 ms on one
+// XCD, 1.63 on all; 35,000: 1.93 and 1.38; 70,000: 2.63 and 1.47).
+constexpr int64_t kRegionAlone = 1700, kRegionAloneRolling = 1400, kRegionSpheres = 400, kSpreadMin = 27000;
+constexpr int64_t kEnvSmallRegion = 800;  // largest region of the per-env plan of small regions
 
 struct EnvHost {
     int64_t n = 0;
@@ -190,6 +192,9 @@ void invalidate_graphs(tr_scene* s)
     s->graphs = false;
 }
 
+// spheres that one block solves sooner than a cluster of blocks
+int64_t region_alone(const tr_scene* s) { return s->desc.material.mu_r > 0.0 ? kRegionAloneRolling : kRegionAlone; }
+
 // The automatic per-env plan, from a cost model measured on MI355X (256 busy
 // blocks, 100 sweeps of 9 or 10 colours; units of microseconds): a block's
 // region of a multi-block cluster costs 900 plus 0.82 per sphere (1,000
@@ -202,9 +207,9 @@ void invalidate_graphs(tr_scene* s)
 // Ns and M are searched for the smallest predicted makespan (sets placed
 // largest first on the least loaded block).  tasks gets each block's cluster
 // share (env, rank, K, first block) and then its sets as (env, set number, 1,
-// 0); false when no candidate fits the blocks.
-bool plan_auto(const tr_scene* s, const std::vector<int>& order, int B, int lds_cap,
-               std::vector<std::vector<int4>>& best_tasks)
+// 0); returns the predicted makespan, 1e300 when no candidate fits the blocks.
+double plan_auto(const tr_scene* s, const std::vector<int>& order, int B, int lds_cap,
+                 std::vector<std::vector<int4>>& best_tasks)
 {
     constexpr double kAc = 900.0, kWc = 0.82, kWs = 0.72, kWset = 650.0, kWg = 4.0;
     const int G = kGroups, PL = B / G, waves = kEnvBlk / 64;
@@ -274,13 +279,78 @@ bool plan_auto(const tr_scene* s, const std::vector<int>& order, int B, int lds_
             }
         }
     }
-    return best < 1e300;
+    return best;
+}
+
+// The plan of small regions, for blocks of 512 threads that keep rows and
+// impulses in LDS: an env of at most kRegionAlone spheres is solved by one
+// block, 470 plus 0.28 per sphere (300 spheres 0.57 ms, 1,000 0.73 ms, where a
+// cluster took 1.1 ms), several of them one after another where envs outnumber
+// the blocks; any other is cut into regions of at most kEnvSmallRegion, 1,000
+// plus 0.35 per sphere (250 spheres 1.09 ms, 600 1.24 ms; from about 1,000 on
+// the rows come from memory, and 1,200 take 2.0 ms).  Same search, result and
+// units as plan_auto; the entries of envs solved alone are (env, 0, 1, block).
+double plan_small(const tr_scene* s, const std::vector<int>& order, int B, int lds_cap,
+                  std::vector<std::vector<int4>>& best_tasks)
+{
+    constexpr double kAa = 470.0, kWa = 0.28, kAr = 1000.0, kWr = 0.35;
+    const int G = kGroups, PL = B / G;
+    const double n_alone = (double)std::min<int64_t>(region_alone(s), lds_cap);
+    double best = 1e300, work0 = 0.0;
+    for (int e : order) work0 += kAa + kWa * (double)s->envs[e].n;
+    const double lo = std::max(0.5 * work0 / B, kAa);
+    for (int m = 0; m <= 64; ++m) {
+        const double M = lo * std::pow(1.03, m);
+        if (M >= best) break;  // no block finishes its largest job before M
+        std::vector<double> load(B, 0.0);
+        std::vector<int> lane_next(G, 0), single;
+        std::vector<std::vector<int4>> tasks(B);
+        bool ok = true;
+        for (int e : order) {
+            const double n = (double)s->envs[e].n;
+            if (n <= n_alone) {
+                single.push_back(e);
+                continue;
+            }
+            int K = std::max(2, (int)std::ceil(n / (double)std::min<int64_t>(kEnvSmallRegion, lds_cap)));
+            if (M > kAr) K = std::max(K, (int)std::ceil(kWr * n / (M - kAr)));
+            int lane = 0;
+            for (int x = 1; x < G; ++x)
+                if (lane_next[x] < lane_next[lane]) lane = x;
+            if (M <= kAr || K > PL - lane_next[lane]) {
+                ok = false;
+                break;
+            }
+            const int first = lane + G * lane_next[lane];
+            for (int r = 0; r < K; ++r) {
+                tasks[first + G * r].push_back(make_int4(e, r, K, first));
+                load[first + G * r] += kAr + kWr * n / K;
+            }
+            lane_next[lane] += K;
+        }
+        if (!ok) continue;
+        std::priority_queue<std::pair<double, int>, std::vector<std::pair<double, int>>, std::greater<>> least;
+        for (int i = 0; i < B; ++i) least.push({load[i], i});
+        for (int e : single) {  // (largest first)
+            const int blk = least.top().second;
+            least.pop();
+            load[blk] += kAa + kWa * (double)s->envs[e].n;
+            least.push({load[blk], blk});
+            tasks[blk].push_back(make_int4(e, 0, 1, blk));
+        }
+        const double mk = *std::max_element(load.begin(), load.end());
+        if (mk < best) {
+            best = mk;
+            best_tasks = std::move(tasks);
+        }
+    }
+    return best;
 }
 
 // Blocks per XCD of a grouped or spread solve of n spheres.
-int region_blocks(int64_t n, bool wide, int bpx)
+int region_blocks(const tr_scene* s, int64_t n, bool wide, int bpx)
 {
-    if (!wide && n <= kRegionAlone) return 1;
+    if (!wide && n <= region_alone(s)) return 1;
     const int64_t per = wide ? (n + kGroups - 1) / kGroups : n;
     return (int)std::max<int64_t>(1, std::min<int64_t>(bpx, (per + kRegionSpheres - 1) / kRegionSpheres));
 }
@@ -318,6 +388,10 @@ int rebuild_plan(tr_scene* s)
     std::vector<uint32_t> plan_idx;
     int lds_cap = 0;
     int blocks = 0;
+    bool env_small = false;  // the plan of small regions
+    // the counter-ordered solve keeps one slot of block partials per sweep;
+    // longer solves take the ordinary one (same results)
+    const bool flow = s->cfg.dataflow != 0 && s->desc.max_sweeps <= kFlowMaxSweeps;
     if (s->cfg.mode == TR_PGS_PER_ENV) {
         lds_cap = std::max(0, std::min(s->cfg.lds_particles, s->max_lds_particles));
         // every block is resident (clusters wait for each other); a whole number per XCD
@@ -357,7 +431,15 @@ int rebuild_plan(tr_scene* s)
                 wb += w[i];
             }
         };
-        if (s->cfg.cluster_particles == 0 && lds_cap > 0 && plan_auto(s, order, B, lds_cap, tasks)) {
+        const bool automatic = s->cfg.cluster_particles == 0 && lds_cap > 0;
+        const double best = automatic ? plan_auto(s, order, B, lds_cap, tasks) : 1e300;
+        std::vector<std::vector<int4>> small_tasks;
+        // (plan_auto's model, fitted to regions of 1,000 spheres and more, is
+        // 10 percent low for the smallest clusters: 250 spheres take 1.2 ms)
+        env_small = automatic && !flow && plan_small(s, order, B, lds_cap, small_tasks) < 1.1 * best;
+        if (env_small) {
+            tasks = std::move(small_tasks);
+        } else if (best < 1e300) {
             for (int blk = 0; blk < B; ++blk) {
                 // plan_auto lists each block's sets as (env, set number) pairs after its cluster share
                 std::vector<int4> mine;
@@ -444,9 +526,6 @@ int rebuild_plan(tr_scene* s)
     int grp_lds = 0;
     std::vector<int> own_x;
     int64_t x_next = 0;
-    // the counter-ordered solve keeps one slot of block partials per sweep;
-    // longer solves take the ordinary one (same results)
-    const bool flow = s->cfg.dataflow != 0 && s->desc.max_sweeps <= kFlowMaxSweeps;
     auto set_env = [&](int e, int own_base, int K, int lds_off, int res_cap, bool coded) {
         EnvDev& D = s->env_host[e];
         D.own_base = own_base;
@@ -470,8 +549,10 @@ int rebuild_plan(tr_scene* s)
         std::vector<int> K(E, 1);
         for (const int4& t : plan)
             if (t.z >= 2) K[t.x] = t.z;
+        s->z.env_small = env_small ? 1 : 0;
         for (int e = 0; e < E; ++e) {
-            set_env(e, (int)own_idx.size(), K[e], 0, K[e] > 1 ? lds_cap : INT32_MAX, K[e] > 1);
+            const bool region = K[e] > 1 || env_small;
+            set_env(e, (int)own_idx.size(), K[e], 0, region ? lds_cap : INT32_MAX, region);
             set_exchange(e, s->env_host[e].chunk);
             for (int r = 0; r < K[e]; ++r) {
                 own_idx.push_back((int)own_seg.size());
@@ -489,7 +570,7 @@ int rebuild_plan(tr_scene* s)
                 if (s->env_host[e].group == g) n += s->env_host[e].n;
             if (n == 0) continue;
             const bool wide = E == 1 && !flow && n > kSpreadMin;
-            const int per = region_blocks(n, wide, bpx), K = wide ? kGroups * per : per;
+            const int per = region_blocks(s, n, wide, bpx), K = wide ? kGroups * per : per;
             const int base = (int)own_idx.size();
             int off = 0;
             for (int e = 0; e < E; ++e) {

@@ -2205,7 +2205,7 @@ __device__ inline BodyRegs await_bodies(const DevBuffers& b, const RegionBodies&
 // The solve of one region (file comment above).  lds holds the bodies of the
 // region's first nb spheres (v, then omega).
 template <bool ROLL, int NW, RowHome HOME>
-__device__ void solve_region(const DevBuffers& b, const StepParams& p, const SolveTask& T, uint32_t ncol, bool through,
+__device__ __forceinline__ void solve_region(const DevBuffers& b, const StepParams& p, const SolveTask& T, uint32_t ncol, bool through,
                              int sweeps_cap, int slot, float4* lds, int nb, const BlockRows<ROLL, HOME>& br,
                              SolveShared<NW>& sh)
 {
@@ -2389,7 +2389,7 @@ __device__ void solve_region(const DevBuffers& b, const StepParams& p, const Sol
 // are fetched before the update, into the other of two sets of registers,
 // unconditionally (a thread without a contact reads the last one's).
 template <bool ROLL, int NW, RowHome HOME>
-__device__ void solve_alone(const DevBuffers& b, const StepParams& p, const SolveTask& T, uint32_t ncol, int sweeps_cap,
+__device__ __forceinline__ void solve_alone(const DevBuffers& b, const StepParams& p, const SolveTask& T, uint32_t ncol, int sweeps_cap,
                             int slot, float4* lds, int nb, const BlockRows<ROLL, HOME>& br, SolveShared<NW>& sh)
 {
     constexpr uint32_t kThreads = NW * 64;
@@ -2485,7 +2485,7 @@ __device__ void solve_alone(const DevBuffers& b, const StepParams& p, const Solv
 // access at every use, and were slower than all of them in memory (3.6 and
 // 3.5 ms for the column of 1,000 above).
 template <bool ROLL, int NW>
-__device__ void pgs_region(const DevBuffers& b, const StepParams& p, const SolveTask& T, uint32_t ncol, bool through,
+__device__ __forceinline__ void pgs_region(const DevBuffers& b, const StepParams& p, const SolveTask& T, uint32_t ncol, bool through,
                            int sweeps_cap, int slot, float4* lds, int lds_cap, int lds_f4, SolveShared<NW>& sh)
 {
     int nb = 0;
@@ -2653,21 +2653,22 @@ __device__ void pgs_local_set(const DevBuffers& b, const StepParams& p, const in
 // most one share (env, rank, cluster size K >= 2, first block) of a
 // multi-block cluster, first, then sets of small envs solved at once (entries
 // (env, waves wb | we << 8, 1, LDS offset); a set starts at wb == 0).
-template <bool ROLL>
-__global__ __launch_bounds__(kEnvBlk) void k_pgs_env(DevBuffers b, StepParams p, int sweeps_cap, int slot, int lds_cap,
-                                                      int flow)
+template <bool ROLL, int NW>
+__global__ __launch_bounds__(64 * NW) void k_pgs_env(DevBuffers b, StepParams p, int sweeps_cap, int slot, int lds_cap,
+                                                     int flow)
 {
     HIP_DYNAMIC_SHARED(float4, dyn_bodies)
-    __shared__ SolveShared<kEnvBlk / 64> sh;
+    __shared__ SolveShared<NW> sh;
     if (b.cnt->overflow) return;  // uniform: written by earlier kernels only
     const uint32_t t0 = b.plan_idx[blockIdx.x], t1 = b.plan_idx[blockIdx.x + 1];
     uint32_t t = t0;
     while (t < t1) {
         const int4 pl = b.plan[t];
-        if (pl.z < 2) {
+        if (64 * NW == kEnvBlk && pl.z < 2) {
             uint32_t u = t + 1;
             while (u < t1 && b.plan[u].z < 2 && (b.plan[u].y & 255) != 0) ++u;
-            pgs_local_set<ROLL>(b, p, b.plan + t, (int)(u - t), sweeps_cap, slot, dyn_bodies, lds_cap, sh.red);
+            if constexpr (64 * NW == kEnvBlk)
+                pgs_local_set<ROLL>(b, p, b.plan + t, (int)(u - t), sweeps_cap, slot, dyn_bodies, lds_cap, sh.red);
             __syncthreads();  // LDS and the reduction scratch are reused
             t = u;
             continue;
@@ -2679,13 +2680,12 @@ __global__ __launch_bounds__(kEnvBlk) void k_pgs_env(DevBuffers b, StepParams p,
                           (first % kGroups) * (gridDim.x / kGroups) + first / kGroups, e};
         const uint32_t ncol = slot == kSlotImpact && !b.ustats[e].imp_any ? 0u : b.env_ncol[e];
         uint32_t* counter = b.env_bar + (size_t)e * 16;
-        const int mode = cluster_placement(b.cnt, counter, T.K, sh.flag);
+        const int mode = T.K > 1 ? cluster_placement(b.cnt, counter, T.K, sh.flag) : 1;
         if (mode == 0) return;  // failed barrier: the step is abandoned
         if (flow)
-            pgs_flow<ROLL, kEnvBlk / 64>(b, p, T, ncol, counter, mode == 2, sweeps_cap, slot, sh);
+            pgs_flow<ROLL, NW>(b, p, T, ncol, counter, mode == 2, sweeps_cap, slot, sh);
         else
-            pgs_region<ROLL, kEnvBlk / 64>(b, p, T, ncol, mode == 2, sweeps_cap, slot, dyn_bodies, lds_cap, 2 * lds_cap,
-                                           sh);
+            pgs_region<ROLL, NW>(b, p, T, ncol, mode == 2, sweeps_cap, slot, dyn_bodies, lds_cap, 2 * lds_cap, sh);
         __syncthreads();
         ++t;
     }
@@ -2705,7 +2705,12 @@ static int max_dynamic_lds(const void* k0, const void* k1)
     return std::max(0, lds - (int)((st + 255) / 256 * 256));
 }
 
-int pgs_env_max_lds() { return max_dynamic_lds((const void*)k_pgs_env<false>, (const void*)k_pgs_env<true>); }
+constexpr int kEnvWaves = kEnvBlk / 64;
+
+int pgs_env_max_lds()
+{
+    return max_dynamic_lds((const void*)k_pgs_env<false, kEnvWaves>, (const void*)k_pgs_env<true, kEnvWaves>);
+}
 
 int pgs_group_max_lds() { return max_dynamic_lds((const void*)k_pgs<false, kPgsWaves>, (const void*)k_pgs<true, kPgsWaves>); }
 
@@ -2728,7 +2733,10 @@ static int resident_blocks(const void* k0, const void* k1, int block, int lds_by
 
 int pgs_env_resident_blocks(int lds_bytes)
 {
-    return resident_blocks((const void*)k_pgs_env<false>, (const void*)k_pgs_env<true>, kEnvBlk, lds_bytes);
+    const int all = resident_blocks((const void*)k_pgs_env<false, kEnvWaves>, (const void*)k_pgs_env<true, kEnvWaves>,
+                                    kEnvBlk, lds_bytes);
+    return std::min(all, resident_blocks((const void*)k_pgs_env<false, kPgsWaves>, (const void*)k_pgs_env<true, kPgsWaves>,
+                                         64 * kPgsWaves, lds_bytes));
 }
 
 int pgs_resident_blocks()
@@ -2762,14 +2770,15 @@ void launch_pgs(const DevBuffers& b, const StepParams& p, const Sizes& z, hipStr
     const int flow = z.flow;
     if (flow && p.n_particles > 0) launch_fill_u32(b.ver, 0u, p.n_particles, s);
     const bool env = z.pgs_mode == kModePerEnv;
-    const dim3 grid((unsigned)(env ? z.plan_blocks : z.pgs_grid)), blk(env ? kEnvBlk : 64 * kPgsWaves);
+    const dim3 grid((unsigned)(env ? z.plan_blocks : z.pgs_grid)), blk(env && !z.env_small ? kEnvBlk : 64 * kPgsWaves);
     const size_t lds = env ? (size_t)z.lds_cap * 32 : (size_t)z.grp_f4 * 16;
     if (grid.x == 0) return;
-    if (env && p.mu_r > 0.f)
-        hipLaunchKernelGGL(k_pgs_env<true>, grid, blk, lds, s, b, p, sw, slot, z.lds_cap, flow);
-    else if (env)
-        hipLaunchKernelGGL(k_pgs_env<false>, grid, blk, lds, s, b, p, sw, slot, z.lds_cap, flow);
-    else if (p.mu_r > 0.f)
+    if (env) {
+        void (*k)(DevBuffers, StepParams, int, int, int, int) =
+            z.env_small ? (p.mu_r > 0.f ? k_pgs_env<true, kPgsWaves> : k_pgs_env<false, kPgsWaves>)
+                        : (p.mu_r > 0.f ? k_pgs_env<true, kEnvWaves> : k_pgs_env<false, kEnvWaves>);
+        hipLaunchKernelGGL(k, grid, blk, lds, s, b, p, sw, slot, z.lds_cap, flow);
+    } else if (p.mu_r > 0.f)
         hipLaunchKernelGGL((k_pgs<true, kPgsWaves>), grid, blk, lds, s, b, p, sw, slot, z.grp_lds, z.grp_f4, flow);
     else
         hipLaunchKernelGGL((k_pgs<false, kPgsWaves>), grid, blk, lds, s, b, p, sw, slot, z.grp_lds, z.grp_f4, flow);

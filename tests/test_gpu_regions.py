@@ -61,6 +61,15 @@ CASES = {
     # regions with their impulses in LDS, and with nothing but bodies
     "grouped_three_blocks": ([(88, 23, 14, 11)], {}, dict(mode="grouped", blocks_per_xcd=3)),
     "grouped_two_blocks": ([(89, 23, 14, 14)], {}, dict(mode="grouped", blocks_per_xcd=2)),
+    # the automatic plan of small regions: envs alone in a block, two of them
+    # on either side of what is solved alone, one after another in a block when
+    # they outnumber the blocks, beside clusters
+    "small_plan": ([(100, 1, 1, 1), (101, 2, 2, 2), (102, 7, 7, 6), (103, 11, 11, 9), (104, 13, 13, 10),
+                    (105, 13, 13, 11), (106, 23, 14, 11)], {}, dict(mode="per_env", cluster_particles=0)),
+    "small_plan_rolling": ([(107, 7, 7, 6), (108, 14, 10, 10), (109, 13, 12, 10), (110, 23, 14, 11)], dict(roll=True),
+                           dict(mode="per_env", cluster_particles=0)),
+    "small_plan_queued": ([(120 + e % 7, 2 + e % 3, 3, 2) for e in range(300)], {},
+                          dict(mode="per_env", cluster_particles=0)),
     # all eight XCDs
     "spread": ([(90, 41, 27, 25)], {}, dict(mode="spread", blocks_per_xcd=32)),
     "spread_rolling": ([(91, 41, 27, 25)], dict(roll=True), dict(mode="spread", blocks_per_xcd=5)),
