@@ -90,6 +90,7 @@ struct tr_scene {
     hipEvent_t read_ev[2] = {nullptr, nullptr};
     char* report = nullptr;           // host, written by the device after the steps of a call
     size_t report_bytes = 0;
+    bool report_own = false;          // not a part of read_buf's memory
     bool report_fresh = false;        // it holds the body forces of the last step
     int64_t cols_alloc = 0;
     bool mlp_loaded = false;
@@ -371,6 +372,13 @@ StepReport step_report(const tr_scene* s, char* base, bool stats)
         base += size[k];
     }
     return r;
+}
+
+size_t report_size(const tr_scene* s)
+{
+    size_t n = 0;
+    for (int64_t w : step_report(s, nullptr, true).words) n += sizeof(uint32_t) * w;
+    return n;
 }
 
 // PGS schedule: the solve unit of every env and, in per-env mode, the plan of
@@ -888,19 +896,18 @@ int rebuild_tables(tr_scene* s)
     s->p.n_bodies = (int)bd.size();
     s->p.n_shapes = (int)sd.size();
     s->p.n_zones = n_zones;
-    s->tables_dirty = false;
     s->report_fresh = false;
-    const StepReport r = step_report(s, nullptr, true);
-    size_t need = 0;
-    for (int64_t w : r.words) need += sizeof(uint32_t) * w;
+    const size_t need = report_size(s);
     if (need > s->report_bytes) {
-        if (s->report) (void)hipHostFree(s->report);
-        s->report = nullptr;
-        s->report_bytes = 0;
-        if (hipHostMalloc((void**)&s->report, need, hipHostMallocDefault) != hipSuccess)
+        char* larger = nullptr;
+        if (hipHostMalloc((void**)&larger, need, hipHostMallocDefault) != hipSuccess)
             return fail(s, TR_E_NOMEM, "step report");
+        if (s->report_own) (void)hipHostFree(s->report);
+        s->report = larger;
         s->report_bytes = need;
+        s->report_own = true;
     }
+    s->tables_dirty = false;
     return rebuild_plan(s);
 }
 
@@ -1043,8 +1050,13 @@ int create_scene(const tr_scene_desc* d, tr_scene** out)
     for (int k = 0; k < 5 && e == hipSuccess; ++k) e = hipEventCreate(&s->ev[k]);
     s->events = e == hipSuccess;
     const int64_t chunk = 10 * std::min(d->cap_particles, kReadChunk);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&s->read_buf[0], sizeof(double) * 2 * chunk, hipHostMallocDefault);
+    s->p.n_bodies = 2 * d->n_envs;  // (a report of more bodies gets memory of its own)
+    s->report_bytes = report_size(s);
+    s->p.n_bodies = 0;
+    if (e == hipSuccess)
+        e = hipHostMalloc((void**)&s->read_buf[0], sizeof(double) * 2 * chunk + s->report_bytes, hipHostMallocDefault);
     s->read_buf[1] = s->read_buf[0] + chunk;
+    s->report = (char*)(s->read_buf[1] + chunk);
     for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreateWithFlags(&s->read_ev[k], hipEventDisableTiming);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) {
@@ -1068,7 +1080,7 @@ int destroy_scene(tr_scene* s)
     if (s->read_buf[0]) (void)hipHostFree(s->read_buf[0]);
     for (int k = 0; k < 2; ++k)
         if (s->read_ev[k]) (void)hipEventDestroy(s->read_ev[k]);
-    if (s->report) (void)hipHostFree(s->report);
+    if (s->report_own) (void)hipHostFree(s->report);
     delete s;
     return TR_OK;
 }
