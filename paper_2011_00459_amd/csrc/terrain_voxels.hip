@@ -8,7 +8,7 @@
 //                     runs of planes
 //   convert cut       solid above the predicted zone's bottom becomes fluid
 //   convert deposit   particle-free fluid outside the zones becomes solid at
-//                     the column's surface (tiles of 16 columns on LDS)
+//                     the column's surface (tiles of 64 columns on LDS)
 //   surface           Eq. surface per column, into the terrain heightfield
 //   grow              particles grow from their voxel's fluid (Eq. eqmotmb)
 //   form              new particles from the fluid inside the zones
@@ -462,54 +462,75 @@ __device__ inline bool in_wedge_set(const WedgeSet& ws, double x, double y, doub
     return false;
 }
 
-__global__ void k_convert_cut(tr_voxel_grid g, double rho_b, WedgeSet ws, double* phi, const double* wc, double* mf,
-                              double* total)
+// A block takes kCutCols neighbouring columns, its kCutParts parts every so
+// manieth wedge of a column (a wedge is a chain of up to five divisions) and
+// then every so manieth run of voxels above the cut.  256 x 256 x 128 voxels
+// under eight wedges: 21 us (one thread a column: 28).
+constexpr int kCutCols = 32, kCutParts = kBlk / kCutCols;
+
+__global__ __launch_bounds__(kBlk) void k_convert_cut(tr_voxel_grid g, double rho_b, WedgeSet ws, double* phi,
+                                                      const double* wc, double* mf, double* total)
 {
 #pragma clang fp contract(off)
+    __shared__ double bottom[kCutParts][kCutCols], sums[kBlk / 64];
     const int64_t nxy = (int64_t)g.nx * g.ny;
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= nxy) return;
+    const int col = threadIdx.x % kCutCols, part = threadIdx.x / kCutCols;
+    const int64_t c = (int64_t)blockIdx.x * kCutCols + col;
     const int i = (int)(c % g.nx), j = (int)(c / g.nx);
     const double x = g.origin[0] + (i + 0.5) * g.l0, y = g.origin[1] + (j + 0.5) * g.l0;
     double zcut = INFINITY, lo;
-    for (int r = 0; r < ws.n_ranges; ++r)
-        for (int k = 0; k < ws.cnt[r]; ++k)
+    int at = 0;  // number of the wedge over all ranges
+    for (int r = 0; r < ws.n_ranges; ++r) {
+        for (int k = (part + kCutParts - at % kCutParts) % kCutParts; k < ws.cnt[r]; k += kCutParts)
             if (wedge_bottom(ws.base[ws.off[r] + k], x, y, lo)) zcut = fmin(zcut, lo);
-    if (zcut == INFINITY) return;
-    const double V0 = g.l0 * g.l0 * g.l0;
+        at += ws.cnt[r];
+    }
+    bottom[part][col] = zcut;
+    __syncthreads();
+    for (int q = 0; q < kCutParts; ++q) zcut = fmin(zcut, bottom[q][col]);
     double sum = 0.0;
-    // voxels a whole voxel or more below the cut keep their solid (occupancy
-    // is at most 1): start one voxel below the cut's, then read kChunk voxels
-    // at a time with every load in flight
-    const double kc = floor((zcut - g.origin[2]) / g.l0) - 1.0;
-    const int k_start = kc <= 0.0 ? 0 : (kc >= (double)g.nz ? g.nz : (int)kc);
-    constexpr int kChunk = 8;
-    for (int k0 = k_start; k0 < g.nz; k0 += kChunk) {
-        double fc[kChunk], wcc[kChunk], mc[kChunk];
+    if (c < nxy && zcut != INFINITY) {
+        const double V0 = g.l0 * g.l0 * g.l0;
+        // voxels a whole voxel or more below the cut keep their solid (occupancy
+        // is at most 1): start one voxel below the cut's, then read kChunk voxels
+        // at a time with every load in flight
+        const double kc = floor((zcut - g.origin[2]) / g.l0) - 1.0;
+        const int k_start = kc <= 0.0 ? 0 : (kc >= (double)g.nz ? g.nz : (int)kc);
+        constexpr int kChunk = 4;
+        for (int k0 = k_start + part * kChunk; k0 < g.nz; k0 += kCutParts * kChunk) {
+            double fc[kChunk], wcc[kChunk], mc[kChunk];
 #pragma unroll
-        for (int q = 0; q < kChunk; ++q) {
-            const bool in = k0 + q < g.nz;
-            const int64_t id = (int64_t)(k0 + q) * nxy + c;
-            fc[q] = in ? phi[id] : 0.0;
-            wcc[q] = in ? wc[id] : 0.0;
-            mc[q] = in ? mf[id] : 0.0;
-        }
+            for (int q = 0; q < kChunk; ++q) {
+                const bool in = k0 + q < g.nz;
+                const int64_t id = (int64_t)(k0 + q) * nxy + c;
+                fc[q] = in ? phi[id] : 0.0;
+                wcc[q] = in ? wc[id] : 0.0;
+                mc[q] = in ? mf[id] : 0.0;
+            }
 #pragma unroll
-        for (int q = 0; q < kChunk; ++q) {
-            const int k = k0 + q;
-            if (k >= g.nz) break;
-            double t = (zcut - (g.origin[2] + k * g.l0)) / g.l0;  // occupancy below the cut
-            t = t < 0.0 ? 0.0 : (t > 1.0 ? 1.0 : t);
-            if (fc[q] > t) {
-                const int64_t id = (int64_t)k * nxy + c;
-                const double dm = wcc[q] * rho_b * V0 * (fc[q] - t);
-                mf[id] = mc[q] + dm;
-                sum += dm;
-                phi[id] = t;
+            for (int q = 0; q < kChunk; ++q) {
+                const int k = k0 + q;
+                if (k >= g.nz) break;
+                double t = (zcut - (g.origin[2] + k * g.l0)) / g.l0;  // occupancy below the cut
+                t = t < 0.0 ? 0.0 : (t > 1.0 ? 1.0 : t);
+                if (fc[q] > t) {
+                    const int64_t id = (int64_t)k * nxy + c;
+                    const double dm = wcc[q] * rho_b * V0 * (fc[q] - t);
+                    mf[id] = mc[q] + dm;
+                    sum += dm;
+                    phi[id] = t;
+                }
             }
         }
     }
-    if (total && sum > 0.0) atomicAdd(total, sum);
+    if (!total) return;
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kBlk / 64; ++w) sum += sums[w];
+        if (sum > 0.0) atomicAdd(total, sum);
+    }
 }
 
 __global__ void k_convert_deposit(tr_voxel_grid g, double rho_b, double w_dep, WedgeSet ws, const double* rho_p,
@@ -585,161 +606,234 @@ __global__ void k_convert_deposit(tr_voxel_grid g, double rho_b, double w_dep, W
     if (total && sum > 0.0) atomicAdd(total, sum);
 }
 
-// The deposit on tiles of kTileCols neighbouring columns of at most kTileNz
-// voxels.  Columns are strided by nx ny in memory, so a column read by one
-// wave touches a cache line per voxel; the tile is read instead as whole
-// lines (each wave instruction: 16 columns at 4 heights), with all of a
-// thread's loads in flight at once.  The voxels whose fluid falls are marked
-// in parallel (bit masks per column), as is each column's first non-full
-// voxel; one thread per column then replays the fills over its marked voxels
-// in increasing height, as the per-thread kernel does.  Fills start at the
-// first non-full voxel and rarely climb far: occupancy and compaction of the
-// kWin voxels from there are held in LDS (a fill beyond them reads and writes
-// memory directly), which keeps the block's LDS small enough for six blocks
-// per CU.  The block writes back what changed.
-constexpr int kTileCols = 16;
-constexpr int kTileNz = 128;
-constexpr int kTileRows = kBlk / kTileCols;  // heights per pass
-constexpr int kTileWords = kTileNz / 64;
-constexpr int kWin = 32;
+// The deposit on tiles of 64 neighbouring columns of at most kTileNz voxels: a
+// wave reads a plane of the tile as whole lines, a block's eight waves take
+// every eighth plane.  The voxels whose fluid falls are marked in parallel
+// (bit masks per column), as is each column's first non-full voxel; one lane
+// per column then replays the fills over its marked voxels in increasing
+// height, as the per-thread kernel does.  Fills start at the first non-full
+// voxel and rarely climb far: occupancy and compaction of the kWin voxels from
+// there are held in LDS (a fill beyond them reads and writes memory directly),
+// the voxel being filled in registers, and the next marked voxel's mass is on
+// its way meanwhile.  The block writes back what changed.
+//
+// Bound by the replay's chain, two divisions and a few LDS accesses a fill
+// (about 0.4 us), of the column with most fills; 64 columns share its latency,
+// and 256 x 256 columns are 1,024 blocks, four a CU, all at once.
+// 256 x 256 x 128 voxels under eight wedges: 98 us (16 columns a block with
+// every mass in LDS and wedge by wedge for every voxel: 156; 16 planes a wave,
+// for which the registers leave three blocks a CU: 120); 200 x 200 x 150, which
+// took a thread a column, 1,100 -> 90.
+constexpr int kTileCols = 64;
+constexpr int kTileNz = 1024;
+constexpr int kTileRows = 8;  // waves of a block
+constexpr int kTilePer = 8;   // planes a wave reads at once
+constexpr int kWin = 28;
+constexpr int kMass = 16;     // planes of masses in LDS at once
 
-__global__ void __launch_bounds__(kBlk) k_convert_deposit_tile(tr_voxel_grid g, double rho_b, double w_dep,
-                                                               WedgeSet ws, const double* rho_p, double* phi,
-                                                               double* wc, double* mf, double* total)
+__global__ void __launch_bounds__(kTileCols* kTileRows, 8) k_convert_deposit_tile(tr_voxel_grid g, double rho_b,
+                                                                               double w_dep, WedgeSet ws,
+                                                                               const double* rho_p, double* phi,
+                                                                               double* wc, double* mf, double* total)
 {
 #pragma clang fp contract(off)
-    // (+1: a column's entries start two banks after the previous column's)
-    __shared__ double M[kTileCols][kTileNz + 1], P[kTileCols][kWin + 1], W[kTileCols][kWin + 1];
-    __shared__ unsigned long long mask[kTileCols][kTileWords];
+    __shared__ double P[kWin][kTileCols], W[kWin][kTileCols], M[kMass][kTileCols];
     __shared__ int first_free[kTileCols], range[kTileCols][2];
-    __shared__ double ssum[kTileCols];
+    __shared__ unsigned long long any;  // kMass planes a bit: some column has a marked voxel
+    HIP_DYNAMIC_SHARED(unsigned long long, mask)  // [words][kTileCols]
     const int64_t nxy = (int64_t)g.nx * g.ny;
     const int col = threadIdx.x % kTileCols, row = threadIdx.x / kTileCols;
     const int64_t c = (int64_t)blockIdx.x * kTileCols + col;
     const bool live = c < nxy;
-    const int nz = g.nz;
+    const int nz = g.nz, words = (nz + 63) / 64;
     const double x = g.origin[0] + ((int)(c % g.nx) + 0.5) * g.l0, y = g.origin[1] + ((int)(c / g.nx) + 0.5) * g.l0;
-    if (threadIdx.x < kTileCols) {
-        for (int w = 0; w < kTileWords; ++w) mask[threadIdx.x][w] = 0ull;
-        first_free[threadIdx.x] = nz;
-    }
+    for (int w = row; w < words; w += kTileRows) mask[w * kTileCols + col] = 0ull;
+    if (row == 0) first_free[col] = nz;
+    if (threadIdx.x == 0) any = 0ull;
     __syncthreads();
-    // a thread's heights row, row + kTileRows, ...: all its loads in flight at once
-    constexpr int kPer = kTileNz / kTileRows;
-    double mv[kPer], rv[kPer];
+    unsigned long long mine = 0ull;
+    for (int k0 = row; k0 < nz; k0 += kTileRows * kTilePer) {
+        double mv[kTilePer], rv[kTilePer];
 #pragma unroll
-    for (int t = 0; t < kPer; ++t) {
-        const int k = row + t * kTileRows;
-        mv[t] = live && k < nz ? mf[(int64_t)k * nxy + c] : 0.0;
-    }
+        for (int t = 0; t < kTilePer; ++t) {
+            const int k = k0 + t * kTileRows;
+            mv[t] = live && k < nz ? mf[(int64_t)k * nxy + c] : 0.0;
+        }
 #pragma unroll
-    for (int t = 0; t < kPer; ++t) {
-        const int k = row + t * kTileRows;
-        rv[t] = mv[t] > 0.0 ? rho_p[(int64_t)k * nxy + c] : 1.0;
-    }
+        for (int t = 0; t < kTilePer; ++t) {
+            const int k = k0 + t * kTileRows;
+            rv[t] = mv[t] > 0.0 ? rho_p[(int64_t)k * nxy + c] : 1.0;
+        }
+        unsigned fall = 0u;  // bit t: plane k0 + 8 t is marked
 #pragma unroll
-    for (int t = 0; t < kPer; ++t) {
-        const int k = row + t * kTileRows;
-        if (k >= nz) continue;
-        M[col][k] = mv[t];
-        if (mv[t] > 0.0 && rv[t] == 0.0 && !in_wedge_set(ws, x, y, g.origin[2] + (k + 0.5) * g.l0))
-            atomicOr(&mask[col][k >> 6], 1ull << (k & 63));
+        for (int t = 0; t < kTilePer; ++t) fall |= (unsigned)(mv[t] > 0.0 && rv[t] == 0.0) << t;
+        // (in_wedge_set's test with a wedge's planes in the outer loop: each
+        // is read once for all of a thread's voxels, and the next wedge's
+        // first one on the way meanwhile)
+        for (int r = 0; r < ws.n_ranges; ++r) {
+            const WedgeDev* w = ws.base + ws.off[r];
+            int n = 0;
+            double first[4];
+            auto begin = [&](int j) {
+                n = w[j].n;
+                for (int q = 0; q < 4; ++q) first[q] = w[j].planes[0][q];
+            };
+            if (ws.cnt[r] > 0) begin(0);
+            for (int j = 0; j < ws.cnt[r] && __any(fall != 0u); ++j) {
+                const int np = n;
+                double pl[4] = {first[0], first[1], first[2], first[3]};
+                begin(min(j + 1, ws.cnt[r] - 1));
+                unsigned in = np > 0 ? fall : 0u;
+                for (int p = 0; p < np && __any(in != 0u); ++p) {
+                    if (p > 0)
+                        for (int q = 0; q < 4; ++q) pl[q] = w[j].planes[p][q];
+                    const double at = pl[0] * x + pl[1] * y;
+#pragma unroll
+                    for (int t = 0; t < kTilePer; ++t) {
+                        const double z = g.origin[2] + (k0 + t * kTileRows + 0.5) * g.l0;
+                        if (at + pl[2] * z - pl[3] > 0.0) in &= ~(1u << t);
+                    }
+                }
+                fall &= ~in;
+            }
+        }
+        for (unsigned f = fall; f; f &= f - 1) {
+            const int k = k0 + (__ffs((int)f) - 1) * kTileRows;
+            atomicOr(&mask[(k >> 6) * kTileCols + col], 1ull << (k & 63));
+            mine |= 1ull << (k / kMass);
+        }
     }
+    if (mine) atomicOr(&any, mine);
     __syncthreads();
     bool work = false;
-    for (int w = 0; w < kTileWords; ++w) work |= mask[col][w] != 0ull;
-    work &= live;
-    double pv[kPer], wv[kPer];
-    if (work) {
+    for (int w = 0; w < words; ++w) work |= mask[w * kTileCols + col] != 0ull;
+    double mr[kMass / kTileRows];
+    auto bring = [&](unsigned long long planes) {
+        const int k0 = planes ? (__ffsll((long long)planes) - 1) * kMass : nz;
 #pragma unroll
-        for (int t = 0; t < kPer; ++t) {
-            const int k = row + t * kTileRows;
-            pv[t] = k < nz ? phi[(int64_t)k * nxy + c] : 1.0;
-            wv[t] = k < nz ? wc[(int64_t)k * nxy + c] : 0.0;
+        for (int t = 0; t < kMass / kTileRows; ++t) {
+            const int k = k0 + row + t * kTileRows;
+            mr[t] = work && k < nz ? mf[(int64_t)k * nxy + c] : 0.0;
         }
+    };
+    unsigned long long planes = any;
+    bring(planes);
+    if (work)
+        for (int k0 = row; k0 < nz; k0 += kTileRows * kTilePer) {
+            double pv[kTilePer];
 #pragma unroll
-        for (int t = 0; t < kPer; ++t) {
-            const int k = row + t * kTileRows;
-            if (k < nz && !(pv[t] >= 1.0)) atomicMin(&first_free[col], k);
+            for (int t = 0; t < kTilePer; ++t) {
+                const int k = k0 + t * kTileRows;
+                pv[t] = k < nz ? phi[(int64_t)k * nxy + c] : 1.0;
+            }
+            int k = nz;
+#pragma unroll
+            for (int t = kTilePer - 1; t >= 0; --t)
+                if (!(pv[t] >= 1.0)) k = k0 + t * kTileRows;
+            if (k < nz) {
+                atomicMin(&first_free[col], k);
+                break;  // (the wave's later planes are higher)
+            }
         }
-    }
     __syncthreads();
     const int ff = first_free[col];
-    if (work) {
-#pragma unroll
-        for (int t = 0; t < kPer; ++t) {
-            const int k = row + t * kTileRows;
-            if (k < nz && k >= ff && k < ff + kWin) {
-                P[col][k - ff] = pv[t];
-                W[col][k - ff] = wv[t];
-            }
+    if (work)
+        for (int q = row; q < kWin && ff + q < nz; q += kTileRows) {
+            P[q][col] = phi[(int64_t)(ff + q) * nxy + c];
+            W[q][col] = wc[(int64_t)(ff + q) * nxy + c];
         }
-    }
     __syncthreads();
-    if (threadIdx.x < kTileCols) {
-        double sum = 0.0;
-        int klo = nz, khi = -1;
-        if (work) {
-            const double V0 = g.l0 * g.l0 * g.l0;
-            // occupancy and compaction of voxel kk: LDS inside the window, memory above it
-            auto pget = [&](int kk) { return kk < ff + kWin ? P[col][kk - ff] : phi[(int64_t)kk * nxy + c]; };
-            int kfree = ff;  // the first voxel that is not full
-            for (int w = 0; w < kTileWords; ++w) {
-                unsigned long long mk = mask[col][w];
-                while (mk) {
-                    const int k = w * 64 + (__ffsll((long long)mk) - 1);
-                    mk &= mk - 1;
-                    double m = M[col][k];
-                    int kk = kfree;
-                    while (kk < nz && pget(kk) >= 1.0) ++kk;
-                    kfree = kk;
-                    klo = kk < klo ? kk : klo;
-                    while (m > 0.0 && kk < nz) {
-                        const bool in_win = kk < ff + kWin;
-                        const int64_t id = (int64_t)kk * nxy + c;
-                        const double f0 = in_win ? P[col][kk - ff] : phi[id];
-                        const double w0 = in_win ? W[col][kk - ff] : wc[id];
-                        const double cap = (1.0 - f0) * w_dep * rho_b * V0;
-                        const double take = m < cap ? m : cap;
-                        const double f = take == cap ? 1.0 : f0 + take / (w_dep * rho_b * V0);
-                        const double before = w0 * rho_b * V0 * f0;
-                        const double wn = f0 > 0.0 ? (before + take) / (rho_b * V0 * f) : w_dep;
-                        if (in_win) {
-                            W[col][kk - ff] = wn;
-                            P[col][kk - ff] = f;
-                        } else {
-                            wc[id] = wn;
-                            phi[id] = f;
-                        }
-                        khi = kk > khi ? kk : khi;
-                        sum += take;
-                        m -= take;
-                        ++kk;
+    // the replay, kMass planes at a time: lane col of the first wave takes
+    // column col, the other waves bring the next planes' masses
+    double sum = 0.0, f0 = 1.0, w0 = 0.0;
+    int klo = nz, khi = -1, kk = ff;
+    const double V0 = g.l0 * g.l0 * g.l0;
+    const double unit = w_dep * rho_b * V0;
+    // the voxel being filled, its occupancy and compaction: LDS inside the window, memory above it
+    auto enter = [&]() {
+        if (kk < ff + kWin && kk < nz) {
+            f0 = P[kk - ff][col];
+            w0 = W[kk - ff][col];
+        } else if (kk < nz) {
+            f0 = phi[(int64_t)kk * nxy + c];
+            w0 = wc[(int64_t)kk * nxy + c];
+        }
+    };
+    if (row == 0 && work) enter();
+    for (; planes; planes &= planes - 1) {
+        const int k0 = (__ffsll((long long)planes) - 1) * kMass;
+#pragma unroll
+        for (int t = 0; t < kMass / kTileRows; ++t) M[row + t * kTileRows][col] = mr[t];
+        __syncthreads();
+        bring(planes & (planes - 1));
+        if (row == 0) {
+            const unsigned long long word = mask[(k0 >> 6) * kTileCols + col];
+            unsigned mk = (unsigned)(word >> (k0 & 63)) & ((1u << kMass) - 1);
+            unsigned keep = 0u;
+            while (mk) {
+                const int q = __ffs((int)mk) - 1;
+                mk &= mk - 1;
+                double m = M[q][col];
+                while (kk < nz && f0 >= 1.0) {
+                    ++kk;
+                    enter();
+                }
+                klo = kk < klo ? kk : klo;
+                while (m > 0.0 && kk < nz) {
+                    const double cap = (1.0 - f0) * w_dep * rho_b * V0;
+                    const double take = m < cap ? m : cap;
+                    const double f = take == cap ? 1.0 : f0 + take / unit;
+                    const double before = w0 * rho_b * V0 * f0;
+                    const double wn = f0 > 0.0 ? (before + take) / (rho_b * V0 * f) : w_dep;
+                    if (kk < ff + kWin) {
+                        W[kk - ff][col] = wn;
+                        P[kk - ff][col] = f;
+                    } else {
+                        wc[(int64_t)kk * nxy + c] = wn;
+                        phi[(int64_t)kk * nxy + c] = f;
                     }
-                    M[col][k] = 0.0 + m;  // what finds the column full stays fluid
+                    khi = kk;
+                    sum += take;
+                    m -= take;
+                    f0 = f;
+                    w0 = wn;
+                    if (m > 0.0) {
+                        ++kk;
+                        enter();
+                    }
+                }
+                if (m != 0.0) {  // the column is full (or its occupancy no number): what is left stays fluid
+                    mf[(int64_t)(k0 + q) * nxy + c] = 0.0 + m;
+                    keep |= 1u << q;
                 }
             }
+            if (keep) mask[(k0 >> 6) * kTileCols + col] = word & ~((unsigned long long)keep << (k0 & 63));
         }
+        __syncthreads();
+    }
+    if (row == 0) {
         range[col][0] = klo;
         range[col][1] = khi;
-        ssum[col] = sum;
+        if (total) {
+            for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+            if (col == 0 && sum > 0.0) atomicAdd(total, sum);  // one atomic per tile
+        }
     }
     __syncthreads();
     if (work) {
         const int klo = range[col][0], khi = range[col][1];
-        for (int k = row; k < nz; k += kTileRows) {
-            const int64_t id = (int64_t)k * nxy + c;
-            if ((mask[col][k >> 6] >> (k & 63)) & 1ull) mf[id] = M[col][k];
-            if (k >= klo && k <= khi && k < ff + kWin) {  // (above the window: written by the fills)
-                phi[id] = P[col][k - ff];
-                wc[id] = W[col][k - ff];
+        for (int w = 0; w < words; ++w)
+            for (unsigned long long mk = mask[w * kTileCols + col] & (0x0101010101010101ull << row); mk; mk &= mk - 1) {
+                const int k = w * 64 + (__ffsll((long long)mk) - 1);
+                mf[(int64_t)k * nxy + c] = 0.0;
+            }
+        for (int q = row; q < kWin; q += kTileRows) {  // (above the window: written by the fills)
+            const int k = ff + q;
+            if (k >= klo && k <= khi) {
+                phi[(int64_t)k * nxy + c] = P[q][col];
+                wc[(int64_t)k * nxy + c] = W[q][col];
             }
         }
-    }
-    if (total && threadIdx.x == 0) {  // one atomic per tile
-        double s = 0.0;
-        for (int q = 0; q < kTileCols; ++q) s += ssum[q];
-        if (s > 0.0) atomicAdd(total, s);
     }
 }
 
@@ -754,7 +848,7 @@ void launch_convert_cut(const tr_voxel_grid& g, double rho_b, const WedgeSet& ws
 {
     const int64_t nxy = (int64_t)g.nx * g.ny;
     if (total) hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, s, total, (int64_t)1, 0.0);
-    hipLaunchKernelGGL(k_convert_cut, dim3((unsigned)cdiv(nxy, kBlk)), dim3(kBlk), 0, s, g, rho_b, ws, phi, wc, mf,
+    hipLaunchKernelGGL(k_convert_cut, dim3((unsigned)cdiv(nxy, kCutCols)), dim3(kBlk), 0, s, g, rho_b, ws, phi, wc, mf,
                        total);
 }
 
@@ -764,8 +858,9 @@ void launch_convert_deposit(const tr_voxel_grid& g, double rho_b, double w_dep, 
     const int64_t nxy = (int64_t)g.nx * g.ny;
     if (total) hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, s, total, (int64_t)1, 0.0);
     if (g.nz <= kTileNz)
-        hipLaunchKernelGGL(k_convert_deposit_tile, dim3((unsigned)cdiv(nxy, kTileCols)), dim3(kBlk), 0, s, g, rho_b,
-                           w_dep, ws, rho_p, phi, wc, mf, total);
+        hipLaunchKernelGGL(k_convert_deposit_tile, dim3((unsigned)cdiv(nxy, kTileCols)), dim3(kTileCols * kTileRows),
+                           (size_t)((g.nz + 63) / 64) * kTileCols * 8, s, g, rho_b, w_dep, ws, rho_p, phi, wc, mf,
+                           total);
     else
         hipLaunchKernelGGL(k_convert_deposit, dim3((unsigned)cdiv(nxy, kBlk)), dim3(kBlk), 0, s, g, rho_b, w_dep, ws,
                            rho_p, phi, wc, mf, total);
