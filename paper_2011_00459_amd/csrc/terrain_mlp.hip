@@ -259,28 +259,36 @@ void launch_learned_lam(const DevBuffers& b, const StepParams& p, const Sizes& z
 
 // ---------------------------------------------------------------------------
 // training: forward + backward of 0.5 mean ||y - label||^2 in FP32 on MFMA
-// (v_mfma_f32_32x32x2f32, FP32 products and sums).  Each wave takes tiles of
-// 32 samples; a block's 4 waves take R tiles each (128 R samples, R from 1
-// to 4 so that a call fills the 256 CUs where the batch allows).  Per tile:
-//   layer 1   Z1[32 x 64] = X[32 x 12] . W1^T          2 N-tiles x 6 K-steps
-//   layer 2   Z2 = H1 . W2^T                           2 N-tiles x 32 K-steps
+// (v_mfma_f32_16x16x4f32, FP32 products and sums).  A block's 16 waves are
+// four groups of four; a group takes tiles of 32 samples, R of them (128 R
+// samples a block, R from 1 to 4 so that a call fills the 256 CUs where the
+// batch allows), and each of its waves a quarter of every product: 16 units
+// of a layer, 16 rows of a weight gradient.  Per tile:
+//   layer 1   Z1[32 x 64] = X[32 x 12] . W1^T          2 x 4 tiles x 3 K-steps
+//   layer 2   Z2 = H1 . W2^T                           2 x 4 tiles x 16 K-steps
 //   layer 3   y = H2 . W3^T (3 outputs: vector ALU)
 //   backward  gZ2 = (gy . W3) o silu'(Z2) (vector ALU)
-//             gZ1 = (gZ2 . W2) o silu'(Z1)             2 N-tiles x 32 K-steps
-//   gradients dW2 += gZ2^T . H1  (64 x 64, K = 32 samples: 2 x 2 tiles x 16)
-//             dW1 += gZ1^T . X   (64 x 12 of one 32-wide N-tile: 2 tiles x 16)
+//             gZ1 = (gZ2 . W2) o silu'(Z1)             2 x 4 tiles x 16 K-steps
+//   gradients dW2 += gZ2^T . H1  (64 x 64, K = 32 samples: 4 x 4 tiles x 8)
+//             dW1 += gZ1^T . X   (64 x 12 of one 16-wide tile: 4 tiles x 8)
 //             dW3, the biases and the loss on the vector ALU
-// The gradient accumulators stay in registers across a wave's tiles; the
-// block's waves add theirs in LDS in a fixed order and write the block's
-// partial to part[block][kNP] (loss at part[.][kNP]).
-// Operand layouts (A 32x2, B 2x32, D 32x32): A[i][k] -> lane i + 32 k,
-// B[k][j] -> lane j + 32 k, D[i][j] -> lane j + 32 ((i / 4) % 2), element
-// (i % 4) + 4 (i / 8).
+// The gradient accumulators stay in registers across a group's tiles; the
+// groups' sums are added in a fixed order and written as the block's partial
+// to part[block][kNP] (loss at part[.][kNP]).
+// Operand layouts (A 16x4, B 4x16, D 16x16): A[i][k] -> lane i + 16 k,
+// B[k][j] -> lane j + 16 k, D[i][j] -> lane j + 16 (i / 4), element i % 4.
+//
+// A batch of 4,096 is 32 blocks, and what bounds it is the chain of one tile:
+// with one wave a tile, and the rows of W2 in LDS all starting at one bank, it
+// took 49 us, now 22.
 // ---------------------------------------------------------------------------
-constexpr int kTrainWaves = 4;
-constexpr int kTP = kH + 1;  // LDS pitch of the 64-wide rows
+constexpr int kTrainWaves = 4;  // tiles of a block at once: groups of kTrainQ waves
+constexpr int kTrainQ = 4;
+// LDS pitch of the 64-wide rows: 16 rows by 4 columns, an operand's lanes, fall into 64 banks
+constexpr int kTP = kH + 4;
+constexpr int kXP = kIn + 1;    // of the 12-wide ones
 
-// tiles per wave and blocks of a batch of B samples
+// tiles per group and blocks of a batch of B samples
 __host__ __device__ constexpr int train_tiles(int64_t B)
 {
     return B > (int64_t)3 * kTrainWaves * 32 * 256 ? 4 : (B > (int64_t)kTrainWaves * 32 * 256 ? 2 : 1);
@@ -290,169 +298,205 @@ __host__ __device__ constexpr int64_t train_blocks(int64_t B)
     return (B + (int64_t)kTrainWaves * 32 * train_tiles(B) - 1) / ((int64_t)kTrainWaves * 32 * train_tiles(B));
 }
 
-__device__ inline floatx16 mfma32(float a, float b, floatx16 c)
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+__device__ inline floatx4 mfma16(float a, float b, floatx4 c)
 {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-__global__ __launch_bounds__(64 * kTrainWaves) void k_mlp_train(const float* __restrict__ W,
-                                                                const float* __restrict__ feat,
-                                                                const float* __restrict__ label, int64_t B,
-                                                                int tiles, float* __restrict__ part)
+// LDS of a group.  h1, h2 and g hold H1, H2 then gZ1, and gZ2; at the end the
+// group's gradients (kNP values) and what its waves add to dW3, b3 and the loss.
+struct TrainGroup {
+    float h1[32][kTP], h2[32][kTP], g[32][kTP];
+    float xs[32][kXP];
+    float gy[32][kOut + 1];
+    float yp[kTrainQ][32][kOut];
+};
+constexpr int kTail = kOut * kH + kOut + 1;  // dW3, b3, loss of one wave
+static_assert(kNP + kTrainQ * kTail <= 3 * 32 * kTP, "a group's gradients take the place of its activations");
+
+__global__ __launch_bounds__(64 * kTrainQ * kTrainWaves) void k_mlp_train(const float* __restrict__ W,
+                                                                          const float* __restrict__ feat,
+                                                                          const float* __restrict__ label, int64_t B,
+                                                                          int tiles, float* __restrict__ part)
 {
-    __shared__ float w[kMlpParams];
-    __shared__ float xs[kTrainWaves][32][kIn + 1];
-    __shared__ float h1s[kTrainWaves][32][kTP];
-    __shared__ float h2s[kTrainWaves][32][kTP];  // H2, then gZ2
-    __shared__ float g1s[kTrainWaves][32][kTP];  // gZ1
-    __shared__ float gys[kTrainWaves][32][kOut];
-    const int t = threadIdx.x, wave = t >> 6, lane = t & 63, col = lane & 31, half = lane >> 5;
-    for (int k = t; k < kMlpParams; k += blockDim.x) w[k] = W[k];
-    __syncthreads();
+    __shared__ float w1[kH][kXP], w2[kH][kTP], w3[kOut][kH], bias[2][kH], b3[kOut];
+    __shared__ TrainGroup gm[kTrainWaves];
+    const int t = threadIdx.x, wave = t >> 6, lane = t & 63, grp = wave / kTrainQ, wq = wave % kTrainQ;
+    const int l16 = lane & 15, q4 = lane >> 4, s32 = lane & 31, half = lane >> 5;
+    const int u0 = 16 * wq, u = u0 + l16;  // the wave's units, the lane's
+    TrainGroup& G = gm[grp];
     const float inv_b = 1.0f / (float)B;
-    floatx16 dW2[2][2], dW1[2];
-    for (int m = 0; m < 2; ++m) {
-        dW1[m] = floatx16{};
-        for (int n = 0; n < 2; ++n) dW2[m][n] = floatx16{};
+    // two of the group's 32 x 12 inputs a lane (the second of half the lanes) and, for its first wave, the labels
+    const int e0 = wq * 64 + lane, e1 = min(e0 + 64 * kTrainQ, 32 * kIn - 1);
+    const float sc0 = W[oScale + e0 % kIn], sc1 = W[oScale + e1 % kIn];
+    float x0 = 0.0f, x1 = 0.0f, lab[kOut] = {0.0f, 0.0f, 0.0f};
+    auto read_tile = [&](int r) {
+        const int64_t s0 = (((int64_t)blockIdx.x * tiles + r) * kTrainWaves + grp) * 32;
+        x0 = s0 + e0 / kIn < B ? feat[s0 * kIn + e0] : 0.0f;
+        x1 = s0 + e1 / kIn < B ? feat[s0 * kIn + e1] : 0.0f;
+        if (wq == 0)
+            for (int q = 0; q < kOut; ++q) lab[q] = s0 + s32 < B ? label[(s0 + s32) * kOut + q] : 0.0f;
+    };
+    read_tile(0);
+    {
+        // every load of the weights in flight at once: one after the other they would cost 10 us
+        static_assert(kH * kIn <= 1024 && kH * kH == 4096 && 64 * kTrainQ * kTrainWaves == 1024, "one pass each");
+        float v2[4];
+        for (int k = 0; k < 4; ++k) v2[k] = W[oW2 + t + 1024 * k];
+        const float v1 = W[oW1 + min(t, kH * kIn - 1)], v3 = W[oW3 + min(t, kOut * kH - 1)];
+        const float vb = W[(t < kH ? ob1 : ob2) + t % kH], v4 = W[ob3 + min(t, kOut - 1)];
+        for (int k = 0; k < 4; ++k) w2[(t + 1024 * k) / kH][t % kH] = v2[k];
+        if (t < kH * kIn) w1[t / kIn][t % kIn] = v1;
+        if (t < kOut * kH) w3[t / kH][t % kH] = v3;
+        if (t < 2 * kH) bias[t / kH][t % kH] = vb;
+        if (t < kOut) b3[t] = v4;
     }
-    float dW3[kOut] = {0.0f, 0.0f, 0.0f}, db1[2] = {0.0f, 0.0f}, db2[2] = {0.0f, 0.0f}, db3 = 0.0f, loss = 0.0f;
+    floatx4 dW2[4], dW1 = {};
+    for (int n = 0; n < 4; ++n) dW2[n] = floatx4{};
+    float dW3[kOut] = {0.0f, 0.0f, 0.0f}, db1 = 0.0f, db2 = 0.0f, db3 = 0.0f, loss = 0.0f;
     for (int r = 0; r < tiles; ++r) {
-        const int64_t s0 = (((int64_t)blockIdx.x * tiles + r) * kTrainWaves + wave) * 32;
-        for (int e = lane; e < 32 * kIn; e += 64) {
-            const int i = e / kIn, k = e % kIn;
-            const int64_t sm = s0 + i;
-            xs[wave][i][k] = sm < B ? feat[sm * kIn + k] * w[oScale + k] : 0.0f;
-        }
+        // (opaque here: the addresses of all LDS operands would else be kept
+        // across tiles, and spill)
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        const int l16 = ln & 15, q4 = ln >> 4, s32 = ln & 31, half = ln >> 5, u = u0 + l16;
+        const int64_t s0 = (((int64_t)blockIdx.x * tiles + r) * kTrainWaves + grp) * 32;
+        G.xs[e0 / kIn][e0 % kIn] = x0 * sc0;
+        if (e1 == e0 + 64 * kTrainQ) G.xs[e1 / kIn][e1 % kIn] = x1 * sc1;
         __syncthreads();
-        // layer 1: Z1 in registers (D layout), H1 into LDS
-        floatx16 z1[2], z2[2];
-        for (int n = 0; n < 2; ++n) {
-            floatx16 acc = {};
-            for (int kk = 0; kk < kIn / 2; ++kk) {
-                const int k = 2 * kk + half;
-                acc = mfma32(xs[wave][col][k], w[oW1 + (n * 32 + col) * kIn + k], acc);
-            }
-            const float bias = w[ob1 + n * 32 + col];
-            for (int e = 0; e < 16; ++e) {
-                const int i = (e & 3) + 8 * (e >> 2) + 4 * half;
-                const float zz = acc[e] + bias;
-                z1[n][e] = zz;
-                h1s[wave][i][n * 32 + col] = silu(zz);
+        // layers 1 and 2: the wave's 16 units of Z in registers (D layout), H into LDS
+        floatx4 z1[2], z2[2];
+        for (int m = 0; m < 2; ++m) {
+            floatx4 acc = {};
+            for (int kk = 0; kk < kIn / 4; ++kk)
+                acc = mfma16(G.xs[m * 16 + l16][4 * kk + q4], w1[u][4 * kk + q4], acc);
+            for (int e = 0; e < 4; ++e) {
+                z1[m][e] = acc[e] + bias[0][u];
+                G.h1[m * 16 + 4 * q4 + e][u] = silu(z1[m][e]);
             }
         }
         __syncthreads();
-        // layer 2: Z2 in registers, H2 into LDS
-        for (int n = 0; n < 2; ++n) {
-            floatx16 acc = {};
-            for (int kk = 0; kk < kH / 2; ++kk) {
-                const int k = 2 * kk + half;
-                acc = mfma32(h1s[wave][col][k], w[oW2 + (n * 32 + col) * kH + k], acc);
+        {
+            floatx4 acc[2] = {};
+#pragma unroll 4
+            for (int kk = 0; kk < kH / 4; ++kk) {
+                const float bw = w2[u][4 * kk + q4];
+                for (int m = 0; m < 2; ++m) acc[m] = mfma16(G.h1[m * 16 + l16][4 * kk + q4], bw, acc[m]);
             }
-            const float bias = w[ob2 + n * 32 + col];
-            for (int e = 0; e < 16; ++e) {
-                const int i = (e & 3) + 8 * (e >> 2) + 4 * half;
-                const float zz = acc[e] + bias;
-                z2[n][e] = zz;
-                h2s[wave][i][n * 32 + col] = silu(zz);
-            }
+            for (int m = 0; m < 2; ++m)
+                for (int e = 0; e < 4; ++e) {
+                    z2[m][e] = acc[m][e] + bias[1][u];
+                    G.h2[m * 16 + 4 * q4 + e][u] = silu(z2[m][e]);
+                }
         }
         __syncthreads();
-        // layer 3 and the error: sample col, the two lane halves summing half
-        // of H2's columns each
+        // layer 3: sample s32, an eighth of H2's columns a lane
         {
             float y[kOut] = {0.0f, 0.0f, 0.0f};
-            for (int k = half * 32; k < half * 32 + 32; ++k) {
-                const float h = h2s[wave][col][k];
-                for (int q = 0; q < kOut; ++q) y[q] += w[oW3 + q * kH + k] * h;
+            const int k0 = u0 + 8 * half;
+            for (int k = k0; k < k0 + 8; ++k) {
+                const float h = G.h2[s32][k];
+                for (int q = 0; q < kOut; ++q) y[q] += w3[q][k] * h;
             }
-            const int64_t sm = s0 + col;
             for (int q = 0; q < kOut; ++q) {
                 y[q] += __shfl_xor(y[q], 32);
-                const float e = sm < B ? (y[q] + w[ob3 + q]) - label[sm * kOut + q] : 0.0f;
-                if (half == 0) {
-                    gys[wave][col][q] = e * inv_b;
-                    loss += 0.5f * e * e;
-                }
+                if (half == 0) G.yp[wq][s32][q] = y[q];
             }
         }
         __syncthreads();
-        // dW3 (row q, column lane), db3
-        for (int i = 0; i < 32; ++i) {
-            const float h = h2s[wave][i][lane];
-            for (int q = 0; q < kOut; ++q) dW3[q] += gys[wave][i][q] * h;
-        }
-        if (lane < kOut)
-            for (int i = 0; i < 32; ++i) db3 += gys[wave][i][lane];
+        if (wq == 0 && half == 0)
+            for (int q = 0; q < kOut; ++q) {
+                const float y = (G.yp[0][s32][q] + G.yp[1][s32][q]) + (G.yp[2][s32][q] + G.yp[3][s32][q]);
+                const float e = s0 + s32 < B ? (y + b3[q]) - lab[q] : 0.0f;
+                G.gy[s32][q] = e * inv_b;
+                loss += 0.5f * e * e;
+            }
+        if (r + 1 < tiles) read_tile(r + 1);
         __syncthreads();
-        // gZ2 = (gy . W3) o silu'(Z2), into h2s
-        for (int n = 0; n < 2; ++n)
-            for (int e = 0; e < 16; ++e) {
-                const int i = (e & 3) + 8 * (e >> 2) + 4 * half, j = n * 32 + col;
+        // dW3 (row q, column lane) and db3 over a quarter of the samples
+        for (int i = 8 * wq; i < 8 * wq + 8; ++i) {
+            const float h = G.h2[i][ln];
+            for (int q = 0; q < kOut; ++q) dW3[q] += G.gy[i][q] * h;
+            if (ln < kOut) db3 += G.gy[i][ln];
+        }
+        // gZ2 = (gy . W3) o silu'(Z2)
+        for (int m = 0; m < 2; ++m)
+            for (int e = 0; e < 4; ++e) {
+                const int i = m * 16 + 4 * q4 + e;
                 float gh = 0.0f;
-                for (int q = 0; q < kOut; ++q) gh += gys[wave][i][q] * w[oW3 + q * kH + j];
-                const float g = gh * dsilu(z2[n][e]);
-                h2s[wave][i][j] = g;
-                db2[n] += g;
+                for (int q = 0; q < kOut; ++q) gh += G.gy[i][q] * w3[q][u];
+                const float g = gh * dsilu(z2[m][e]);
+                G.g[i][u] = g;
+                db2 += g;
             }
         __syncthreads();
-        // dW2 += gZ2^T . H1
-        for (int m = 0; m < 2; ++m)
-            for (int n = 0; n < 2; ++n)
-                for (int kk = 0; kk < 16; ++kk) {
-                    const int i = 2 * kk + half;
-                    dW2[m][n] = mfma32(h2s[wave][i][m * 32 + col], h1s[wave][i][n * 32 + col], dW2[m][n]);
-                }
-        // gZ1 = (gZ2 . W2) o silu'(Z1), into g1s
-        for (int n = 0; n < 2; ++n) {
-            floatx16 acc = {};
-            for (int kk = 0; kk < kH / 2; ++kk) {
-                const int o = 2 * kk + half;
-                acc = mfma32(h2s[wave][col][o], w[oW2 + o * kH + n * 32 + col], acc);
-            }
-            for (int e = 0; e < 16; ++e) {
-                const int i = (e & 3) + 8 * (e >> 2) + 4 * half;
-                const float g = acc[e] * dsilu(z1[n][e]);
-                g1s[wave][i][n * 32 + col] = g;
-                db1[n] += g;
-            }
+        // dW2 += gZ2^T . H1, rows u0 .. u0 + 15
+#pragma unroll 4
+        for (int kk = 0; kk < 8; ++kk) {
+            const int i = 4 * kk + q4;
+            const float ag = G.g[i][u];
+            for (int n = 0; n < 4; ++n) dW2[n] = mfma16(ag, G.h1[i][n * 16 + l16], dW2[n]);
         }
-        __syncthreads();
-        // dW1 += gZ1^T . X (columns col < 12 of one N-tile)
-        for (int m = 0; m < 2; ++m)
-            for (int kk = 0; kk < 16; ++kk) {
-                const int i = 2 * kk + half;
-                dW1[m] = mfma32(g1s[wave][i][m * 32 + col], col < kIn ? xs[wave][i][col] : 0.0f, dW1[m]);
+        // gZ1 = (gZ2 . W2) o silu'(Z1), in H2's place
+        {
+            floatx4 acc[2] = {};
+#pragma unroll 4
+            for (int kk = 0; kk < kH / 4; ++kk) {
+                const float bw = w2[4 * kk + q4][u];
+                for (int m = 0; m < 2; ++m) acc[m] = mfma16(G.g[m * 16 + l16][4 * kk + q4], bw, acc[m]);
             }
-        __syncthreads();  // the wave's buffers are rewritten by its next tile
-    }
-    // the block's partial: the waves add theirs in order
-    float* red = &h1s[0][0][0];
-    for (int wv = 0; wv < kTrainWaves; ++wv) {
-        if (wave == wv) {
-            auto put = [&](int idx, float v) { red[idx] = wv == 0 ? v : red[idx] + v; };
             for (int m = 0; m < 2; ++m)
-                for (int e = 0; e < 16; ++e) {
-                    const int o = m * 32 + (e & 3) + 8 * (e >> 2) + 4 * half;
-                    for (int n = 0; n < 2; ++n) put(oW2 + o * kH + n * 32 + col, dW2[m][n][e]);
-                    if (col < kIn) put(oW1 + o * kIn + col, dW1[m][e]);
+                for (int e = 0; e < 4; ++e) {
+                    const float g = acc[m][e] * dsilu(z1[m][e]);
+                    G.h2[m * 16 + 4 * q4 + e][u] = g;
+                    db1 += g;
                 }
-            for (int q = 0; q < kOut; ++q) put(oW3 + q * kH + lane, dW3[q]);
-            for (int n = 0; n < 2; ++n) {
-                const float v1 = db1[n] + __shfl_xor(db1[n], 32), v2 = db2[n] + __shfl_xor(db2[n], 32);
-                if (half == 0) {
-                    put(ob1 + n * 32 + col, v1);
-                    put(ob2 + n * 32 + col, v2);
-                }
-            }
-            if (lane < kOut) put(ob3 + lane, db3);
-            float l = loss;
-            for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
-            if (lane == 0) put(kNP, l * inv_b);
         }
+        // dW1 += gZ1^T . X, rows u0 .. u0 + 15 (of this wave's own units), columns l16 < 12
         __syncthreads();
+#pragma unroll 4
+        for (int kk = 0; kk < 8; ++kk) {
+            const int i = 4 * kk + q4;
+            dW1 = mfma16(G.h2[i][u], l16 < kIn ? G.xs[i][l16] : 0.0f, dW1);
+        }
+        __syncthreads();  // the group's buffers are rewritten by its next tile
     }
+    // the group's gradients over its activations; dW3, b3 and the loss a wave at a time behind them
+    float* red = &G.h1[0][0];
+    for (int e = 0; e < 4; ++e) {
+        const int o = u0 + 4 * q4 + e;
+        for (int n = 0; n < 4; ++n) red[oW2 + o * kH + n * 16 + l16] = dW2[n][e];
+        if (l16 < kIn) red[oW1 + o * kIn + l16] = dW1[e];
+    }
+    db1 += __shfl_xor(db1, 16);
+    db1 += __shfl_xor(db1, 32);
+    db2 += __shfl_xor(db2, 16);
+    db2 += __shfl_xor(db2, 32);
+    if (q4 == 0) {
+        red[ob1 + u] = db1;
+        red[ob2 + u] = db2;
+    }
+    float* tail = red + kNP + wq * kTail;
+    for (int q = 0; q < kOut; ++q) tail[q * kH + lane] = dW3[q];
+    if (lane < kOut) tail[kOut * kH + lane] = db3;
+    for (int o = 32; o > 0; o >>= 1) loss += __shfl_xor(loss, o);
+    if (lane == 0) tail[kTail - 1] = loss * inv_b;
+    __syncthreads();
     float* out = part + (size_t)blockIdx.x * (kNP + 1);
-    for (int k = t; k <= kNP; k += blockDim.x) out[k] = red[k];
+    for (int k = t; k <= kNP; k += blockDim.x) {
+        const int at = k >= oW3 && k < oW3 + kOut * kH ? k - oW3
+                       : k >= ob3 && k < ob3 + kOut    ? kOut * kH + k - ob3
+                                                       : (k == kNP ? kTail - 1 : -1);
+        float v = 0.0f;
+        for (int gq = 0; gq < kTrainWaves; ++gq) {
+            const float* rg = &gm[gq].h1[0][0];
+            if (at < 0) v += rg[k];
+            else
+                for (int q = 0; q < kTrainQ; ++q) v += rg[kNP + q * kTail + at];
+        }
+        out[k] = v;
+    }
 }
 
 // the blocks' partials summed in a fixed order: 64 parameters per block of
@@ -498,7 +542,7 @@ void launch_mlp_grad(const float* W, const float* feat, const float* label, int6
                      float* scratch, hipStream_t s)
 {
     const int nb = (int)train_blocks(B);
-    hipLaunchKernelGGL(k_mlp_train, dim3(nb), dim3(64 * kTrainWaves), 0, s, W, feat, label, B, train_tiles(B),
+    hipLaunchKernelGGL(k_mlp_train, dim3(nb), dim3(64 * kTrainQ * kTrainWaves), 0, s, W, feat, label, B, train_tiles(B),
                        scratch);
     hipLaunchKernelGGL(k_grad_reduce, dim3((kNP + 1 + 63) / 64), dim3(64 * kRedGroups), 0, s, scratch, nb, grad, loss);
 }
