@@ -444,7 +444,8 @@ int rebuild_plan(tr_scene* s)
         std::vector<std::vector<int4>> small_tasks;
         // (plan_auto's model, fitted to regions of 1,000 spheres and more, is
         // 10 percent low for the smallest clusters: 250 spheres take 1.2 ms)
-        env_small = automatic && !flow && plan_small(s, order, B, lds_cap, small_tasks) < 1.1 * best;
+        const double small = automatic && !flow ? plan_small(s, order, B, lds_cap, small_tasks) : 1e300;
+        env_small = small < 1e300 && small < 1.1 * best;  // (both are 1e300 for an env too large for either)
         if (env_small) {
             tasks = std::move(small_tasks);
         } else if (best < 1e300) {

@@ -70,6 +70,8 @@ CASES = {
                            dict(mode="per_env", cluster_particles=0)),
     "small_plan_queued": ([(120 + e % 7, 2 + e % 3, 3, 2) for e in range(300)], {},
                           dict(mode="per_env", cluster_particles=0)),
+    # an env that fits neither automatic plan: the plan by spheres per block
+    "no_plan_fits": ([(140, 23, 14, 11)], {}, dict(mode="per_env", lds_particles=64, cluster_particles=0)),
     # all eight XCDs
     "spread": ([(90, 41, 27, 25)], {}, dict(mode="spread", blocks_per_xcd=32)),
     "spread_rolling": ([(91, 41, 27, 25)], dict(roll=True), dict(mode="spread", blocks_per_xcd=5)),
