@@ -12,9 +12,10 @@ U(0.3, 1.5) m/s, dt 1/60 s, 100 PGS sweeps, previous-step warm start, settled
 on the GPU before timing.  value = sum over the timed steps of contacts x PGS
 sweeps / wall time of those steps.
 
-roofline: the per-env PGS kernel (k_pgs_env): algorithmic bytes (176 B per
-pair contact-sweep, 128 B per boundary contact-sweep) / its HIP-event
-duration on the scene's stream, summed over the timed steps.
+roofline: the per-env PGS kernel (k_pgs_env): algorithmic bytes (80 B per
+contact-sweep: 48 B of rows and 16 B of impulses read, 16 B of impulses
+written; the bodies stay in LDS) / its HIP-event duration on the scene's
+stream, summed over the timed steps.
 cpu_baseline: the FP64 oracle as it stands on the same 256 beds (settled by
 the oracle itself), one process per host core, one step of each bed.
 
@@ -41,22 +42,22 @@ from paper_2011_00459_amd import terrain as T  # noqa: E402
 from paper_2011_00459_amd import zones as Z  # noqa: E402
 
 HBM_PEAK_GBS = 8000.0
-PAIR_BYTES, BOUND_BYTES = 176, 128
+ROW_BYTES = 80
 
 # HBM traffic of one PGS launch, from the FETCH_SIZE and WRITE_SIZE counter
 # runs scaled by a copy kernel of known size (profiles named below); valid
 # only for the kernel source it was measured on, else reported as null.
 PGS_TRAFFIC = {
-    "batched": {"kernels_sha256_prefix": "02315f89cb19c419", "bytes_per_launch": 52.76e9,
+    "batched": {"kernels_sha256_prefix": "0e6bea17055ed3e1", "bytes_per_launch": 28.12e9,
                 "profile": "profiles/k_pgs_env_batched256_hbm_traffic.md"},
-    "bed": {"kernels_sha256_prefix": "02315f89cb19c419", "bytes_per_launch": 3.494e9,
+    "bed": {"kernels_sha256_prefix": "0e6bea17055ed3e1", "bytes_per_launch": 1.326e9,
             "profile": "profiles/k_pgs_bed50k_hbm_traffic.md"},
-    "excavation": {"kernels_sha256_prefix": "02315f89cb19c419", "bytes_per_launch": 71.00e9,
+    "excavation": {"kernels_sha256_prefix": "0e6bea17055ed3e1", "bytes_per_launch": 27.35e9,
                    "profile": "profiles/k_pgs_excavation500k_hbm_traffic.md"},
 }
 # The same for k_advect on the 256 x 256 x 128 voxel grid
 # (profiles/k_advect_voxels256_kernel_trace.md), keyed to terrain_voxels.hip.
-ADVECT_TRAFFIC = {"kernels_sha256_prefix": "92ca9f936e1a6af0", "bytes_per_launch": 0.3757e9,
+ADVECT_TRAFFIC = {"kernels_sha256_prefix": "8ceb484fd0d1a552", "bytes_per_launch": 0.3756e9,
                   "profile": "profiles/k_advect_voxels256_kernel_trace.md"}
 
 
@@ -93,8 +94,7 @@ def timed_steps(sc, k):
         ph = sc.get_phase_times()
         for x in st:
             tot["cs"] += x["contacts"] * x["sweeps"]
-            tot["bytes"] += (x["pair_contacts"] * PAIR_BYTES + (x["contacts"] - x["pair_contacts"]) * BOUND_BYTES) \
-                * x["sweeps"]
+            tot["bytes"] += x["contacts"] * ROW_BYTES * x["sweeps"]
         tot["pgs_ms"] += ph["pgs"]
         tot["steps"] += 1
         last = (st, ph)
@@ -126,9 +126,9 @@ def roofline(tot, kernel, traffic_key):
 
 def pgs_kernel_name(sc):
     mode = sc.get_solver_config()["mode"]
-    return {"grouped": "k_pgs (grouped persistent colour-synchronous PGS)",
-            "spread": "k_pgs (spread: one env on all XCDs, colour-synchronous PGS)",
-            "per_env": "k_pgs_env (per-env persistent colour-synchronous PGS)"}[mode]
+    return {"grouped": "k_pgs (grouped: regions of one XCD, persistent PGS)",
+            "spread": "k_pgs (spread: regions of one env on all XCDs, persistent PGS)",
+            "per_env": "k_pgs_env (per-env persistent PGS)"}[mode]
 
 
 # bulk properties of the aggregate in the timed macroscale step: the bed's

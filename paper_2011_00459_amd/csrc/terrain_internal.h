@@ -37,7 +37,7 @@ constexpr int kMlpParams = 64 * 12 + 64 + 64 * 64 + 64 + 3 * 64 + 3 + 12;
 
 // PGS solve modes
 enum : int {
-    kModeGrouped = 0,  // envs in kGroups XCD groups, grid-wide colour barriers per group
+    kModeGrouped = 0,  // envs in kGroups groups, each solved on one XCD
     kModePerEnv = 1,   // each env solved by its own block (or cluster of blocks)
     kModeSpread = 2,   // one env spread over the blocks of all XCDs by space
 };

@@ -19,9 +19,9 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <type_traits>
 #include <cmath>
 #include <cstddef>
+#include <type_traits>
 
 #include "terrain_internal.h"
 #include "terrain_geom.h"
