@@ -35,6 +35,7 @@ constexpr int kFlowMaxSweeps = 8192;  // longest counter-ordered solve
 // slower, but one XCD's 32 blocks are full (20,000 spheres: 1.27 ms on one
 // XCD, 1.63 on all; 35,000: 1.93 and 1.38; 70,000: 2.63 and 1.47).
 constexpr int64_t kRegionAlone = 1700, kRegionAloneRolling = 1400, kRegionSpheres = 400, kSpreadMin = 27000;
+constexpr int64_t kWideRegion = 600;      // largest region of 512-thread blocks (beside kPgsWide)
 constexpr int64_t kEnvSmallRegion = 800;  // largest region of the per-env plan of small regions
 
 struct EnvHost {
@@ -283,7 +284,7 @@ double plan_auto(const tr_scene* s, const std::vector<int>& order, int B, int ld
     return best;
 }
 
-// The plan of small regions, for blocks of 512 threads that keep rows and
+// The plan of small regions, for blocks of 512 or 640 threads that keep rows and
 // impulses in LDS: an env of at most kRegionAlone spheres is solved by one
 // block, 470 plus 0.28 per sphere (300 spheres 0.57 ms, 1,000 0.73 ms, where a
 // cluster took 1.1 ms), several of them one after another where envs outnumber
@@ -647,6 +648,13 @@ int rebuild_plan(tr_scene* s)
         HIP_CHECK(s, hipMemcpyAsync(s->b.grp_task, tasks_g.data(), sizeof(int4) * tasks_g.size(), hipMemcpyHostToDevice, st));
     s->z.n_own = n_own;
     s->z.grp_lds = grp_lds;
+    int64_t largest = 0;
+    for (int k = 0; k + 1 < (int)own_idx.size(); ++k) {
+        int64_t n = 0;
+        for (int q = own_idx[k]; q < own_idx[k + 1]; ++q) n += own_seg[q].y;
+        largest = std::max(largest, n);
+    }
+    s->z.pgs_wide = largest > kWideRegion ? 1 : 0;
     s->z.grp_f4 = pgs_group_max_lds() / 16;
     s->z.n_flags = (int)flags;
     if ((int64_t)plan.size() > s->plan_alloc) {

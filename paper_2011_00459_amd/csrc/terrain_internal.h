@@ -297,7 +297,8 @@ struct Sizes {
     int pgs_mode;   // kModeGrouped, kModePerEnv or kModeSpread
     int plan_blocks;  // blocks of the per-env PGS kernel
     int lds_cap;    // particles whose bodies a per-env block keeps in LDS (0: none)
-    int env_small;  // per-env solve of small regions only: blocks of 512 threads
+    int env_small;  // per-env solve under the plan of small regions
+    int pgs_wide;   // some region of the grouped, spread or small per-env solve has more than kWideRegion spheres
     int n_units;    // entries of ustats
     int flow;       // colour order kept by per-sphere update counters instead of barriers
     int col_grid;   // resident blocks of the colouring kernel

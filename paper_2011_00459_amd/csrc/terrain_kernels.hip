@@ -1533,7 +1533,12 @@ void launch_warm_apply(const DevBuffers& b, const StepParams& p, const Sizes& z,
 // fixed order and combined identically by every block of the cluster, which
 // then all take the same stopping decision.
 // ---------------------------------------------------------------------------
-constexpr int kPgsWaves = 8;  // waves of a block of the grouped and spread solves
+// waves of a block of the grouped, spread and small per-env solves: the wide
+// ones for regions of more than kWideRegion spheres, whose colours have more
+// contacts than 512 threads (300,000 spheres on all XCDs 3.04 -> 2.58 ms,
+// 500,000 7.9 -> 7.5, eight rolling columns of 1,000 1.04 -> 0.95; a column of
+// 300 0.293 -> 0.302; with 12 waves 450,000 spheres 3.46 -> 3.52)
+constexpr int kPgsWaves = 8, kPgsWide = 10;
 constexpr int kCoherent = 16;  // cache-policy bits of a device-scope (sc1) access
 
 __device__ inline __amdgpu_buffer_rsrc_t raw_rsrc(const void* p)
@@ -2232,7 +2237,7 @@ __device__ __forceinline__ void solve_region(const DevBuffers& b, const StepPara
     // first private contact of a phase are both fetched ahead by 512-thread
     // blocks; 1024-thread ones have registers for one, and take the private
     // contact of a thread with both as it comes.
-    constexpr bool kBoth = NW <= 8;
+    constexpr bool kBoth = NW <= kPgsWide;
     const uint32_t ts = kThreads - 1 - tid, wave_ts = ts & ~63u;  // this wave's first shared contact
     RowRegs cs, cp;
     float4 ms;  // masses of the shared contact's bodies
@@ -2501,14 +2506,14 @@ __device__ __forceinline__ void pgs_region(const DevBuffers& b, const StepParams
     const uint32_t room = (uint32_t)max(0, lds_f4 - 2 * nb);
     auto solve = [&](auto home) {
         const BlockRows<ROLL, decltype(home)::value> br(lds + 2 * nb, base, n);
-        if (NW <= 8 && alone)
+        if (NW <= kPgsWide && alone)
             solve_alone<ROLL, NW>(b, p, T, ncol, sweeps_cap, slot, lds, nb, br, sh);
         else
             solve_region<ROLL, NW>(b, p, T, ncol, through, sweeps_cap, slot, lds, nb, br, sh);
     };
-    if (NW <= 8 && BlockRows<ROLL, kRowsLds>::size(n) <= room)
+    if (NW <= kPgsWide && BlockRows<ROLL, kRowsLds>::size(n) <= room)
         solve(std::integral_constant<RowHome, kRowsLds>{});
-    else if (NW <= 8 && BlockRows<ROLL, kRowsImpulses>::size(n) <= room)
+    else if (NW <= kPgsWide && BlockRows<ROLL, kRowsImpulses>::size(n) <= room)
         solve(std::integral_constant<RowHome, kRowsImpulses>{});
     else
         solve(std::integral_constant<RowHome, kRowsMemory>{});
@@ -2712,7 +2717,11 @@ int pgs_env_max_lds()
     return max_dynamic_lds((const void*)k_pgs_env<false, kEnvWaves>, (const void*)k_pgs_env<true, kEnvWaves>);
 }
 
-int pgs_group_max_lds() { return max_dynamic_lds((const void*)k_pgs<false, kPgsWaves>, (const void*)k_pgs<true, kPgsWaves>); }
+int pgs_group_max_lds()
+{
+    return std::min(max_dynamic_lds((const void*)k_pgs<false, kPgsWaves>, (const void*)k_pgs<true, kPgsWaves>),
+                    max_dynamic_lds((const void*)k_pgs<false, kPgsWide>, (const void*)k_pgs<true, kPgsWide>));
+}
 
 // blocks of either instance (plain or with rolling rows) of a persistent
 // solve resident at once: its blocks wait for each other
@@ -2735,14 +2744,20 @@ int pgs_env_resident_blocks(int lds_bytes)
 {
     const int all = resident_blocks((const void*)k_pgs_env<false, kEnvWaves>, (const void*)k_pgs_env<true, kEnvWaves>,
                                     kEnvBlk, lds_bytes);
-    return std::min(all, resident_blocks((const void*)k_pgs_env<false, kPgsWaves>, (const void*)k_pgs_env<true, kPgsWaves>,
-                                         64 * kPgsWaves, lds_bytes));
+    return std::min({all,
+                     resident_blocks((const void*)k_pgs_env<false, kPgsWaves>, (const void*)k_pgs_env<true, kPgsWaves>,
+                                     64 * kPgsWaves, lds_bytes),
+                     resident_blocks((const void*)k_pgs_env<false, kPgsWide>, (const void*)k_pgs_env<true, kPgsWide>,
+                                     64 * kPgsWide, lds_bytes)});
 }
 
 int pgs_resident_blocks()
 {
-    return resident_blocks((const void*)k_pgs<false, kPgsWaves>, (const void*)k_pgs<true, kPgsWaves>, 64 * kPgsWaves,
-                           pgs_group_max_lds());
+    const int lds = pgs_group_max_lds();
+    return std::min(resident_blocks((const void*)k_pgs<false, kPgsWaves>, (const void*)k_pgs<true, kPgsWaves>,
+                                    64 * kPgsWaves, lds),
+                    resident_blocks((const void*)k_pgs<false, kPgsWide>, (const void*)k_pgs<true, kPgsWide>,
+                                    64 * kPgsWide, lds));
 }
 
 // The colouring's blocks wait for each other, so all of them must run at
@@ -2770,18 +2785,21 @@ void launch_pgs(const DevBuffers& b, const StepParams& p, const Sizes& z, hipStr
     const int flow = z.flow;
     if (flow && p.n_particles > 0) launch_fill_u32(b.ver, 0u, p.n_particles, s);
     const bool env = z.pgs_mode == kModePerEnv;
-    const dim3 grid((unsigned)(env ? z.plan_blocks : z.pgs_grid)), blk(env && !z.env_small ? kEnvBlk : 64 * kPgsWaves);
+    const bool roll = p.mu_r > 0.f;
+    const dim3 grid((unsigned)(env ? z.plan_blocks : z.pgs_grid));
+    const dim3 blk(env && !z.env_small ? kEnvBlk : 64 * (z.pgs_wide ? kPgsWide : kPgsWaves));
     const size_t lds = env ? (size_t)z.lds_cap * 32 : (size_t)z.grp_f4 * 16;
     if (grid.x == 0) return;
     if (env) {
-        void (*k)(DevBuffers, StepParams, int, int, int, int) =
-            z.env_small ? (p.mu_r > 0.f ? k_pgs_env<true, kPgsWaves> : k_pgs_env<false, kPgsWaves>)
-                        : (p.mu_r > 0.f ? k_pgs_env<true, kEnvWaves> : k_pgs_env<false, kEnvWaves>);
+        auto k = !z.env_small ? (roll ? k_pgs_env<true, kEnvWaves> : k_pgs_env<false, kEnvWaves>)
+                 : z.pgs_wide ? (roll ? k_pgs_env<true, kPgsWide> : k_pgs_env<false, kPgsWide>)
+                              : (roll ? k_pgs_env<true, kPgsWaves> : k_pgs_env<false, kPgsWaves>);
         hipLaunchKernelGGL(k, grid, blk, lds, s, b, p, sw, slot, z.lds_cap, flow);
-    } else if (p.mu_r > 0.f)
-        hipLaunchKernelGGL((k_pgs<true, kPgsWaves>), grid, blk, lds, s, b, p, sw, slot, z.grp_lds, z.grp_f4, flow);
-    else
-        hipLaunchKernelGGL((k_pgs<false, kPgsWaves>), grid, blk, lds, s, b, p, sw, slot, z.grp_lds, z.grp_f4, flow);
+    } else {
+        auto k = z.pgs_wide ? (roll ? k_pgs<true, kPgsWide> : k_pgs<false, kPgsWide>)
+                            : (roll ? k_pgs<true, kPgsWaves> : k_pgs<false, kPgsWaves>);
+        hipLaunchKernelGGL(k, grid, blk, lds, s, b, p, sw, slot, z.grp_lds, z.grp_f4, flow);
+    }
 }
 
 // ---------------------------------------------------------------------------
