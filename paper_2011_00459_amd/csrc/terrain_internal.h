@@ -172,14 +172,15 @@ struct UnitStats {
     double r1_trial[2];    // first-sweep residual from the learned / previous start
     uint32_t imp_any;      // some contact of the unit is an impact this step
     uint32_t imp_sweeps;   // sweeps of the unit's impact stage
-    uint32_t pad2[2];
+    uint32_t colours;      // colours of the unit's contacts (0: it has none)
+    uint32_t pad2;
 };
 
 struct Counters {
     uint32_t n_raw;        // contacts found by detection (may exceed capacity)
     uint32_t n_pairs;
     uint32_t overflow;     // kOvf* / kFail* bits, sticky within a step
-    uint32_t n_colours;
+    uint32_t pad0;
     uint32_t failed;       // OR of the overflow bits of every step since the host last read it
     uint32_t n_pos;        // solve-order positions handed out to owners
     uint32_t pad[10];

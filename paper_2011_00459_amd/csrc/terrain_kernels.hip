@@ -752,7 +752,6 @@ __global__ __launch_bounds__(kColBlk) void k_colour(DevBuffers b, int n, int per
     }
     state.order();
     __syncthreads();
-    int top = 0;
     bool left = true, ovf = false;
     for (int pass = 0; pass < max_pass && left; ++pass) {
         left = false;
@@ -776,7 +775,6 @@ __global__ __launch_bounds__(kColBlk) void k_colour(DevBuffers b, int n, int per
                     if (used == ~0ull) { ovf = true; break; }
                     const int col = __builtin_ctzll(~used);
                     b.colour[c] = col;
-                    top = max(top, col + 1);
                     state.set_used(i, used | (1ull << col));
                     continue;
                 }
@@ -815,7 +813,6 @@ __global__ __launch_bounds__(kColBlk) void k_colour(DevBuffers b, int n, int per
             const int col = __builtin_ctzll(~both);
             const unsigned long long bit = 1ull << col;
             __hip_atomic_store(&b.colour[c], col, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            top = max(top, col + 1);
             moved = true;
             state.set_used(i, mine | bit);
             if (how != kAcrossAnswer) state.set_used((int)how, theirs | bit);
@@ -836,9 +833,6 @@ __global__ __launch_bounds__(kColBlk) void k_colour(DevBuffers b, int n, int per
             break;
         }
     }
-    // one atomic per wave (same-address atomics from every lane serialise)
-    for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o, 64));
-    if ((threadIdx.x & 63) == 0 && top) atomicMax(&b.cnt->n_colours, (uint32_t)top);
     if (ovf) atomicOr(&b.cnt->overflow, kOvfColours);
     if (left) atomicOr(&b.cnt->overflow, kFailColouring);
 }
@@ -983,7 +977,10 @@ __global__ __launch_bounds__(kOrdBlk) void k_order(DevBuffers b)
             }
         }
         for (int k = 32; k > 0; k >>= 1) ncol = max(ncol, __shfl_xor(ncol, k, 64));
-        if (lane == 0 && ncol) atomicMax(&b.env_ncol[S.w], (uint32_t)ncol);
+        if (lane == 0 && ncol) {
+            atomicMax(&b.env_ncol[S.w], (uint32_t)ncol);
+            atomicMax(&b.ustats[E.unit].colours, (uint32_t)ncol);
+        }
     }
     __syncthreads();
     if (threadIdx.x < kOrdBuckets) {
@@ -2392,7 +2389,8 @@ __device__ __forceinline__ void solve_region(const DevBuffers& b, const StepPara
 // SIMD issues: the update's hundred operations, its bodies out of LDS and
 // back, a barrier.  Everything else is kept off it: the rows of the next phase
 // are fetched before the update, into the other of two sets of registers,
-// unconditionally (a thread without a contact reads the last one's).
+// unconditionally (a thread without a contact reads the last one's, so there
+// must be one).
 template <bool ROLL, int NW, RowHome HOME>
 __device__ __forceinline__ void solve_alone(const DevBuffers& b, const StepParams& p, const SolveTask& T, uint32_t ncol, int sweeps_cap,
                             int slot, float4* lds, int nb, const BlockRows<ROLL, HOME>& br, SolveShared<NW>& sh)
@@ -2401,7 +2399,7 @@ __device__ __forceinline__ void solve_alone(const DevBuffers& b, const StepParam
     const uint32_t tid = threadIdx.x;
     float4 *sv = lds, *sw = lds + nb;
     const int sg0 = b.own_idx[T.owner], sg1 = b.own_idx[T.owner + 1];
-    if (ncol == 0 || sweeps_cap <= 0) {
+    if (ncol == 0 || br.n == 0 || sweeps_cap <= 0) {
         if (tid == 0) write_stats(b, T.unit, slot, 0, 0.0, 0.0);
         return;
     }
@@ -2539,7 +2537,8 @@ __global__ __launch_bounds__(64 * NW) void k_pgs(DevBuffers b, StepParams p, int
     if (q.x < 0) return;
     const SolveTask T{q.x, (unsigned)q.y & 0xffffu, (unsigned)q.y >> 16, (unsigned)q.z, q.w & 0x7fffffff};
     bool through = q.w < 0;
-    uint32_t ncol = b.cnt->n_colours;
+    // (of the unit: one whose envs have no contacts runs no sweep)
+    uint32_t ncol = b.ustats[T.unit].colours;
     if (slot == kSlotImpact && !b.ustats[T.unit].imp_any) ncol = 0;  // no impact in the unit
     uint32_t* counter = &b.cnt->bar[blockIdx.x % kGroups][0];
     if ((T.K > 1 || flow) && !through) {
