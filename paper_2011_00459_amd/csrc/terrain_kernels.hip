@@ -29,7 +29,7 @@
 namespace trk {
 
 constexpr int kBlk = 256;
-constexpr unsigned long long kNoMask = ~0ull;  // no colours sent yet (DevBuffers::cmsg)
+constexpr unsigned long long kNoMask = ~0ull;  // no colours sent yet (DevBuffers::cmsg); a full mask is never sent
 #ifndef TRK_BARRIER_SPINS
 #define TRK_BARRIER_SPINS (1l << 22)
 #endif
@@ -769,10 +769,12 @@ __global__ __launch_bounds__(kColBlk) void k_colour(DevBuffers b, int n, int per
                     state.set_next(i, kNextDone);
                     continue;
                 }
+                // more contacts than colours (also for the block across, which
+                // would take the full mask for none sent)
+                if (used == ~0ull) { ovf = true; break; }
                 const uint2 en = b.pinc[pos];
                 const uint32_t c = en.x;
                 if (en.y == kBoundary) {  // conflicts at its sphere only
-                    if (used == ~0ull) { ovf = true; break; }
                     const int col = __builtin_ctzll(~used);
                     b.colour[c] = col;
                     state.set_used(i, used | (1ull << col));
