@@ -35,6 +35,11 @@ constexpr int kFlowMaxSweeps = 8192;  // longest counter-ordered solve
 // slower, but one XCD's 32 blocks are full (20,000 spheres: 1.27 ms on one
 // XCD, 1.63 on all; 35,000: 1.93 and 1.38; 70,000: 2.63 and 1.47).
 constexpr int64_t kRegionAlone = 1700, kRegionAloneRolling = 1400, kRegionSpheres = 400, kSpreadMin = 27000;
+// The counter-ordered solve keeps its bodies in memory and gains nothing from
+// one block or large regions: 100 spheres a block (a step of 600 spheres takes
+// 0.83 ms at 50 and 100, 0.91 at 200, 0.90 at 400; 1,600 spheres 0.88, 0.89,
+// 0.94 and 0.98, one block 1.79; from 6,000 on the same up to 200).
+constexpr int64_t kFlowSpheres = 100;
 constexpr int64_t kWideRegion = 600;      // largest region of 512-thread blocks (beside kPgsWide)
 constexpr int64_t kEnvSmallRegion = 800;  // largest region of the per-env plan of small regions
 
@@ -349,12 +354,12 @@ double plan_small(const tr_scene* s, const std::vector<int>& order, int B, int l
     return best;
 }
 
-// Blocks per XCD of a grouped or spread solve of n spheres.
-int region_blocks(const tr_scene* s, int64_t n, bool wide, int bpx)
+// Blocks per XCD of a grouped or spread solve of n spheres (flow: counter-ordered).
+int region_blocks(const tr_scene* s, int64_t n, bool wide, bool flow, int bpx)
 {
-    if (!wide && n <= region_alone(s)) return 1;
-    const int64_t per = wide ? (n + kGroups - 1) / kGroups : n;
-    return (int)std::max<int64_t>(1, std::min<int64_t>(bpx, (per + kRegionSpheres - 1) / kRegionSpheres));
+    if (!wide && !flow && n <= region_alone(s)) return 1;
+    const int64_t per = wide ? (n + kGroups - 1) / kGroups : n, region = flow ? kFlowSpheres : kRegionSpheres;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(bpx, (per + region - 1) / region));
 }
 
 // the tables of a step's report, laid out from base: the counters, the body
@@ -580,7 +585,7 @@ int rebuild_plan(tr_scene* s)
                 if (s->env_host[e].group == g) n += s->env_host[e].n;
             if (n == 0) continue;
             const bool wide = E == 1 && !flow && n > kSpreadMin;
-            const int per = region_blocks(s, n, wide, bpx), K = wide ? kGroups * per : per;
+            const int per = region_blocks(s, n, wide, flow, bpx), K = wide ? kGroups * per : per;
             const int base = (int)own_idx.size();
             int off = 0;
             for (int e = 0; e < E; ++e) {

@@ -21,6 +21,7 @@ GROUPED = dict(mode="grouped", blocks_per_xcd=32, dataflow=0)
 SPREAD = dict(mode="spread", blocks_per_xcd=32, dataflow=0)
 FLOW = dict(mode="grouped", blocks_per_xcd=32, dataflow=1)
 
+FEW = [(5, 5, 4), (101, 1, 1), (1, 1, 1)]        # 100, 101 and 1: one or two blocks of update counters
 WIDE = [(41, 27, 25)]                           # 27,675 spheres: all XCDs
 MIXED = [(19, 14, 10), (6, 5, 4), (23, 14, 11)]  # 2,660, 120 and 3,542: a cluster, one block, a cluster
 
@@ -55,8 +56,8 @@ def states(specs, cfg, steps=2):
 
 @pytest.mark.parametrize("kw", [{}, dict(roll=True), dict(impact=True), dict(warm_start="learned")],
                          ids=["plain", "rolling", "impact", "learned"])
-@pytest.mark.parametrize("dims,cfg", [(MIXED, GROUPED), (MIXED, FLOW), (WIDE, GROUPED), (WIDE, SPREAD), (WIDE, FLOW)],
-                         ids=["clusters", "clusters_flow", "wide_grouped", "wide_spread", "one_xcd_flow"])
+@pytest.mark.parametrize("dims,cfg", [(MIXED, GROUPED), (MIXED, FLOW), (FEW, FLOW), (WIDE, GROUPED), (WIDE, SPREAD), (WIDE, FLOW)],
+                         ids=["clusters", "clusters_flow", "few_flow", "wide_grouped", "wide_spread", "one_xcd_flow"])
 def test_clusters_are_bitwise_one_block(dims, cfg, kw):
     specs = beds(dims, **kw)
     sa, a = states(specs, ALONE)
