@@ -83,11 +83,14 @@ __device__ inline double lane_value(double v, int l)
 // order are neighbours in space, so a block takes a run of them and adds
 // their shares up in LDS over the box of voxels that they reach together; one
 // atomic a voxel and value is left for the whole run (80 us with 8 waves a
-// block, 99 with 4: what bounds it is the chain of an exponential).  A run whose box
-// does not fit is cut where it stops fitting; a particle whose own box does
-// not fit goes to memory directly.  A wave takes a particle at a time, a lane
-// a column of its voxels.  (The exponential as the product of its three axes',
-// computed once a particle, took 6 us less and rounds twice more.)
+// block, 99 with 4: what bounds it is the chain of an exponential).  A run
+// whose box does not fit is cut where it stops fitting.  Particles that share
+// no box (it would be larger than theirs together, or too large), as after
+// positions were set in any order, go to memory directly: 50,000 of them with
+// R = l0 / 2 take 120 us, where a box each took 408 and a thread a particle
+// 155.  A wave takes a particle at a time, a lane a column of its voxels.  (The
+// exponential as the product of its three axes', computed once a particle,
+// took 6 us less and rounds twice more.)
 constexpr int kCgWaves = 8;
 constexpr int kCgVox = 2048;   // voxels of a run's box: 64 KB of LDS, two blocks a CU
 constexpr int kCgAxis = 64;    // voxels of a particle's box along the three axes together
@@ -122,8 +125,21 @@ __global__ __launch_bounds__(64 * kCgWaves) void k_coarse_grain_smooth(DevBuffer
     const bool some = lane < np && lo[0] <= hi[0] && lo[1] <= hi[1] && lo[2] <= hi[2];
     const double sq = sqrt(2.0 * 3.14159265358979323846) * R;
     const double norm = 1.0 / (sq * sq * sq), inv = 2.0 * R * R;
-    const unsigned long long alone = __ballot(
-        some && (double)(hi[0] - lo[0] + 1) * (hi[1] - lo[1] + 1) * (hi[2] - lo[2] + 1) > (double)kCgVox);
+    auto volume = [](const int* l, const int* h) {
+        return l[0] <= h[0] && l[1] <= h[1] && l[2] <= h[2]
+                   ? (double)(h[0] - l[0] + 1) * (h[1] - l[1] + 1) * (h[2] - l[2] + 1) : 0.0;
+    };
+    // voxels of the largest box, and the particles that share one with the next
+    double most = some ? volume(lo, hi) : 0.0;
+    for (int o = 32; o > 0; o >>= 1) most = fmax(most, __shfl_xor(most, o));
+    int nl[3], nh[3];
+    for (int k = 0; k < 3; ++k) {
+        const int l = some ? lo[k] : 0x7fffffff, h = some ? hi[k] : -1;
+        nl[k] = min(l, __shfl_down(l, 1));
+        nh[k] = max(h, __shfl_down(h, 1));
+    }
+    const double both = volume(nl, nh);
+    const unsigned long long near = __ballot(lane + 1 < np && both <= (double)kCgVox && both <= 2.0 * most);
     for (int q0 = 0; q0 < np;) {
         // the box of particles q0 .. lane, and the first lane at which it no longer fits
         int bl[3], bh[3];
@@ -136,14 +152,14 @@ __global__ __launch_bounds__(64 * kCgWaves) void k_coarse_grain_smooth(DevBuffer
                 const int l = __shfl_up(bl[k], o), h = __shfl_up(bh[k], o);
                 if (lane >= o) { bl[k] = min(bl[k], l); bh[k] = max(bh[k], h); }
             }
-        const bool any = bl[0] <= bh[0];
-        const double vol = any ? (double)(bh[0] - bl[0] + 1) * (bh[1] - bl[1] + 1) * (bh[2] - bl[2] + 1) : 0.0;
+        const double vol = volume(bl, bh);
         const unsigned long long over = __ballot(vol > (double)kCgVox && lane >= q0);
-        const int first = over ? __ffsll((long long)over) - 1 : np;
-        const bool local = first > q0;  // (else particle q0 does not fit, and neither may those after it)
-        const unsigned long long fits = ~alone >> q0;
+        const int first = over ? __ffsll((long long)over) - 1 : np, n = first - q0;
+        const bool local = n > 1 && lane_value(vol, max(first, 1) - 1) <= n * most;
+        const int from = max(first, q0 + 1);
+        const unsigned long long pairs = from < 64 ? near >> from : 0ull;
         const int q1 = __builtin_amdgcn_readfirstlane(
-            min(np, local ? first : (fits ? q0 + __ffsll((long long)fits) - 1 : 64)));
+            local ? first : (pairs ? from + __ffsll((long long)pairs) - 1 : np));
         int base[3], side[3];
         for (int k = 0; k < 3; ++k) {
             base[k] = lane_value(bl[k], q1 - 1);
@@ -152,8 +168,9 @@ __global__ __launch_bounds__(64 * kCgWaves) void k_coarse_grain_smooth(DevBuffer
         const int nbox = local && side[0] > 0 ? side[0] * side[1] * side[2] : 0;
         for (int t = threadIdx.x; t < nbox; t += 64 * kCgWaves)
             for (int k = 0; k < 4; ++k) acc[k][t] = 0.0;
-        __syncthreads();
-        for (int p = q0 + wave; p < q1; p += kCgWaves) {
+        if (local) __syncthreads();
+        // (particle p is wave p's, mod their number, whatever the cuts)
+        for (int p = q0 + ((wave - q0) & (kCgWaves - 1)); p < q1; p += kCgWaves) {
             if (!lane_value((int)some, p)) continue;
             int plo[3], ps[3];
             double px[3], pmv[3];
@@ -201,6 +218,8 @@ __global__ __launch_bounds__(64 * kCgWaves) void k_coarse_grain_smooth(DevBuffer
             }
             __builtin_amdgcn_wave_barrier();  // the tables are rewritten for the next particle
         }
+        q0 = q1;
+        if (!local) continue;
         __syncthreads();
         for (int t = threadIdx.x; t < nbox; t += 64 * kCgWaves) {
             const double mass = acc[0][t];
@@ -211,7 +230,6 @@ __global__ __launch_bounds__(64 * kCgWaves) void k_coarse_grain_smooth(DevBuffer
             for (int k = 0; k < 3; ++k) atomicAdd(&mom[3 * id + k], acc[1 + k][t]);
         }
         __syncthreads();
-        q0 = q1;
     }
 }
 
