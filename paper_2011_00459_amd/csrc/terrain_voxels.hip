@@ -17,6 +17,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "terrain_internal.h"
 
@@ -480,32 +481,37 @@ __device__ inline bool in_wedge_set(const WedgeSet& ws, double x, double y, doub
     return false;
 }
 
-// A block takes kCutCols neighbouring columns, its kCutParts parts every so
+// A block takes kCols neighbouring columns, its kBlk / kCols parts every so
 // manieth wedge of a column (a wedge is a chain of up to five divisions) and
-// then every so manieth run of voxels above the cut.  256 x 256 x 128 voxels
-// under eight wedges: 21 us (one thread a column: 28).
-constexpr int kCutCols = 32, kCutParts = kBlk / kCutCols;
+// then every so manieth run of voxels above the cut.  Eight parts while the
+// columns alone leave the chip short of waves, a thread a column beyond: under
+// eight wedges 256 x 256 x 128 voxels take 36 us with eight parts, 47 with
+// one; 430 x 430 x 128 50 and 63; 512 x 512 x 32 42 and 34, 512 x 512 x 128
+// 137 and 66 (the parts' planes lie 2 MB apart).
+constexpr int64_t kCutFew = 200000;
 
+template <int kCols>
 __global__ __launch_bounds__(kBlk) void k_convert_cut(tr_voxel_grid g, double rho_b, WedgeSet ws, double* phi,
                                                       const double* wc, double* mf, double* total)
 {
 #pragma clang fp contract(off)
-    __shared__ double bottom[kCutParts][kCutCols], sums[kBlk / 64];
+    constexpr int kParts = kBlk / kCols;
+    __shared__ double bottom[kParts][kCols], sums[kBlk / 64];
     const int64_t nxy = (int64_t)g.nx * g.ny;
-    const int col = threadIdx.x % kCutCols, part = threadIdx.x / kCutCols;
-    const int64_t c = (int64_t)blockIdx.x * kCutCols + col;
+    const int col = threadIdx.x % kCols, part = threadIdx.x / kCols;
+    const int64_t c = (int64_t)blockIdx.x * kCols + col;
     const int i = (int)(c % g.nx), j = (int)(c / g.nx);
     const double x = g.origin[0] + (i + 0.5) * g.l0, y = g.origin[1] + (j + 0.5) * g.l0;
     double zcut = INFINITY, lo;
     int at = 0;  // number of the wedge over all ranges
     for (int r = 0; r < ws.n_ranges; ++r) {
-        for (int k = (part + kCutParts - at % kCutParts) % kCutParts; k < ws.cnt[r]; k += kCutParts)
+        for (int k = (part + kParts - at % kParts) % kParts; k < ws.cnt[r]; k += kParts)
             if (wedge_bottom(ws.base[ws.off[r] + k], x, y, lo)) zcut = fmin(zcut, lo);
         at += ws.cnt[r];
     }
     bottom[part][col] = zcut;
     __syncthreads();
-    for (int q = 0; q < kCutParts; ++q) zcut = fmin(zcut, bottom[q][col]);
+    for (int q = 0; q < kParts; ++q) zcut = fmin(zcut, bottom[q][col]);
     double sum = 0.0;
     if (c < nxy && zcut != INFINITY) {
         const double V0 = g.l0 * g.l0 * g.l0;
@@ -515,7 +521,7 @@ __global__ __launch_bounds__(kBlk) void k_convert_cut(tr_voxel_grid g, double rh
         const double kc = floor((zcut - g.origin[2]) / g.l0) - 1.0;
         const int k_start = kc <= 0.0 ? 0 : (kc >= (double)g.nz ? g.nz : (int)kc);
         constexpr int kChunk = 4;
-        for (int k0 = k_start + part * kChunk; k0 < g.nz; k0 += kCutParts * kChunk) {
+        for (int k0 = k_start + part * kChunk; k0 < g.nz; k0 += kParts * kChunk) {
             double fc[kChunk], wcc[kChunk], mc[kChunk];
 #pragma unroll
             for (int q = 0; q < kChunk; ++q) {
@@ -624,62 +630,70 @@ __global__ void k_convert_deposit(tr_voxel_grid g, double rho_b, double w_dep, W
     if (total && sum > 0.0) atomicAdd(total, sum);
 }
 
-// The deposit on tiles of 64 neighbouring columns of at most kTileNz voxels: a
-// wave reads a plane of the tile as whole lines, a block's eight waves take
-// every eighth plane.  The voxels whose fluid falls are marked in parallel
-// (bit masks per column), as is each column's first non-full voxel; one lane
-// per column then replays the fills over its marked voxels in increasing
-// height, as the per-thread kernel does.  Fills start at the first non-full
-// voxel and rarely climb far: occupancy and compaction of the kWin voxels from
-// there are held in LDS (a fill beyond them reads and writes memory directly),
-// the voxel being filled in registers, and the next marked voxel's mass is on
-// its way meanwhile.  The block writes back what changed.
+// The deposit on tiles of kCols neighbouring columns of at most kTileNz
+// voxels: a wave reads whole lines of one plane (or of four, with 16 columns),
+// a block's waves take every so manieth.  The voxels whose fluid falls are
+// marked in parallel (bit masks per column), as is each column's first non-full
+// voxel; one lane per column then replays the fills over its marked voxels in
+// increasing height, as the per-thread kernel does.  Fills start at the first
+// non-full voxel and rarely climb far: occupancy and compaction of the kWin
+// voxels from there are held in LDS (a fill beyond them reads and writes memory
+// directly), the voxel being filled in registers, and the next marked voxel's
+// mass is on its way meanwhile.  The block writes back what changed.
 //
 // Bound by the replay's chain, two divisions and a few LDS accesses a fill
-// (about 0.4 us), of the column with most fills; 64 columns share its latency,
-// and 256 x 256 columns are 1,024 blocks, four a CU, all at once.
-// 256 x 256 x 128 voxels under eight wedges: 98 us (16 columns a block with
-// every mass in LDS and wedge by wedge for every voxel: 156; 16 planes a wave,
-// for which the registers leave three blocks a CU: 120); 200 x 200 x 150, which
-// took a thread a column, 1,100 -> 90.
-constexpr int kTileCols = 64;
+// (about 0.4 us), of the column with most fills.  With 64 columns a tile many
+// columns share its latency, and 256 x 256 columns are 1,024 blocks, four a CU,
+// all at once; with 16 a wave waits for the longest of fewer columns, and few
+// columns still give blocks to all CUs.  Under eight wedges, with 16 and 64
+// columns a tile: 64 x 64 x 64 voxels 49 and 61 us, 160 x 160 x 60 59 and 63,
+// 200 x 200 x 60 74 and 68, 256 x 256 x 128 182 and 137 (without wedges 29 and
+// 40, 33 and 42, 40 and 43, 128 and 104).  16 columns with every mass in LDS
+// and wedge by wedge for every voxel took 59, 62, 70 and 183 us (without
+// wedges 32, 36, 38 and 100), and a thread a column 1,100 us for 200 x 200 x
+// 150, which takes 141.
+constexpr int64_t kFewColumns = 32768;
+constexpr int kTileBlk = 512;
 constexpr int kTileNz = 1024;
-constexpr int kTileRows = 8;  // waves of a block
 constexpr int kTilePer = 8;   // planes a wave reads at once
 constexpr int kWin = 28;
-constexpr int kMass = 16;     // planes of masses in LDS at once
 
-__global__ void __launch_bounds__(kTileCols* kTileRows, 8) k_convert_deposit_tile(tr_voxel_grid g, double rho_b,
-                                                                               double w_dep, WedgeSet ws,
-                                                                               const double* rho_p, double* phi,
-                                                                               double* wc, double* mf, double* total)
+// kCols: columns of a tile; kMass: planes of masses in LDS at once; kOcc: waves a SIMD
+template <int kCols, int kMass, int kOcc>
+__global__ void __launch_bounds__(kTileBlk, kOcc) k_convert_deposit_tile(tr_voxel_grid g, double rho_b,
+                                                                         double w_dep, WedgeSet ws,
+                                                                         const double* rho_p, double* phi,
+                                                                         double* wc, double* mf, double* total)
 {
 #pragma clang fp contract(off)
-    __shared__ double P[kWin][kTileCols], W[kWin][kTileCols], M[kMass][kTileCols];
-    __shared__ int first_free[kTileCols], range[kTileCols][2];
+    constexpr int kRows = kTileBlk / kCols;
+    typedef std::conditional_t<kMass <= 32, unsigned, unsigned long long> Bits;
+    static_assert(64 % kRows == 0 && kMass % kRows == 0 && 64 % kMass == 0, "planes of a thread and of a mask word");
+    __shared__ double P[kWin][kCols], W[kWin][kCols], M[kMass][kCols];
+    __shared__ int first_free[kCols], range[kCols][2];
     __shared__ unsigned long long any;  // kMass planes a bit: some column has a marked voxel
-    HIP_DYNAMIC_SHARED(unsigned long long, mask)  // [words][kTileCols]
+    HIP_DYNAMIC_SHARED(unsigned long long, mask)  // [words][kCols]
     const int64_t nxy = (int64_t)g.nx * g.ny;
-    const int col = threadIdx.x % kTileCols, row = threadIdx.x / kTileCols;
-    const int64_t c = (int64_t)blockIdx.x * kTileCols + col;
+    const int col = threadIdx.x % kCols, row = threadIdx.x / kCols;
+    const int64_t c = (int64_t)blockIdx.x * kCols + col;
     const bool live = c < nxy;
     const int nz = g.nz, words = (nz + 63) / 64;
     const double x = g.origin[0] + ((int)(c % g.nx) + 0.5) * g.l0, y = g.origin[1] + ((int)(c / g.nx) + 0.5) * g.l0;
-    for (int w = row; w < words; w += kTileRows) mask[w * kTileCols + col] = 0ull;
+    for (int w = row; w < words; w += kRows) mask[w * kCols + col] = 0ull;
     if (row == 0) first_free[col] = nz;
     if (threadIdx.x == 0) any = 0ull;
     __syncthreads();
     unsigned long long mine = 0ull;
-    for (int k0 = row; k0 < nz; k0 += kTileRows * kTilePer) {
+    for (int k0 = row; k0 < nz; k0 += kRows * kTilePer) {
         double mv[kTilePer], rv[kTilePer];
 #pragma unroll
         for (int t = 0; t < kTilePer; ++t) {
-            const int k = k0 + t * kTileRows;
+            const int k = k0 + t * kRows;
             mv[t] = live && k < nz ? mf[(int64_t)k * nxy + c] : 0.0;
         }
 #pragma unroll
         for (int t = 0; t < kTilePer; ++t) {
-            const int k = k0 + t * kTileRows;
+            const int k = k0 + t * kRows;
             rv[t] = mv[t] > 0.0 ? rho_p[(int64_t)k * nxy + c] : 1.0;
         }
         unsigned fall = 0u;  // bit t: plane k0 + 8 t is marked
@@ -708,7 +722,7 @@ __global__ void __launch_bounds__(kTileCols* kTileRows, 8) k_convert_deposit_til
                     const double at = pl[0] * x + pl[1] * y;
 #pragma unroll
                     for (int t = 0; t < kTilePer; ++t) {
-                        const double z = g.origin[2] + (k0 + t * kTileRows + 0.5) * g.l0;
+                        const double z = g.origin[2] + (k0 + t * kRows + 0.5) * g.l0;
                         if (at + pl[2] * z - pl[3] > 0.0) in &= ~(1u << t);
                     }
                 }
@@ -716,38 +730,38 @@ __global__ void __launch_bounds__(kTileCols* kTileRows, 8) k_convert_deposit_til
             }
         }
         for (unsigned f = fall; f; f &= f - 1) {
-            const int k = k0 + (__ffs((int)f) - 1) * kTileRows;
-            atomicOr(&mask[(k >> 6) * kTileCols + col], 1ull << (k & 63));
+            const int k = k0 + (__ffs((int)f) - 1) * kRows;
+            atomicOr(&mask[(k >> 6) * kCols + col], 1ull << (k & 63));
             mine |= 1ull << (k / kMass);
         }
     }
     if (mine) atomicOr(&any, mine);
     __syncthreads();
     bool work = false;
-    for (int w = 0; w < words; ++w) work |= mask[w * kTileCols + col] != 0ull;
-    double mr[kMass / kTileRows];
+    for (int w = 0; w < words; ++w) work |= mask[w * kCols + col] != 0ull;
+    double mr[kMass / kRows];
     auto bring = [&](unsigned long long planes) {
         const int k0 = planes ? (__ffsll((long long)planes) - 1) * kMass : nz;
 #pragma unroll
-        for (int t = 0; t < kMass / kTileRows; ++t) {
-            const int k = k0 + row + t * kTileRows;
+        for (int t = 0; t < kMass / kRows; ++t) {
+            const int k = k0 + row + t * kRows;
             mr[t] = work && k < nz ? mf[(int64_t)k * nxy + c] : 0.0;
         }
     };
     unsigned long long planes = any;
     bring(planes);
     if (work)
-        for (int k0 = row; k0 < nz; k0 += kTileRows * kTilePer) {
+        for (int k0 = row; k0 < nz; k0 += kRows * kTilePer) {
             double pv[kTilePer];
 #pragma unroll
             for (int t = 0; t < kTilePer; ++t) {
-                const int k = k0 + t * kTileRows;
+                const int k = k0 + t * kRows;
                 pv[t] = k < nz ? phi[(int64_t)k * nxy + c] : 1.0;
             }
             int k = nz;
 #pragma unroll
             for (int t = kTilePer - 1; t >= 0; --t)
-                if (!(pv[t] >= 1.0)) k = k0 + t * kTileRows;
+                if (!(pv[t] >= 1.0)) k = k0 + t * kRows;
             if (k < nz) {
                 atomicMin(&first_free[col], k);
                 break;  // (the wave's later planes are higher)
@@ -756,7 +770,7 @@ __global__ void __launch_bounds__(kTileCols* kTileRows, 8) k_convert_deposit_til
     __syncthreads();
     const int ff = first_free[col];
     if (work)
-        for (int q = row; q < kWin && ff + q < nz; q += kTileRows) {
+        for (int q = row; q < kWin && ff + q < nz; q += kRows) {
             P[q][col] = phi[(int64_t)(ff + q) * nxy + c];
             W[q][col] = wc[(int64_t)(ff + q) * nxy + c];
         }
@@ -781,15 +795,14 @@ __global__ void __launch_bounds__(kTileCols* kTileRows, 8) k_convert_deposit_til
     for (; planes; planes &= planes - 1) {
         const int k0 = (__ffsll((long long)planes) - 1) * kMass;
 #pragma unroll
-        for (int t = 0; t < kMass / kTileRows; ++t) M[row + t * kTileRows][col] = mr[t];
+        for (int t = 0; t < kMass / kRows; ++t) M[row + t * kRows][col] = mr[t];
         __syncthreads();
         bring(planes & (planes - 1));
         if (row == 0) {
-            const unsigned long long word = mask[(k0 >> 6) * kTileCols + col];
-            unsigned mk = (unsigned)(word >> (k0 & 63)) & ((1u << kMass) - 1);
-            unsigned keep = 0u;
+            const unsigned long long word = mask[(k0 >> 6) * kCols + col];
+            Bits mk = (Bits)(word >> (k0 & 63)) & (Bits)(~0ull >> (64 - kMass)), keep = 0;
             while (mk) {
-                const int q = __ffs((int)mk) - 1;
+                const int q = (kMass <= 32 ? __ffs((int)mk) : __ffsll((long long)mk)) - 1;
                 mk &= mk - 1;
                 double m = M[q][col];
                 while (kk < nz && f0 >= 1.0) {
@@ -822,10 +835,10 @@ __global__ void __launch_bounds__(kTileCols* kTileRows, 8) k_convert_deposit_til
                 }
                 if (m != 0.0) {  // the column is full (or its occupancy no number): what is left stays fluid
                     mf[(int64_t)(k0 + q) * nxy + c] = 0.0 + m;
-                    keep |= 1u << q;
+                    keep |= (Bits)1 << q;
                 }
             }
-            if (keep) mask[(k0 >> 6) * kTileCols + col] = word & ~((unsigned long long)keep << (k0 & 63));
+            if (keep) mask[(k0 >> 6) * kCols + col] = word & ~((unsigned long long)keep << (k0 & 63));
         }
         __syncthreads();
     }
@@ -833,19 +846,20 @@ __global__ void __launch_bounds__(kTileCols* kTileRows, 8) k_convert_deposit_til
         range[col][0] = klo;
         range[col][1] = khi;
         if (total) {
-            for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+            for (int o = kCols / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
             if (col == 0 && sum > 0.0) atomicAdd(total, sum);  // one atomic per tile
         }
     }
     __syncthreads();
     if (work) {
         const int klo = range[col][0], khi = range[col][1];
+        constexpr unsigned long long every = ~0ull / ((1ull << kRows) - 1);  // every kRows-th bit
         for (int w = 0; w < words; ++w)
-            for (unsigned long long mk = mask[w * kTileCols + col] & (0x0101010101010101ull << row); mk; mk &= mk - 1) {
+            for (unsigned long long mk = mask[w * kCols + col] & (every << row); mk; mk &= mk - 1) {
                 const int k = w * 64 + (__ffsll((long long)mk) - 1);
                 mf[(int64_t)k * nxy + c] = 0.0;
             }
-        for (int q = row; q < kWin; q += kTileRows) {  // (above the window: written by the fills)
+        for (int q = row; q < kWin; q += kRows) {  // (above the window: written by the fills)
             const int k = ff + q;
             if (k >= klo && k <= khi) {
                 phi[(int64_t)k * nxy + c] = P[q][col];
@@ -866,8 +880,9 @@ void launch_convert_cut(const tr_voxel_grid& g, double rho_b, const WedgeSet& ws
 {
     const int64_t nxy = (int64_t)g.nx * g.ny;
     if (total) hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, s, total, (int64_t)1, 0.0);
-    hipLaunchKernelGGL(k_convert_cut, dim3((unsigned)cdiv(nxy, kCutCols)), dim3(kBlk), 0, s, g, rho_b, ws, phi, wc, mf,
-                       total);
+    const bool few = nxy <= kCutFew;
+    hipLaunchKernelGGL(few ? k_convert_cut<32> : k_convert_cut<kBlk>, dim3((unsigned)cdiv(nxy, few ? 32 : kBlk)),
+                       dim3(kBlk), 0, s, g, rho_b, ws, phi, wc, mf, total);
 }
 
 void launch_convert_deposit(const tr_voxel_grid& g, double rho_b, double w_dep, const WedgeSet& ws,
@@ -875,13 +890,16 @@ void launch_convert_deposit(const tr_voxel_grid& g, double rho_b, double w_dep, 
 {
     const int64_t nxy = (int64_t)g.nx * g.ny;
     if (total) hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, s, total, (int64_t)1, 0.0);
-    if (g.nz <= kTileNz)
-        hipLaunchKernelGGL(k_convert_deposit_tile, dim3((unsigned)cdiv(nxy, kTileCols)), dim3(kTileCols * kTileRows),
-                           (size_t)((g.nz + 63) / 64) * kTileCols * 8, s, g, rho_b, w_dep, ws, rho_p, phi, wc, mf,
-                           total);
-    else
+    if (g.nz <= kTileNz) {
+        const bool few = nxy <= kFewColumns;
+        const int cols = few ? 16 : 64;
+        auto k = few ? k_convert_deposit_tile<16, 64, 4> : k_convert_deposit_tile<64, 16, 8>;
+        hipLaunchKernelGGL(k, dim3((unsigned)cdiv(nxy, cols)), dim3(kTileBlk), (size_t)((g.nz + 63) / 64) * cols * 8, s,
+                           g, rho_b, w_dep, ws, rho_p, phi, wc, mf, total);
+    } else {
         hipLaunchKernelGGL(k_convert_deposit, dim3((unsigned)cdiv(nxy, kBlk)), dim3(kBlk), 0, s, g, rho_b, w_dep, ws,
                            rho_p, phi, wc, mf, total);
+    }
 }
 
 // ---------------------------------------------------------------------------
