@@ -41,6 +41,7 @@ constexpr int64_t kRegionAlone = 1700, kRegionAloneRolling = 1400, kRegionSphere
 // 0.94 and 0.98, one block 1.79; from 6,000 on the same up to 200).
 constexpr int64_t kFlowSpheres = 100;
 constexpr int64_t kWideRegion = 600;      // largest region of 512-thread blocks (beside kPgsWide)
+constexpr double kPlanRegion = 800.0;      // region of the per-env plan by spheres per block
 constexpr int64_t kEnvSmallRegion = 800;  // largest region of the per-env plan of small regions
 
 struct EnvHost {
@@ -469,17 +470,22 @@ int rebuild_plan(tr_scene* s)
                 for (const auto& st : sets_b) place_set(blk, st);
             }
         } else {
-            // T: spheres per block (given, or the mean load).  Envs above T get
-            // ceil(n / T) blocks of one XCD lane; the rest are packed (first fit,
-            // largest first) into sets of at most T spheres and 16 envs, each solved
-            // by one block at once, placed largest first on the least loaded block (a
-            // cluster share counts twice its spheres).
+            // T: spheres per block, given or kPlanRegion where that gives every
+            // env its blocks (no LDS for bodies, or an env too large for the
+            // automatic plans; 20,000 spheres without LDS take 1.18 ms a step at
+            // 800, 1.54 at 1,500, 2.34 at 2,500 and 3.54 at 4,096; 256 envs of
+            // 3,000, 3,000 a block, 6.1 ms at 3,000 and 5.2 at 4,096).
+            // Envs above T get ceil(n / T) blocks of one XCD lane; the rest are
+            // packed (first fit, largest first) into sets of at most T spheres
+            // and 16 envs, each solved by one block at once, placed largest first
+            // on the least loaded block (a cluster share counts twice its
+            // spheres).
+            const double mean = total / B;
             const double T = s->cfg.cluster_particles > 0 ? (double)s->cfg.cluster_particles
-                                                           : std::max(total / B, 4096.0);
+                             : mean <= kPlanRegion        ? kPlanRegion
+                                                          : std::max(mean, 4096.0);
             // single-block solves only: an env too large for LDS takes a block of
-            // its own (measured on MI355X, a multi-block share pays about 12 us of
-            // cross-block barrier per colour, where one block of 1,024 threads
-            // solving the env alone meets at workgroup barriers)
+            // its own, in which nothing waits for another block
             const bool solo = s->cfg.cluster_particles == TR_CLUSTER_NONE;
             const double set_cap = solo ? (double)std::max(lds_cap, 1) : T;
             std::vector<double> load(B, 0.0);

@@ -19,6 +19,7 @@ T = pytest.importorskip("paper_2011_00459_amd.terrain")
 ALONE = dict(mode="per_env", lds_particles=100000, cluster_particles=-1, dataflow=0)
 GROUPED = dict(mode="grouped", blocks_per_xcd=32, dataflow=0)
 SPREAD = dict(mode="spread", blocks_per_xcd=32, dataflow=0)
+NO_LDS = dict(mode="per_env", lds_particles=0, cluster_particles=0, dataflow=0)
 FLOW = dict(mode="grouped", blocks_per_xcd=32, dataflow=1)
 
 FEW = [(5, 5, 4), (101, 1, 1), (1, 1, 1)]        # 100, 101 and 1: one or two blocks of update counters
@@ -56,8 +57,8 @@ def states(specs, cfg, steps=2):
 
 @pytest.mark.parametrize("kw", [{}, dict(roll=True), dict(impact=True), dict(warm_start="learned")],
                          ids=["plain", "rolling", "impact", "learned"])
-@pytest.mark.parametrize("dims,cfg", [(MIXED, GROUPED), (MIXED, FLOW), (FEW, FLOW), (WIDE, GROUPED), (WIDE, SPREAD), (WIDE, FLOW)],
-                         ids=["clusters", "clusters_flow", "few_flow", "wide_grouped", "wide_spread", "one_xcd_flow"])
+@pytest.mark.parametrize("dims,cfg", [(MIXED, GROUPED), (MIXED, FLOW), (FEW, FLOW), (MIXED, NO_LDS), (WIDE, GROUPED), (WIDE, SPREAD), (WIDE, FLOW)],
+                         ids=["clusters", "clusters_flow", "few_flow", "no_lds", "wide_grouped", "wide_spread", "one_xcd_flow"])
 def test_clusters_are_bitwise_one_block(dims, cfg, kw):
     specs = beds(dims, **kw)
     sa, a = states(specs, ALONE)
