@@ -180,7 +180,7 @@ struct Counters {
     uint32_t n_raw;        // contacts found by detection (may exceed capacity)
     uint32_t n_pairs;
     uint32_t overflow;     // kOvf* / kFail* bits, sticky within a step
-    uint32_t pad0;
+    uint32_t n_colours;
     uint32_t failed;       // OR of the overflow bits of every step since the host last read it
     uint32_t n_pos;        // solve-order positions handed out to owners
     uint32_t pad[10];

@@ -910,10 +910,11 @@ __global__ __launch_bounds__(kOrdBlk) void k_order(DevBuffers b)
 {
     __shared__ uint32_t wc[kOrdWaves][kOrdBuckets];
     __shared__ uint32_t bst[kOrdBuckets + 1];
-    __shared__ uint32_t base;
+    __shared__ uint32_t base, unit_col;
     const int o = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int sg0 = b.own_idx[o], sg1 = b.own_idx[o + 1];
     for (int k = threadIdx.x; k < kOrdWaves * kOrdBuckets; k += kOrdBlk) wc[0][k] = 0;
+    if (threadIdx.x == 0) unit_col = 0;
     for (int sg = sg0; sg < sg1; ++sg) {
         const int4 S = b.own_seg[sg];
         const EnvDev& E = b.envs[S.w];
@@ -981,7 +982,7 @@ __global__ __launch_bounds__(kOrdBlk) void k_order(DevBuffers b)
         for (int k = 32; k > 0; k >>= 1) ncol = max(ncol, __shfl_xor(ncol, k, 64));
         if (lane == 0 && ncol) {
             atomicMax(&b.env_ncol[S.w], (uint32_t)ncol);
-            atomicMax(&b.ustats[E.unit].colours, (uint32_t)ncol);
+            atomicMax(&unit_col, (uint32_t)ncol);  // (an owner's envs are of one unit)
         }
     }
     __syncthreads();
@@ -1003,6 +1004,10 @@ __global__ __launch_bounds__(kOrdBlk) void k_order(DevBuffers b)
         if (lane == 63) {
             bst[kOrdBuckets] = inc;
             base = atomicAdd(&b.cnt->n_pos, inc);
+            if (unit_col) {
+                atomicMax(&b.cnt->n_colours, unit_col);
+                atomicMax(&b.ustats[b.envs[b.own_seg[sg0].w].unit].colours, unit_col);
+            }
         }
     }
     __syncthreads();
@@ -2401,7 +2406,7 @@ __device__ __forceinline__ void solve_alone(const DevBuffers& b, const StepParam
     const uint32_t tid = threadIdx.x;
     float4 *sv = lds, *sw = lds + nb;
     const int sg0 = b.own_idx[T.owner], sg1 = b.own_idx[T.owner + 1];
-    if (ncol == 0 || br.n == 0 || sweeps_cap <= 0) {
+    if (ncol == 0 || sweeps_cap <= 0) {
         if (tid == 0) write_stats(b, T.unit, slot, 0, 0.0, 0.0);
         return;
     }
@@ -2539,8 +2544,8 @@ __global__ __launch_bounds__(64 * NW) void k_pgs(DevBuffers b, StepParams p, int
     if (q.x < 0) return;
     const SolveTask T{q.x, (unsigned)q.y & 0xffffu, (unsigned)q.y >> 16, (unsigned)q.z, q.w & 0x7fffffff};
     bool through = q.w < 0;
-    // (of the unit: one whose envs have no contacts runs no sweep)
-    uint32_t ncol = b.ustats[T.unit].colours;
+    uint32_t ncol = b.cnt->n_colours;
+    if (!b.ustats[T.unit].colours) ncol = 0;  // no contact in the unit
     if (slot == kSlotImpact && !b.ustats[T.unit].imp_any) ncol = 0;  // no impact in the unit
     uint32_t* counter = &b.cnt->bar[blockIdx.x % kGroups][0];
     if ((T.K > 1 || flow) && !through) {
