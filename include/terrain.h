@@ -22,6 +22,15 @@
  *  - A scene owns its device buffers (allocated through desc.alloc_fn when
  *    given, else hipMalloc) and runs all work on desc.stream (the null stream
  *    when NULL).  Handles are not thread-safe; one scene uses one stream.
+ *    Scenes of one process may be stepped from several threads on streams of
+ *    their own: the blocks of a large scene's solve wait for each other, so
+ *    step() waits on the host while the scenes already stepping on that GPU
+ *    leave too few compute units for them.  (A scene's steps are captured as
+ *    graphs when it steps for the second time, and again after a change of its
+ *    tables; a call of another thread that uses the null stream meanwhile makes
+ *    the capture fail: see set_step_graphs.)  Other processes on the same GPU
+ *    are not known to step(): a solve that cannot get its blocks onto the GPU
+ *    gives up after a bounded wait, TR_E_CAPACITY.  Give a GPU to one process.
  *  - Positions are stored in FP32 in the frame they are given in; callers
  *    should place each environment near the origin (FP32 resolution).
  *  - Particle ids are consecutive per environment: env e owns the id range

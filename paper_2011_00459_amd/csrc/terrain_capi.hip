@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "terrain.h"
+#include "terrain_gate.h"
 #include "terrain_internal.h"
 
 using namespace trk;
@@ -105,6 +106,8 @@ struct tr_scene {
     bool capture = false;             // set_learn_capture: every step writes the learned-start features
     bool features_last = false;       // the last step wrote them
     tr_solver_config cfg{};           // PGS schedule
+    int device = 0;                   // the GPU of the scene
+    int pgs_cus = 0;                  // CUs per XCD that waiting blocks of the solve take
     int64_t own_alloc = 0;            // owners allocated (starts, segment ranges)
     int64_t seg_alloc = 0;            // owner segments allocated
     int64_t task_alloc = 0;           // grouped / spread block tasks allocated
@@ -545,6 +548,7 @@ int rebuild_plan(tr_scene* s)
     std::vector<int> own_idx;
     std::vector<int4> own_seg, tasks_g;
     int grp_lds = 0;
+    int cus = 0;  // CUs per XCD of clusters (a block each)
     std::vector<int> own_x;
     int64_t x_next = 0;
     auto set_env = [&](int e, int own_base, int K, int lds_off, int res_cap, bool coded) {
@@ -568,8 +572,12 @@ int rebuild_plan(tr_scene* s)
     };
     if (s->cfg.mode == TR_PGS_PER_ENV) {
         std::vector<int> K(E, 1);
+        std::vector<int> lane_cus(kGroups, 0);
         for (const int4& t : plan)
-            if (t.z >= 2) K[t.x] = t.z;
+            if (t.z >= 2) {
+                K[t.x] = t.z;
+                cus = std::max(cus, ++lane_cus[t.w % kGroups]);
+            }
         s->z.env_small = env_small ? 1 : 0;
         for (int e = 0; e < E; ++e) {
             const bool region = K[e] > 1 || env_small;
@@ -592,6 +600,7 @@ int rebuild_plan(tr_scene* s)
             if (n == 0) continue;
             const bool wide = E == 1 && !flow && n > kSpreadMin;
             const int per = region_blocks(s, n, wide, flow, bpx), K = wide ? kGroups * per : per;
+            if (K > 1) cus = std::max(cus, per);
             const int base = (int)own_idx.size();
             int off = 0;
             for (int e = 0; e < E; ++e) {
@@ -615,6 +624,7 @@ int rebuild_plan(tr_scene* s)
             }
         }
     }
+    s->pgs_cus = cus;
     const int n_own = (int)own_idx.size();
     own_idx.push_back((int)own_seg.size());
     const int64_t flags = std::max<int64_t>({(int64_t)s->z.pgs_grid, (int64_t)blocks, 1});
@@ -1010,6 +1020,7 @@ int create_scene(const tr_scene_desc* d, tr_scene** out)
     s->bounds.assign(d->env_bounds, d->env_bounds + 6 * d->n_envs);
     s->desc.env_bounds = s->bounds.data();
     s->stream = (hipStream_t)d->stream;
+    (void)hipGetDevice(&s->device);
     s->envs.resize(d->n_envs);
     fill_params(s);
     Sizes& z = s->z;
@@ -1331,6 +1342,41 @@ int set_step_graphs(tr_scene* s, int32_t enable)
     return TR_OK;
 }
 
+namespace {
+
+// A step's place among those of the process's other scenes on the GPU, held
+// until the stream has run it.
+class StepPlace {
+public:
+    explicit StepPlace(const tr_scene* s) : s_(s)
+    {
+        const int cap = std::max(1, s->z.col_grid / kGroups), blocks = colour_blocks(s->p, s->z);
+        const int col = blocks > 1 ? (blocks + kGroups - 1) / kGroups : 0;
+        need_ = std::min(cap, std::max(col, s->pgs_cus));
+        if (need_ > 0) gate().enter(need_, cap);
+    }
+    ~StepPlace()
+    {
+        if (need_ == 0) return;
+        if (!done) (void)hipStreamSynchronize(s_->stream);  // (an error return with steps on their way)
+        gate().leave(need_);
+    }
+    StepPlace(const StepPlace&) = delete;
+    StepPlace& operator=(const StepPlace&) = delete;
+    bool done = false;  // the stream has been waited for
+
+private:
+    CuGate& gate() const
+    {
+        static CuGate gates[16];  // one per GPU (further ones share)
+        return gates[s_->device % 16];
+    }
+    const tr_scene* s_;
+    int need_ = 0;
+};
+
+}  // namespace
+
 // Library-internal callers use step_scene: the exported name `step` is also a
 // (legacy regex) function of the C library, which a call through the PLT
 // could bind to.
@@ -1347,7 +1393,12 @@ static int step_scene(tr_scene* s, int32_t n_steps, tr_step_stats* stats)
         int rc = rebuild_tables(s);
         if (rc) return rc;
     }
+    if (n_steps == 0 && !stats) {
+        hipError_t e = hipGetLastError();
+        return e != hipSuccess ? hip_fail(s, e, "step launch") : TR_OK;
+    }
     hipStream_t st = s->stream;
+    StepPlace place(s);
     s->report_fresh = false;
     for (int k = 0; k < n_steps; ++k) {
         if (s->use_graphs && s->have_prev && !s->graphs) {
@@ -1373,13 +1424,13 @@ static int step_scene(tr_scene* s, int32_t n_steps, tr_step_stats* stats)
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(s, e, "step launch");
-    if (n_steps == 0 && !stats) return TR_OK;
     // every call waits for its steps and reads the failure flags of all of
     // them: the current step's word and the word earlier steps folded theirs into
     const StepReport r = step_report(s, s->report, stats != nullptr);
     launch_report(r, st);
     HIP_CHECK(s, hipGetLastError());
     HIP_CHECK(s, hipStreamSynchronize(st));
+    place.done = true;
     s->report_fresh = true;
     const Counters& c = *(const Counters*)r.to[0];
     const uint32_t bad = c.failed | c.overflow;

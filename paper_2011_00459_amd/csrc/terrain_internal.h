@@ -429,5 +429,6 @@ int pgs_group_max_lds();
 int pgs_env_resident_blocks(int lds_bytes);
 int pgs_env_max_lds();
 int colour_resident_blocks(int* per_block);
+int colour_blocks(const StepParams& p, const Sizes& z);
 
 }  // namespace trk

@@ -1047,13 +1047,19 @@ __global__ __launch_bounds__(kOrdBlk) void k_order(DevBuffers b)
     }
 }
 
+// spheres of a colouring block, at least 1,024: chains across blocks cost about
+// a microsecond a link
+static int colour_range(const StepParams& p, const Sizes& z)
+{
+    return (int)std::max<int64_t>(kColBlk, cdiv(p.n_particles, z.col_grid));
+}
+int colour_blocks(const StepParams& p, const Sizes& z) { return (int)cdiv(p.n_particles, colour_range(p, z)); }
+
 void launch_colour(const DevBuffers& b, const StepParams& p, const Sizes& z, hipStream_t s)
 {
     if (p.n_particles > 0) {
-        // at least 1,024 spheres a block: chains across blocks cost about a
-        // microsecond a link
-        const int per = (int)std::max<int64_t>(kColBlk, cdiv(p.n_particles, z.col_grid));
-        const unsigned g = (unsigned)cdiv(p.n_particles, per);
+        const int per = colour_range(p, z);
+        const unsigned g = (unsigned)colour_blocks(p, z);
         if (per <= z.col_per)
             hipLaunchKernelGGL(k_colour<true>, dim3(g), dim3(kColBlk), (size_t)per * 16, s, b, p.n_particles, per, 1 << 22);
         else
