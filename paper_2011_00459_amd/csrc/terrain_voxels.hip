@@ -88,7 +88,7 @@ __device__ inline double lane_value(double v, int l)
 // whose box does not fit is cut where it stops fitting.  Particles that share
 // no box (it would be larger than theirs together, or too large), as after
 // positions were set in any order, go to memory directly: 50,000 of them with
-// R = l0 / 2 take 120 us, where a box each took 408 and a thread a particle
+// R = l0 / 2 take 117 us, where a box each took 408 and a thread a particle
 // 155.  A wave takes a particle at a time, a lane a column of its voxels.  (The
 // exponential as the product of its three axes', computed once a particle,
 // took 6 us less and rounds twice more.)
@@ -130,17 +130,18 @@ __global__ __launch_bounds__(64 * kCgWaves) void k_coarse_grain_smooth(DevBuffer
         return l[0] <= h[0] && l[1] <= h[1] && l[2] <= h[2]
                    ? (double)(h[0] - l[0] + 1) * (h[1] - l[1] + 1) * (h[2] - l[2] + 1) : 0.0;
     };
-    // voxels of the largest box, and the particles that share one with the next
-    double most = some ? volume(lo, hi) : 0.0;
-    for (int o = 32; o > 0; o >>= 1) most = fmax(most, __shfl_xor(most, o));
-    int nl[3], nh[3];
-    for (int k = 0; k < 3; ++k) {
-        const int l = some ? lo[k] : 0x7fffffff, h = some ? hi[k] : -1;
-        nl[k] = min(l, __shfl_down(l, 1));
-        nh[k] = max(h, __shfl_down(h, 1));
-    }
-    const double both = volume(nl, nh);
-    const unsigned long long near = __ballot(lane + 1 < np && both <= (double)kCgVox && both <= 2.0 * most);
+    const double reach = fmax(1.0, 6.0 * R / g.l0), most = reach * reach * reach;  // voxels of a particle's box
+    // the particles that share a box with the next
+    auto sharing = [&] {
+        int nl[3], nh[3];
+        for (int k = 0; k < 3; ++k) {
+            const int l = some ? lo[k] : 0x7fffffff, h = some ? hi[k] : -1;
+            nl[k] = min(l, __shfl_down(l, 1));
+            nh[k] = max(h, __shfl_down(h, 1));
+        }
+        const double both = volume(nl, nh);
+        return __ballot(lane + 1 < np && both <= (double)kCgVox && both <= 2.0 * most);
+    };
     for (int q0 = 0; q0 < np;) {
         // the box of particles q0 .. lane, and the first lane at which it no longer fits
         int bl[3], bh[3];
@@ -157,10 +158,13 @@ __global__ __launch_bounds__(64 * kCgWaves) void k_coarse_grain_smooth(DevBuffer
         const unsigned long long over = __ballot(vol > (double)kCgVox && lane >= q0);
         const int first = over ? __ffsll((long long)over) - 1 : np, n = first - q0;
         const bool local = n > 1 && lane_value(vol, max(first, 1) - 1) <= n * most;
-        const int from = max(first, q0 + 1);
-        const unsigned long long pairs = from < 64 ? near >> from : 0ull;
-        const int q1 = __builtin_amdgcn_readfirstlane(
-            local ? first : (pairs ? from + __ffsll((long long)pairs) - 1 : np));
+        int end = first;
+        if (!local) {
+            const int from = max(first, q0 + 1);
+            const unsigned long long pairs = from < 64 ? sharing() >> from : 0ull;
+            end = pairs ? from + __ffsll((long long)pairs) - 1 : np;
+        }
+        const int q1 = __builtin_amdgcn_readfirstlane(end);
         int base[3], side[3];
         for (int k = 0; k < 3; ++k) {
             base[k] = lane_value(bl[k], q1 - 1);
