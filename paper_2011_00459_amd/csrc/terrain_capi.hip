@@ -1084,10 +1084,16 @@ int create_scene(const tr_scene_desc* d, tr_scene** out)
     s->p.n_bodies = 2 * d->n_envs;  // (a report of more bodies gets memory of its own)
     s->report_bytes = report_size(s);
     s->p.n_bodies = 0;
-    if (e == hipSuccess)
-        e = hipHostMalloc((void**)&s->read_buf[0], sizeof(double) * 2 * chunk + s->report_bytes, hipHostMallocDefault);
-    s->read_buf[1] = s->read_buf[0] + chunk;
-    s->report = (char*)(s->read_buf[1] + chunk);
+    if (e == hipSuccess) {
+        if (hipHostMalloc((void**)&s->read_buf[0], sizeof(double) * 2 * chunk + s->report_bytes, hipHostMallocDefault) !=
+            hipSuccess) {
+            s->read_buf[0] = nullptr;
+            destroy_scene(s);
+            return TR_E_NOMEM;
+        }
+        s->read_buf[1] = s->read_buf[0] + chunk;
+        s->report = (char*)(s->read_buf[1] + chunk);
+    }
     for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreateWithFlags(&s->read_ev[k], hipEventDisableTiming);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) {
