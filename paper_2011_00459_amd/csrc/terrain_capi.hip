@@ -11,6 +11,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <limits>
+#include <mutex>
 #include <queue>
 #include <string>
 #include <vector>
@@ -44,6 +45,56 @@ constexpr int64_t kFlowSpheres = 100;
 constexpr int64_t kWideRegion = 600;      // largest region of 512-thread blocks (beside kPgsWide)
 constexpr double kPlanRegion = 800.0;      // region of the per-env plan by spheres per block
 constexpr int64_t kEnvSmallRegion = 800;  // largest region of the per-env plan of small regions
+
+// Pinned host memory of closed scenes, kept for the next ones: allocating and
+// freeing it is half of what a small scene takes to make and to close (50 of 120
+// us, 30 of 60).  At most kKept blocks of kKeptBytes together; a block serves
+// a request of at least half its size.  Shared by all threads; a scene's
+// stream has been waited for before its block comes back.
+class PinnedBlocks {
+public:
+    void* take(size_t& bytes)
+    {
+        {
+            std::lock_guard<std::mutex> lock(m_);
+            for (size_t k = 0; k < free_.size(); ++k)
+                if (free_[k].second >= bytes && free_[k].second / 2 <= bytes) {
+                    const auto b = free_[k];
+                    free_.erase(free_.begin() + (long)k);
+                    held_ -= b.second;
+                    bytes = b.second;
+                    return b.first;
+                }
+        }
+        void* p = nullptr;
+        return hipHostMalloc(&p, bytes, hipHostMallocPortable) == hipSuccess ? p : nullptr;
+    }
+    void give(void* p, size_t bytes)
+    {
+        if (!p) return;
+        {
+            std::lock_guard<std::mutex> lock(m_);
+            if (free_.size() < kKept && held_ + bytes <= kKeptBytes) {
+                free_.push_back({p, bytes});
+                held_ += bytes;
+                return;
+            }
+        }
+        (void)hipHostFree(p);
+    }
+    // (never destroyed: the runtime may be gone by then)
+    static PinnedBlocks& shared()
+    {
+        static PinnedBlocks* b = new PinnedBlocks;
+        return *b;
+    }
+
+private:
+    static constexpr size_t kKept = 8, kKeptBytes = 16u << 20;
+    std::mutex m_;
+    std::vector<std::pair<void*, size_t>> free_;
+    size_t held_ = 0;
+};
 
 struct EnvHost {
     int64_t n = 0;
@@ -95,6 +146,7 @@ struct tr_scene {
     bool events = false;
     float* staging = nullptr;         // 12 floats per particle (device), id-order exchange
     double* read_buf[2] = {nullptr, nullptr};  // host, written by the device: kReadChunk particles each
+    size_t read_bytes = 0;            // of read_buf and the report behind it
     hipEvent_t read_ev[2] = {nullptr, nullptr};
     char* report = nullptr;           // host, written by the device after the steps of a call
     size_t report_bytes = 0;
@@ -1085,9 +1137,9 @@ int create_scene(const tr_scene_desc* d, tr_scene** out)
     s->report_bytes = report_size(s);
     s->p.n_bodies = 0;
     if (e == hipSuccess) {
-        if (hipHostMalloc((void**)&s->read_buf[0], sizeof(double) * 2 * chunk + s->report_bytes, hipHostMallocDefault) !=
-            hipSuccess) {
-            s->read_buf[0] = nullptr;
+        s->read_bytes = sizeof(double) * 2 * chunk + s->report_bytes;
+        s->read_buf[0] = (double*)PinnedBlocks::shared().take(s->read_bytes);
+        if (!s->read_buf[0]) {
             destroy_scene(s);
             return TR_E_NOMEM;
         }
@@ -1114,7 +1166,7 @@ int destroy_scene(tr_scene* s)
     while (!s->allocs.empty()) dfree(s, s->allocs.back().first);
     if (s->events)
         for (int k = 0; k < 5; ++k) (void)hipEventDestroy(s->ev[k]);
-    if (s->read_buf[0]) (void)hipHostFree(s->read_buf[0]);
+    PinnedBlocks::shared().give(s->read_buf[0], s->read_bytes);
     for (int k = 0; k < 2; ++k)
         if (s->read_ev[k]) (void)hipEventDestroy(s->read_ev[k]);
     if (s->report_own) (void)hipHostFree(s->report);
