@@ -422,6 +422,15 @@ struct StepReport {
     int64_t words[kParts];
 };
 void launch_report(const StepReport& r, hipStream_t s);
+// several arrays of whole 32-bit words set to zero
+struct ZeroList {
+    static constexpr int kParts = 8;
+    struct Part {
+        void* p;
+        size_t bytes;
+    } part[kParts];
+};
+void launch_zero(const ZeroList& l, hipStream_t s);
 void launch_scatter_by_id(const DevBuffers& b, int id_base, int n, const float4* xi, const float4* vi,
                           const float4* wi, int mask, hipStream_t s);
 int pgs_resident_blocks();

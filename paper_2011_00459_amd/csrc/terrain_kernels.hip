@@ -3404,6 +3404,21 @@ void launch_report(const StepReport& r, hipStream_t s)
     hipLaunchKernelGGL(k_report, dim3((unsigned)std::min<int64_t>(cdiv(most, kBlk), 64)), dim3(kBlk), 0, s, r);
 }
 
+__global__ void k_zero(ZeroList l)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    for (int k = 0; k < ZeroList::kParts; ++k)
+        for (int64_t w = t; w < (int64_t)(l.part[k].bytes / 4); w += step) ((uint32_t*)l.part[k].p)[w] = 0u;
+}
+
+void launch_zero(const ZeroList& l, hipStream_t s)
+{
+    size_t most = 0;
+    for (const ZeroList::Part& q : l.part) most = std::max(most, q.bytes / 4);
+    hipLaunchKernelGGL(k_zero, dim3((unsigned)std::min<int64_t>(std::max<int64_t>(cdiv((int64_t)most, kBlk), 1), 1024)),
+                       dim3(kBlk), 0, s, l);
+}
+
 __global__ void k_scatter_by_id(DevBuffers b, int id_base, int n, const float4* xi, const float4* vi,
                                 const float4* wi, int mask)
 {
