@@ -596,11 +596,12 @@ int mlp_adam_step(float* weights, const float* grad, float* m, float* v, float l
  *     particles get clusters of ceil(n / T) blocks, the others sets of at
  *     most T particles.  TR_CLUSTER_NONE: no env takes more than one block
  *     (sets of at most lds_particles particles, larger envs alone).
- *   TR_PGS_SPREAD: one env (n_envs must be 1) over the blocks of all 8 XCDs,
- *     blocks_per_xcd each: its sorted spheres in compact regions of the Morton
- *     order, one per block, neighbouring regions on one XCD, the states of
- *     spheres on their surfaces written through to be seen across XCDs.  (A
- *     small env takes the blocks of one XCD.) */
+ *   TR_PGS_SPREAD: one env (n_envs must be 1) by TR_PGS_GROUPED's rule, which
+ *     for a large env takes the blocks of all 8 XCDs, blocks_per_xcd each: its
+ *     sorted spheres in compact regions of the Morton order, one per block,
+ *     neighbouring regions on one XCD, the states of spheres on their surfaces
+ *     written through to be seen across XCDs.  (For one env the two schedules
+ *     launch the same blocks; without dataflow.) */
 #define TR_PGS_GROUPED 0
 #define TR_PGS_PER_ENV 1
 #define TR_PGS_SPREAD 2
@@ -628,12 +629,11 @@ int get_solver_config(tr_scene* s, tr_solver_config* cfg);
  * whole (get_phase_times). */
 int set_step_graphs(tr_scene* s, int32_t enable);
 
-/* Autotuner of the PGS schedule.  Times candidate schedules (grouped with 64,
- * 32, 16 or 8 blocks per XCD; spread with 32 for a single env; per-env with
- * automatic, 8192- and 16384-sphere clusters; per-env without LDS; grouped is
- * left out when a residual
- * tolerance is set with more than 8 envs, where it would let envs share their
- * stopping test) over `steps` eager steps each, every
+/* Autotuner of the PGS schedule.  Times candidate schedules (grouped with 32,
+ * 16 or 8 blocks per XCD, where these limits differ in the blocks they give;
+ * per-env with automatic, 8192- and 16384-sphere clusters, with single blocks
+ * only, and without LDS; grouped is left out when a residual tolerance is set
+ * with more than 8 envs, where it would let envs share their stopping test) over `steps` eager steps each, every
  * candidate from the scene's current state (saved and restored, so the scene
  * is left as it was), and keeps the fastest.  With cache_path, a matching
  * entry (device architecture, log2 of envs, log2 of spheres) is applied

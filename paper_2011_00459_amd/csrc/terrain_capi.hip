@@ -410,6 +410,18 @@ double plan_small(const tr_scene* s, const std::vector<int>& order, int B, int l
     return best;
 }
 
+// spheres of the envs that group g solves
+int64_t group_spheres(const tr_scene* s, int g)
+{
+    int64_t n = 0;
+    for (int e = 0; e < s->desc.n_envs; ++e)
+        if (s->env_host[e].group == g) n += s->env_host[e].n;
+    return n;
+}
+
+// whether a grouped or spread solve of n spheres takes the blocks of all XCDs
+bool solve_wide(const tr_scene* s, int64_t n, bool flow) { return s->desc.n_envs == 1 && !flow && n > kSpreadMin; }
+
 // Blocks per XCD of a grouped or spread solve of n spheres (flow: counter-ordered).
 int region_blocks(const tr_scene* s, int64_t n, bool wide, bool flow, int bpx)
 {
@@ -646,11 +658,9 @@ int rebuild_plan(tr_scene* s)
         const int bpx = s->z.pgs_grid / kGroups, cap = pgs_group_max_lds() / 32;
         tasks_g.assign(s->z.pgs_grid, make_int4(-1, 0, 0, 0));
         for (int g = 0; g < kGroups; ++g) {
-            int64_t n = 0;
-            for (int e = 0; e < E; ++e)
-                if (s->env_host[e].group == g) n += s->env_host[e].n;
+            const int64_t n = group_spheres(s, g);
             if (n == 0) continue;
-            const bool wide = E == 1 && !flow && n > kSpreadMin;
+            const bool wide = solve_wide(s, n, flow);
             const int per = region_blocks(s, n, wide, flow, bpx), K = wide ? kGroups * per : per;
             if (K > 1) cus = std::max(cus, per);
             const int base = (int)own_idx.size();
@@ -2064,7 +2074,7 @@ int set_solver_config(tr_scene* s, const tr_solver_config* cfg)
         (cfg->dataflow != 0 && cfg->dataflow != 1))
         return fail(s, TR_E_INVAL, "set_solver_config: bad field");
     if (cfg->mode == TR_PGS_SPREAD && (s->desc.n_envs != 1 || cfg->dataflow))
-        return fail(s, TR_E_INVAL, "set_solver_config: the spread schedule takes one env and barriers");
+        return fail(s, TR_E_INVAL, "set_solver_config: the spread schedule takes one env and no update counters");
     s->cfg = *cfg;
     s->cfg.blocks_per_xcd = std::min(cfg->blocks_per_xcd, std::max(1, pgs_resident_blocks() / kGroups));
     s->cfg.lds_particles = std::min(cfg->lds_particles, s->max_lds_particles);
@@ -2532,10 +2542,21 @@ int autotune(tr_scene* s, int32_t steps, const char* cache_path, tr_solver_confi
     s->use_graphs = false;
     std::vector<tr_solver_config> cands;
     // grouped mode shares the stopping test of a group's envs: not offered when
-    // that would change results (a residual tolerance with more than 8 envs)
+    // that would change results (a residual tolerance with more than 8 envs).
+    // Limits that give the same blocks are timed once, and the spread schedule,
+    // which is the grouped one for a single env, not at all.
+    std::vector<std::vector<int>> shapes;
     if (!(s->desc.tol > 0.0 && s->desc.n_envs > kGroups))
-        for (int bpx : {64, 32, 16, 8}) cands.push_back({TR_PGS_GROUPED, bpx, s->max_lds_particles, 0, 0});
-    if (s->desc.n_envs == 1) cands.push_back({TR_PGS_SPREAD, 32, s->max_lds_particles, 0, 0});
+        for (int bpx : {32, 16, 8}) {
+            std::vector<int> shape;
+            for (int g = 0; g < kGroups; ++g) {
+                const int64_t n = group_spheres(s, g);
+                shape.push_back(n > 0 ? region_blocks(s, n, solve_wide(s, n, false), false, bpx) : 0);
+            }
+            if (std::find(shapes.begin(), shapes.end(), shape) != shapes.end()) continue;
+            shapes.push_back(shape);
+            cands.push_back({TR_PGS_GROUPED, bpx, s->max_lds_particles, 0, 0});
+        }
     for (int cp : {0, 8192, 16384, (int)TR_CLUSTER_NONE}) cands.push_back({TR_PGS_PER_ENV, 32, s->max_lds_particles, cp, 0});
     cands.push_back({TR_PGS_PER_ENV, 32, 0, 0, 0});
     hipEvent_t e0 = nullptr, e1 = nullptr;
