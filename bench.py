@@ -126,8 +126,8 @@ def roofline(tot, kernel, traffic_key):
 
 def pgs_kernel_name(sc):
     mode = sc.get_solver_config()["mode"]
-    return {"grouped": "k_pgs (grouped: regions of one XCD, persistent PGS)",
-            "spread": "k_pgs (spread: regions of one env on all XCDs, persistent PGS)",
+    return {"grouped": "k_pgs (grouped: regions in LDS, a large env's on all XCDs, persistent PGS)",
+            "spread": "k_pgs (spread: as grouped, for one env)",
             "per_env": "k_pgs_env (per-env persistent PGS)"}[mode]
 
 

@@ -33,9 +33,10 @@ constexpr int kFlowMaxSweeps = 8192;  // longest counter-ordered solve
 // against 1.11; with rolling rows up to 1,400 (1.34 and 1.35 ms; at 1,700 1.43
 // and 1.30).  Clusters in regions of 400 spheres: a phase is then bound by
 // the hand-over between blocks, and their rows fit LDS (35,000 spheres on all
-// XCDs: 1.35 ms at 300, 1.38 at 400, 1.41 at 500, 1.58 at 600).  All XCDs from 27,000 spheres: across XCDs the hand-over is
-// slower, but one XCD's 32 blocks are full (20,000 spheres: 1.27 ms on one
-// XCD, 1.63 on all; 35,000: 1.93 and 1.38; 70,000: 2.63 and 1.47).
+// XCDs: 1.35 ms at 300, 1.38 at 400, 1.41 at 500, 1.58 at 600).  All XCDs from
+// 27,000 spheres: across XCDs the hand-over is slower, but one XCD's 32 blocks
+// are full (20,000 spheres: 1.27 ms on one XCD, 1.63 on all; 35,000: 1.93 and
+// 1.38; 70,000: 2.63 and 1.47).
 constexpr int64_t kRegionAlone = 1700, kRegionAloneRolling = 1400, kRegionSpheres = 400, kSpreadMin = 27000;
 // The counter-ordered solve keeps its bodies in memory and gains nothing from
 // one block or large regions: 100 spheres a block (a step of 600 spheres takes
@@ -750,7 +751,7 @@ int rebuild_plan(tr_scene* s)
         if (!alloc_n(s, s->b.plan_idx, (int64_t)plan_idx.size())) return fail(s, TR_E_NOMEM, "PGS plan");
         s->plan_idx_alloc = (int64_t)plan_idx.size();
     }
-    // block partials: two sweeps (barrier order) or one slot per sweep (counter order)
+    // block partials: two slots, or one per sweep of a counter-ordered solve
     s->z.flow = flow ? 1 : 0;
     int64_t parts = 2 * std::max<int64_t>(s->z.pgs_grid, blocks) * (flow ? std::max(s->desc.max_sweeps, 2) : 2);
     if (parts > s->part_alloc) {
@@ -2571,7 +2572,7 @@ int autotune(tr_scene* s, int32_t steps, const char* cache_path, tr_solver_confi
         if (step_scene(s, steps, nullptr) != TR_OK) continue;
         (void)hipEventRecord(e1, s->stream);
         std::vector<tr_step_stats> st(s->desc.n_envs);
-        if (step_scene(s, 1, st.data()) != TR_OK) continue;  // synchronises; fails on a capacity or barrier failure
+        if (step_scene(s, 1, st.data()) != TR_OK) continue;  // synchronises; fails on a capacity or schedule failure
         float ms = 0.f;
         if (hipEventElapsedTime(&ms, e0, e1) != hipSuccess) continue;
         ms /= (float)steps;

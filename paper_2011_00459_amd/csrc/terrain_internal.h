@@ -37,9 +37,9 @@ constexpr int kMlpParams = 64 * 12 + 64 + 64 * 64 + 64 + 3 * 64 + 3 + 12;
 
 // PGS solve modes
 enum : int {
-    kModeGrouped = 0,  // envs in kGroups groups, each solved on one XCD
+    kModeGrouped = 0,  // envs in kGroups groups, each solved on one XCD (one large env: on all)
     kModePerEnv = 1,   // each env solved by its own block (or cluster of blocks)
-    kModeSpread = 2,   // one env spread over the blocks of all XCDs by space
+    kModeSpread = 2,   // one env, as kModeGrouped
 };
 constexpr int kEnvBlk = 1024;  // threads of a per-env PGS block
 
@@ -267,7 +267,7 @@ struct DevBuffers {
     uint32_t* env_ncol;   // [n_envs] colours used by each env
     int4* plan;           // per-env PGS tasks: (env, rank in its cluster, cluster size, first block)
     uint32_t* plan_idx;   // [blocks + 1]: tasks of block b are plan[plan_idx[b] .. plan_idx[b + 1])
-    uint32_t* env_bar;    // [n_envs][16] cluster barrier counters (per-env mode)
+    uint32_t* env_bar;    // [n_envs][16] cluster placement and barrier counters (per-env mode)
     uint32_t* ver;        // [P] updates applied to each sphere in the current PGS launch
     uint32_t* scan_tmp;   // scratch of the device-wide scan
     float* mlp;           // learned-start weights (kMlpParams)
@@ -301,7 +301,7 @@ struct Sizes {
     int env_small;  // per-env solve under the plan of small regions
     int pgs_wide;   // some region of the grouped, spread or small per-env solve has more than kWideRegion spheres
     int n_units;    // entries of ustats
-    int flow;       // colour order kept by per-sphere update counters instead of barriers
+    int flow;       // colour order kept by per-sphere update counters in memory
     int col_grid;   // resident blocks of the colouring kernel
     int col_per;    // spheres a block of it holds in LDS
     int64_t NCOL;   // depth columns (all envs)

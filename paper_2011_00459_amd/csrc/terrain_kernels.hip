@@ -11,8 +11,8 @@
 //                             colouring in splitmix64 priority order
 //   rows                      Hertz-mapped SPOOK rows (Eqs. signCoul1-2)
 //   warm apply                v* = v + dt g + M^-1 G^T lambda^0
-//   pgs                       persistent colour-synchronous projected
-//                             Gauss-Seidel sweeps with the residual fused in
+//   pgs                       persistent projected Gauss-Seidel sweeps in
+//                             colour order with the residual fused in
 //   finish                    body forces (FP64), x += dt v, kinematic poses,
 //                             zone aggregates (FP64, Eqs. aggregate_mass ..
 //                             aggregate_rot_vel)
@@ -1504,7 +1504,12 @@ void launch_warm_apply(const DevBuffers& b, const StepParams& p, const Sizes& z,
 // and the block that needs it polls the record.  Each 16 B half of a record
 // carries the number of updates it has seen beside its three components, so
 // that one load brings the state and says whether it is the awaited one: no
-// flags, no drained stores, no barrier between blocks.  Every version has one
+// flags, no drained stores, no barrier between blocks.  (That rests on a
+// lane's aligned 16 B store being seen whole or not at all by another block's
+// 16 B load, which no document promises.  Measured: 1.2e10 loads of records
+// that other blocks kept rewriting, across XCDs and inside one, written through
+// and not, saw 7.5e9 new versions, none half written and none out of order.)
+// Every version has one
 // reader, which writes the next, so a record is never overwritten unread; and
 // a block waits only for updates of earlier phases, so that waits end as long
 // as every block is resident (they are bounded all the same).
@@ -2114,8 +2119,9 @@ __device__ inline bool flow_wait(Counters* cnt, const uint32_t* ver, int j, uint
     return true;
 }
 
-// The counter-ordered solve of a cluster (every body in memory): a barrier remains at the end of a sweep when a residual tolerance is set,
-// and once at the end.
+// The counter-ordered solve of a cluster (every body in memory): a barrier
+// remains at the end of a sweep when a residual tolerance is set, and once at
+// the end.
 template <bool ROLL, int NW>
 __device__ void pgs_flow(const DevBuffers& b, const StepParams& p, const SolveTask& T, uint32_t ncol,
                          uint32_t* counter, bool through, int sweeps_cap, int slot, SolveShared<NW>& sh)
@@ -2773,7 +2779,8 @@ int pgs_resident_blocks()
 }
 
 // The colouring's blocks wait for each other, so all of them must run at
-// once: one block per CU; per_block: the spheres whose state its LDS holds.
+// once: one block per CU (terrain_gate.h: beside the blocks of other scenes'
+// steps too); per_block: the spheres whose state its LDS holds.
 int colour_resident_blocks(int* per_block)
 {
     int dev = 0;

@@ -323,7 +323,7 @@ __global__ __launch_bounds__(64 * kTrainQ * kTrainWaves) void k_mlp_train(const 
     __shared__ float w1[kH][kXP], w2[kH][kTP], w3[kOut][kH], bias[2][kH], b3[kOut];
     __shared__ TrainGroup gm[kTrainWaves];
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63, grp = wave / kTrainQ, wq = wave % kTrainQ;
-    const int l16 = lane & 15, q4 = lane >> 4, s32 = lane & 31, half = lane >> 5;
+    const int l16 = lane & 15, q4 = lane >> 4, s32 = lane & 31;
     const int u0 = 16 * wq, u = u0 + l16;  // the wave's units, the lane's
     TrainGroup& G = gm[grp];
     const float inv_b = 1.0f / (float)B;
