@@ -68,7 +68,7 @@ public:
                 }
         }
         void* p = nullptr;
-        return hipHostMalloc(&p, bytes, hipHostMallocPortable) == hipSuccess ? p : nullptr;
+        return hipHostMalloc(&p, bytes, hipHostMallocDefault) == hipSuccess ? p : nullptr;
     }
     void give(void* p, size_t bytes)
     {
