@@ -2557,8 +2557,11 @@ __global__ __launch_bounds__(64 * NW) void k_pgs(DevBuffers b, StepParams p, int
     const SolveTask T{q.x, (unsigned)q.y & 0xffffu, (unsigned)q.y >> 16, (unsigned)q.z, q.w & 0x7fffffff};
     bool through = q.w < 0;
     uint32_t ncol = b.cnt->n_colours;
-    if (!b.ustats[T.unit].colours) ncol = 0;  // no contact in the unit
     if (slot == kSlotImpact && !b.ustats[T.unit].imp_any) ncol = 0;  // no impact in the unit
+    // no contact in the unit (K is never 0: with the test of it the compiler
+    // leaves the solve's loops as they are without this line, 2.07 ms of PGS on
+    // the 50,000-sphere bed; else they take 2.09)
+    if (T.K > 0 && b.ustats[T.unit].colours == 0) ncol = 0;
     uint32_t* counter = &b.cnt->bar[blockIdx.x % kGroups][0];
     if ((T.K > 1 || flow) && !through) {
         const int mode = cluster_placement(b.cnt, counter, T.K, sh.flag);
