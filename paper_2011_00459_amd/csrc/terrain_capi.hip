@@ -1114,8 +1114,8 @@ int create_scene(const tr_scene_desc* d, tr_scene** out)
               alloc_n(s, b.id_count, z.NID) && alloc_n(s, b.id_start, z.NID + 1) &&
               alloc_n(s, b.pid_start, z.NID + 1) && alloc_n(s, b.inc_count, z.P) &&
               alloc_n(s, b.inc_start, z.P + 1) && alloc_n(s, b.inc, 2 * z.C) &&
-              alloc_n(s, b.colour, z.C) && alloc_n(s, b.pinc, 2 * z.C) && alloc_n(s, b.cmsg, z.C) && alloc_n(s, b.icode, 2 * z.C) &&
-              alloc_n(s, b.smask, z.P) && alloc_n(s, b.seq, z.C) && alloc_n(s, b.rm, z.C) && alloc_n(s, b.cpos, z.C) &&
+              alloc_n(s, b.colour, z.C) && alloc_n(s, b.smask, z.P) && alloc_n(s, b.seq, z.C) &&
+              alloc_n(s, b.rm, z.C) && alloc_n(s, b.cpos, z.C) &&
               alloc_n(s, b.r0, z.C) && alloc_n(s, b.r1, z.C) && alloc_n(s, b.r2, z.C) && alloc_n(s, b.rk, z.C) &&
               alloc_n(s, b.r3, z.roll_C) && alloc_n(s, b.lamr, z.roll_C) && alloc_n(s, b.lamr0, z.roll_C) &&
               alloc_n(s, b.lamrc, z.roll_C) && alloc_n(s, b.plamr, z.roll_C) &&
@@ -1133,6 +1133,12 @@ int create_scene(const tr_scene_desc* d, tr_scene** out)
         destroy_scene(s);
         return TR_E_NOMEM;
     }
+    // what the colouring and the solve order keep of a contact lies where its
+    // rows, which are written after them, come to lie
+    static_assert(2 * sizeof(uint2) <= sizeof(float4) && sizeof(unsigned long long) + 2 <= sizeof(float4), "in a row");
+    b.pinc = (uint2*)b.r0;
+    b.cmsg = (unsigned long long*)b.rm;
+    b.icode = (uint8_t*)(b.cmsg + z.C);
     // one launch: a memset each would take half as long as the allocations
     launch_zero({{{b.cnt, sizeof(Counters)},
                   {b.env_stats, sizeof(EnvStats) * d->n_envs},

@@ -216,6 +216,7 @@ struct DevBuffers {
     uint32_t *id_count, *id_start, *pid_start;      // [NID], [NID+1], [NID+1]
     uint32_t *inc_count, *inc_start, *inc;          // [P], [P+1], [2C]
     int* colour;                                    // [C]
+    // (pinc, cmsg and icode: until k_rows writes r0 and rm in their place)
     uint2* pinc;                                    // [2C] incident contacts in order of colouring priority, with the other sphere
     unsigned long long* cmsg;                       // [C] colouring across blocks: the first sphere's used colours
     uint8_t* icode;                                 // [2C] bucket of each incidence entry in its owner's order
