@@ -48,16 +48,16 @@ ROW_BYTES = 80
 # runs scaled by a copy kernel of known size (profiles named below); valid
 # only for the kernel source it was measured on, else reported as null.
 PGS_TRAFFIC = {
-    "batched": {"kernels_sha256_prefix": "6a13175890c3aff2", "bytes_per_launch": 28.1e9,
+    "batched": {"kernels_sha256_prefix": "b8b1517783c78c0b", "bytes_per_launch": 28.15e9,
                 "profile": "profiles/k_pgs_env_batched256_hbm_traffic.md"},
-    "bed": {"kernels_sha256_prefix": "6a13175890c3aff2", "bytes_per_launch": 1.331e9,
+    "bed": {"kernels_sha256_prefix": "b8b1517783c78c0b", "bytes_per_launch": 1.327e9,
             "profile": "profiles/k_pgs_bed50k_hbm_traffic.md"},
-    "excavation": {"kernels_sha256_prefix": "6a13175890c3aff2", "bytes_per_launch": 27.34e9,
+    "excavation": {"kernels_sha256_prefix": "b8b1517783c78c0b", "bytes_per_launch": 27.34e9,
                    "profile": "profiles/k_pgs_excavation500k_hbm_traffic.md"},
 }
 # The same for k_advect on the 256 x 256 x 128 voxel grid
 # (profiles/k_advect_voxels256_kernel_trace.md), keyed to terrain_voxels.hip.
-ADVECT_TRAFFIC = {"kernels_sha256_prefix": "2d9d2079078d5907", "bytes_per_launch": 0.3759e9,
+ADVECT_TRAFFIC = {"kernels_sha256_prefix": "2d9d2079078d5907", "bytes_per_launch": 0.3753e9,
                   "profile": "profiles/k_advect_voxels256_kernel_trace.md"}
 
 
